@@ -25,10 +25,9 @@
 // Stores beyond the sample size take a threshold plan (score_topk) whose
 // sample and filter passes multiply the hi part alone -- half the MFMAs --
 // with thresholds lowered by twice a per-query bound on the hi part's error;
-// the few candidates near the k-th are then rescored exactly.  At D = 768 and
-// 1,024 the filter pass is k_filter: one tile per workgroup on the
-// similarity screen's pipeline (two LDS stages), 128 x 128 or, for launches
-// of many tiles, 256 x 256.
+// the few candidates near the k-th are then rescored exactly.  Both passes
+// are k_filter: one tile per workgroup on the similarity screen's pipeline
+// (two LDS stages), 128 x 128 or, for launches of many tiles, 256 x 256.
 #include <cmath>
 #include <cstring>
 #include <mutex>
@@ -206,6 +205,7 @@ struct ScoreArgs {
   int64_t tiles_per_split;
   float* part_s;             // list modes: [nq][splits][2][KL]
   int32_t* part_r;
+  int sample_tiles;          // sample pass: store tiles with entries of their own (later tiles fold onto them)
   const float* thr;          // filter mode: per-query threshold
   float* cand_s;             // filter mode: [nq][cap]
   int32_t* cand_r;
@@ -281,15 +281,13 @@ __device__ __forceinline__ void unpack32(const uint32_t* __restrict__ w, _Float1
   }
 }
 
-// NC (16 or 32) b-bit codes from NC * B / 32 whole words (element 0 at bit 0)
-// to fp16, as unpack32 does.
-template <int B, int NC>
-__device__ __forceinline__ void unpack_codes(const uint32_t* __restrict__ w, _Float16* __restrict__ out) {
-  static_assert(NC == 16 || NC == 32, "a half or a whole group");
-  constexpr int NW = NC * B / 32;
-  if constexpr (NC == 32) {
-    unpack32<B>(w, out);
-  } else if constexpr (B == 8) {
+// The 16 b-bit codes of half `h` of a group of 32 to fp16, as unpack32 does.
+// w: the words that hold them, (B + 1) / 2 words from word h * (B / 2) of the
+// group; for odd widths the upper half starts at bit 16 of its first word.
+template <int B>
+__device__ __forceinline__ void unpack16(const uint32_t (&w)[(B + 1) / 2], int h, _Float16* __restrict__ out) {
+  constexpr int NW = (B + 1) / 2;
+  if constexpr (B == 8) {
 #pragma unroll
     for (int i = 0; i < NW; ++i) {
       const uint32_t x = w[i] ^ 0x80808080u;
@@ -306,10 +304,13 @@ __device__ __forceinline__ void unpack_codes(const uint32_t* __restrict__ w, _Fl
   } else {
     uint32_t v[NW + 1];
 #pragma unroll
-    for (int i = 0; i < NW; ++i) v[i] = w[i];
+    for (int i = 0; i < NW; ++i) {
+      if constexpr ((B & 1) != 0) v[i] = __builtin_amdgcn_alignbit(i + 1 < NW ? w[i + 1] : 0u, w[i], h ? 16u : 0u);
+      else v[i] = w[i];
+    }
     v[NW] = 0u;
 #pragma unroll
-    for (int e = 0; e < NC; ++e) {
+    for (int e = 0; e < 16; ++e) {
       const int bit = e * B, wi = bit >> 5, off = bit & 31;
       uint32_t u = v[wi] >> off;
       if (off + B > 32) u |= v[wi + 1] << (32 - off);
@@ -319,48 +320,41 @@ __device__ __forceinline__ void unpack_codes(const uint32_t* __restrict__ w, _Fl
   }
 }
 
-// One group of 32 b-bit codes (B consecutive words starting at word w0 of the
-// buffer, or zeros when !ok): the widest loads the group's alignment allows
-// (a group starts at a multiple of B words), so a lane asks for its bytes in
-// one or two pieces rather than B.
-template <int B>
-__device__ __forceinline__ void load_group(__amdgpu_buffer_rsrc_t rs, bool ok, uint32_t w0, uint32_t (&cw)[B]) {
-  if constexpr (B % 4 == 0) {
+// NW consecutive words at byte offset voff + soff of the buffer in the widest
+// pieces (16, 8, then 4 bytes; multi-dword buffer loads need 4-byte alignment
+// only), so that a lane asks for its bytes in one to three requests.
+template <int NW>
+__device__ __forceinline__ void load_words(__amdgpu_buffer_rsrc_t rs, uint32_t voff, uint32_t soff, uint32_t (&cw)[NW]) {
 #pragma unroll
-    for (int i = 0; i < B; i += 4) {
-      const uint4 v = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(rs, ok ? (w0 + i) * 4u : kOffOOB, 0, 0));
-      cw[i] = v.x;
-      cw[i + 1] = v.y;
-      cw[i + 2] = v.z;
-      cw[i + 3] = v.w;
-    }
-  } else if constexpr (B % 2 == 0) {
-#pragma unroll
-    for (int i = 0; i < B; i += 2) {
-      const uint2 v = __builtin_bit_cast(uint2, __builtin_amdgcn_raw_buffer_load_b64(rs, ok ? (w0 + i) * 4u : kOffOOB, 0, 0));
-      cw[i] = v.x;
-      cw[i + 1] = v.y;
-    }
-  } else {
-#pragma unroll
-    for (int i = 0; i < B; ++i)
-      cw[i] = (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(rs, ok ? (w0 + i) * 4u : kOffOOB, 0, 0);
+  for (int i = 0; i + 4 <= NW; i += 4) {
+    const uint4 v = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(rs, voff + i * 4u, soff, 0));
+    cw[i] = v.x;
+    cw[i + 1] = v.y;
+    cw[i + 2] = v.z;
+    cw[i + 3] = v.w;
   }
+  constexpr int r = NW & ~3;
+  if constexpr ((NW & 2) != 0) {
+    const uint2 v = __builtin_bit_cast(uint2, __builtin_amdgcn_raw_buffer_load_b64(rs, voff + r * 4u, soff, 0));
+    cw[r] = v.x;
+    cw[r + 1] = v.y;
+  }
+  if constexpr ((NW & 1) != 0)
+    cw[NW - 1] = (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(rs, voff + (NW - 1) * 4u, soff, 0);
 }
 
 // acc[t] (t = 0..3) <- the 128 x 128 tile of raw scores: store rows
 // [rbase, rbase + rows) against the workgroup's 128 queries (wave w holds
 // queries [32w, 32w + 32), lane j % 32, store rows t*32 + acc_row(r, lane)).
-// Codes are unpacked straight into an fp16 LDS slab; queries enter as hi/lo
-// (LO), or as the hi part alone.
+// Codes are unpacked straight into an fp16 LDS slab; queries enter as hi and lo.
 //
-// One LDS stage (codes, hi[, lo]: 2 or 3 x 128 rows of kLdk halves) is refilled
+// One LDS stage (codes, hi, lo: 3 x 128 rows of kLdk halves) is refilled
 // between two barriers while the next slab's loads are in flight in
 // registers; loads go through buffer resources (zeros past the tile) so none
 // sits behind a branch.  With one slab in flight, the wait at the top of each
 // step is for all outstanding loads, which is exactly the slab being stored.
 // Ends with a barrier, so the caller may reuse the LDS.
-template <int B, bool LO>
+template <int B>
 __device__ __forceinline__ void score_tile(const ScoreArgs& a, int64_t rbase, int rows, const _Float16* QH,
                                            const _Float16* QL, int qrows, _Float16* lds, floatx16 (&acc)[4]) {
   _Float16* sc = lds;
@@ -378,9 +372,9 @@ __device__ __forceinline__ void score_tile(const ScoreArgs& a, int64_t rbase, in
   auto load_slab = [&](int k0, uint32_t (&cw)[B], uint4 (&rh)[4], uint4 (&rl)[4]) {
     const bool ok = urow < rows && k0 + 32 * uhalf < a.D;
     const uint32_t w0 = (uint32_t)(urow * a.row_words + (int64_t)(k0 / 32 + uhalf) * B);
-    load_group<B>(rsC, ok, w0, cw);
+    load_words<B>(rsC, ok ? w0 * 4u : kOffOOB, 0u, cw);
     slab_load_n<4>(rsH, qrows, a.D, k0, a.D, rh, kWG);
-    if (LO) slab_load_n<4>(rsL, qrows, a.D, k0, a.D, rl, kWG);
+    slab_load_n<4>(rsL, qrows, a.D, k0, a.D, rl, kWG);
   };
   auto compute = [&]() {
 #pragma unroll
@@ -391,11 +385,9 @@ __device__ __forceinline__ void score_tile(const ScoreArgs& a, int64_t rbase, in
       for (int t = 0; t < 4; ++t) fa[t] = frag_load(sc, t * 32, kk);
 #pragma unroll
       for (int t = 0; t < 4; ++t) acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_f16(fa[t], bh, acc[t], 0, 0, 0);
-      if (LO) {
-        const half8 bl = frag_load(sl, wave * 32, kk);
+      const half8 bl = frag_load(sl, wave * 32, kk);
 #pragma unroll
-        for (int t = 0; t < 4; ++t) acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_f16(fa[t], bl, acc[t], 0, 0, 0);
-      }
+      for (int t = 0; t < 4; ++t) acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_f16(fa[t], bl, acc[t], 0, 0, 0);
     }
   };
   const int S = (a.D + kBK - 1) / kBK;
@@ -412,7 +404,7 @@ __device__ __forceinline__ void score_tile(const ScoreArgs& a, int64_t rbase, in
       for (int i = 0; i < 32; i += 8) *reinterpret_cast<uint4*>(dst + i) = *reinterpret_cast<const uint4*>(h + i);
     }
     slab_store_n<4>(sh, rh, kWG);
-    if (LO) slab_store_n<4>(sl, rl, kWG);
+    slab_store_n<4>(sl, rl, kWG);
     __syncthreads();
     load_slab((s + 1) * kBK, cw, rh, rl);   // past the last slab: zeros, no memory touched
     __builtin_amdgcn_sched_barrier(0);      // issue the loads before the MFMAs
@@ -421,26 +413,23 @@ __device__ __forceinline__ void score_tile(const ScoreArgs& a, int64_t rbase, in
   __syncthreads();
 }
 
-enum { kModeLists = 0, kModeFilter = 1, kModeFallback = 2 };
+enum { kModeLists = 0, kModeFallback = 1 };
 
-template <int KL, int SEG>
+template <int KL>
 __device__ void merge_query(int64_t j, int cands, int k, const float* __restrict__ ps,
                             const int32_t* __restrict__ pr, const QMeta* __restrict__ meta,
                             const int64_t* __restrict__ ids, float* __restrict__ out_s, int64_t* __restrict__ out_i,
-                            float* __restrict__ bound, float* __restrict__ kth);
+                            float* __restrict__ bound);
 
-// MODE kModeLists / kModeFallback: each lane keeps a sorted private list of its
-// best KL (score, row) pairs; the lists go to part_s/part_r.  kModeFallback
-// only runs query tiles flagged in tflag.  MODE kModeFilter: every score at or
-// above the query's threshold is appended to its candidate buffer.  LO: the
-// scores include the query's lo part; without it they are the hi-only scores
-// H of the sample and filter passes (within QMeta::err of the rescored ones).
-template <int B, int KL, int MODE, bool LO>
+// Exact scores (hi and lo parts) of a range of store tiles: each lane keeps a
+// sorted private list of its best KL (score, row) pairs; the lists go to
+// part_s/part_r.  MODE kModeFallback only runs query tiles flagged in tflag.
+template <int B, int KL, int MODE>
 __global__ __launch_bounds__(kWG, 2) void k_score(ScoreArgs a) {
-  // one slab stage (codes, hi[, lo]: 128 rows each) or the list epilogue's
+  // one slab stage (codes, hi, lo: 128 rows each) or the list epilogue's
   // 4 x 64 x 64 scores
-  constexpr int kSlab = (LO ? 3 : 2) * kTB * kLdk;
-  constexpr int kLists = MODE == kModeFilter ? 0 : 2 * 4 * 64 * 64;
+  constexpr int kSlab = 3 * kTB * kLdk;
+  constexpr int kLists = 2 * 4 * 64 * 64;
   constexpr int kLdsHalves = kSlab > kLists ? kSlab : kLists;
   __shared__ __attribute__((aligned(16))) _Float16 lds[kLdsHalves];
   const int qt = blockIdx.x % a.nqt;
@@ -454,25 +443,22 @@ __global__ __launch_bounds__(kWG, 2) void k_score(ScoreArgs a) {
   const int qrows = (int)min<int64_t>(kTB, a.nq - qbase);
   const int64_t j = qbase + wave * 32 + (lane & 31);
   const float osc = (j < a.nq) ? a.meta[j].osc : 0.0f;
-  const float th = (MODE == kModeFilter && j < a.nq) ? a.thr[j] : 0.0f;
   const _Float16* QH = a.qhi + qbase * a.D;
   const _Float16* QL = a.qlo + qbase * a.D;
 
-  float ls[MODE == kModeFilter ? 1 : KL];
-  int lr[MODE == kModeFilter ? 1 : KL];
-  if constexpr (MODE != kModeFilter) {
+  float ls[KL];
+  int lr[KL];
 #pragma unroll
-    for (int p = 0; p < KL; ++p) {
-      ls[p] = -INFINITY;
-      lr[p] = kNoRow;
-    }
+  for (int p = 0; p < KL; ++p) {
+    ls[p] = -INFINITY;
+    lr[p] = kNoRow;
   }
 
   for (int64_t tile = t0; tile < t1; ++tile) {
     const int64_t rbase = tile * kTB;
     const int rows = (int)min<int64_t>(kTB, a.n - rbase);
     floatx16 acc[4];
-    score_tile<B, LO>(a, rbase, rows, QH, QL, qrows, lds, acc);
+    score_tile<B>(a, rbase, rows, QH, QL, qrows, lds, acc);
 
     // The scale osc is positive, so the largest score is osc times the
     // largest accumulator; only a partial tile needs the row check.
@@ -489,35 +475,6 @@ __global__ __launch_bounds__(kWG, 2) void k_score(ScoreArgs a) {
         for (int r = 0; r < 16; ++r) amx = (t * 32 + acc_row(r, lane) < rows) ? fmaxf(amx, acc[t][r]) : amx;
     }
     const float mx = amx * osc;
-    if constexpr (MODE == kModeFilter) {
-      const bool hot = j < a.nq && mx >= th;
-      if (__ballot(hot) != 0ull && hot) {
-        // count this lane's candidates, reserve their slots with one atomic,
-        // then write them
-        uint32_t c = 0u;
-#pragma unroll
-        for (int t = 0; t < 4; ++t)
-#pragma unroll
-          for (int r = 0; r < 16; ++r)
-            c += (t * 32 + acc_row(r, lane) < rows && acc[t][r] * osc >= th) ? 1u : 0u;
-        uint32_t idx = atomicAdd(&a.cand_cnt[j], c);
-#pragma unroll
-        for (int t = 0; t < 4; ++t)
-#pragma unroll
-          for (int r = 0; r < 16; ++r) {
-            const int rl_ = t * 32 + acc_row(r, lane);
-            const float sc = acc[t][r] * osc;
-            if (rl_ < rows && sc >= th) {
-              if (idx < a.cap) {
-                a.cand_s[j * a.cap + idx] = sc;
-                a.cand_r[j * a.cap + idx] = (int)(rbase + rl_);
-              }
-              ++idx;
-            }
-          }
-      }
-      // no LDS use here: score_tile's barriers protect the slabs
-    } else {
     const bool hot = mx >= ls[KL - 1];
     if (__ballot(hot) != 0ull) {
       // Park this wave's 64 scores per lane in LDS (free after the K loop) and
@@ -539,17 +496,14 @@ __global__ __launch_bounds__(kWG, 2) void k_score(ScoreArgs a) {
       }
     }
     __syncthreads();   // LDS is reused by the next tile's first slab
-    }
   }
-  if constexpr (MODE != kModeFilter) {
-    if (j < a.nq) {
-      const int slot = lane >> 5;
-      const int64_t o = ((j * a.splits + split) * 2 + slot) * (int64_t)KL;
+  if (j < a.nq) {
+    const int slot = lane >> 5;
+    const int64_t o = ((j * a.splits + split) * 2 + slot) * (int64_t)KL;
 #pragma unroll
-      for (int p = 0; p < KL; ++p) {
-        a.part_s[o + p] = ls[p];
-        a.part_r[o + p] = lr[p];
-      }
+    for (int p = 0; p < KL; ++p) {
+      a.part_s[o + p] = ls[p];
+      a.part_r[o + p] = lr[p];
     }
   }
   if constexpr (MODE == kModeFallback) {
@@ -567,8 +521,7 @@ __global__ __launch_bounds__(kWG, 2) void k_score(ScoreArgs a) {
     for (int q = wave; q < qrows; q += kWG / 64) {
       const int64_t jq = qbase + q;
       if (a.qflag[jq] == 0u) continue;
-      merge_query<KL, KL>(jq, a.splits * 2 * KL, a.k, a.part_s, a.part_r, a.meta, a.ids, a.out_s, a.out_i,
-                          a.out_bound, nullptr);
+      merge_query<KL>(jq, a.splits * 2 * KL, a.k, a.part_s, a.part_r, a.meta, a.ids, a.out_s, a.out_i, a.out_bound);
     }
   }
 }
@@ -576,14 +529,12 @@ __global__ __launch_bounds__(kWG, 2) void k_score(ScoreArgs a) {
 // Fold a lane's share of candidates into a sorted register list, then take k
 // rounds of the best list head of the wave under (score desc, row asc).  Rows
 // are distinct, so the winning head identifies its lane.  Writes the k picks
-// (ids mapped to global ids) and/or the k-th score.  The head's order is that
-// of the key (order-encoded score, complement of the row): larger is better;
+// (ids mapped to global ids).  The head's order is that of the key (order-encoded score, complement of the row): larger is better;
 // scores are taken + 0.0f so that -0 and +0 are equal, as in `better`.
 template <int KL>
 __device__ __forceinline__ void wave_select(int k, float (&ls)[KL], int (&lr)[KL], int64_t j,
                                             const int64_t* __restrict__ ids, float* __restrict__ out_s,
-                                            int64_t* __restrict__ out_i, float* __restrict__ kth,
-                                            float kth_drop = 0.0f) {
+                                            int64_t* __restrict__ out_i) {
   const int lane = threadIdx.x & 63;
   for (int t = 0; t < k; ++t) {
     const unsigned long long key =
@@ -601,11 +552,8 @@ __device__ __forceinline__ void wave_select(int k, float (&ls)[KL], int (&lr)[KL
       lr[KL - 1] = kNoRow;
     }
     if (lane == 0) {
-      if (out_s) {
-        out_s[j * k + t] = (br == kNoRow) ? -INFINITY : bs;
-        out_i[j * k + t] = (br == kNoRow) ? -1 : ids[br];
-      }
-      if (kth && t == k - 1) kth[j] = (br == kNoRow) ? -INFINITY : rd32((double)bs - (double)kth_drop);
+      out_s[j * k + t] = (br == kNoRow) ? -INFINITY : bs;
+      out_i[j * k + t] = (br == kNoRow) ? -1 : ids[br];
     }
   }
 }
@@ -615,40 +563,34 @@ __device__ __forceinline__ bool write_bad(const QMeta& m, int64_t j, int k, floa
   const int lane = threadIdx.x & 63;
   if (lane == 0 && bound) bound[j] = m.bound;
   if (!m.bad) return false;
-  if (out_s)
-    for (int t = lane; t < k; t += 64) {
-      out_s[j * k + t] = __builtin_nanf("");
-      out_i[j * k + t] = -1;
-    }
+  for (int t = lane; t < k; t += 64) {
+    out_s[j * k + t] = __builtin_nanf("");
+    out_i[j * k + t] = -1;
+  }
   return true;
 }
 
-// One wave per query: the k best of the per-lane lists (segments of SEG sorted
-// entries, of which only the first k can matter), each lane folding its share
-// into a register list of KL.  With KL >= k and the shares' lists complete this
-// is the exact k best; otherwise the k picks are still k distinct entries.
-template <int KL, int SEG = KL>
+// One wave per query: the k best of the per-lane lists (segments of KL >= k
+// sorted entries, of which only the first k can matter), each lane folding its
+// share into a register list of KL.
+template <int KL>
 __global__ __launch_bounds__(256) void k_topk_merge(int64_t nq, int cands, int k, const float* __restrict__ ps,
                                                     const int32_t* __restrict__ pr, const QMeta* __restrict__ meta,
                                                     const int64_t* __restrict__ ids, float* __restrict__ out_s,
-                                                    int64_t* __restrict__ out_i, float* __restrict__ bound,
-                                                    float* __restrict__ kth) {
+                                                    int64_t* __restrict__ out_i, float* __restrict__ bound) {
   const int64_t j = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
   if (j >= nq) return;
-  merge_query<KL, SEG>(j, cands, k, ps, pr, meta, ids, out_s, out_i, bound, kth);
+  merge_query<KL>(j, cands, k, ps, pr, meta, ids, out_s, out_i, bound);
 }
 
 // One wave: the merge of query j's lists (the body of k_topk_merge).
-template <int KL, int SEG>
+template <int KL>
 __device__ void merge_query(int64_t j, int cands, int k, const float* __restrict__ ps,
                             const int32_t* __restrict__ pr, const QMeta* __restrict__ meta,
                             const int64_t* __restrict__ ids, float* __restrict__ out_s, int64_t* __restrict__ out_i,
-                            float* __restrict__ bound, float* __restrict__ kth) {
+                            float* __restrict__ bound) {
   const int lane = threadIdx.x & 63;
-  if (write_bad(meta[j], j, k, out_s, out_i, bound)) {
-    if (kth && lane == 0) kth[j] = __builtin_nanf("");
-    return;
-  }
+  if (write_bad(meta[j], j, k, out_s, out_i, bound)) return;
   const float* s = ps + j * (int64_t)cands;
   const int32_t* r = pr + j * (int64_t)cands;
   float ls[KL];
@@ -659,16 +601,15 @@ __device__ void merge_query(int64_t j, int cands, int k, const float* __restrict
     lr[p] = kNoRow;
   }
   // a lane's next entries loaded together before any is used (one load
-  // after another's test had put two round trips per entry on the path);
-  // four for the sample's unsorted entries, two beside 16-entry lists
-  constexpr int kU = (SEG == 1 || KL < 16) ? 4 : 2;
+  // after another's test had put two round trips per entry on the path)
+  constexpr int kU = 2;
   for (int c0 = lane; c0 < cands; c0 += 64 * kU) {
     float cs[kU];
     int cr[kU];
 #pragma unroll
     for (int u = 0; u < kU; ++u) {
       const int c = c0 + 64 * u;
-      const bool in = c < cands && (c % SEG) < k;   // not below rank k of its own sorted segment
+      const bool in = c < cands && (c % KL) < k;   // not below rank k of its own sorted segment
       cr[u] = in ? r[c] : kNoRow;
       cs[u] = in ? s[c] : -INFINITY;
     }
@@ -678,140 +619,62 @@ __device__ void merge_query(int64_t j, int cands, int k, const float* __restrict
       list_insert<KL>(ls, lr, cs[u], cr[u]);
     }
   }
-  // the sample's k-th hi-only score, lowered by 2 err: a threshold no row of
-  // the final top-k falls below in hi-only terms
-  wave_select<KL>(k, ls, lr, j, ids, out_s, out_i, kth, kth ? 2.0f * meta[j].err : 0.0f);
+  wave_select<KL>(k, ls, lr, j, ids, out_s, out_i);
 }
 
-// ------------------------------------------------------------------ radix selection (k > 16)
+// ------------------------------------------------------------------ thresholds
 constexpr int kCandCap = 4096;   // candidate buffer entries per query
 constexpr int kNoAllocMaxQ = 256;   // queries of one allocation-free scoring call
 
-// The kth largest (1-based) of keys[0, n) in LDS, found one 8-bit digit at a
-// time from the top: a histogram of the digit among keys that match the
-// digits found so far, then the digit whose suffix count first reaches kth.
-// Returns the key; *ties is the number of keys equal to it and *above the
-// number of keys above it.  Called by the single wave of a workgroup.
-__device__ uint32_t wave_kth_key(const uint32_t* keys, int n, int kth, uint32_t* hist, int* ties, int* above) {
-  const int lane = threadIdx.x & 63;
-  uint32_t prefix = 0u, mask = 0u;
-  int need = kth, tie = 0;
-  for (int shift = 24; shift >= 0; shift -= 8) {
-    for (int b = lane; b < 256; b += 64) hist[b] = 0u;
-    __syncthreads();   // (a workgroup of one wave)
-    for (int i = lane; i < n; i += 64) {
-      const uint32_t key = keys[i];
-      if ((key & mask) == prefix) atomicAdd(&hist[(key >> shift) & 255u], 1u);
-    }
-    __syncthreads();
-    // lane L holds bins 4L .. 4L + 3; suffix sums over the lanes above
-    uint32_t h[4];
+// A lower bound, within 2^-15 relative, of the k-th largest of a wave's order
+// keys (R per lane, 0 for none): the top 24 bits of it, found bit by bit from
+// the top, one ballot and one scalar bit count per lane register and bit, so
+// the cost does not depend on k.  (Sorted per-lane lists and k rounds of the
+// best head: 8.5 us for 1,024 queries of 128 keys at k = 10, 41 us for 300
+// queries of up to 7,360 at k = 50; the threshold kernel built on this: 6.8 us
+// and, for 736 keys, 13 us.)  0 when fewer than k keys
+// are set.  nr: the registers in use (uniform).
+template <int R>
+__device__ __forceinline__ uint32_t wave_kth_floor(const uint32_t (&key)[R], int nr, int k) {
+  uint32_t T = 0u;
+  for (int bit = 31; bit >= 8; --bit) {
+    const uint32_t c = T | (1u << bit);
+    int n = 0;
 #pragma unroll
-    for (int b = 0; b < 4; ++b) h[b] = hist[4 * lane + b];
-    const uint32_t sl = h[0] + h[1] + h[2] + h[3];
-    uint32_t incl = sl;
-    for (int o = 1; o < 64; o <<= 1) {
-      const uint32_t t = __shfl_down(incl, o);
-      if (lane + o < 64) incl += t;
-    }
-    uint32_t acc = incl - sl;   // keys in higher bins than this lane's
-    int digit = -1, rest = 0, cnt = 0;
-#pragma unroll
-    for (int b = 3; b >= 0; --b) {
-      if (digit < 0 && acc < (uint32_t)need && acc + h[b] >= (uint32_t)need) {
-        digit = 4 * lane + b;
-        rest = need - (int)acc;
-        cnt = (int)h[b];
-      }
-      acc += h[b];
-    }
-    const int src = __builtin_ctzll(__ballot(digit >= 0));   // exactly one lane found it
-    digit = __shfl(digit, src);
-    need = __shfl(rest, src);
-    tie = __shfl(cnt, src);
-    prefix |= (uint32_t)digit << shift;
-    mask |= 255u << shift;
-    __syncthreads();
+    for (int r = 0; r < R; ++r)
+      if (r < nr) n += __popcll(__ballot(key[r] >= c));
+    T = n >= k ? c : T;
   }
-  *ties = tie;
-  *above = kth - need;
-  return prefix;
+  return T;
 }
 
-// One wave per query: the k best (score desc, row asc) of the candidate
-// buffer, by radix selection of the kth score (and, among the scores equal to
-// it, of the rows), then a bitonic sort of the k winners across the wave.
-__global__ __launch_bounds__(64) void k_cand_select_radix(int64_t nq, uint32_t cap, int k,
-                                                          const uint32_t* __restrict__ cnt,
-                                                          const float* __restrict__ cs, const int32_t* __restrict__ cr,
-                                                          const QMeta* __restrict__ meta,
-                                                          const int64_t* __restrict__ ids, float* __restrict__ out_s,
-                                                          int64_t* __restrict__ out_i, float* __restrict__ bound,
-                                                          uint32_t* __restrict__ qflag, uint32_t* __restrict__ tflag) {
-  __shared__ uint32_t keys[kCandCap];
-  __shared__ uint32_t hist[256];
-  __shared__ uint32_t n_win;
-  __shared__ unsigned long long win[64];
+// One wave per query: the threshold of the filter pass from the sample's
+// entries (scores of distinct rows): the k-th best, lowered by 2 err, so that
+// no row of the final top-k falls below it in hi-only terms.  Beyond 1,024
+// entries several share a key as their maximum: the k-th best key is then
+// still the score of k distinct rows, only a little lower.
+constexpr int kThrKeys = 16;   // keys per lane
+
+__global__ __launch_bounds__(256) void k_sample_thr(int64_t nq, int entries, int folded, int k,
+                                                    const float* __restrict__ ps, const QMeta* __restrict__ meta,
+                                                    float* __restrict__ thr) {
   const int lane = threadIdx.x & 63;
-  const int64_t j = blockIdx.x;
+  const int64_t j = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
   if (j >= nq) return;
-  const uint32_t c = cnt[j];
-  const bool over = c > cap;
-  if (lane == 0) {
-    qflag[j] = over ? 1u : 0u;
-    if (over) atomicOr(&tflag[j / kTB], 1u);
-  }
-  if (write_bad(meta[j], j, k, out_s, out_i, bound) || over) return;
-  const float* sj = cs + j * cap;
-  const int32_t* rj = cr + j * cap;
-  const int n = (int)c;
-  // order keys of the scores (-0 counts as +0, as in the comparison)
-  for (int i = lane; i < n; i += 64) keys[i] = f2ord(sj[i] + 0.0f);
-  const int kk = min(k, n);
-  if (lane == 0) n_win = 0u;
-  win[lane] = 0ull;
-  __syncthreads();   // (a workgroup of one wave)
-  if (kk > 0) {
-    int ties = 0, above = 0;
-    const uint32_t T = wave_kth_key(keys, n, kk, hist, &ties, &above);
-    const int need_t = kk - above;    // entries equal to T to take
-    // Entries above T are all taken; of those equal to T, the need_t with the
-    // smallest rows: the keys become ~row for the ties (the larger, the
-    // smaller the row; every tie key exceeds 0) and 0 for the rest.
-    uint32_t R = 0u;
-    if (need_t < ties) {
-      for (int i = lane; i < n; i += 64) keys[i] = (keys[i] == T) ? ~(uint32_t)rj[i] : 0u;
-      __syncthreads();
-      int t2 = 0, a2 = 0;
-      R = wave_kth_key(keys, n, need_t, hist, &t2, &a2);
-    }
-    for (int i = lane; i < n; i += 64) {
-      const uint32_t ord = f2ord(sj[i] + 0.0f);
-      const uint32_t row = (uint32_t)rj[i];
-      const bool take = ord > T || (ord == T && (need_t >= ties || ~row >= R));
-      if (take) win[atomicAdd(&n_win, 1u)] = ((unsigned long long)ord << 32) | (unsigned long long)(~row);
-    }
-  }
-  __syncthreads();
-  // bitonic sort, descending, one key per lane (empty slots hold 0)
-  unsigned long long key = win[lane];
-  for (int size = 2; size <= 64; size <<= 1) {
-    for (int stride = size >> 1; stride > 0; stride >>= 1) {
-      const unsigned long long other = __shfl_xor(key, stride);
-      const bool desc = (lane & size) == 0;          // the direction of this run
-      const bool lower = (lane & stride) == 0;
-      key = (desc == lower) ? (key > other ? key : other) : (key < other ? key : other);
-    }
-  }
-  if (lane < k) {
-    if (lane < kk) {
-      out_s[j * k + lane] = ord2f((uint32_t)(key >> 32));
-      out_i[j * k + lane] = ids[~(uint32_t)(key & 0xffffffffull)];
-    } else {
-      out_s[j * k + lane] = -INFINITY;
-      out_i[j * k + lane] = -1;
-    }
-  }
+  const float* s = ps + j * (int64_t)entries;
+  const QMeta m = meta[j];
+  // folded: the sample shared entries and left order codes
+  auto code = [&](int e) { return folded ? __float_as_uint(s[e]) : f2ord(s[e] + 0.0f); };
+  uint32_t key[kThrKeys];
+#pragma unroll
+  for (int r = 0; r < kThrKeys; ++r) key[r] = lane + r * 64 < entries ? code(lane + r * 64) : 0u;
+  for (int e0 = 64 * kThrKeys; e0 < entries; e0 += 64 * kThrKeys)
+#pragma unroll
+    for (int r = 0; r < kThrKeys; ++r)
+      if (e0 + lane + r * 64 < entries) key[r] = max(key[r], code(e0 + lane + r * 64));
+  const uint32_t T = wave_kth_floor<kThrKeys>(key, min(kThrKeys, (entries + 63) / 64), k);
+  if (lane == 0)
+    thr[j] = m.bad ? __builtin_nanf("") : (T == 0u ? -INFINITY : rd32((double)ord2f(T) - 2.0 * (double)m.err));
 }
 
 // ------------------------------------------------------------------ filter pass on the screen's pipeline
@@ -822,32 +685,42 @@ using FilterTile = Tile<2, 4, 2, 1, 4>;
 using FilterTileL = Tile<4, 4, 2, 2, 4>;
 constexpr int kFilterGroupQ = 8;   // query tiles per group in the tile order
 constexpr int kSampleEntries = 4;  // entries per query and 128-row store tile of the sample pass
+constexpr int64_t kSampleTiles = 2048;   // sample tiles with entries of their own (later ones share them)
 constexpr int64_t kFilterLargeMinTiles = 1024;   // large filter tiles from this many per launch
 
-// The threshold plan's filter pass (hi-only scores H) for D = 64 NS: one
-// C::BM x C::BN tile (store rows x queries) per workgroup, each wave 64 rows x
-// 32 TJ queries (2 x TJ tiles of v_mfma_f32_32x32x16_f16); K-slabs of 64
-// through two LDS stages, one barrier per slab, every load issued three slabs
-// before its LDS store (SETS = 3) or one (SETS = 1, for the large tile).  For
-// even code widths four threads share a row's 64-code slab (16 codes, B / 2
-// whole words each), so every wave unpacks; for odd widths threads 0 to
-// 2 BM - 1 take 32 codes (B words) each.  Codes are unpacked straight to fp16
-// (exact for B <= 12); the queries' hi part is loaded in 16-byte pieces.  Tile
-// order: groups of 8 query tiles against every store tile, query tile
-// fastest, each XCD a contiguous range, so an XCD holds its query tiles in L2
-// while the codes stream past.  Every row with H >= the query's threshold is
-// appended to its candidate buffer, as in k_score's filter mode.
+// The threshold plan's filter pass (hi-only scores H): one C::BM x C::BN tile
+// (store rows x queries) per workgroup, each wave 64 rows x 32 TJ queries (2 x
+// TJ tiles of v_mfma_f32_32x32x16_f16); K-slabs of 64 through two LDS stages,
+// one barrier per slab, every load issued three slabs before its LDS store
+// (SETS = 3) or one (SETS = 1, for the large tile).  Four threads share a
+// row's 64-code slab (16 codes each: B / 2 words, or the (B + 1) / 2 that hold
+// them), so every wave unpacks.  Codes are unpacked straight to fp16 (exact
+// for B <= 12); the queries' hi part is loaded in 16-byte pieces.  The slab
+// loop takes D at run time, six slabs (both LDS stages, all three register
+// sets) per trip: the offsets of a slab are one scalar, and loads past the
+// last slab fall outside the buffer bound (no memory touched).  Tile order:
+// groups of 8 query tiles against every store tile, query tile fastest, each
+// XCD a contiguous range, so an XCD holds its query tiles in L2 while the codes
+// stream past.  Every row with H >= the query's threshold is appended to its
+// candidate buffer.  (120,001 rows x 300 queries at D = 384, 9-bit codes: 106
+// us in the former one-stage kernel with two waves' worth of loads in flight,
+// 81 us here; its sample pass 54 -> 16 us.  The run-time slab loop is as fast as
+// one unrolled for D = 768: 54 us at 23,969 rows x 1,024 queries, 2.30 ms at
+// 361,802 x 4,096, both as before.)
 // SAMPLE (FilterTile only): the sample pass of the threshold plan over store
-// tiles [0, tile_end) instead: per query and tile, the best H of each of the
-// four lanes holding the query (disjoint sets of 32 rows) at entries [4 t,
-// 4 t + 4) of the query's partial list.  The k-th best of these entries is the
-// H of k distinct rows, so at most the sample's k-th best H: a valid base for
-// the threshold (lower only where several of the best rows share a lane).
+// tiles [0, tile_end) (all of them whole) instead: per query and tile, the best
+// H of each of the four lanes holding the query (disjoint sets of 32 rows) at
+// entries [4 t, 4 t + 4) of the query's list, t the tile (modulo sample_tiles:
+// beyond those, tiles share entries as their maximum, order-encoded).  The
+// k-th best of these entries is the H of k distinct rows, so at most the
+// sample's k-th best H: a valid base for the threshold (lower only where
+// several of the best rows share a lane).
 // a.nqt and a.tile_end count tiles of this kernel's size.
-template <class C, int B, int NS, bool SAMPLE, int SETS>
+template <class C, int B, bool SAMPLE, int SETS>
 __global__ __launch_bounds__(C::kThreads, C::kMinWaves) void k_filter(ScoreArgs a) {
   static_assert(!SAMPLE || (C::BM == kTB && C::TJ == 1), "the sample pass runs on 128-row tiles of one query block");
   static_assert(SETS == 1 || SETS == 3, "one or three register sets");
+  static_assert(C::kThreads == 4 * C::BM, "four threads per row");
   __shared__ _Float16 lds[C::kLdsHalves];
   const int64_t nt = a.tile_end;   // store tiles of this pass (tile_begin = 0)
   // 32-bit index arithmetic: the host keeps the grid (nqt * nt) below 2^31
@@ -887,34 +760,35 @@ __global__ __launch_bounds__(C::kThreads, C::kMinWaves) void k_filter(ScoreArgs 
   const __amdgpu_buffer_rsrc_t rsC = __builtin_amdgcn_make_buffer_rsrc(
       const_cast<uint32_t*>(a.codes + rbase * a.row_words), (short)0, (int)(rows * a.row_words * 4), 0x00020000);
   const __amdgpu_buffer_rsrc_t rsQ = tile_rsrc(a.qhi + qbase * a.D, qrows, a.D);
-  // Code unpacking: for even widths every thread takes 16 codes of its row's
-  // 64-code slab (B / 2 whole words: a quarter of the row), so all waves
-  // share it; for odd widths threads 0 to 2 BM - 1 take 32 codes (B words)
-  // each.  (With half the waves unpacking, the other half waited at every
-  // slab's barrier.)
-  constexpr bool kQuarter = (B % 2) == 0;
-  constexpr int kNW = kQuarter ? B / 2 : B;   // code words per thread and slab
-  constexpr int kNC = kQuarter ? 16 : 32;     // codes per thread and slab
-  static_assert(!kQuarter || C::kThreads == 4 * C::BM, "four threads per row");
-  static_assert(C::kThreads >= 2 * C::BM, "two threads per row for odd widths");
-  const int urow = kQuarter ? tid >> 2 : tid >> 1;
-  const int upart = kQuarter ? tid & 3 : tid & 1;
-  const bool unpacker = kQuarter || tid < 2 * C::BM;
+  // this thread's share of a slab: 16 codes of row tid / 4, and kPerB 16-byte
+  // pieces of the queries; byte offsets of slab 0
+  constexpr int kNW = (B + 1) / 2;
+  const int urow = tid >> 2, upart = tid & 3;
+  const uint32_t voc =
+      urow < rows ? (uint32_t)(urow * a.row_words + (upart >> 1) * B + (upart & 1) * (B / 2)) * 4u : kOffOOB;
+  uint32_t voq[C::kPerB];
+#pragma unroll
+  for (int q = 0; q < C::kPerB; ++q) {
+    const int c = tid + C::kThreads * q;
+    voq[q] = (c >> 3) < qrows ? (uint32_t)((c >> 3) * a.D + (c & 7) * 8) * 2u : kOffOOB;
+  }
+  // columns k0 + cc (codes) and k0 + cq (queries) must lie inside the row (D is
+  // a multiple of 32, so the last slab may be half full)
+  const int cc = (upart >> 1) * 32, cq = (tid & 7) * 8;
   auto load = [&](int s, uint32_t (&cw)[kNW], uint4 (&qv)[C::kPerB]) {
     const int k0 = s * kBK;
-    const bool ok = unpacker && urow < rows && k0 < a.D;
-    const uint32_t w0 = (uint32_t)(urow * a.row_words + (int64_t)(k0 / 32) * B + upart * kNW);
-    load_group<kNW>(rsC, ok, w0, cw);
-    slab_load_n<C::kPerB>(rsQ, qrows, a.D, k0, a.D, qv, C::kThreads);
+    load_words<kNW>(rsC, k0 + cc < a.D ? voc : kOffOOB, (uint32_t)(2 * s * B) * 4u, cw);
+#pragma unroll
+    for (int q = 0; q < C::kPerB; ++q)
+      qv[q] = __builtin_bit_cast(
+          uint4, __builtin_amdgcn_raw_buffer_load_b128(rsQ, k0 + cq < a.D ? voq[q] : kOffOOB, (uint32_t)k0 * 2u, 0));
   };
   auto store = [&](int st, const uint32_t (&cw)[kNW], const uint4 (&qv)[C::kPerB]) {
-    if (unpacker) {
-      _Float16 h[kNC];
-      unpack_codes<B, kNC>(cw, h);
-      _Float16* dst = sa(st) + urow * kLdk + upart * kNC;
-#pragma unroll
-      for (int i = 0; i < kNC; i += 8) *reinterpret_cast<uint4*>(dst + i) = *reinterpret_cast<const uint4*>(h + i);
-    }
+    _Float16 h[16];
+    unpack16<B>(cw, upart & 1, h);
+    _Float16* dst = sa(st) + urow * kLdk + upart * 16;
+    *reinterpret_cast<uint4*>(dst) = *reinterpret_cast<const uint4*>(h);
+    *reinterpret_cast<uint4*>(dst + 8) = *reinterpret_cast<const uint4*>(h + 8);
     slab_store_n<C::kPerB>(sb(st), qv, C::kThreads);
   };
   auto compute = [&](int st) {
@@ -932,6 +806,7 @@ __global__ __launch_bounds__(C::kThreads, C::kMinWaves) void k_filter(ScoreArgs 
           acc[x][y] = __builtin_amdgcn_mfma_f32_32x32x16_f16(fa[x], fb[y], acc[x][y], 0, 0, 0);
     }
   };
+  const int S = (a.D + kBK - 1) / kBK;
   if constexpr (SETS == 3) {
     uint32_t cw[3][kNW];
     uint4 qv[3][C::kPerB];
@@ -940,15 +815,16 @@ __global__ __launch_bounds__(C::kThreads, C::kMinWaves) void k_filter(ScoreArgs 
     store(0, cw[0], qv[0]);
     load(3, cw[0], qv[0]);
     __syncthreads();
+    for (int s = 0; s < S; s += 6) {
 #pragma unroll
-    for (int s = 0; s < NS; ++s) {
-      compute(s & 1);
-      if (s + 1 < NS) {
-        const int u = (s + 1) % 3;
-        store((s + 1) & 1, cw[u], qv[u]);
-        load(s + 4, cw[u], qv[u]);   // past the last slab: zeros, no memory touched
+      for (int u = 0; u < 6; ++u) {
+        compute(u & 1);
+        if (s + u + 1 >= S) break;
+        const int v = (u + 1) % 3;
+        store((u + 1) & 1, cw[v], qv[v]);
+        load(s + u + 4, cw[v], qv[v]);
+        __syncthreads();
       }
-      __syncthreads();
     }
   } else {
     uint32_t cw[kNW];
@@ -957,34 +833,31 @@ __global__ __launch_bounds__(C::kThreads, C::kMinWaves) void k_filter(ScoreArgs 
     store(0, cw, qv);
     load(1, cw, qv);
     __syncthreads();
+    for (int s = 0; s < S; s += 2) {
 #pragma unroll
-    for (int s = 0; s < NS; ++s) {
-      compute(s & 1);
-      if (s + 1 < NS) {
-        store((s + 1) & 1, cw, qv);
-        if (s + 2 < NS) load(s + 2, cw, qv);
+      for (int u = 0; u < 2; ++u) {
+        compute(u);
+        if (s + u + 1 >= S) break;
+        store(u ^ 1, cw, qv);
+        load(s + u + 2, cw, qv);
+        __syncthreads();
       }
-      __syncthreads();
     }
   }
   if constexpr (SAMPLE) {
-    // this lane's best H over its 32 rows (the lowest row among equals)
+    // this lane's best H over its 32 rows
     float best = -INFINITY;
-    int brow = kNoRow;
 #pragma unroll
     for (int x = 0; x < C::TI; ++x)
 #pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int rl_ = wm * 64 + x * 32 + acc_row(r, lane);   // ascending in (x, r)
-        const float sc = acc[x][0][r] * osc[0];
-        const bool take = rl_ < rows && sc > best;
-        best = take ? sc : best;
-        brow = take ? (int)(rbase + rl_) : brow;
-      }
+      for (int r = 0; r < 16; ++r) best = fmaxf(best, acc[x][0][r]);
     if (jv[0]) {
-      const int64_t o = j[0] * (nt * kSampleEntries) + (rbase / kTB) * kSampleEntries + wm * 2 + (lane >> 5);
-      a.part_s[o] = best;
-      a.part_r[o] = brow;
+      const int tile = (int)(l / gsize);
+      const int64_t o = j[0] * ((int64_t)a.sample_tiles * kSampleEntries) +
+                        (tile % a.sample_tiles) * kSampleEntries + wm * 2 + (lane >> 5);
+      // (osc > 0; folded entries were set to order code 0 and are read as such)
+      if (nt <= a.sample_tiles) a.part_s[o] = best * osc[0];
+      else atomicMax(reinterpret_cast<uint32_t*>(a.part_s) + o, f2ord(best * osc[0]));
     }
     return;
   }
@@ -1034,30 +907,26 @@ __global__ __launch_bounds__(C::kThreads, C::kMinWaves) void k_filter(ScoreArgs 
 
 // large: the filter pass on FilterTileL (a.nqt and a.tile_end in its tiles)
 template <int B, bool SAMPLE>
-lam_status launch_filter(int b, int D, bool large, dim3 grid, hipStream_t st, const ScoreArgs& a) {
+lam_status launch_filter(int b, bool large, dim3 grid, hipStream_t st, const ScoreArgs& a) {
   if (b == B) {
     if constexpr (!SAMPLE) {
       if (large) {
-        if (D == 768)
-          hipLaunchKernelGGL((k_filter<FilterTileL, B, 12, false, 1>), grid, dim3(FilterTileL::kThreads), 0, st, a);
-        else
-          hipLaunchKernelGGL((k_filter<FilterTileL, B, 16, false, 1>), grid, dim3(FilterTileL::kThreads), 0, st, a);
+        hipLaunchKernelGGL((k_filter<FilterTileL, B, false, 1>), grid, dim3(FilterTileL::kThreads), 0, st, a);
         LAM_HIP(hipGetLastError());
         return LAM_OK;
       }
     }
-    if (D == 768) hipLaunchKernelGGL((k_filter<FilterTile, B, 12, SAMPLE, 3>), grid, dim3(FilterTile::kThreads), 0, st, a);
-    else hipLaunchKernelGGL((k_filter<FilterTile, B, 16, SAMPLE, 3>), grid, dim3(FilterTile::kThreads), 0, st, a);
+    hipLaunchKernelGGL((k_filter<FilterTile, B, SAMPLE, 3>), grid, dim3(FilterTile::kThreads), 0, st, a);
     LAM_HIP(hipGetLastError());
     return LAM_OK;
   }
-  if constexpr (B < 12) return launch_filter<B + 1, SAMPLE>(b, D, large, grid, st, a);
+  if constexpr (B < 12) return launch_filter<B + 1, SAMPLE>(b, large, grid, st, a);
   set_error("scoring supports codes of at most 12 bits (got %d)", b);
   return LAM_ESTATE;
 }
 
 // ------------------------------------------------------------------ rescoring
-constexpr int kRescoreCap = 256;     // candidates near the k-th score rescored per query
+constexpr int kRescoreCap = 1024;    // candidates near the k-th score rescored per query
 constexpr int kRescoreThreads = 256;
 constexpr int kRescoreLanes = 8;     // lanes per rescored row
 
@@ -1123,63 +992,20 @@ __device__ __forceinline__ void rescore_sort(int64_t j, uint32_t m, int kk, int 
   }
 }
 
-// One workgroup per query, after the selection of the k best hi-only scores H
-// among the candidates.  With h_k the k-th of them, every row of the final
-// top-k has H >= h_k - 2 err (k rows have S >= h_k - err, and |H - S| <= err),
-// so those candidates are rescored from the codes and the float32 query,
-// summed in binary64 and rounded once to float32, and the k best by (S desc,
-// row asc) replace the selection's output.  More than kRescoreCap such
-// candidates (many near-equal scores) flag the query for the exact fallback
-// pass.  Queries already flagged, or invalid, are left as the selection wrote
-// them.  Eight lanes share a row (32 rows in flight per workgroup); a lane
-// takes whole groups of 32 codes (B words), unpacked as the scoring kernel
-// unpacks them (exactly, to fp16).
-template <int B>
-__global__ __launch_bounds__(kRescoreThreads) void k_rescore(
-    int64_t nq, uint32_t cap, int k, const uint32_t* __restrict__ cnt, const float* __restrict__ cs,
-    const int32_t* __restrict__ cr, const QMeta* __restrict__ meta, const int64_t* __restrict__ ids,
-    const float* __restrict__ q, double step, const uint32_t* __restrict__ codes, int64_t row_words, int D,
-    float* __restrict__ out_s, int64_t* __restrict__ out_i, uint32_t* __restrict__ qflag,
-    uint32_t* __restrict__ tflag) {
-  __shared__ int32_t rows[kRescoreCap];
-  __shared__ unsigned long long keys[kRescoreCap];
-  __shared__ uint32_t m_sh;
-  const int tid = threadIdx.x;
-  const int64_t j = blockIdx.x;
-  if (j >= nq) return;
-  const QMeta mj = meta[j];
-  if (qflag[j] != 0u || mj.bad) return;
-  const uint32_t c = cnt[j];
-  const int kk = (int)min((uint32_t)k, c);
-  if (kk == 0) return;
-  const float thr = rd32((double)out_s[j * k + kk - 1] - 2.0 * (double)mj.err);
-  if (tid == 0) m_sh = 0u;
-  __syncthreads();
-  for (uint32_t i = tid; i < c; i += kRescoreThreads) {
-    if (cs[j * cap + i] >= thr) {
-      const uint32_t p = atomicAdd(&m_sh, 1u);
-      if (p < (uint32_t)kRescoreCap) rows[p] = cr[j * cap + i];
-    }
-  }
-  __syncthreads();
-  const uint32_t m = m_sh;
-  if (m > (uint32_t)kRescoreCap) {
-    if (tid == 0) {
-      qflag[j] = 1u;
-      atomicOr(&tflag[j / kTB], 1u);
-    }
-    return;
-  }
-  rescore_sort<B>(j, m, kk, k, rows, keys, ids, q, step, codes, row_words, D, out_s, out_i);
-}
-
-// The selection and the rescoring in one workgroup per query (k <= 16):
-// wave 0 finds the k-th best hi-only score H among the candidates (per-lane
-// lists of 16, then k rounds of the wave's best head as in wave_select, only
-// the last one kept), and the workgroup then rescores the candidates within
-// 2 err of it as k_rescore does.  Also does the selection's other work:
-// flags an overflowed buffer, writes the bound, NaN outputs for an invalid
-// query, and (-inf, -1) past the candidates.
+// One workgroup per query: the selection among the candidates and the exact
+// scores.  With h_k the k-th best hi-only score H of the candidates, every row
+// of the final top-k has H >= h_k - 2 err (k rows have S >= h_k - err, and
+// |H - S| <= err), so those candidates are rescored from the codes and the
+// float32 query, summed in binary64 and rounded once to float32, and the k
+// best by (S desc, row asc) are the answer.  Any lower bound of h_k serves:
+// wave 0 takes the one of wave_kth_floor (beyond 1,024 candidates several
+// share a key as their maximum), which costs the same for every k.  More than
+// kRescoreCap rows to rescore (many near-equal scores) flag the query for the
+// exact fallback pass, as an overflowed buffer does.  Also writes the bound,
+// NaN outputs for an invalid query, and (-inf, -1) past the candidates.  Eight
+// lanes share a rescored row (32 rows in flight per workgroup); a lane takes
+// whole groups of 32 codes (B words), unpacked as the scoring kernel unpacks
+// them (exactly, to fp16).
 template <int B>
 __global__ __launch_bounds__(kRescoreThreads) void k_select_rescore(
     int64_t nq, uint32_t cap, int k, const uint32_t* __restrict__ cnt, const float* __restrict__ cs,
@@ -1187,7 +1013,6 @@ __global__ __launch_bounds__(kRescoreThreads) void k_select_rescore(
     const float* __restrict__ q, double step, const uint32_t* __restrict__ codes, int64_t row_words, int D,
     float* __restrict__ out_s, int64_t* __restrict__ out_i, float* __restrict__ bound, uint32_t* __restrict__ qflag,
     uint32_t* __restrict__ tflag) {
-  constexpr int KL = 16;
   __shared__ int32_t rows[kRescoreCap];
   __shared__ unsigned long long keys[kRescoreCap];
   __shared__ uint32_t m_sh;
@@ -1228,52 +1053,21 @@ __global__ __launch_bounds__(kRescoreThreads) void k_select_rescore(
     fr[u] = i < c ? cr[j * cap + i] : 0;
   }
   if (wave == 0) {
-    float ls[KL];
-    int lr[KL];
+    uint32_t key[kThrKeys];
 #pragma unroll
-    for (int p = 0; p < KL; ++p) {
-      ls[p] = -INFINITY;
-      lr[p] = kNoRow;
+    for (int r = 0; r < kThrKeys; ++r) {
+      const uint32_t i = (uint32_t)(lane + r * 64);
+      key[r] = i < c ? f2ord(cs[j * cap + i] + 0.0f) : 0u;
     }
-    // a lane's first kPre candidates are loaded before any is inserted
-    constexpr int kPre = 8;
-    float ps[kPre];
-    int pr[kPre];
+    for (uint32_t e0 = 64 * kThrKeys; e0 < c; e0 += 64 * kThrKeys)
 #pragma unroll
-    for (int u = 0; u < kPre; ++u) {
-      const uint32_t i = (uint32_t)(lane + u * 64);
-      ps[u] = i < c ? cs[j * cap + i] : 0.0f;
-      pr[u] = i < c ? cr[j * cap + i] : 0;
-    }
-#pragma unroll
-    for (int u = 0; u < kPre; ++u)
-      if ((uint32_t)(lane + u * 64) < c && better(ps[u], pr[u], ls[KL - 1], lr[KL - 1]))
-        list_insert<KL>(ls, lr, ps[u], pr[u]);
-    for (uint32_t i = lane + kPre * 64; i < c; i += 64) {
-      const int row = cr[j * cap + i];
-      const float sc = cs[j * cap + i];
-      if (!better(sc, row, ls[KL - 1], lr[KL - 1])) continue;
-      list_insert<KL>(ls, lr, sc, row);
-    }
-    float hk = -INFINITY;
-    for (int t = 0; t < kk; ++t) {
-      const unsigned long long key =
-          ((unsigned long long)f2ord(ls[0] + 0.0f) << 32) | (unsigned long long)(uint32_t)~(uint32_t)lr[0];
-      const unsigned long long best = wave_max_u64(key);
-      const int br = (int)~(uint32_t)best;
-      hk = ord2f((uint32_t)(best >> 32));
-      if (br != kNoRow && lr[0] == br) {
-#pragma unroll
-        for (int p = 0; p < KL - 1; ++p) {
-          ls[p] = ls[p + 1];
-          lr[p] = lr[p + 1];
-        }
-        ls[KL - 1] = -INFINITY;
-        lr[KL - 1] = kNoRow;
+      for (int r = 0; r < kThrKeys; ++r) {
+        const uint32_t i = e0 + (uint32_t)(lane + r * 64);
+        if (i < c) key[r] = max(key[r], f2ord(cs[j * cap + i] + 0.0f));
       }
-    }
+    const uint32_t T = wave_kth_floor<kThrKeys>(key, (int)min((uint32_t)kThrKeys, (c + 63u) / 64u), kk);
     if (lane == 0) {
-      thr_sh = rd32((double)hk - 2.0 * (double)mj.err);
+      thr_sh = T == 0u ? -INFINITY : rd32((double)ord2f(T) - 2.0 * (double)mj.err);
       m_sh = 0u;
     }
   }
@@ -1304,26 +1098,16 @@ __global__ __launch_bounds__(kRescoreThreads) void k_select_rescore(
   rescore_sort<B>(j, m, kk, k, rows, keys, ids, q, step, codes, row_words, D, out_s, out_i);
 }
 
-// Lists and fallback give final scores (hi and lo); the filter pass works on
-// hi-only scores.
-template <int B, int KL>
-void launch_mode(int mode, dim3 grid, hipStream_t st, const ScoreArgs& a) {
-  if (mode == kModeLists) hipLaunchKernelGGL((k_score<B, KL, kModeLists, true>), grid, dim3(kWG), 0, st, a);
-  else if (mode == kModeFilter) hipLaunchKernelGGL((k_score<B, KL, kModeFilter, false>), grid, dim3(kWG), 0, st, a);
-  else hipLaunchKernelGGL((k_score<B, KL, kModeFallback, true>), grid, dim3(kWG), 0, st, a);
-}
-
 template <int B>
 lam_status dispatch_bits(int b, int kl, int mode, dim3 grid, hipStream_t st, const ScoreArgs& a) {
   if (b == B) {
-    if (kl == 4) {   // the sample pass: short lists of hi-only scores
-      if (mode != kModeLists) {
-        set_error("internal: lists of 4 serve the sample pass only");
-        return LAM_EINVAL;
-      }
-      hipLaunchKernelGGL((k_score<B, 4, kModeLists, false>), grid, dim3(kWG), 0, st, a);
-    } else if (kl == 16) launch_mode<B, 16>(mode, grid, st, a);
-    else launch_mode<B, 64>(mode, grid, st, a);
+    if (mode == kModeLists) {
+      if (kl == 16) hipLaunchKernelGGL((k_score<B, 16, kModeLists>), grid, dim3(kWG), 0, st, a);
+      else hipLaunchKernelGGL((k_score<B, 64, kModeLists>), grid, dim3(kWG), 0, st, a);
+    } else {
+      if (kl == 16) hipLaunchKernelGGL((k_score<B, 16, kModeFallback>), grid, dim3(kWG), 0, st, a);
+      else hipLaunchKernelGGL((k_score<B, 64, kModeFallback>), grid, dim3(kWG), 0, st, a);
+    }
     return LAM_OK;
   }
   if constexpr (B < 12) return dispatch_bits<B + 1>(b, kl, mode, grid, st, a);
@@ -1331,28 +1115,27 @@ lam_status dispatch_bits(int b, int kl, int mode, dim3 grid, hipStream_t st, con
   return LAM_ESTATE;
 }
 
-// The rescoring after the radix selection (k > 16), or the fused selection
-// and rescoring (k <= 16, fused = true; bound written there too).
 template <int B>
-lam_status launch_rescore(int b, bool fused, dim3 grid, hipStream_t st, int64_t nq, uint32_t cap, int k,
-                          const uint32_t* cnt, const float* cs, const int32_t* cr, const QMeta* meta,
-                          const int64_t* ids, const float* q, double step, const uint32_t* codes, int64_t row_words,
-                          int D, float* out_s, int64_t* out_i, float* bound, uint32_t* qflag, uint32_t* tflag) {
+lam_status launch_rescore(int b, dim3 grid, hipStream_t st, int64_t nq, uint32_t cap, int k, const uint32_t* cnt,
+                          const float* cs, const int32_t* cr, const QMeta* meta, const int64_t* ids, const float* q,
+                          double step, const uint32_t* codes, int64_t row_words, int D, float* out_s, int64_t* out_i,
+                          float* bound, uint32_t* qflag, uint32_t* tflag) {
   if (b == B) {
-    if (fused)
-      hipLaunchKernelGGL((k_select_rescore<B>), grid, dim3(kRescoreThreads), 0, st, nq, cap, k, cnt, cs, cr, meta,
-                         ids, q, step, codes, row_words, D, out_s, out_i, bound, qflag, tflag);
-    else
-      hipLaunchKernelGGL((k_rescore<B>), grid, dim3(kRescoreThreads), 0, st, nq, cap, k, cnt, cs, cr, meta, ids, q,
-                         step, codes, row_words, D, out_s, out_i, qflag, tflag);
+    hipLaunchKernelGGL((k_select_rescore<B>), grid, dim3(kRescoreThreads), 0, st, nq, cap, k, cnt, cs, cr, meta, ids,
+                       q, step, codes, row_words, D, out_s, out_i, bound, qflag, tflag);
     LAM_HIP(hipGetLastError());
     return LAM_OK;
   }
   if constexpr (B < 12)
-    return launch_rescore<B + 1>(b, fused, grid, st, nq, cap, k, cnt, cs, cr, meta, ids, q, step, codes, row_words, D,
-                                 out_s, out_i, bound, qflag, tflag);
+    return launch_rescore<B + 1>(b, grid, st, nq, cap, k, cnt, cs, cr, meta, ids, q, step, codes, row_words, D, out_s,
+                                 out_i, bound, qflag, tflag);
   set_error("scoring supports codes of at most 12 bits (got %d)", b);
   return LAM_ESTATE;
+}
+
+__global__ __launch_bounds__(256) void k_fill_zero(uint32_t* __restrict__ p, int64_t n) {
+  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (i < n) p[i] = 0u;
 }
 
 // Split a tile range over query tiles so that the grid holds about 1024
@@ -1496,22 +1279,19 @@ lam_status widen(lam_ctx* ctx, ScoreView& v, const float*& q, int64_t nq) {
 
 }  // namespace
 
-// Scoring plan.  With at most S store rows (S = k * n / 1024, at least 4,096)
+// Scoring plan.  With at most S store rows (S = k * n / 256, at least 4,096)
 // one pass of per-lane lists gives the exact top-k.  Beyond that (H: scores
 // of the hi part alone, within err of the rescored scores S):
-//   1. theta_j, the k-th best H of per-lane lists of the 4 best H over the
-//      first S rows, minus 2 err_j: k distinct rows have S >= theta_j + err_j,
-//      so every row of the final top-k has H >= theta_j (short lists keep
-//      this pass cheap -- the insertions, not the MFMAs, dominate it -- at
-//      the price of a slightly lower theta_j when one lane holds more than 4
-//      of the sample's best k; the splits give at least 2k entries);
+//   1. theta_j, the k-th best H of disjoint 32-row sets' best over the first S
+//      rows, minus 2 err_j: k distinct rows have S >= theta_j + err_j, so every
+//      row of the final top-k has H >= theta_j;
 //   2. a full scan of H appends every row with H >= theta_j to query j's
-//      candidate buffer (about k * n / S = 1,024 entries expected; capacity
+//      candidate buffer (about k * n / S = 256 entries expected; capacity
 //      4,096);
-//   3. the k best candidates by H; the candidates within 2 err_j of the k-th
-//      of them are rescored exactly and their k best by (S desc, id asc) are
-//      the answer (k_rescore);
-//   4. a query whose buffer overflowed, or with more than 256 candidates to
+//   3. the candidates within 2 err_j of the k-th best H of them are rescored
+//      exactly and their k best by (S desc, id asc) are the answer
+//      (k_select_rescore);
+//   4. a query whose buffer overflowed, or with more than 1,024 candidates to
 //      rescore (many equal scores, say), is redone with exact per-lane lists
 //      over the whole store; launched always, it returns at once when nothing
 //      was flagged, so the call stays asynchronous.
@@ -1561,25 +1341,18 @@ lam_status score_topk_impl(lam_ctx* ctx, const ScoreView& st, const float* q, in
   const int64_t stiles = std::min<int64_t>(ntiles, (sample_rows + kTB - 1) / kTB);
   const bool two_pass = stiles < ntiles;
 
-  int sp1 = 1, sp2 = 1;
-  int64_t tps1 = 0, tps2 = 0;
-  plan_splits(nqt, stiles, &sp1, &tps1, max_splits);
+  int sp2 = 1;
+  int64_t tps2 = 0;
   plan_splits(nqt, ntiles, &sp2, &tps2, max_splits);
-  constexpr int kSampleKL = 4;
-  if (two_pass && (int64_t)sp1 * 2 * kSampleKL < 2 * (int64_t)k) {
-    const int64_t want = std::min<int64_t>(stiles, (k + kSampleKL - 1) / kSampleKL);
-    tps1 = (stiles + want - 1) / want;
-    sp1 = (int)((stiles + tps1 - 1) / tps1);
-  }
-  const int cands_max = std::max(sp1, sp2) * 2 * KL;
-  // the sample pass on the filter's pipeline at D = 768 and 1,024 when its
-  // entries fit the partial lists' buffer
-  const bool filter_sample =
-      two_pass && (D == 768 || D == 1024) && stiles * kSampleEntries <= (int64_t)cands_max;
+  const int64_t cands_max = (int64_t)sp2 * 2 * KL;
+  // the sample's entries share the list passes' buffer (they are read before
+  // the fallback writes its lists); beyond kSampleTiles tiles, or what a fixed
+  // workspace holds, tiles share entries
+  const int64_t sample_tiles = std::min<int64_t>(stiles, kSampleTiles);
+  const int64_t entries = two_pass ? sample_tiles * kSampleEntries : 0;
   // the filter pipeline's grids (sample and filter passes) are one workgroup
   // per (query tile, store tile), indexed in 32 bits
-  LAM_CHECK(!two_pass || !(D == 768 || D == 1024) || (int64_t)nqt * ntiles < (1LL << 31), LAM_EINVAL,
-            "scoring grid too large");
+  LAM_CHECK(!two_pass || (int64_t)nqt * ntiles < (1LL << 31), LAM_EINVAL, "scoring grid too large");
   const uint32_t cap = kCandCap;
 
   // every buffer first
@@ -1590,7 +1363,7 @@ lam_status score_topk_impl(lam_ctx* ctx, const ScoreView& st, const float* q, in
   LAM_TRY(w.take(ctx, S_QHI, (size_t)nq * D * 2, &qhi));
   LAM_TRY(w.take(ctx, S_QLO, (size_t)nq * D * 2, &qlo));
   LAM_TRY(w.take(ctx, S_QMETA, (size_t)nq * sizeof(QMeta), &qmeta));
-  LAM_TRY(w.take(ctx, S_PART, (size_t)nq * cands_max * 8, &part_s));
+  LAM_TRY(w.take(ctx, S_PART, (size_t)nq * std::max<int64_t>(cands_max * 8, entries * 4), &part_s));
   if (two_pass) LAM_TRY(w.take(ctx, S_CAND, (size_t)nq * cap * 8 + (size_t)nq * 12 + (size_t)nqt * 8 + 256, &cand_s));
   int32_t* part_r = reinterpret_cast<int32_t*>(part_s + (size_t)nq * cands_max);
   int32_t* cand_r = two_pass ? reinterpret_cast<int32_t*>(cand_s + (size_t)nq * cap) : nullptr;
@@ -1634,10 +1407,10 @@ lam_status score_topk_impl(lam_ctx* ctx, const ScoreView& st, const float* q, in
     const int nc = ntiles > 0 ? sp2 * 2 * KL : 0;
     if (KL == 16)
       hipLaunchKernelGGL((k_topk_merge<16>), gq, dim3(256), 0, ctx->stream, nq, nc, k, part_s, part_r, qmeta, st.ids,
-                         scores, ids, bound, nullptr);
+                         scores, ids, bound);
     else
       hipLaunchKernelGGL((k_topk_merge<64>), gq, dim3(256), 0, ctx->stream, nq, nc, k, part_s, part_r, qmeta, st.ids,
-                         scores, ids, bound, nullptr);
+                         scores, ids, bound);
     LAM_HIP(hipGetLastError());
     return LAM_OK;
   }
@@ -1645,20 +1418,17 @@ lam_status score_topk_impl(lam_ctx* ctx, const ScoreView& st, const float* q, in
   // (the candidate counts and tile flags were cleared by k_score_prep)
   {  // 1. a k-th best score of the sample -> thresholds
     ProfScope ps(ctx, "score_sample", prof);
-    a.tile_begin = 0;
     a.tile_end = stiles;
-    a.splits = sp1;
-    a.tiles_per_split = tps1;
-    if (filter_sample) {
-      // one tile per workgroup on the filter's pipeline; entries unsorted (segments of 1)
-      LAM_TRY((launch_filter<1, true>(b, D, false, dim3((unsigned)(nqt * stiles)), ctx->stream, a)));
-      hipLaunchKernelGGL((k_topk_merge<16, 1>), gq, dim3(256), 0, ctx->stream, nq, (int)stiles * kSampleEntries, k,
-                         part_s, part_r, qmeta, st.ids, nullptr, nullptr, nullptr, thr);
-    } else {
-      LAM_TRY(dispatch_bits<1>(b, kSampleKL, kModeLists, dim3((unsigned)(nqt * sp1)), ctx->stream, a));
-      hipLaunchKernelGGL((k_topk_merge<16, kSampleKL>), gq, dim3(256), 0, ctx->stream, nq, sp1 * 2 * kSampleKL, k,
-                         part_s, part_r, qmeta, st.ids, nullptr, nullptr, nullptr, thr);
+    a.sample_tiles = (int)sample_tiles;
+    const bool folded = sample_tiles < stiles;
+    if (folded) {
+      const int64_t ne = nq * entries;
+      hipLaunchKernelGGL(k_fill_zero, dim3((unsigned)((ne + 255) / 256)), dim3(256), 0, ctx->stream,
+                         reinterpret_cast<uint32_t*>(part_s), ne);
     }
+    LAM_TRY((launch_filter<1, true>(b, false, dim3((unsigned)(nqt * stiles)), ctx->stream, a)));
+    hipLaunchKernelGGL(k_sample_thr, gq, dim3(256), 0, ctx->stream, nq, (int)entries, folded ? 1 : 0, k, part_s, qmeta,
+                       thr);
     LAM_HIP(hipGetLastError());
   }
   a.tile_begin = 0;
@@ -1673,34 +1443,22 @@ lam_status score_topk_impl(lam_ctx* ctx, const ScoreView& st, const float* q, in
   a.tflag = tflag;
   {  // 2. full scan with the thresholds
     ProfScope ps(ctx, "score_mfma", prof);
-    if (D == 768 || D == 1024) {
-      // one tile per workgroup on the screen's pipeline: 256 x 256 when the
-      // launch holds many of them, else 128 x 128
-      const int nqtL = (int)((nq + FilterTileL::BN - 1) / FilterTileL::BN);
-      const int64_t ntilesL = (n + FilterTileL::BM - 1) / FilterTileL::BM;
-      const bool large = (int64_t)nqtL * ntilesL >= kFilterLargeMinTiles;
-      ScoreArgs af = a;
-      if (large) {
-        af.nqt = nqtL;
-        af.tile_end = ntilesL;
-      }
-      const int64_t grid = (int64_t)af.nqt * af.tile_end;
-      LAM_CHECK(grid < (1LL << 31), LAM_EINVAL, "scoring grid too large");
-      LAM_TRY((launch_filter<1, false>(b, D, large, dim3((unsigned)grid), ctx->stream, af)));
-    } else {
-      LAM_TRY(dispatch_bits<1>(b, KL, kModeFilter, dim3((unsigned)(nqt * sp2)), ctx->stream, a));
-      LAM_HIP(hipGetLastError());
+    // one tile per workgroup on the screen's pipeline: 256 x 256 when the
+    // launch holds many of them, else 128 x 128
+    const int nqtL = (int)((nq + FilterTileL::BN - 1) / FilterTileL::BN);
+    const int64_t ntilesL = (n + FilterTileL::BM - 1) / FilterTileL::BM;
+    const bool large = (int64_t)nqtL * ntilesL >= kFilterLargeMinTiles;
+    ScoreArgs af = a;
+    if (large) {
+      af.nqt = nqtL;
+      af.tile_end = ntilesL;
     }
+    LAM_TRY((launch_filter<1, false>(b, large, dim3((unsigned)((int64_t)af.nqt * af.tile_end)), ctx->stream, af)));
   }
   {  // 3. select; 4. exact fallback for overflowed buffers (returns at once otherwise)
     ProfScope ps(ctx, "score_merge", prof);
-    if (KL != 16) {
-      hipLaunchKernelGGL(k_cand_select_radix, dim3((unsigned)nq), dim3(64), 0, ctx->stream, nq, cap, k, cand_cnt, cand_s, cand_r,
-                         qmeta, st.ids, scores, ids, bound, qflag, tflag);
-      LAM_HIP(hipGetLastError());
-    }
-    LAM_TRY(launch_rescore<1>(b, KL == 16, dim3((unsigned)nq), ctx->stream, nq, cap, k, cand_cnt, cand_s, cand_r,
-                              qmeta, st.ids, q, st.step, a.codes, a.row_words, D, scores, ids, bound, qflag, tflag));
+    LAM_TRY(launch_rescore<1>(b, dim3((unsigned)nq), ctx->stream, nq, cap, k, cand_cnt, cand_s, cand_r, qmeta, st.ids,
+                              q, st.step, a.codes, a.row_words, D, scores, ids, bound, qflag, tflag));
   }
   {
     // exact lists for the flagged query tiles, merged by each tile's last
@@ -1759,7 +1517,14 @@ lam_status score_topk(lam_ctx* ctx, const lam_store* st, const float* q, int64_t
   ScoreWork w;
   ScoreView v = store_view(st, codes);
   if (v.b > 12) LAM_TRY(widen(ctx, v, q, nq));
-  return score_topk_impl(ctx, v, q, nq, k, scores, ids, bound, w, 1 << 30, true);
+  // the passes index (query tile, store tile) in 31 bits: more queries than
+  // that allows go in several passes
+  const int64_t ntiles = std::max<int64_t>(1, (v.n + kTB - 1) / kTB);
+  const int64_t most = std::max<int64_t>(1, ((1LL << 31) - 1) / ntiles) * kTB;
+  for (int64_t j = 0; j < nq; j += most)
+    LAM_TRY(score_topk_impl(ctx, v, q + j * v.D, std::min(most, nq - j), k, scores + j * k, ids + j * k,
+                            bound ? bound + j : nullptr, w, 1 << 30, true));
+  return LAM_OK;
 }
 
 lam_status score_topk_noalloc(lam_ctx* ctx, const lam_store* st, const float* q, int64_t nq, int32_t k, float* scores,
