@@ -278,18 +278,14 @@ lam_status lam_store_export(lam_ctx* ctx, const lam_store* store, int64_t* ids_d
 
 /* Score nq float32 queries (row-major, dim each) against the quantized store:
  * score(j, y) = step * sum_d q_j,d * code_y,d, i.e. q_j . x_hat_y with the
- * exact dequantized row (|error| <= 1e-5 for unit rows: float32 accumulation
- * of the query's fp16 hi and lo parts, or, for the rows of a large store that
- * reach a query's top-k, a binary64 sum rounded once; the ranking is the one
- * these scores give).  Per query the k best by (score desc, id asc) go to scores_dev and
- * ids_dev (nq x k, row-major), padded with (-inf, -1) past the store size.
- * bound_dev (optional): eps * ||q_j||_1 rounded up to float32.
- * 1 <= k <= 64.  Codes of up to 12 bits are multiplied as exact float16
- * values; codes of 13 to 22 bits are scored in a split form, each code c as
- * the two 12-bit parts c >> 11 and c & 2047 against the query scaled by 2^11
- * and the query itself (the same scores; twice the matrix work, 3 dim bytes
- * per stored row and 8 dim bytes per query of context scratch; a query with
- * |q| * 2^11 beyond float32 range counts as holding Inf).  ESTATE if the
+ * exact dequantized row (a binary64 sum rounded once to float32; the ranking
+ * is the one these scores give).  Per query the k best by (score desc, id asc)
+ * go to scores_dev and ids_dev (nq x k, row-major), padded with (-inf, -1) past
+ * the store size.  bound_dev (optional): eps * ||q_j||_1 rounded up to float32.
+ * 1 <= k <= 64.  Codes of up to 22 bits are scored.  With codes of 13 bits and
+ * more a query with |q| * 2^11 beyond float32 range counts as holding Inf.
+ * Context scratch: 32 KB and 2 dim bytes per query, for at most 65,536 queries
+ * at once.  ESTATE if the
  * store is not quantized (or has rows added since), or if its codes are wider
  * than 22 bits (quantize with a larger eps: 22 bits hold absmax / (2 eps) <
  * 2,097,151.5).  A query row holding NaN/Inf gets (NaN, -1) in all k slots
@@ -303,8 +299,7 @@ lam_status lam_score_topk(lam_ctx* ctx, const lam_store* store, const float* q_d
  * that each device holds from the library's load until the process ends (set
  * up by lam_ctx_create); the call itself allocates nothing.  Results equal
  * lam_score_topk's.  Limits: nq <= 256 (EINVAL beyond); codes of at most 12
- * bits (ESTATE for wider ones, whose split form needs scratch in proportion
- * to the store).  The store must be
+ * bits (ESTATE for wider ones).  The store must be
  * quantized and settled: ESTATE while ingest calls that did not wait are in
  * flight (lam_store_get_info settles them) -- settling can need the host.
  * Every call on one device shares that device's array: calls that overlap on

@@ -498,6 +498,13 @@ lam_status lam_store_quantize(lam_ctx* ctx, lam_store* st, double eps, float abs
   st->q = p;
   st->coded_rows = st->size;
   st->hn_max = st->hnmax_bits;
+  {  // the exact maximum's code: rounding is monotone, so no row has a larger one
+    float mx = 0.0f;
+    memcpy(&mx, &st->absmax_bits, 4);
+    lam_qparams used{};
+    LAM_TRY(qeps_plan_host(eps, mx, LAM_PACK_BITS, 0, &used));
+    st->max_code = used.max_code;
+  }
   if (out) *out = p;
   return LAM_OK;
 }

@@ -45,16 +45,14 @@ struct Status {
   } while (0)
 
 // ------------------------------------------------------------------ device buffer
-// Context scratch slots: 0-6 ingest (dedup.hip), 7-11 scoring (score.hip),
+// Context scratch slots: 0-6 ingest (dedup.hip), 7-10 scoring (score.hip),
 // then the ones below.
 constexpr int kScratchCeilingRep = 12;   // representatives of the ceiling passes (not returned)
 constexpr int kScratchCertify = 13;      // top-(k+1) lists of the certified scoring
 constexpr int kScratchBlocks = 14;       // block codec: row word counts and scan sums
 constexpr int kScratchExpand = 15;       // block codec: codes expanded back to the b-bit stream for scoring
 constexpr int kScratchLsh = 16;          // banded candidates: chunk keys and the chunk's own index
-constexpr int kScratchWideCodes = 17;    // scoring: wide codes in their split 12-bit form
-constexpr int kScratchWideQueries = 18;  // scoring: queries in the split form [2^11 q, q]
-constexpr int kScratchSlots = 19;
+constexpr int kScratchSlots = 17;
 
 struct DevBuf {
   void* p = nullptr;
@@ -139,6 +137,7 @@ struct lam_store {
   void* meta_host = nullptr;  // pinned host copy of that block, made when settling
   bool meta_reset = false;    // cleared: the next ingest's first kernel zeroes the block
   uint32_t hn_max = 0;        // max of hn over the coded rows (float bits), set with the codes
+  int32_t max_code = 0;       // largest |code| of the coded rows, set with the codes
   // the device bookkeeping's maxima over the retained rows, as last read by the host
   bool maxima_known = false;  // false until read again after calls that may have changed them
   uint32_t absmax_bits = 0;   // max |x| (float bits)

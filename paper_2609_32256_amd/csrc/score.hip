@@ -3,31 +3,18 @@
 // the per-coordinate bound of Q_eps, Appendix "Rank invariance, in full").
 //
 // score(j, y) = s * sum_d q_j,d * code_y,d  (s = 2 eps), i.e. q_j . x_hat_y with
-// the exact dequantized row.  Codes of at most 12 bits are exact in fp16.
-// Codes of 13 to 22 bits are scored as a 12-bit store of 2D columns, each
-// code c split as 2^11 (c >> 11) + (c & 2047), against queries [2^11 q, q]:
-// the same score term by term (see widen).
-// Each query is scaled by a power of two 2^e_j (max |q| into [2^14, 2^15)) and
-// split into fp16 hi + lo parts, q 2^e = hi + lo + r with |r| <= 2^-22 |q 2^e|;
-// hi*code and lo*code are exact in fp32 and the MFMA accumulates in fp32.  The
-// score is acc * float32(s 2^-e_j).
+// the exact dequantized row: a binary64 sum, rounded once to float32.
 //
-// Kernel layout: a workgroup owns 128 queries and a contiguous range ("split")
-// of the store, walked in 128-row tiles.  Per tile the codes are unpacked from
-// their b-bit words straight into an fp16 LDS slab (no dequantized copy exists
-// in HBM) and multiplied with the query slabs on v_mfma_f32_32x32x16_f16.  Wave
-// w holds queries [32w, 32w + 32) against all 128 rows of the tile, so every
-// query lives in two lanes of one wave; each lane keeps a sorted private list
-// of its best KL (score, row) pairs in registers, touched only when a score
-// reaches the list's current threshold.  A merge kernel then picks the k best
-// per query from all lists by (score desc, id asc).
-//
-// Stores beyond the sample size take a threshold plan (score_topk) whose
-// sample and filter passes multiply the hi part alone -- half the MFMAs --
-// with thresholds lowered by twice a per-query bound on the hi part's error;
-// the few candidates near the k-th are then rescored exactly.  Both passes
-// are k_filter: one tile per workgroup on the similarity screen's pipeline
-// (two LDS stages), 128 x 128 or, for launches of many tiles, 256 x 256.
+// The matrix units find the few rows that can be in a query's top-k.  A scan
+// forms H, the score from fp16 operands: the query's fp16 part h (each query
+// scaled by a power of two 2^e_j, max |q| into [2^14, 2^15)) times the codes,
+// unpacked from their b-bit words straight into fp16 LDS slabs (no dequantized
+// copy exists in HBM) and accumulated in fp32 by v_mfma_f32_32x32x16_f16.  Codes
+// of values below 2^11 are exact in fp16; of wider ones the scan takes the top
+// 12 bits.  A per-query bound err on |H - score| (see k_score_prep) turns the
+// k-th best H into a threshold; the rows above it are scored exactly and the k
+// best by (score desc, id asc) are the answer.  See score_topk_impl for the
+// plan.
 #include <cmath>
 #include <cstring>
 #include <mutex>
@@ -41,13 +28,13 @@ namespace {
 
 constexpr int kNoRow = 0x7fffffff;
 
-enum ScoreScratch { S_QHI = 7, S_QLO, S_QMETA, S_PART, S_CAND };
+enum ScoreScratch { S_QHI = 7, S_QMETA, S_PART, S_CAND };
 
 struct QMeta {
-  float osc;     // float32(s * 2^-e): multiplies the raw accumulator
+  float osc;     // float32(s * 2^(sh - e)): multiplies the raw accumulator
   float bound;   // eps * ||q||_1 rounded up, or NaN for an invalid query
   int bad;       // query holds NaN/Inf
-  float err;     // >= |hi-only score - rescored score| for every store row (rounded up)
+  float err;     // >= |H + c - score| for every store row, c a constant of the query (rounded up)
 };
 
 __device__ __forceinline__ float ru32(double d) {
@@ -62,36 +49,37 @@ __device__ __forceinline__ float rd32(double d) {
   return f;
 }
 
-// Per query: the hi/lo split and the meta block.  err bounds the difference
-// between a score from the hi part alone (H) and the rescored one (S), both
-// against T = s sum_d q_d code_d, in score units, with R >= s ||code_y|| for
-// every row y (row_norm_bound) and h = hi 2^-e the query's hi part in its own
-// units; the reported bound is eps times the l1 norm of columns [l1_from, D)
-// (all of them, except for the split form of wide codes):
-//   hi part:   |s sum_d (q_d - h_d) code_d| <= ||q - h||_2 R (Cauchy-Schwarz;
-//              ||q - h||_2 is computed here in binary64);
-//   fp32 sum:  g = 2 (D + 64) 2^-24 of s sum |h_d code_d| <= (||q|| + ||q - h||) R
+// Per query: its fp16 part and the meta block.  err bounds the difference
+// between a score H of the scan and the exact one S (with a constant of the
+// query left out: only differences between rows of one query matter), both
+// against T = s sum_d q_d code_d, in score units.  With h = fp16 part * 2^-e in
+// the query's own units and, for codes taken without their low sh bits,
+// code = 2^sh top + low, low in [0, 2^sh - 1]:
+//   h:         |s 2^sh sum_d (q_d - h_d) top_d| <= ||q - h||_2 R (Cauchy-Schwarz;
+//              ||q - h||_2 is computed here in binary64), R >= s 2^sh ||top||;
+//   low bits:  s sum_d q_d low_d = c + (at most s (2^sh - 1) / 2 sqrt(D) ||q||);
+//              trunc = s (2^sh - 1) / 2 sqrt(D);
+//   fp32 sum:  g = 2 (D + 64) 2^-24 of s 2^sh sum |h_d top_d| <= (||q|| + ||q - h||) R
 //              (two roundings per addition, in any order);
 //   scalings:  osc and the final product, 2^-24 each;
 //   S:         the rescoring sums in binary64 and rounds once to float32.
-// |H - S| <= |H - T| + |T - S| <= ||q - h|| R + (g + 2^-21)(||q|| + ||q - h||) R.
-__global__ __launch_bounds__(256) void k_score_prep(const float* __restrict__ q, int64_t nq, int D, double s,
-                                                    double eps, double R, int l1_from,
-                                                    _Float16* __restrict__ qhi,
-                                                    _Float16* __restrict__ qlo, QMeta* __restrict__ meta,
-                                                    uint32_t* __restrict__ cand_cnt, uint32_t* __restrict__ tflag) {
+// |H + c - S| <= ||q - h|| R + trunc ||q|| + (g + 2^-21)(||q|| + ||q - h||) R.
+// qmax: the largest |q| taken (a query row above it, or holding NaN/Inf, is
+// invalid).  cand_cnt, done: this query's candidate count and finished
+// workgroups of the exact pass, and n_flag the number of flagged queries,
+// start at zero (the buffers may hold anything from an earlier call).
+__global__ __launch_bounds__(256) void k_score_prep(const float* __restrict__ q, int64_t nq, int D, double step_f,
+                                                    double eps, double R, double trunc, float qmax,
+                                                    _Float16* __restrict__ qhi, QMeta* __restrict__ meta,
+                                                    uint32_t* __restrict__ cand_cnt, uint32_t* __restrict__ done,
+                                                    uint32_t* __restrict__ n_flag) {
   const int lane = threadIdx.x & 63;
   const int64_t j = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
   if (j >= nq) return;
-  // the threshold plan's candidate count of this query and flag of its query
-  // tile start at zero (the buffers may hold anything from an earlier call)
   if (cand_cnt && lane == 0) {
     cand_cnt[j] = 0u;
-    if (j % kTB == 0) {
-      const int64_t nqt = (nq + kTB - 1) / kTB;
-      tflag[j / kTB] = 0u;          // the tile's flag
-      tflag[nqt + j / kTB] = 0u;    // and its fallback workgroups' completion count
-    }
+    done[j] = 0u;
+    if (j == 0) *n_flag = 0u;
   }
   const float* p = q + j * D;
   float mx = 0.0f;
@@ -110,11 +98,11 @@ __global__ __launch_bounds__(256) void k_score_prep(const float* __restrict__ q,
     for (int u = 0; u < kVec; ++u)
       v4[u] = __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(rs, (uint32_t)(u * 256 + lane * 4) * 4u, 0, 0));
   }
-  auto take1 = [&](float v, bool in_l1) {
+  auto take1 = [&](float v) {
     const float a = fabsf(v);
-    bad |= !(a <= 3.402823466e38f);
+    bad |= !(a <= qmax);
     mx = fmaxf(mx, a);
-    l1 += in_l1 ? (double)a : 0.0;
+    l1 += (double)a;
     l2 = fma((double)v, (double)v, l2);
   };
   if (vec) {
@@ -122,14 +110,13 @@ __global__ __launch_bounds__(256) void k_score_prep(const float* __restrict__ q,
     for (int u = 0; u < kVec; ++u) {
       const int d = u * 256 + lane * 4;
       if (d >= D) break;
-      const bool in = d >= l1_from;   // (l1_from is a multiple of 32)
-      take1(v4[u].x, in);
-      take1(v4[u].y, in);
-      take1(v4[u].z, in);
-      take1(v4[u].w, in);
+      take1(v4[u].x);
+      take1(v4[u].y);
+      take1(v4[u].z);
+      take1(v4[u].w);
     }
   } else {
-    for (int d = lane; d < D; d += 64) take1(p[d], d >= l1_from);
+    for (int d = lane; d < D; d += 64) take1(p[d]);
   }
   mx = wave_max_f32(mx);
   l1 = wave_sum_f64(l1);
@@ -140,10 +127,8 @@ __global__ __launch_bounds__(256) void k_score_prep(const float* __restrict__ q,
   const float sc = ldexpf(1.0f, e);
   const double isc = ldexp(1.0, -e);
   double dh2 = 0.0;   // ||q - h||^2
-  auto split = [&](float x, _Float16& h, _Float16& l) {
-    const float v = bad ? 0.0f : x * sc;     // exact power-of-two scaling
-    h = (_Float16)v;
-    l = (_Float16)(v - (float)h);
+  auto part = [&](float x, _Float16& h) {
+    h = (_Float16)(bad ? 0.0f : x * sc);     // exact power-of-two scaling
     const double r = bad ? 0.0 : (double)x - (double)(float)h * isc;   // exact in binary64
     dh2 = fma(r, r, dh2);
   };
@@ -153,27 +138,20 @@ __global__ __launch_bounds__(256) void k_score_prep(const float* __restrict__ q,
       const int d = u * 256 + lane * 4;
       if (d >= D) break;
       const float c[4] = {v4[u].x, v4[u].y, v4[u].z, v4[u].w};
-      _Float16 h[4], l[4];
+      _Float16 h[4];
 #pragma unroll
-      for (int e = 0; e < 4; ++e) split(c[e], h[e], l[e]);
-      uint2 ph, pl;
+      for (int i = 0; i < 4; ++i) part(c[i], h[i]);
+      uint2 ph;
       __builtin_memcpy(&ph, h, 8);
-      __builtin_memcpy(&pl, l, 8);
       *reinterpret_cast<uint2*>(qhi + j * D + d) = ph;
-      *reinterpret_cast<uint2*>(qlo + j * D + d) = pl;
     }
   } else {
-    for (int d = lane; d < D; d += 64) {
-      _Float16 h, l;
-      split(p[d], h, l);
-      qhi[j * D + d] = h;
-      qlo[j * D + d] = l;
-    }
+    for (int d = lane; d < D; d += 64) part(p[d], qhi[j * D + d]);
   }
   dh2 = wave_sum_f64(dh2);
   if (lane == 0) {
     QMeta m;
-    m.osc = (float)ldexp(s, -e);
+    m.osc = (float)ldexp(step_f, -e);
     // (a binary64 sum of D non-negative terms is below the exact one by at most
     // (D - 1) 2^-53 relative, in any order; products and sqrt add 2^-53 each)
     const double up = 1.0 + (double)(D + 4) * 0x1p-52;
@@ -182,7 +160,7 @@ __global__ __launch_bounds__(256) void k_score_prep(const float* __restrict__ q,
     const double g = 2.0 * (double)(D + 64) * 0x1p-24;
     const double qn = sqrt(l2) * up;
     const double dh = sqrt(dh2) * up;
-    const double E = dh * R + (g + 0x1p-21) * (qn + dh) * R;
+    const double E = dh * R + trunc * qn + (g + 0x1p-21) * (qn + dh) * R;
     m.err = bad ? 0.0f : ru32(E * (1.0 + 0x1p-20));
     meta[j] = m;
   }
@@ -193,66 +171,47 @@ struct ScoreArgs {
   const uint32_t* codes;
   int64_t n;                 // store rows
   int D;
+  int sh;                    // low bits of a code that the scan leaves out (codes of more than 12 bits)
   int64_t row_words;         // D * b / 32
   const _Float16* qhi;
-  const _Float16* qlo;
   const QMeta* meta;
   int64_t nq;
-  int nqt;                   // query tiles of 128
-  int64_t tile_begin;        // store tiles [tile_begin, tile_end) scanned by this launch
-  int64_t tile_end;
-  int splits;                // contiguous tile ranges per query tile
-  int64_t tiles_per_split;
-  float* part_s;             // list modes: [nq][splits][2][KL]
-  int32_t* part_r;
+  int nqt;                   // query tiles of this launch
+  int64_t tile_end;          // store tiles [0, tile_end) scanned by this launch
+  float* part_s;             // sample pass: [nq][entries]
   int sample_tiles;          // sample pass: store tiles with entries of their own (later tiles fold onto them)
-  const float* thr;          // filter mode: per-query threshold
-  float* cand_s;             // filter mode: [nq][cap]
-  int32_t* cand_r;
+  const float* thr;          // filter pass: per-query threshold
+  float* cand_s;             // filter pass: [nq][cap] scores (dense: of rows 0, 1, ...)
+  int32_t* cand_r;           //              and rows
   uint32_t* cand_cnt;
   uint32_t cap;
-  const uint32_t* tflag;     // fallback mode: query tiles to redo
-  // fallback mode: the last workgroup of a query tile merges its flagged queries
-  const uint32_t* qflag;     // queries to redo
-  uint32_t* tdone;           // per query tile: workgroups finished
-  int k;
-  float* out_s;
-  int64_t* out_i;
-  float* out_bound;
-  const int64_t* ids;        // store row -> global id
 };
-
-__device__ __forceinline__ bool better(float a, int ra, float b, int rb) {
-  return a > b || (a == b && ra < rb);
-}
-
-// Sorted insertion into a descending register list (entry KL-1 is dropped).
-template <int KL>
-__device__ __forceinline__ void list_insert(float (&ls)[KL], int (&lr)[KL], float sc, int row) {
-  int qpos = 0;
-#pragma unroll
-  for (int p = 0; p < KL; ++p) qpos += better(ls[p], lr[p], sc, row) ? 1 : 0;
-#pragma unroll
-  for (int p = KL - 1; p >= 0; --p) {
-    const float ps = (p > 0) ? ls[p - 1] : 0.0f;
-    const int pr = (p > 0) ? lr[p - 1] : 0;
-    ls[p] = (p > qpos) ? ps : (p == qpos ? sc : ls[p]);
-    lr[p] = (p > qpos) ? pr : (p == qpos ? row : lr[p]);
-  }
-}
 
 typedef _Float16 half2v __attribute__((ext_vector_type(2)));
 
-// Unpacks 32 b-bit codes starting at word w (element 0 at bit 0) to fp16.
-// Byte codes take an exact shortcut, two codes per step: the byte c + 128
-// (c XOR 0x80) becomes the low byte of the fp16 bit pattern 0x6400 | byte,
-// which is the value 1024 + c + 128 exactly; one packed fp16 subtraction of
-// 1152 leaves c.
+// Code e (a compile-time constant) of the b-bit codes that start at bit 0 of v;
+// a word past the codes is read only for a field that straddles into it.
 template <int B>
-__device__ __forceinline__ void unpack32(const uint32_t* __restrict__ w, _Float16* __restrict__ out) {
+__device__ __forceinline__ int32_t code_at(const uint32_t* v, int e) {
+  const int bit = e * B, wi = bit >> 5, off = bit & 31;
+  uint32_t u = v[wi] >> off;
+  if (off + B > 32) u |= v[wi + 1] << (32 - off);
+  return (int32_t)(u << (32 - B)) >> (32 - B);
+}
+
+// The 16 b-bit codes of half `h` of a group of 32 to fp16 (without their low
+// sh bits when B > 12).  w: the words that hold them, (B + 1) / 2 words from word
+// h * (B / 2) of the group; for odd widths the upper half starts at bit 16 of
+// its first word.  Byte codes take an exact shortcut, two codes per step: the
+// byte c + 128 (c XOR 0x80) becomes the low byte of the fp16 bit pattern 0x6400 |
+// byte, which is the value 1024 + c + 128 exactly; one packed fp16 subtraction
+// of 1152 leaves c.
+template <int B>
+__device__ __forceinline__ void unpack16(const uint32_t (&w)[(B + 1) / 2], int h, int sh, _Float16* __restrict__ out) {
+  constexpr int NW = (B + 1) / 2;
   if constexpr (B == 8) {
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
+    for (int i = 0; i < NW; ++i) {
       const uint32_t x = w[i] ^ 0x80808080u;
       // bytes 0..3 of the selection come from x, 4..7 from the constant 0x64646464
       const uint32_t lo = __builtin_amdgcn_perm(0x64646464u, x, 0x04010400u);
@@ -265,57 +224,18 @@ __device__ __forceinline__ void unpack32(const uint32_t* __restrict__ w, _Float1
       out[4 * i + 2] = b.x;
       out[4 * i + 3] = b.y;
     }
-    return;
-  }
-  uint32_t v[B + 1];
-#pragma unroll
-  for (int i = 0; i < B; ++i) v[i] = w[i];
-  v[B] = 0u;
-#pragma unroll
-  for (int e = 0; e < 32; ++e) {
-    const int bit = e * B, wi = bit >> 5, off = bit & 31;
-    uint32_t u = v[wi] >> off;
-    if (off + B > 32) u |= v[wi + 1] << (32 - off);
-    const int32_t c = (int32_t)(u << (32 - B)) >> (32 - B);
-    out[e] = (_Float16)(float)c;
-  }
-}
-
-// The 16 b-bit codes of half `h` of a group of 32 to fp16, as unpack32 does.
-// w: the words that hold them, (B + 1) / 2 words from word h * (B / 2) of the
-// group; for odd widths the upper half starts at bit 16 of its first word.
-template <int B>
-__device__ __forceinline__ void unpack16(const uint32_t (&w)[(B + 1) / 2], int h, _Float16* __restrict__ out) {
-  constexpr int NW = (B + 1) / 2;
-  if constexpr (B == 8) {
-#pragma unroll
-    for (int i = 0; i < NW; ++i) {
-      const uint32_t x = w[i] ^ 0x80808080u;
-      const uint32_t lo = __builtin_amdgcn_perm(0x64646464u, x, 0x04010400u);
-      const uint32_t hi = __builtin_amdgcn_perm(0x64646464u, x, 0x04030402u);
-      const half2v off = {(_Float16)1152.0f, (_Float16)1152.0f};
-      const half2v a = __builtin_bit_cast(half2v, lo) - off;
-      const half2v b = __builtin_bit_cast(half2v, hi) - off;
-      out[4 * i + 0] = a.x;
-      out[4 * i + 1] = a.y;
-      out[4 * i + 2] = b.x;
-      out[4 * i + 3] = b.y;
-    }
   } else {
-    uint32_t v[NW + 1];
+    uint32_t v[NW];
 #pragma unroll
     for (int i = 0; i < NW; ++i) {
       if constexpr ((B & 1) != 0) v[i] = __builtin_amdgcn_alignbit(i + 1 < NW ? w[i + 1] : 0u, w[i], h ? 16u : 0u);
       else v[i] = w[i];
     }
-    v[NW] = 0u;
 #pragma unroll
     for (int e = 0; e < 16; ++e) {
-      const int bit = e * B, wi = bit >> 5, off = bit & 31;
-      uint32_t u = v[wi] >> off;
-      if (off + B > 32) u |= v[wi + 1] << (32 - off);
-      const int32_t c = (int32_t)(u << (32 - B)) >> (32 - B);
-      out[e] = (_Float16)(float)c;
+      int32_t c = code_at<B>(v, e);
+      if constexpr (B > 12) c >>= sh;
+      out[e] = (_Float16)(short)c;   // |c| <= 2^11
     }
   }
 }
@@ -341,285 +261,6 @@ __device__ __forceinline__ void load_words(__amdgpu_buffer_rsrc_t rs, uint32_t v
   }
   if constexpr ((NW & 1) != 0)
     cw[NW - 1] = (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(rs, voff + (NW - 1) * 4u, soff, 0);
-}
-
-// acc[t] (t = 0..3) <- the 128 x 128 tile of raw scores: store rows
-// [rbase, rbase + rows) against the workgroup's 128 queries (wave w holds
-// queries [32w, 32w + 32), lane j % 32, store rows t*32 + acc_row(r, lane)).
-// Codes are unpacked straight into an fp16 LDS slab; queries enter as hi and lo.
-//
-// One LDS stage (codes, hi, lo: 3 x 128 rows of kLdk halves) is refilled
-// between two barriers while the next slab's loads are in flight in
-// registers; loads go through buffer resources (zeros past the tile) so none
-// sits behind a branch.  With one slab in flight, the wait at the top of each
-// step is for all outstanding loads, which is exactly the slab being stored.
-// Ends with a barrier, so the caller may reuse the LDS.
-template <int B>
-__device__ __forceinline__ void score_tile(const ScoreArgs& a, int64_t rbase, int rows, const _Float16* QH,
-                                           const _Float16* QL, int qrows, _Float16* lds, floatx16 (&acc)[4]) {
-  _Float16* sc = lds;
-  _Float16* sh = lds + kTB * kLdk;
-  _Float16* sl = lds + 2 * kTB * kLdk;
-  const int wave = threadIdx.x >> 6;
-  const int urow = threadIdx.x >> 1, uhalf = threadIdx.x & 1;   // unpack: 2 threads per row
-#pragma unroll
-  for (int t = 0; t < 4; ++t)
-#pragma unroll
-    for (int r = 0; r < 16; ++r) acc[t][r] = 0.0f;
-  const __amdgpu_buffer_rsrc_t rsC = __builtin_amdgcn_make_buffer_rsrc(
-      const_cast<uint32_t*>(a.codes + rbase * a.row_words), (short)0, (int)(rows * a.row_words * 4), 0x00020000);
-  const __amdgpu_buffer_rsrc_t rsH = tile_rsrc(QH, qrows, a.D), rsL = tile_rsrc(QL, qrows, a.D);
-  auto load_slab = [&](int k0, uint32_t (&cw)[B], uint4 (&rh)[4], uint4 (&rl)[4]) {
-    const bool ok = urow < rows && k0 + 32 * uhalf < a.D;
-    const uint32_t w0 = (uint32_t)(urow * a.row_words + (int64_t)(k0 / 32 + uhalf) * B);
-    load_words<B>(rsC, ok ? w0 * 4u : kOffOOB, 0u, cw);
-    slab_load_n<4>(rsH, qrows, a.D, k0, a.D, rh, kWG);
-    slab_load_n<4>(rsL, qrows, a.D, k0, a.D, rl, kWG);
-  };
-  auto compute = [&]() {
-#pragma unroll
-    for (int kk = 0; kk < kBK / 16; ++kk) {
-      const half8 bh = frag_load(sh, wave * 32, kk);
-      half8 fa[4];
-#pragma unroll
-      for (int t = 0; t < 4; ++t) fa[t] = frag_load(sc, t * 32, kk);
-#pragma unroll
-      for (int t = 0; t < 4; ++t) acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_f16(fa[t], bh, acc[t], 0, 0, 0);
-      const half8 bl = frag_load(sl, wave * 32, kk);
-#pragma unroll
-      for (int t = 0; t < 4; ++t) acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_f16(fa[t], bl, acc[t], 0, 0, 0);
-    }
-  };
-  const int S = (a.D + kBK - 1) / kBK;
-  uint32_t cw[B];
-  uint4 rh[4], rl[4];
-  load_slab(0, cw, rh, rl);
-  for (int s = 0; s < S; ++s) {
-    __syncthreads();   // every wave is done with the previous slab (or tile)
-    {
-      _Float16 h[32];
-      unpack32<B>(cw, h);
-      _Float16* dst = sc + urow * kLdk + uhalf * 32;
-#pragma unroll
-      for (int i = 0; i < 32; i += 8) *reinterpret_cast<uint4*>(dst + i) = *reinterpret_cast<const uint4*>(h + i);
-    }
-    slab_store_n<4>(sh, rh, kWG);
-    slab_store_n<4>(sl, rl, kWG);
-    __syncthreads();
-    load_slab((s + 1) * kBK, cw, rh, rl);   // past the last slab: zeros, no memory touched
-    __builtin_amdgcn_sched_barrier(0);      // issue the loads before the MFMAs
-    compute();
-  }
-  __syncthreads();
-}
-
-enum { kModeLists = 0, kModeFallback = 1 };
-
-template <int KL>
-__device__ void merge_query(int64_t j, int cands, int k, const float* __restrict__ ps,
-                            const int32_t* __restrict__ pr, const QMeta* __restrict__ meta,
-                            const int64_t* __restrict__ ids, float* __restrict__ out_s, int64_t* __restrict__ out_i,
-                            float* __restrict__ bound);
-
-// Exact scores (hi and lo parts) of a range of store tiles: each lane keeps a
-// sorted private list of its best KL (score, row) pairs; the lists go to
-// part_s/part_r.  MODE kModeFallback only runs query tiles flagged in tflag.
-template <int B, int KL, int MODE>
-__global__ __launch_bounds__(kWG, 2) void k_score(ScoreArgs a) {
-  // one slab stage (codes, hi, lo: 128 rows each) or the list epilogue's
-  // 4 x 64 x 64 scores
-  constexpr int kSlab = 3 * kTB * kLdk;
-  constexpr int kLists = 2 * 4 * 64 * 64;
-  constexpr int kLdsHalves = kSlab > kLists ? kSlab : kLists;
-  __shared__ __attribute__((aligned(16))) _Float16 lds[kLdsHalves];
-  const int qt = blockIdx.x % a.nqt;
-  const int split = blockIdx.x / a.nqt;
-  if (MODE == kModeFallback && a.tflag[qt] == 0u) return;
-  const int64_t t0 = a.tile_begin + (int64_t)split * a.tiles_per_split;
-  const int64_t t1 = min(a.tile_end, t0 + a.tiles_per_split);
-  const int lane = threadIdx.x & 63;
-  const int wave = threadIdx.x >> 6;
-  const int64_t qbase = (int64_t)qt * kTB;
-  const int qrows = (int)min<int64_t>(kTB, a.nq - qbase);
-  const int64_t j = qbase + wave * 32 + (lane & 31);
-  const float osc = (j < a.nq) ? a.meta[j].osc : 0.0f;
-  const _Float16* QH = a.qhi + qbase * a.D;
-  const _Float16* QL = a.qlo + qbase * a.D;
-
-  float ls[KL];
-  int lr[KL];
-#pragma unroll
-  for (int p = 0; p < KL; ++p) {
-    ls[p] = -INFINITY;
-    lr[p] = kNoRow;
-  }
-
-  for (int64_t tile = t0; tile < t1; ++tile) {
-    const int64_t rbase = tile * kTB;
-    const int rows = (int)min<int64_t>(kTB, a.n - rbase);
-    floatx16 acc[4];
-    score_tile<B>(a, rbase, rows, QH, QL, qrows, lds, acc);
-
-    // The scale osc is positive, so the largest score is osc times the
-    // largest accumulator; only a partial tile needs the row check.
-    float amx = -INFINITY;
-    if (rows == kTB) {
-#pragma unroll
-      for (int t = 0; t < 4; ++t)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) amx = fmaxf(amx, acc[t][r]);
-    } else {
-#pragma unroll
-      for (int t = 0; t < 4; ++t)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) amx = (t * 32 + acc_row(r, lane) < rows) ? fmaxf(amx, acc[t][r]) : amx;
-    }
-    const float mx = amx * osc;
-    const bool hot = mx >= ls[KL - 1];
-    if (__ballot(hot) != 0ull) {
-      // Park this wave's 64 scores per lane in LDS (free after the K loop) and
-      // let the hot lanes walk them in a plain loop.
-      float* wl = reinterpret_cast<float*>(lds) + wave * 64 * 64;
-#pragma unroll
-      for (int t = 0; t < 4; ++t)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) wl[(t * 16 + r) * 64 + lane] = acc[t][r] * osc;
-      if (hot) {
-        for (int e = 0; e < 64; ++e) {
-          const int rl_ = (e >> 4) * 32 + acc_row(e & 15, lane);
-          if (rl_ >= rows) continue;
-          const float sc = wl[e * 64 + lane];
-          const int row = (int)(rbase + rl_);
-          if (!better(sc, row, ls[KL - 1], lr[KL - 1])) continue;
-          list_insert<KL>(ls, lr, sc, row);
-        }
-      }
-    }
-    __syncthreads();   // LDS is reused by the next tile's first slab
-  }
-  if (j < a.nq) {
-    const int slot = lane >> 5;
-    const int64_t o = ((j * a.splits + split) * 2 + slot) * (int64_t)KL;
-#pragma unroll
-    for (int p = 0; p < KL; ++p) {
-      a.part_s[o + p] = ls[p];
-      a.part_r[o + p] = lr[p];
-    }
-  }
-  if constexpr (MODE == kModeFallback) {
-    // The last of the tile's workgroups to finish merges the lists of the
-    // tile's flagged queries (one wave per query), so the pass needs no merge
-    // launch of its own.  Runs only for flagged tiles: the fences (release
-    // of every workgroup's lists, acquire by the last) cost nothing otherwise.
-    __shared__ bool last;
-    __threadfence();
-    __syncthreads();
-    if (threadIdx.x == 0) last = atomicAdd(&a.tdone[qt], 1u) == (uint32_t)(a.splits - 1);
-    __syncthreads();
-    if (!last) return;
-    __threadfence();
-    for (int q = wave; q < qrows; q += kWG / 64) {
-      const int64_t jq = qbase + q;
-      if (a.qflag[jq] == 0u) continue;
-      merge_query<KL>(jq, a.splits * 2 * KL, a.k, a.part_s, a.part_r, a.meta, a.ids, a.out_s, a.out_i, a.out_bound);
-    }
-  }
-}
-
-// Fold a lane's share of candidates into a sorted register list, then take k
-// rounds of the best list head of the wave under (score desc, row asc).  Rows
-// are distinct, so the winning head identifies its lane.  Writes the k picks
-// (ids mapped to global ids).  The head's order is that of the key (order-encoded score, complement of the row): larger is better;
-// scores are taken + 0.0f so that -0 and +0 are equal, as in `better`.
-template <int KL>
-__device__ __forceinline__ void wave_select(int k, float (&ls)[KL], int (&lr)[KL], int64_t j,
-                                            const int64_t* __restrict__ ids, float* __restrict__ out_s,
-                                            int64_t* __restrict__ out_i) {
-  const int lane = threadIdx.x & 63;
-  for (int t = 0; t < k; ++t) {
-    const unsigned long long key =
-        ((unsigned long long)f2ord(ls[0] + 0.0f) << 32) | (unsigned long long)(uint32_t)~(uint32_t)lr[0];
-    const unsigned long long best = wave_max_u64(key);
-    const float bs = ord2f((uint32_t)(best >> 32));
-    const int br = (int)~(uint32_t)best;
-    if (br != kNoRow && lr[0] == br) {        // this lane's head won: pop it
-#pragma unroll
-      for (int p = 0; p < KL - 1; ++p) {
-        ls[p] = ls[p + 1];
-        lr[p] = lr[p + 1];
-      }
-      ls[KL - 1] = -INFINITY;
-      lr[KL - 1] = kNoRow;
-    }
-    if (lane == 0) {
-      out_s[j * k + t] = (br == kNoRow) ? -INFINITY : bs;
-      out_i[j * k + t] = (br == kNoRow) ? -1 : ids[br];
-    }
-  }
-}
-
-__device__ __forceinline__ bool write_bad(const QMeta& m, int64_t j, int k, float* out_s, int64_t* out_i,
-                                          float* bound) {
-  const int lane = threadIdx.x & 63;
-  if (lane == 0 && bound) bound[j] = m.bound;
-  if (!m.bad) return false;
-  for (int t = lane; t < k; t += 64) {
-    out_s[j * k + t] = __builtin_nanf("");
-    out_i[j * k + t] = -1;
-  }
-  return true;
-}
-
-// One wave per query: the k best of the per-lane lists (segments of KL >= k
-// sorted entries, of which only the first k can matter), each lane folding its
-// share into a register list of KL.
-template <int KL>
-__global__ __launch_bounds__(256) void k_topk_merge(int64_t nq, int cands, int k, const float* __restrict__ ps,
-                                                    const int32_t* __restrict__ pr, const QMeta* __restrict__ meta,
-                                                    const int64_t* __restrict__ ids, float* __restrict__ out_s,
-                                                    int64_t* __restrict__ out_i, float* __restrict__ bound) {
-  const int64_t j = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (j >= nq) return;
-  merge_query<KL>(j, cands, k, ps, pr, meta, ids, out_s, out_i, bound);
-}
-
-// One wave: the merge of query j's lists (the body of k_topk_merge).
-template <int KL>
-__device__ void merge_query(int64_t j, int cands, int k, const float* __restrict__ ps,
-                            const int32_t* __restrict__ pr, const QMeta* __restrict__ meta,
-                            const int64_t* __restrict__ ids, float* __restrict__ out_s, int64_t* __restrict__ out_i,
-                            float* __restrict__ bound) {
-  const int lane = threadIdx.x & 63;
-  if (write_bad(meta[j], j, k, out_s, out_i, bound)) return;
-  const float* s = ps + j * (int64_t)cands;
-  const int32_t* r = pr + j * (int64_t)cands;
-  float ls[KL];
-  int lr[KL];
-#pragma unroll
-  for (int p = 0; p < KL; ++p) {
-    ls[p] = -INFINITY;
-    lr[p] = kNoRow;
-  }
-  // a lane's next entries loaded together before any is used (one load
-  // after another's test had put two round trips per entry on the path)
-  constexpr int kU = 2;
-  for (int c0 = lane; c0 < cands; c0 += 64 * kU) {
-    float cs[kU];
-    int cr[kU];
-#pragma unroll
-    for (int u = 0; u < kU; ++u) {
-      const int c = c0 + 64 * u;
-      const bool in = c < cands && (c % KL) < k;   // not below rank k of its own sorted segment
-      cr[u] = in ? r[c] : kNoRow;
-      cs[u] = in ? s[c] : -INFINITY;
-    }
-#pragma unroll
-    for (int u = 0; u < kU; ++u) {
-      if (cr[u] == kNoRow || !better(cs[u], cr[u], ls[KL - 1], lr[KL - 1])) continue;
-      list_insert<KL>(ls, lr, cs[u], cr[u]);
-    }
-  }
-  wave_select<KL>(k, ls, lr, j, ids, out_s, out_i);
 }
 
 // ------------------------------------------------------------------ thresholds
@@ -683,6 +324,7 @@ using FilterTile = Tile<2, 4, 2, 1, 4>;
 // registers, one workgroup per CU: half the code and query loads per flop of
 // FilterTile; for the filter pass of stores with many tiles
 using FilterTileL = Tile<4, 4, 2, 2, 4>;
+constexpr int kMaxBits = 22;       // code widths that can be scored
 constexpr int kFilterGroupQ = 8;   // query tiles per group in the tile order
 constexpr int kSampleEntries = 4;  // entries per query and 128-row store tile of the sample pass
 constexpr int64_t kSampleTiles = 2048;   // sample tiles with entries of their own (later ones share them)
@@ -707,7 +349,9 @@ constexpr int64_t kFilterLargeMinTiles = 1024;   // large filter tiles from this
 // 81 us here; its sample pass 54 -> 16 us.  The run-time slab loop is as fast as
 // one unrolled for D = 768: 54 us at 23,969 rows x 1,024 queries, 2.30 ms at
 // 361,802 x 4,096, both as before.)
-// SAMPLE (FilterTile only): the sample pass of the threshold plan over store
+// kDense (FilterTile only): every H is written, to entry r of the query's
+// buffer for row r (cap: the rows rounded up to whole tiles).
+// kSample (FilterTile only): the sample pass of the threshold plan over store
 // tiles [0, tile_end) (all of them whole) instead: per query and tile, the best
 // H of each of the four lanes holding the query (disjoint sets of 32 rows) at
 // entries [4 t, 4 t + 4) of the query's list, t the tile (modulo sample_tiles:
@@ -716,9 +360,11 @@ constexpr int64_t kFilterLargeMinTiles = 1024;   // large filter tiles from this
 // sample's k-th best H: a valid base for the threshold (lower only where
 // several of the best rows share a lane).
 // a.nqt and a.tile_end count tiles of this kernel's size.
-template <class C, int B, bool SAMPLE, int SETS>
+enum { kFilter = 0, kSample = 1, kDense = 2 };
+
+template <class C, int B, int MODE, int SETS>
 __global__ __launch_bounds__(C::kThreads, C::kMinWaves) void k_filter(ScoreArgs a) {
-  static_assert(!SAMPLE || (C::BM == kTB && C::TJ == 1), "the sample pass runs on 128-row tiles of one query block");
+  static_assert(MODE == kFilter || (C::BM == kTB && C::TJ == 1), "128-row tiles of one query block");
   static_assert(SETS == 1 || SETS == 3, "one or three register sets");
   static_assert(C::kThreads == 4 * C::BM, "four threads per row");
   __shared__ _Float16 lds[C::kLdsHalves];
@@ -744,7 +390,7 @@ __global__ __launch_bounds__(C::kThreads, C::kMinWaves) void k_filter(ScoreArgs 
   for (int y = 0; y < C::TJ; ++y) {
     j[y] = qbase + wn * C::TJ * 32 + y * 32 + (lane & 31);
     jv[y] = j[y] < a.nq;
-    th[y] = (jv[y] && !SAMPLE) ? a.thr[j[y]] : 0.0f;
+    th[y] = (jv[y] && MODE == kFilter) ? a.thr[j[y]] : 0.0f;
     osc[y] = jv[y] ? a.meta[j[y]].osc : 0.0f;
   }
 
@@ -785,7 +431,7 @@ __global__ __launch_bounds__(C::kThreads, C::kMinWaves) void k_filter(ScoreArgs 
   };
   auto store = [&](int st, const uint32_t (&cw)[kNW], const uint4 (&qv)[C::kPerB]) {
     _Float16 h[16];
-    unpack16<B>(cw, upart & 1, h);
+    unpack16<B>(cw, upart & 1, a.sh, h);
     _Float16* dst = sa(st) + urow * kLdk + upart * 16;
     *reinterpret_cast<uint4*>(dst) = *reinterpret_cast<const uint4*>(h);
     *reinterpret_cast<uint4*>(dst + 8) = *reinterpret_cast<const uint4*>(h + 8);
@@ -844,7 +490,21 @@ __global__ __launch_bounds__(C::kThreads, C::kMinWaves) void k_filter(ScoreArgs 
       }
     }
   }
-  if constexpr (SAMPLE) {
+  if constexpr (MODE == kDense) {
+    // this lane's rows, four consecutive ones per store
+    if (jv[0]) {
+      float* o = a.cand_s + j[0] * a.cap + rbase + wm * C::TI * 32;
+#pragma unroll
+      for (int x = 0; x < C::TI; ++x)
+#pragma unroll
+        for (int g4 = 0; g4 < 4; ++g4)
+          *reinterpret_cast<float4*>(o + x * 32 + acc_row(4 * g4, lane)) =
+              make_float4(acc[x][0][4 * g4] * osc[0], acc[x][0][4 * g4 + 1] * osc[0], acc[x][0][4 * g4 + 2] * osc[0],
+                          acc[x][0][4 * g4 + 3] * osc[0]);
+    }
+    return;
+  }
+  if constexpr (MODE == kSample) {
     // this lane's best H over its 32 rows
     float best = -INFINITY;
 #pragma unroll
@@ -905,74 +565,64 @@ __global__ __launch_bounds__(C::kThreads, C::kMinWaves) void k_filter(ScoreArgs 
   }
 }
 
-// large: the filter pass on FilterTileL (a.nqt and a.tile_end in its tiles)
-template <int B, bool SAMPLE>
-lam_status launch_filter(int b, bool large, dim3 grid, hipStream_t st, const ScoreArgs& a) {
+// large: the filter pass on FilterTileL (a.nqt and a.tile_end in its tiles).
+// Codes of more than 14 bits keep one slab of loads in flight (three sets of
+// their words do not fit in the registers).
+template <int B, int MODE>
+lam_status launch_filter(int b, bool large, int64_t grid, hipStream_t st, const ScoreArgs& a) {
   if (b == B) {
-    if constexpr (!SAMPLE) {
+    if constexpr (MODE == kFilter) {
       if (large) {
-        hipLaunchKernelGGL((k_filter<FilterTileL, B, false, 1>), grid, dim3(FilterTileL::kThreads), 0, st, a);
+        hipLaunchKernelGGL((k_filter<FilterTileL, B, kFilter, 1>), dim3((unsigned)grid), dim3(FilterTileL::kThreads), 0,
+                           st, a);
         LAM_HIP(hipGetLastError());
         return LAM_OK;
       }
     }
-    hipLaunchKernelGGL((k_filter<FilterTile, B, SAMPLE, 3>), grid, dim3(FilterTile::kThreads), 0, st, a);
+    hipLaunchKernelGGL((k_filter<FilterTile, B, MODE, (B <= 14 ? 3 : 1)>), dim3((unsigned)grid),
+                       dim3(FilterTile::kThreads), 0, st, a);
     LAM_HIP(hipGetLastError());
     return LAM_OK;
   }
-  if constexpr (B < 12) return launch_filter<B + 1, SAMPLE>(b, large, grid, st, a);
-  set_error("scoring supports codes of at most 12 bits (got %d)", b);
+  if constexpr (B < kMaxBits) return launch_filter<B + 1, MODE>(b, large, grid, st, a);
+  set_error("scoring supports codes of at most %d bits (got %d)", kMaxBits, b);
   return LAM_ESTATE;
 }
 
 // ------------------------------------------------------------------ rescoring
-constexpr int kRescoreCap = 1024;    // candidates near the k-th score rescored per query
 constexpr int kRescoreThreads = 256;
 constexpr int kRescoreLanes = 8;     // lanes per rescored row
 
-// The rescoring of m rows (in LDS) of query j from the codes and the float32
-// query, summed in binary64 and rounded once, and a bitonic sort of the keys
-// (score desc, row asc); the kk best go to the outputs.
+// q . code over the groups of 32 codes g = sl, sl + 8, ... of a row (words at
+// w), in binary64: one lane's share.  Products of a float32 and a code of at
+// most 22 bits are exact in binary64.
 template <int B>
-__device__ __forceinline__ void rescore_sort(int64_t j, uint32_t m, int kk, int k, const int32_t* rows,
-                                             unsigned long long* keys, const int64_t* __restrict__ ids,
-                                             const float* __restrict__ q, double step,
-                                             const uint32_t* __restrict__ codes, int64_t row_words, int D,
-                                             float* __restrict__ out_s, int64_t* __restrict__ out_i) {
-  const int tid = threadIdx.x;
-  const float* qj = q + j * D;
-  const int slot = tid / kRescoreLanes, sl = tid % kRescoreLanes;
-  const int ngroups = D / 32;
-  for (uint32_t t0 = 0; t0 < m; t0 += kRescoreThreads / kRescoreLanes) {
-    const uint32_t t = t0 + (uint32_t)slot;
-    double acc = 0.0;
-    if (t < m) {
-      const uint32_t* w = codes + (int64_t)rows[t] * row_words;
-      for (int g = sl; g < ngroups; g += kRescoreLanes) {
-        uint32_t cw[B];
+__device__ __forceinline__ double lane_dot(const uint32_t* __restrict__ w, const float* __restrict__ q, int ngroups,
+                                           int sl) {
+  double acc = 0.0;
+  for (int g = sl; g < ngroups; g += kRescoreLanes) {
+    uint32_t cw[B];
 #pragma unroll
-        for (int i = 0; i < B; ++i) cw[i] = w[g * B + i];
-        float qv[32];
+    for (int i = 0; i < B; ++i) cw[i] = w[g * B + i];
+    float qv[32];
 #pragma unroll
-        for (int e = 0; e < 32; ++e) qv[e] = qj[g * 32 + e];
-        _Float16 h[32];
-        unpack32<B>(cw, h);
+    for (int e = 0; e < 32; ++e) qv[e] = q[g * 32 + e];
 #pragma unroll
-        for (int e = 0; e < 32; ++e) acc = fma((double)qv[e], (double)(float)h[e], acc);
-      }
-    }
-    for (int o = kRescoreLanes / 2; o > 0; o >>= 1) acc += __shfl_xor(acc, o);   // within the row's lanes
-    if (t < m && sl == 0)
-      keys[t] = ((unsigned long long)f2ord((float)(acc * step) + 0.0f) << 32) | (unsigned long long)(~(uint32_t)rows[t]);
+    for (int e = 0; e < 32; ++e) acc = fma((double)qv[e], (double)code_at<B>(cw, e), acc);
   }
-  // bitonic sort of the m keys, descending (score, then ~row); padding keys 0
-  uint32_t P = 1u;
-  while (P < m) P <<= 1;
-  for (uint32_t i = m + tid; i < P; i += kRescoreThreads) keys[i] = 0ull;
-  __syncthreads();
+  return acc;
+}
+
+// The key of a row's score, ordered by (score desc, row asc): larger is better.
+__device__ __forceinline__ unsigned long long score_key(double acc, double step, uint32_t row) {
+  return ((unsigned long long)f2ord((float)(acc * step) + 0.0f) << 32) | (unsigned long long)(~row);
+}
+
+// Descending bitonic sort of P keys in LDS (P a power of two) by the workgroup.
+__device__ __forceinline__ void sort_keys(unsigned long long* keys, uint32_t P) {
   for (uint32_t size = 2; size <= P; size <<= 1) {
     for (uint32_t stride = size >> 1; stride > 0; stride >>= 1) {
-      for (uint32_t i = tid; i < P; i += kRescoreThreads) {
+      for (uint32_t i = threadIdx.x; i < P; i += kRescoreThreads) {
         const uint32_t l = i ^ stride;
         if (l > i) {
           const unsigned long long x = keys[i], y = keys[l];
@@ -986,10 +636,60 @@ __device__ __forceinline__ void rescore_sort(int64_t j, uint32_t m, int kk, int 
       __syncthreads();
     }
   }
-  for (int t = tid; t < kk; t += kRescoreThreads) {
-    out_s[j * k + t] = ord2f((uint32_t)(keys[t] >> 32));
-    out_i[j * k + t] = ids[~(uint32_t)(keys[t] & 0xffffffffull)];
+}
+
+// The best k of any number of keys: keys above the k-th found so far are
+// appended to a buffer, which is sorted and cut back to k when the next step
+// might not fit.
+constexpr int kExactBuf = 1024;
+
+struct TopBuf {
+  unsigned long long keys[kExactBuf];
+  unsigned long long floor;   // keys up to it are not in the top k
+  uint32_t cnt;
+};
+
+// Called by the whole workgroup; ends with a barrier.
+__device__ __forceinline__ void topbuf_clear(TopBuf& b) {
+  if (threadIdx.x == 0) {
+    b.cnt = 0u;
+    b.floor = 0ull;
   }
+  __syncthreads();
+}
+
+__device__ __forceinline__ void topbuf_push(TopBuf& b, unsigned long long key) {
+  if (key > b.floor) b.keys[atomicAdd(&b.cnt, 1u)] = key;
+}
+
+// Called by the whole workgroup past a barrier: room for `room` more keys.
+__device__ __forceinline__ void topbuf_cut(TopBuf& b, int k, uint32_t room) {
+  const uint32_t c = b.cnt;
+  __syncthreads();   // every thread has the same count before any pushes again
+  if (c + room <= (uint32_t)kExactBuf) return;
+  for (uint32_t i = c + threadIdx.x; i < (uint32_t)kExactBuf; i += kRescoreThreads) b.keys[i] = 0ull;
+  __syncthreads();
+  sort_keys(b.keys, kExactBuf);
+  if (threadIdx.x == 0) {
+    b.cnt = min(c, (uint32_t)k);
+    b.floor = c >= (uint32_t)k ? b.keys[k - 1] : 0ull;
+  }
+  __syncthreads();
+}
+
+// The exact score of row t of a list of m rows in LDS, by the eight lanes of
+// slot t % 32; true for the lane that holds the key.
+template <int B>
+__device__ __forceinline__ bool rescore_row(uint32_t t, uint32_t m, const int32_t* rows, const float* __restrict__ qj,
+                                            double step, const uint32_t* __restrict__ codes, int64_t row_words, int D,
+                                            unsigned long long& key) {
+  const int sl = (int)threadIdx.x % kRescoreLanes;
+  double acc = 0.0;
+  if (t < m) acc = lane_dot<B>(codes + (int64_t)rows[t] * row_words, qj, D / 32, sl);
+  for (int o = kRescoreLanes / 2; o > 0; o >>= 1) acc += __shfl_xor(acc, o);   // within the row's lanes
+  if (t >= m || sl != 0) return false;
+  key = score_key(acc, step, (uint32_t)rows[t]);
+  return true;
 }
 
 // One workgroup per query: the selection among the candidates and the exact
@@ -999,35 +699,32 @@ __device__ __forceinline__ void rescore_sort(int64_t j, uint32_t m, int kk, int 
 // float32 query, summed in binary64 and rounded once to float32, and the k
 // best by (S desc, row asc) are the answer.  Any lower bound of h_k serves:
 // wave 0 takes the one of wave_kth_floor (beyond 1,024 candidates several
-// share a key as their maximum), which costs the same for every k.  More than
-// kRescoreCap rows to rescore (many near-equal scores) flag the query for the
-// exact fallback pass, as an overflowed buffer does.  Also writes the bound,
-// NaN outputs for an invalid query, and (-inf, -1) past the candidates.  Eight
-// lanes share a rescored row (32 rows in flight per workgroup); a lane takes
-// whole groups of 32 codes (B words), unpacked as the scoring kernel unpacks
-// them (exactly, to fp16).
-template <int B>
+// share a key as their maximum), which costs the same for every k.  Up to 1,024
+// such rows are sorted at once; more (many near-equal scores) go through the
+// buffer in steps of 256 candidates.  An overflowed candidate buffer flags the
+// query for the exact pass.  Also writes the bound, NaN outputs for an invalid
+// query, and (-inf, -1) past the candidates.  Eight lanes share a rescored row
+// (32 rows in flight per workgroup); a lane takes whole groups of 32 codes (B
+// words).
+// DENSE: the candidates are the store's n rows in order (no query is flagged).
+template <int B, bool DENSE>
 __global__ __launch_bounds__(kRescoreThreads) void k_select_rescore(
-    int64_t nq, uint32_t cap, int k, const uint32_t* __restrict__ cnt, const float* __restrict__ cs,
+    int64_t nq, uint32_t n, uint32_t cap, int k, const uint32_t* __restrict__ cnt, const float* __restrict__ cs,
     const int32_t* __restrict__ cr, const QMeta* __restrict__ meta, const int64_t* __restrict__ ids,
     const float* __restrict__ q, double step, const uint32_t* __restrict__ codes, int64_t row_words, int D,
-    float* __restrict__ out_s, int64_t* __restrict__ out_i, float* __restrict__ bound, uint32_t* __restrict__ qflag,
-    uint32_t* __restrict__ tflag) {
-  __shared__ int32_t rows[kRescoreCap];
-  __shared__ unsigned long long keys[kRescoreCap];
+    float* __restrict__ out_s, int64_t* __restrict__ out_i, float* __restrict__ bound, uint32_t* __restrict__ n_flag,
+    uint32_t* __restrict__ flagged) {
+  constexpr int kCap = kExactBuf;
+  __shared__ int32_t rows[kCap];
+  __shared__ TopBuf buf;
   __shared__ uint32_t m_sh;
   __shared__ float thr_sh;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int64_t j = blockIdx.x;
   if (j >= nq) return;
-  const uint32_t c = cnt[j];
+  const uint32_t c = DENSE ? n : cnt[j];
   const QMeta mj = meta[j];
-  const bool over = c > cap;
-  if (tid == 0) {
-    qflag[j] = over ? 1u : 0u;
-    if (over) atomicOr(&tflag[j / kTB], 1u);
-    if (bound) bound[j] = mj.bound;
-  }
+  if (tid == 0 && bound) bound[j] = mj.bound;
   if (mj.bad) {
     for (int t = tid; t < k; t += kRescoreThreads) {
       out_s[j * k + t] = __builtin_nanf("");
@@ -1035,7 +732,10 @@ __global__ __launch_bounds__(kRescoreThreads) void k_select_rescore(
     }
     return;
   }
-  if (over) return;   // the exact fallback redoes the query
+  if (!DENSE && c > cap) {   // the exact pass redoes the query
+    if (tid == 0) flagged[atomicAdd(n_flag, 1u)] = (uint32_t)j;
+    return;
+  }
   const int kk = (int)min((uint32_t)k, c);
   for (int t = kk + tid; t < k; t += kRescoreThreads) {   // fewer candidates than k
     out_s[j * k + t] = -INFINITY;
@@ -1050,7 +750,7 @@ __global__ __launch_bounds__(kRescoreThreads) void k_select_rescore(
   for (int u = 0; u < 2; ++u) {
     const uint32_t i = (uint32_t)(tid + u * kRescoreThreads);
     fs[u] = i < c ? cs[j * cap + i] : 0.0f;
-    fr[u] = i < c ? cr[j * cap + i] : 0;
+    fr[u] = DENSE ? (int)i : (i < c ? cr[j * cap + i] : 0);
   }
   if (wave == 0) {
     uint32_t key[kThrKeys];
@@ -1077,59 +777,196 @@ __global__ __launch_bounds__(kRescoreThreads) void k_select_rescore(
   for (int u = 0; u < 2; ++u) {
     if ((uint32_t)(tid + u * kRescoreThreads) < c && fs[u] >= thr) {
       const uint32_t p = atomicAdd(&m_sh, 1u);
-      if (p < (uint32_t)kRescoreCap) rows[p] = fr[u];
+      if (p < (uint32_t)kCap) rows[p] = fr[u];
     }
   }
   for (uint32_t i = tid + 2 * kRescoreThreads; i < c; i += kRescoreThreads) {
     if (cs[j * cap + i] >= thr) {
       const uint32_t p = atomicAdd(&m_sh, 1u);
-      if (p < (uint32_t)kRescoreCap) rows[p] = cr[j * cap + i];
+      if (p < (uint32_t)kCap) rows[p] = DENSE ? (int)i : cr[j * cap + i];
     }
   }
   __syncthreads();
   const uint32_t m = m_sh;
-  if (m > (uint32_t)kRescoreCap) {
-    if (tid == 0) {
-      qflag[j] = 1u;
-      atomicOr(&tflag[j / kTB], 1u);
+  const float* qj = q + j * D;
+  const uint32_t slot = (uint32_t)(tid / kRescoreLanes);
+  constexpr uint32_t kSlots = kRescoreThreads / kRescoreLanes;
+  unsigned long long key;
+  if (m <= (uint32_t)kCap) {
+    for (uint32_t t0 = 0; t0 < m; t0 += kSlots)
+      if (rescore_row<B>(t0 + slot, m, rows, qj, step, codes, row_words, D, key)) buf.keys[t0 + slot] = key;
+    uint32_t P = 1u;
+    while (P < m) P <<= 1;
+    for (uint32_t i = m + tid; i < P; i += kRescoreThreads) buf.keys[i] = 0ull;   // padding
+    __syncthreads();
+    sort_keys(buf.keys, P);
+  } else {
+    topbuf_clear(buf);
+    for (uint32_t i0 = 0; i0 < c; i0 += kRescoreThreads) {
+      if (tid == 0) m_sh = 0u;
+      __syncthreads();
+      const uint32_t i = i0 + (uint32_t)tid;
+      if (i < c && cs[j * cap + i] >= thr) rows[atomicAdd(&m_sh, 1u)] = DENSE ? (int)i : cr[j * cap + i];
+      __syncthreads();
+      const uint32_t mi = m_sh;
+      for (uint32_t t0 = 0; t0 < mi; t0 += kSlots)
+        if (rescore_row<B>(t0 + slot, mi, rows, qj, step, codes, row_words, D, key)) topbuf_push(buf, key);
+      __syncthreads();
+      topbuf_cut(buf, k, kRescoreThreads);
     }
-    return;
+    topbuf_cut(buf, k, kExactBuf);   // sorts what is left
   }
-  rescore_sort<B>(j, m, kk, k, rows, keys, ids, q, step, codes, row_words, D, out_s, out_i);
+  for (int t = tid; t < kk; t += kRescoreThreads) {
+    out_s[j * k + t] = ord2f((uint32_t)(buf.keys[t] >> 32));
+    out_i[j * k + t] = ids[~(uint32_t)(buf.keys[t] & 0xffffffffull)];
+  }
 }
 
+// The exact pass over the flagged queries (those whose candidates overflowed):
+// a work item is one flagged query and one of `splits` ranges of store rows,
+// all scored exactly.  Eight lanes share four rows at a time (the query's
+// values, held in LDS in binary64, serve all four, and their sums are
+// independent chains), 128 rows per step.  The range's best k go to the query's
+// candidate buffer (no longer needed; splits * k <= cap entries), and the last
+// of a query's workgroups merges them the same way.  Launched always; without
+// flagged queries every workgroup returns after one load.
+// Per flagged query 0.11 ms at 361,802 rows, D = 768 (bound by reading the codes
+// and by the conversions to binary64; 0.21 ms with one row at a time) and 18 us
+// at 60,000 x 384.  The former pass kept sorted lists of the k best in every
+// lane of an MFMA scan, for all 128 queries of a flagged query's tile: one
+// flagged query in 128 cost 0.77 ms, now 0.28 ms; all 128 flagged 4.8 ms, now
+// 14 ms (top-10, D = 768), or 16 ms, now 2.4 ms (top-50, 60,000 x 384).
+constexpr int kExactRows = 4;   // rows per slot and step
+
 template <int B>
-lam_status dispatch_bits(int b, int kl, int mode, dim3 grid, hipStream_t st, const ScoreArgs& a) {
+__global__ __launch_bounds__(kRescoreThreads) void k_exact(
+    int64_t n, int splits, int64_t rows_per_split, uint32_t cap, int k, const int64_t* __restrict__ ids,
+    const float* __restrict__ q, double step, const uint32_t* __restrict__ codes, int64_t row_words, int D,
+    float* __restrict__ cs, int32_t* __restrict__ cr, uint32_t* __restrict__ done, const uint32_t* __restrict__ n_flag,
+    const uint32_t* __restrict__ flagged, float* __restrict__ out_s, int64_t* __restrict__ out_i) {
+  const uint32_t nf = *n_flag;
+  if (nf == 0u) return;
+  extern __shared__ double qd[];   // the query, one pad per group of 32
+  __shared__ TopBuf buf;
+  __shared__ bool last;
+  const int tid = threadIdx.x;
+  const int slot = tid / kRescoreLanes, sl = tid % kRescoreLanes;
+  constexpr int kSlots = kRescoreThreads / kRescoreLanes;
+  const int ngroups = D / 32;
+  const uint64_t items = (uint64_t)nf * (uint64_t)splits;
+  for (uint64_t it = blockIdx.x; it < items; it += gridDim.x) {
+    const int64_t j = flagged[it / (uint64_t)splits];
+    const int sp = (int)(it % (uint64_t)splits);
+    const int64_t r0 = sp * rows_per_split, r1 = min(n, r0 + rows_per_split);
+    for (int d = tid; d < D; d += kRescoreThreads) qd[d + (d >> 5)] = (double)q[j * D + d];
+    topbuf_clear(buf);
+    for (int64_t r = r0; r < r1; r += kSlots * kExactRows) {
+      double acc[kExactRows];
+      const uint32_t* w[kExactRows];
+#pragma unroll
+      for (int u = 0; u < kExactRows; ++u) {
+        acc[u] = 0.0;
+        w[u] = codes + min(r + u * kSlots + slot, n - 1) * row_words;   // (a row past the range is not used)
+      }
+      for (int g = sl; g < ngroups; g += kRescoreLanes) {
+        uint32_t cw[kExactRows][B];
+#pragma unroll
+        for (int u = 0; u < kExactRows; ++u)
+#pragma unroll
+          for (int i = 0; i < B; ++i) cw[u][i] = w[u][g * B + i];
+#pragma unroll
+        for (int e = 0; e < 32; ++e) {
+          const double qe = qd[g * 33 + e];
+#pragma unroll
+          for (int u = 0; u < kExactRows; ++u) acc[u] = fma(qe, (double)code_at<B>(cw[u], e), acc[u]);
+        }
+      }
+#pragma unroll
+      for (int u = 0; u < kExactRows; ++u) {
+        for (int o = kRescoreLanes / 2; o > 0; o >>= 1) acc[u] += __shfl_xor(acc[u], o);
+        const int64_t row = r + u * kSlots + slot;
+        if (row < r1 && sl == 0) topbuf_push(buf, score_key(acc[u], step, (uint32_t)row));
+      }
+      __syncthreads();
+      topbuf_cut(buf, k, kSlots * kExactRows);
+    }
+    topbuf_cut(buf, k, kExactBuf);   // sorts what is left
+    for (int t = tid; t < k; t += kRescoreThreads) {
+      const unsigned long long key = t < (int)buf.cnt ? buf.keys[t] : 0ull;
+      cs[j * cap + sp * k + t] = __uint_as_float((uint32_t)(key >> 32));
+      cr[j * cap + sp * k + t] = (int32_t)(uint32_t)key;
+    }
+    // release this range's keys, count it, and let the query's last range
+    // acquire all of them
+    __threadfence();
+    __syncthreads();
+    if (tid == 0) last = atomicAdd(&done[j], 1u) == (uint32_t)(splits - 1);
+    __syncthreads();
+    if (!last) continue;
+    __threadfence();
+    topbuf_clear(buf);
+    for (int t0 = 0; t0 < splits * k; t0 += kRescoreThreads) {
+      const int t = t0 + tid;
+      if (t < splits * k)
+        topbuf_push(buf, ((unsigned long long)__float_as_uint(cs[j * cap + t]) << 32) |
+                             (unsigned long long)(uint32_t)cr[j * cap + t]);
+      __syncthreads();
+      topbuf_cut(buf, k, kRescoreThreads);
+    }
+    topbuf_cut(buf, k, kExactBuf);
+    for (int t = tid; t < k; t += kRescoreThreads) {   // (a flagged query has more than k rows)
+      out_s[j * k + t] = ord2f((uint32_t)(buf.keys[t] >> 32));
+      out_i[j * k + t] = ids[~(uint32_t)(buf.keys[t] & 0xffffffffull)];
+    }
+    __syncthreads();
+  }
+}
+
+// The rows scored exactly: arguments shared by the selection and the exact pass.
+struct ExactArgs {
+  int64_t nq, n;
+  uint32_t cap;
+  int k;
+  uint32_t* cnt;
+  float* cs;
+  int32_t* cr;
+  const QMeta* meta;
+  const int64_t* ids;
+  const float* q;
+  double step;
+  const uint32_t* codes;
+  int64_t row_words;
+  int D;
+  float* out_s;
+  int64_t* out_i;
+  float* bound;
+  uint32_t *n_flag, *flagged, *done;
+  int splits;
+};
+
+enum { kSelect = 0, kSelectDense = 1, kExactPass = 2 };
+
+template <int B>
+lam_status launch_exact(int b, int what, hipStream_t st, const ExactArgs& a) {
   if (b == B) {
-    if (mode == kModeLists) {
-      if (kl == 16) hipLaunchKernelGGL((k_score<B, 16, kModeLists>), grid, dim3(kWG), 0, st, a);
-      else hipLaunchKernelGGL((k_score<B, 64, kModeLists>), grid, dim3(kWG), 0, st, a);
+    if (what == kSelect) {
+      hipLaunchKernelGGL((k_select_rescore<B, false>), dim3((unsigned)a.nq), dim3(kRescoreThreads), 0, st, a.nq,
+                         (uint32_t)a.n, a.cap, a.k, a.cnt, a.cs, a.cr, a.meta, a.ids, a.q, a.step, a.codes,
+                         a.row_words, a.D, a.out_s, a.out_i, a.bound, a.n_flag, a.flagged);
+    } else if (what == kSelectDense) {
+      hipLaunchKernelGGL((k_select_rescore<B, true>), dim3((unsigned)a.nq), dim3(kRescoreThreads), 0, st, a.nq,
+                         (uint32_t)a.n, a.cap, a.k, a.cnt, a.cs, a.cr, a.meta, a.ids, a.q, a.step, a.codes,
+                         a.row_words, a.D, a.out_s, a.out_i, a.bound, a.n_flag, a.flagged);
     } else {
-      if (kl == 16) hipLaunchKernelGGL((k_score<B, 16, kModeFallback>), grid, dim3(kWG), 0, st, a);
-      else hipLaunchKernelGGL((k_score<B, 64, kModeFallback>), grid, dim3(kWG), 0, st, a);
+      hipLaunchKernelGGL((k_exact<B>), dim3(1024), dim3(kRescoreThreads), (size_t)(a.D / 32) * 33 * 8, st, a.n, a.splits,
+                         (a.n + a.splits - 1) / a.splits, a.cap, a.k, a.ids, a.q, a.step, a.codes, a.row_words, a.D,
+                         a.cs, a.cr, a.done, a.n_flag, a.flagged, a.out_s, a.out_i);
     }
-    return LAM_OK;
-  }
-  if constexpr (B < 12) return dispatch_bits<B + 1>(b, kl, mode, grid, st, a);
-  set_error("scoring supports codes of at most 12 bits (got %d)", b);
-  return LAM_ESTATE;
-}
-
-template <int B>
-lam_status launch_rescore(int b, dim3 grid, hipStream_t st, int64_t nq, uint32_t cap, int k, const uint32_t* cnt,
-                          const float* cs, const int32_t* cr, const QMeta* meta, const int64_t* ids, const float* q,
-                          double step, const uint32_t* codes, int64_t row_words, int D, float* out_s, int64_t* out_i,
-                          float* bound, uint32_t* qflag, uint32_t* tflag) {
-  if (b == B) {
-    hipLaunchKernelGGL((k_select_rescore<B>), grid, dim3(kRescoreThreads), 0, st, nq, cap, k, cnt, cs, cr, meta, ids,
-                       q, step, codes, row_words, D, out_s, out_i, bound, qflag, tflag);
     LAM_HIP(hipGetLastError());
     return LAM_OK;
   }
-  if constexpr (B < 12)
-    return launch_rescore<B + 1>(b, grid, st, nq, cap, k, cnt, cs, cr, meta, ids, q, step, codes, row_words, D, out_s,
-                                 out_i, bound, qflag, tflag);
-  set_error("scoring supports codes of at most 12 bits (got %d)", b);
+  if constexpr (B < kMaxBits) return launch_exact<B + 1>(b, what, st, a);
+  set_error("scoring supports codes of at most %d bits (got %d)", kMaxBits, b);
   return LAM_ESTATE;
 }
 
@@ -1138,84 +975,19 @@ __global__ __launch_bounds__(256) void k_fill_zero(uint32_t* __restrict__ p, int
   if (i < n) p[i] = 0u;
 }
 
-// Split a tile range over query tiles so that the grid holds about 1024
-// workgroups; returns (splits, tiles per split).
-void plan_splits(int nqt, int64_t ntiles, int* splits, int64_t* tps, int max_splits) {
-  if (ntiles <= 0) {
-    *splits = 1;
-    *tps = 0;
-    return;
-  }
-  const int64_t want = std::min<int64_t>(max_splits, std::max<int64_t>(1, (1024 + nqt - 1) / nqt));
-  int64_t s = std::min<int64_t>(want, ntiles);
-  const int64_t t = (ntiles + s - 1) / s;
-  *tps = t;
-  *splits = (int)((ntiles + t - 1) / t);
-}
-
-// ---- codes of 13 to 22 bits
-// A code c of b bits is 2^11 (c >> 11) + (c & 2047) with |c >> 11| <= 2^(b-12)
-// <= 1,024 and 0 <= c & 2047 <= 2,047: both parts are 12-bit codes, exact in
-// fp16.  The split store has 2D columns, column d holding c_d >> 11 and column
-// D + d holding c_d & 2047; a query q becomes [2^11 q, q] (exact scalings), so
-// that s sum_d' q'_d' code'_d' = s sum_d q_d code_d term by term.
-constexpr int kWideMaxBits = 22;
-constexpr int kWideShift = 11;
-
-// One thread per 32 columns of a split row (12 words of 12-bit codes).
-__global__ __launch_bounds__(256) void k_wide_codes(const uint32_t* __restrict__ src, int64_t n, int D, int b,
-                                                    uint32_t* __restrict__ dst) {
-  const int G = 2 * D / 32;   // groups of 32 split columns per row
-  const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (t >= n * G) return;
-  const int64_t row = t / G;
-  const int g = (int)(t - row * G);
-  const bool low = g >= D / 32;
-  const int d0 = (low ? g - D / 32 : g) * 32;
-  const uint32_t* w = src + row * ((int64_t)D * b / 32);
-  uint32_t o[12];
-#pragma unroll
-  for (int i = 0; i < 12; ++i) o[i] = 0u;
-#pragma unroll
-  for (int e = 0; e < 32; ++e) {
-    const int64_t bit = (int64_t)(d0 + e) * b;
-    const int wi = (int)(bit >> 5), off = (int)(bit & 31);
-    uint32_t u = w[wi] >> off;
-    if (off + b > 32) u |= w[wi + 1] << (32 - off);   // the code's bits lie inside the row
-    const int32_t c = (int32_t)(u << (32 - b)) >> (32 - b);
-    const uint32_t v = (uint32_t)(low ? (c & ((1 << kWideShift) - 1)) : (c >> kWideShift)) & 0xfffu;
-    const int ob = e * 12, ow = ob >> 5, oo = ob & 31;
-    o[ow] |= v << oo;
-    if (oo + 12 > 32) o[ow + 1] |= v >> (32 - oo);
-  }
-  uint32_t* out = dst + row * ((int64_t)2 * D * 12 / 32) + (int64_t)g * 12;
-#pragma unroll
-  for (int i = 0; i < 12; ++i) out[i] = o[i];
-}
-
-// q' = [2^11 q, q], one thread per element.
-__global__ __launch_bounds__(256) void k_wide_queries(const float* __restrict__ q, int64_t nq, int D,
-                                                      float* __restrict__ qw) {
-  const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (t >= nq * 2 * D) return;
-  const int64_t j = t / (2 * D);
-  const int d = (int)(t - j * 2 * D);
-  qw[t] = d < D ? q[j * D + d] * (float)(1 << kWideShift) : q[j * D + d - D];
-}
-
 }  // namespace
 
 // What the scoring passes read of a store: its coded rows (D columns of b-bit
-// codes, step s = 2 eps), their ids, R >= s ||code_y|| for every row y, and
-// the first column counted in the reported bound.
+// codes, step s = 2 eps), their ids, R >= s ||code_y|| for every row y, and the
+// low bits sh that the scan leaves out so that the rest fits 12 bits.
 struct ScoreView {
   int D;
   int b;
+  int sh;
   int64_t n;
   double step;
   double eps;
   double R;
-  int l1_from;
   const uint32_t* codes;
   const int64_t* ids;
 };
@@ -1235,66 +1007,36 @@ ScoreView store_view(const lam_store* st, const uint32_t* codes) {
   ScoreView v;
   v.D = st->dim;
   v.b = st->q.bits;
+  // the width of the codes that occur, which a declared absmax may exceed
+  int used = 1;
+  while (used < 32 && ((1u << (used - 1)) - 1u) < (uint32_t)st->max_code) ++used;
+  v.sh = std::max(0, used - 12);
   v.n = st->size;
   v.step = st->q.step;
   v.eps = st->q.eps;
   v.R = row_norm_bound(st->hn_max, st->q.eps, st->dim);
-  v.l1_from = 0;
   v.codes = codes ? codes : st->codes;
   v.ids = st->ids;
   return v;
 }
 
-// The split form of a store with wide codes and of the queries, in the
-// context's arena.  With |c >> 11| <= ||c|| / 2^11 + 1 per column and
-// c & 2047 <= 2,047, s ||code'|| <= R / 2^11 + 2^12 eps sqrt(D).
-lam_status widen(lam_ctx* ctx, ScoreView& v, const float*& q, int64_t nq) {
-  LAM_CHECK(v.b <= kWideMaxBits, LAM_ESTATE,
-            "scoring supports codes of at most %d bits (store codes have %d); quantize with a larger eps",
-            kWideMaxBits, v.b);
-  const int D = v.D;
-  LAM_TRY(ctx->scratch[kScratchWideCodes].ensure(std::max<size_t>((size_t)v.n * 2 * D * 12 / 8, 4)));
-  LAM_TRY(ctx->scratch[kScratchWideQueries].ensure(std::max<size_t>((size_t)nq * 2 * D * 4, 4)));
-  uint32_t* wc = ctx->scratch[kScratchWideCodes].as<uint32_t>();
-  float* wq = ctx->scratch[kScratchWideQueries].as<float>();
-  const int64_t ng = v.n * (2 * D / 32);
-  if (ng > 0) {
-    hipLaunchKernelGGL(k_wide_codes, dim3((unsigned)((ng + 255) / 256)), dim3(256), 0, ctx->stream, v.codes, v.n, D,
-                       v.b, wc);
-    LAM_HIP(hipGetLastError());
-  }
-  const int64_t ne = nq * 2 * D;
-  if (ne > 0) {
-    hipLaunchKernelGGL(k_wide_queries, dim3((unsigned)((ne + 255) / 256)), dim3(256), 0, ctx->stream, q, nq, D, wq);
-    LAM_HIP(hipGetLastError());
-  }
-  v.R = (v.R * 0x1p-11 + 4096.0 * v.eps * std::sqrt((double)D) * (1.0 + 0x1p-50)) * (1.0 + 0x1p-50);
-  v.D = 2 * D;
-  v.b = 12;
-  v.l1_from = D;
-  v.codes = wc;
-  q = wq;
-  return LAM_OK;
-}
-
 }  // namespace
 
-// Scoring plan.  With at most S store rows (S = k * n / 256, at least 4,096)
-// one pass of per-lane lists gives the exact top-k.  Beyond that (H: scores
-// of the hi part alone, within err of the rescored scores S):
+// Scoring plan (H: scores of the scan, within err of the exact scores S but for
+// a constant of the query).  A store of at most 4,096 rows is scored densely:
+// every H is written, and step 3 works on all rows.  Beyond that:
 //   1. theta_j, the k-th best H of disjoint 32-row sets' best over the first S
-//      rows, minus 2 err_j: k distinct rows have S >= theta_j + err_j, so every
-//      row of the final top-k has H >= theta_j;
-//   2. a full scan of H appends every row with H >= theta_j to query j's
-//      candidate buffer (about k * n / S = 256 entries expected; capacity
-//      4,096);
-//   3. the candidates within 2 err_j of the k-th best H of them are rescored
+//      rows (S = k * n / 256, at least 4,096), minus 2 err_j: k distinct rows
+//      have S >= theta_j + err_j, so every row of the final top-k has H >=
+//      theta_j;
+//   2. a full scan appends every row with H >= theta_j to query j's candidate
+//      buffer (about k * n / S = 256 entries expected; capacity 4,096);
+//   3. the candidates within 2 err_j of the k-th best H of them are scored
 //      exactly and their k best by (S desc, id asc) are the answer
 //      (k_select_rescore);
-//   4. a query whose buffer overflowed, or with more than 1,024 candidates to
-//      rescore (many equal scores, say), is redone with exact per-lane lists
-//      over the whole store; launched always, it returns at once when nothing
-//      was flagged, so the call stays asynchronous.
+//   4. a query whose buffer overflowed (many equal scores, say) is scored
+//      exactly over the whole store (k_exact); launched always, it returns at
+//      once when nothing was flagged, so the call stays asynchronous.
 namespace {
 
 // Scratch of one scoring call: the context's arena (grown on demand), or a
@@ -1320,62 +1062,61 @@ struct ScoreWork {
 };
 
 // score_topk on the workspace w.  Every buffer is taken before the first
-// launch, so a workspace that is too small fails with nothing enqueued.
-// max_splits caps the store ranges per query tile of the list passes (their
-// candidate lists grow with it); no profiling events are recorded unless prof.
+// launch, so a workspace that is too small fails with nothing enqueued.  No
+// profiling events are recorded unless prof.
 lam_status score_topk_impl(lam_ctx* ctx, const ScoreView& st, const float* q, int64_t nq, int32_t k, float* scores,
-                           int64_t* ids, float* bound, ScoreWork& w, int max_splits, bool prof) {
+                           int64_t* ids, float* bound, ScoreWork& w, bool prof) {
   if (nq == 0) return LAM_OK;
   const int D = st.D;
   const int b = st.b;
-  LAM_CHECK(b >= 1 && b <= 12, LAM_ESTATE, "internal: the scoring passes take codes of 1 to 12 bits (got %d)", b);
-  const int KL = (k <= 16) ? 16 : 64;
   const int64_t n = st.n;
   const int nqt = (int)((nq + kTB - 1) / kTB);
   const int64_t ntiles = (n + kTB - 1) / kTB;
+  const bool dense = n <= kCandCap;
   // the sample: the store's first max(4,096, k n / 256) rows, so that at
   // most about k n / sample = 256 rows per query pass the filter (a sample of
   // k n / 1,024 rows let about 1,024 through: the corpus call 2.65-2.71 ->
   // 2.57-2.59 ms, 60 K rows at top-50 265 -> 238 us; k n / 128 was no faster)
   const int64_t sample_rows = std::max<int64_t>(4096, ((int64_t)k * n + 255) / 256);
-  const int64_t stiles = std::min<int64_t>(ntiles, (sample_rows + kTB - 1) / kTB);
-  const bool two_pass = stiles < ntiles;
-
-  int sp2 = 1;
-  int64_t tps2 = 0;
-  plan_splits(nqt, ntiles, &sp2, &tps2, max_splits);
-  const int64_t cands_max = (int64_t)sp2 * 2 * KL;
-  // the sample's entries share the list passes' buffer (they are read before
-  // the fallback writes its lists); beyond kSampleTiles tiles, or what a fixed
-  // workspace holds, tiles share entries
+  const int64_t stiles = dense ? 0 : std::min<int64_t>(n / kTB, (sample_rows + kTB - 1) / kTB);   // whole tiles
   const int64_t sample_tiles = std::min<int64_t>(stiles, kSampleTiles);
-  const int64_t entries = two_pass ? sample_tiles * kSampleEntries : 0;
-  // the filter pipeline's grids (sample and filter passes) are one workgroup
-  // per (query tile, store tile), indexed in 32 bits
-  LAM_CHECK(!two_pass || (int64_t)nqt * ntiles < (1LL << 31), LAM_EINVAL, "scoring grid too large");
-  const uint32_t cap = kCandCap;
+  const int64_t entries = sample_tiles * kSampleEntries;
+  // the passes are one workgroup per (query tile, store tile), indexed in 32 bits
+  LAM_CHECK((int64_t)nqt * ntiles < (1LL << 31), LAM_EINVAL, "scoring grid too large");
+  const uint32_t cap = dense ? (uint32_t)(ntiles * kTB) : (uint32_t)kCandCap;
 
   // every buffer first
-  _Float16 *qhi = nullptr, *qlo = nullptr;
+  _Float16* qhi = nullptr;
   QMeta* qmeta = nullptr;
   float* part_s = nullptr;
   float* cand_s = nullptr;
   LAM_TRY(w.take(ctx, S_QHI, (size_t)nq * D * 2, &qhi));
-  LAM_TRY(w.take(ctx, S_QLO, (size_t)nq * D * 2, &qlo));
   LAM_TRY(w.take(ctx, S_QMETA, (size_t)nq * sizeof(QMeta), &qmeta));
-  LAM_TRY(w.take(ctx, S_PART, (size_t)nq * std::max<int64_t>(cands_max * 8, entries * 4), &part_s));
-  if (two_pass) LAM_TRY(w.take(ctx, S_CAND, (size_t)nq * cap * 8 + (size_t)nq * 12 + (size_t)nqt * 8 + 256, &cand_s));
-  int32_t* part_r = reinterpret_cast<int32_t*>(part_s + (size_t)nq * cands_max);
-  int32_t* cand_r = two_pass ? reinterpret_cast<int32_t*>(cand_s + (size_t)nq * cap) : nullptr;
-  uint32_t* cand_cnt = two_pass ? reinterpret_cast<uint32_t*>(cand_r + (size_t)nq * cap) : nullptr;
-  float* thr = two_pass ? reinterpret_cast<float*>(cand_cnt + nq) : nullptr;
-  uint32_t* qflag = two_pass ? reinterpret_cast<uint32_t*>(thr + nq) : nullptr;
-  uint32_t* tflag = two_pass ? qflag + nq : nullptr;
+  if (dense) {
+    LAM_TRY(w.take(ctx, S_CAND, (size_t)nq * cap * 4, &cand_s));
+  } else {
+    LAM_TRY(w.take(ctx, S_PART, (size_t)nq * entries * 4, &part_s));
+    LAM_TRY(w.take(ctx, S_CAND, (size_t)nq * cap * 8 + (size_t)nq * 16 + 4, &cand_s));
+  }
+  int32_t* cand_r = dense ? nullptr : reinterpret_cast<int32_t*>(cand_s + (size_t)nq * cap);
+  uint32_t* cand_cnt = dense ? nullptr : reinterpret_cast<uint32_t*>(cand_r + (size_t)nq * cap);
+  float* thr = dense ? nullptr : reinterpret_cast<float*>(cand_cnt + nq);
+  uint32_t* flagged = dense ? nullptr : cand_cnt + 2 * nq;
+  uint32_t* done = dense ? nullptr : cand_cnt + 3 * nq;
+  uint32_t* n_flag = dense ? nullptr : cand_cnt + 4 * nq;
 
   {
     ProfScope ps(ctx, "score_prep", prof);
-    hipLaunchKernelGGL(k_score_prep, dim3((unsigned)((nq + 3) / 4)), dim3(256), 0, ctx->stream, q, nq, D, st.step,
-                       st.eps, st.R, st.l1_from, qhi, qlo, qmeta, cand_cnt, tflag);
+    // the scan's operand s 2^sh top, and what the left-out bits add
+    const double two = std::ldexp(1.0, st.sh);
+    const double rootD = std::sqrt((double)D) * (1.0 + 0x1p-50);
+    const double R = st.R + (two - 1.0) * st.step * rootD;
+    const double trunc = 0.5 * (two - 1.0) * st.step * rootD;
+    // (a query that the former split form of codes over 12 bits, 2^11 q, could
+    // not hold in float32 counts as holding Inf)
+    const float qmax = b > 12 ? 3.402823466e38f / 2048.0f : 3.402823466e38f;
+    hipLaunchKernelGGL(k_score_prep, dim3((unsigned)((nq + 3) / 4)), dim3(256), 0, ctx->stream, q, nq, D,
+                       st.step * two, st.eps, R, trunc, qmax, qhi, qmeta, cand_cnt, done, n_flag);
     LAM_HIP(hipGetLastError());
   }
 
@@ -1383,39 +1124,30 @@ lam_status score_topk_impl(lam_ctx* ctx, const ScoreView& st, const float* q, in
   a.codes = st.codes;
   a.n = n;
   a.D = D;
+  a.sh = st.sh;
   a.row_words = (int64_t)D * b / 32;
   a.qhi = qhi;
-  a.qlo = qlo;
   a.meta = qmeta;
   a.nq = nq;
   a.nqt = nqt;
   a.part_s = part_s;
-  a.part_r = part_r;
-  const dim3 gq((unsigned)((nq + 3) / 4));
+  a.thr = thr;
+  a.cand_s = cand_s;
+  a.cand_r = cand_r;
+  a.cand_cnt = cand_cnt;
+  a.cap = cap;
+  ExactArgs x{nq,    n,      cap,     k,         cand_cnt, cand_s, cand_r, qmeta, st.ids,  q,    st.step, st.codes,
+              a.row_words, D, scores, ids, bound, n_flag, flagged, done, 1};
 
-  if (!two_pass) {
-    if (ntiles > 0) {
-      a.tile_begin = 0;
-      a.tile_end = ntiles;
-      a.splits = sp2;
-      a.tiles_per_split = tps2;
+  if (dense) {
+    if (n > 0) {
       ProfScope ps(ctx, "score_mfma", prof);
-      LAM_TRY(dispatch_bits<1>(b, KL, kModeLists, dim3((unsigned)(nqt * sp2)), ctx->stream, a));
-      LAM_HIP(hipGetLastError());
+      a.tile_end = ntiles;
+      LAM_TRY((launch_filter<1, kDense>(b, false, (int64_t)nqt * ntiles, ctx->stream, a)));
     }
     ProfScope ps(ctx, "score_merge", prof);
-    const int nc = ntiles > 0 ? sp2 * 2 * KL : 0;
-    if (KL == 16)
-      hipLaunchKernelGGL((k_topk_merge<16>), gq, dim3(256), 0, ctx->stream, nq, nc, k, part_s, part_r, qmeta, st.ids,
-                         scores, ids, bound);
-    else
-      hipLaunchKernelGGL((k_topk_merge<64>), gq, dim3(256), 0, ctx->stream, nq, nc, k, part_s, part_r, qmeta, st.ids,
-                         scores, ids, bound);
-    LAM_HIP(hipGetLastError());
-    return LAM_OK;
+    return launch_exact<1>(b, kSelectDense, ctx->stream, x);
   }
-
-  // (the candidate counts and tile flags were cleared by k_score_prep)
   {  // 1. a k-th best score of the sample -> thresholds
     ProfScope ps(ctx, "score_sample", prof);
     a.tile_end = stiles;
@@ -1426,53 +1158,29 @@ lam_status score_topk_impl(lam_ctx* ctx, const ScoreView& st, const float* q, in
       hipLaunchKernelGGL(k_fill_zero, dim3((unsigned)((ne + 255) / 256)), dim3(256), 0, ctx->stream,
                          reinterpret_cast<uint32_t*>(part_s), ne);
     }
-    LAM_TRY((launch_filter<1, true>(b, false, dim3((unsigned)(nqt * stiles)), ctx->stream, a)));
-    hipLaunchKernelGGL(k_sample_thr, gq, dim3(256), 0, ctx->stream, nq, (int)entries, folded ? 1 : 0, k, part_s, qmeta,
-                       thr);
+    LAM_TRY((launch_filter<1, kSample>(b, false, (int64_t)nqt * stiles, ctx->stream, a)));
+    hipLaunchKernelGGL(k_sample_thr, dim3((unsigned)((nq + 3) / 4)), dim3(256), 0, ctx->stream, nq, (int)entries,
+                       folded ? 1 : 0, k, part_s, qmeta, thr);
     LAM_HIP(hipGetLastError());
   }
-  a.tile_begin = 0;
-  a.tile_end = ntiles;
-  a.splits = sp2;
-  a.tiles_per_split = tps2;
-  a.thr = thr;
-  a.cand_s = cand_s;
-  a.cand_r = cand_r;
-  a.cand_cnt = cand_cnt;
-  a.cap = cap;
-  a.tflag = tflag;
-  {  // 2. full scan with the thresholds
+  {  // 2. full scan with the thresholds: 256 x 256 tiles when the launch holds
+     //    many of them, else 128 x 128
     ProfScope ps(ctx, "score_mfma", prof);
-    // one tile per workgroup on the screen's pipeline: 256 x 256 when the
-    // launch holds many of them, else 128 x 128
     const int nqtL = (int)((nq + FilterTileL::BN - 1) / FilterTileL::BN);
     const int64_t ntilesL = (n + FilterTileL::BM - 1) / FilterTileL::BM;
     const bool large = (int64_t)nqtL * ntilesL >= kFilterLargeMinTiles;
-    ScoreArgs af = a;
-    if (large) {
-      af.nqt = nqtL;
-      af.tile_end = ntilesL;
-    }
-    LAM_TRY((launch_filter<1, false>(b, large, dim3((unsigned)((int64_t)af.nqt * af.tile_end)), ctx->stream, af)));
+    a.nqt = large ? nqtL : nqt;
+    a.tile_end = large ? ntilesL : ntiles;
+    LAM_TRY((launch_filter<1, kFilter>(b, large, (int64_t)a.nqt * a.tile_end, ctx->stream, a)));
   }
-  {  // 3. select; 4. exact fallback for overflowed buffers (returns at once otherwise)
+  {  // 3. select and rescore
     ProfScope ps(ctx, "score_merge", prof);
-    LAM_TRY(launch_rescore<1>(b, dim3((unsigned)nq), ctx->stream, nq, cap, k, cand_cnt, cand_s, cand_r, qmeta, st.ids,
-                              q, st.step, a.codes, a.row_words, D, scores, ids, bound, qflag, tflag));
+    LAM_TRY(launch_exact<1>(b, kSelect, ctx->stream, x));
   }
-  {
-    // exact lists for the flagged query tiles, merged by each tile's last
-    // workgroup (returns at once when nothing is flagged)
+  {  // 4. the exact pass over flagged queries (returns at once otherwise)
     ProfScope ps(ctx, "score_fallback", prof);
-    a.qflag = qflag;
-    a.tdone = tflag + nqt;
-    a.k = k;
-    a.out_s = scores;
-    a.out_i = ids;
-    a.out_bound = bound;
-    a.ids = st.ids;
-    LAM_TRY(dispatch_bits<1>(b, KL, kModeFallback, dim3((unsigned)(nqt * sp2)), ctx->stream, a));
-    LAM_HIP(hipGetLastError());
+    x.splits = (int)std::min<int64_t>(kCandCap / k, (n + 255) / 256);
+    LAM_TRY(launch_exact<1>(b, kExactPass, ctx->stream, x));
   }
   return LAM_OK;
 }
@@ -1480,15 +1188,12 @@ lam_status score_topk_impl(lam_ctx* ctx, const ScoreView& st, const float* q, in
 // ------------------------------------------------------------------ allocation-free scoring
 // Its scratch memory: one array per device, allocated with the code object,
 // held until the process ends.  Sized for kNoAllocMaxQ queries of up to 4,096
-// dimensions with at most kNoAllocSplits store ranges per query tile:
-// fp16 hi and lo query parts (4 D bytes per query), the query meta block, the
-// list passes' candidates (2 x 64 entries of 8 bytes per range) and the
-// threshold plan's candidate buffer (kCandCap entries of 8 bytes, 12 bytes
-// of counts and flags) -- 112 KB per query, 28 MB at the limits.
-constexpr int kNoAllocSplits = 64;
+// dimensions: the fp16 query parts (2 D bytes per query), the query meta block,
+// the sample's entries and the candidate buffer (kCandCap entries of 8 bytes,
+// 16 bytes of counts and flags) -- 72 KB per query, 18 MB at the limits.
 constexpr size_t kNoAllocBytes = (size_t)32 << 20;
-static_assert((size_t)kNoAllocMaxQ * (4 * 4096 + 16 + (size_t)kNoAllocSplits * 2 * 64 * 8 + (size_t)kCandCap * 8 + 12) +
-                      6 * 256 + 256 <= kNoAllocBytes,
+static_assert((size_t)kNoAllocMaxQ * (2 * 4096 + sizeof(QMeta) + (size_t)kSampleTiles * kSampleEntries * 4 +
+                                      (size_t)kCandCap * 8 + 16) + 4 + 4 * 256 <= kNoAllocBytes,
               "the workspace holds a call at the limits");
 
 }  // namespace
@@ -1514,16 +1219,18 @@ lam_status noalloc_setup(int device) {
 lam_status score_topk(lam_ctx* ctx, const lam_store* st, const float* q, int64_t nq, int32_t k, float* scores,
                       int64_t* ids, float* bound, const uint32_t* codes) {
   if (nq == 0) return LAM_OK;
+  LAM_CHECK(st->q.bits <= kMaxBits, LAM_ESTATE,
+            "scoring supports codes of at most %d bits (store codes have %d); quantize with a larger eps", kMaxBits,
+            st->q.bits);
   ScoreWork w;
-  ScoreView v = store_view(st, codes);
-  if (v.b > 12) LAM_TRY(widen(ctx, v, q, nq));
-  // the passes index (query tile, store tile) in 31 bits: more queries than
-  // that allows go in several passes
+  const ScoreView v = store_view(st, codes);
+  // the passes index (query tile, store tile) in 31 bits, and scratch is held
+  // for at most 65,536 queries: more go in several passes
   const int64_t ntiles = std::max<int64_t>(1, (v.n + kTB - 1) / kTB);
-  const int64_t most = std::max<int64_t>(1, ((1LL << 31) - 1) / ntiles) * kTB;
+  const int64_t most = std::min<int64_t>(65536, ((1LL << 31) - 1) / ntiles * kTB);
   for (int64_t j = 0; j < nq; j += most)
     LAM_TRY(score_topk_impl(ctx, v, q + j * v.D, std::min(most, nq - j), k, scores + j * k, ids + j * k,
-                            bound ? bound + j : nullptr, w, 1 << 30, true));
+                            bound ? bound + j : nullptr, w, true));
   return LAM_OK;
 }
 
@@ -1542,7 +1249,7 @@ lam_status score_topk_noalloc(lam_ctx* ctx, const lam_store* st, const float* q,
   ScoreWork w;
   w.base = static_cast<char*>(p);
   w.bytes = kNoAllocBytes;
-  return score_topk_impl(ctx, store_view(st, nullptr), q, nq, k, scores, ids, bound, w, kNoAllocSplits, false);
+  return score_topk_impl(ctx, store_view(st, nullptr), q, nq, k, scores, ids, bound, w, false);
 }
 
 // ------------------------------------------------------------------ certificate
@@ -1611,15 +1318,14 @@ lam_status score_certify(lam_ctx* ctx, const lam_store* st, const float* q, int6
   float* b1 = s1 + (size_t)nq * K1;
   LAM_TRY(score_topk(ctx, st, q, nq, K1, s1, i1, b1));
   // error bound of the float32 score per unit of ||q||_1: kappa (A + eps).
-  // Wide codes are scored in their split form (2 D columns): twice the terms,
-  // and sum |q'_d' x_hat'_d'| <= ||q||_1 (A + eps + 2^12 s) since
-  // 2^11 |c >> 11| <= |c| + 2^11 and c & 2047 < 2^11.
+  // It is stated for float32 sums of hi and lo query parts, and for codes of
+  // more than 12 bits for the sums of their two halves (twice the terms, and
+  // sum |q'_d' x_hat'_d'| <= ||q||_1 (A + eps + 2^12 s)); the scores are
+  // binary64 sums rounded once, far inside it.
   const bool wide = st->q.bits > 12;
   const double Dt = (wide ? 2.0 : 1.0) * st->dim;
   const double u = std::ldexp(1.0, -24);
   const double g2d = 2.0 * Dt * u / (1.0 - 2.0 * Dt * u);
-  // (the split residual, the sums, the two scalings; a rescored score is
-  // within 2^-24 relative of its binary64 sum, far inside this)
   const double kappa = 1.01 * (std::ldexp(1.0, -22) + g2d + std::ldexp(1.0, -23));
   const double mag = (double)st->q.absmax + st->q.eps + (wide ? 4096.0 * st->q.step : 0.0);
   const double err_per_l1 = kappa * mag;

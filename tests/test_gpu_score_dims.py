@@ -49,3 +49,30 @@ def test_many_equal_rows(lam, group, n, k):
     gi = gi.cpu().numpy()
     assert np.array_equal(gi[2], np.concatenate([[200], np.arange(300, 300 + k - 1)]))
     _compare(gs.cpu().numpy(), gi, c, np.arange(n), q, eps, k)
+
+
+@pytest.mark.parametrize("d,n,bits,absmax", [
+    (96, 4225, 13, None),       # one low bit left out of the scan, one row past a tile
+    (160, 5000, 15, None),
+    (384, 4500, 22, None),      # ten bits left out
+    (64, 4300, 16, 50.0),       # a declared absmax far above the rows: 16-bit codes of 10-bit values
+])
+def test_wide_codes_scan(lam, d, n, bits, absmax):
+    """Codes of more than 12 bits are scanned without their low bits; the
+    scores and the order are those of the whole codes.  A query entry that
+    overflows float32 when scaled by 2^11 makes its row invalid."""
+    rng = np.random.default_rng(bits)
+    x = synth.unit_rows(rng, n, d).astype(np.float32)
+    s = _store_from_rows(lam, x)
+    eps = (absmax or float(np.abs(x).max())) / 2.0 ** bits * 1.01
+    p = s.quantize(eps, absmax=absmax)
+    assert p.bits == bits
+    q = np.concatenate([synth.unit_rows(rng, 20, d),
+                        synth.members(rng, x[rng.choice(n, 20)].astype(np.float64), rng.uniform(0.6, 0.99, 20))])
+    q = q.astype(np.float32)
+    q[5, 3] = 1e36
+    gs, gi, gb = (t.cpu().numpy() for t in s.score_topk(_dev(q), 20))
+    assert np.all(gi[5] == -1) and np.all(np.isnan(gs[5])) and np.isnan(gb[5])
+    keep = [j for j in range(q.shape[0]) if j != 5]
+    c = qeps.codes(x, eps).reshape(n, -1)
+    _compare(gs[keep], gi[keep], c, np.arange(n), q[keep], eps, 20)
