@@ -45,7 +45,7 @@ struct Status {
   } while (0)
 
 // ------------------------------------------------------------------ device buffer
-// Context scratch slots: 0-6 ingest (dedup.hip), 7-10 scoring (score.hip),
+// Context scratch slots: 0-6 ingest (dedup.hip), 7-11 scoring (score.hip),
 // then the ones below.
 constexpr int kScratchCeilingRep = 12;   // representatives of the ceiling passes (not returned)
 constexpr int kScratchCertify = 13;      // top-(k+1) lists of the certified scoring

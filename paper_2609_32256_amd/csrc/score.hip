@@ -11,7 +11,10 @@
 // unpacked from their b-bit words straight into fp16 LDS slabs (no dequantized
 // copy exists in HBM) and accumulated in fp32 by v_mfma_f32_32x32x16_f16.  Codes
 // of values below 2^11 are exact in fp16; of wider ones the scan takes the top
-// 12 bits.  A per-query bound err on |H - score| (see k_score_prep) turns the
+// 12 bits.  Where every code fits 8 bits the full scan multiplies bytes instead
+// (the query rounded to 127ths of its largest entry, twice the matrix rate),
+// unless the sample shows that the wider error bound would let too many rows
+// through.  A per-query bound err on |H - score| (see k_score_prep) turns the
 // k-th best H into a threshold; the rows above it are scored exactly and the k
 // best by (score desc, id asc) are the answer.  See score_topk_impl for the
 // plan.
@@ -28,14 +31,18 @@ namespace {
 
 constexpr int kNoRow = 0x7fffffff;
 
-enum ScoreScratch { S_QHI = 7, S_QMETA, S_PART, S_CAND };
+enum ScoreScratch { S_QHI = 7, S_QMETA, S_PART, S_CAND, S_Q8, S_QLO = S_Q8 };
 
 struct QMeta {
   float osc;     // float32(s * 2^(sh - e)): multiplies the raw accumulator
   float bound;   // eps * ||q||_1 rounded up, or NaN for an invalid query
   int bad;       // query holds NaN/Inf
   float err;     // >= |H + c - score| for every store row, c a constant of the query (rounded up)
+  float osc8;    // the same two for the byte scan: float32(s * qs), qs = max|q| / 127
+  float err8;
 };
+
+constexpr int kPrecQueries = 256;   // queries that share the choice of the scan's operands
 
 __device__ __forceinline__ float ru32(double d) {
   float f = (float)d;
@@ -64,22 +71,27 @@ __device__ __forceinline__ float rd32(double d) {
 //   scalings:  osc and the final product, 2^-24 each;
 //   S:         the rescoring sums in binary64 and rounds once to float32.
 // |H + c - S| <= ||q - h|| R + trunc ||q|| + (g + 2^-21)(||q|| + ||q - h||) R.
+// The byte scan (q8 not NULL; codes of at most 8 bits, so trunc = 0) has h = qs
+// rint(q / qs) and exact int32 sums: err8 = (||q - h|| + 2^-21 (||q|| + ||q - h||)) R.
 // qmax: the largest |q| taken (a query row above it, or holding NaN/Inf, is
 // invalid).  cand_cnt, done: this query's candidate count and finished
-// workgroups of the exact pass, and n_flag the number of flagged queries,
-// start at zero (the buffers may hold anything from an earlier call).
+// workgroups of the exact pass, n_flag the number of flagged queries, and coarse,
+// a flag per kPrecQueries queries (see k_sample_thr), start at zero (the buffers
+// may hold anything from an earlier call).
 __global__ __launch_bounds__(256) void k_score_prep(const float* __restrict__ q, int64_t nq, int D, double step_f,
                                                     double eps, double R, double trunc, float qmax,
-                                                    _Float16* __restrict__ qhi, QMeta* __restrict__ meta,
-                                                    uint32_t* __restrict__ cand_cnt, uint32_t* __restrict__ done,
-                                                    uint32_t* __restrict__ n_flag) {
+                                                    _Float16* __restrict__ qhi, int8_t* __restrict__ q8,
+                                                    QMeta* __restrict__ meta, uint32_t* __restrict__ cand_cnt,
+                                                    uint32_t* __restrict__ done, uint32_t* __restrict__ n_flag,
+                                                    uint32_t* __restrict__ coarse) {
   const int lane = threadIdx.x & 63;
   const int64_t j = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
   if (j >= nq) return;
-  if (cand_cnt && lane == 0) {
+  if (lane == 0) {
     cand_cnt[j] = 0u;
     done[j] = 0u;
     if (j == 0) *n_flag = 0u;
+    if (j % kPrecQueries == 0) coarse[j / kPrecQueries] = 0u;
   }
   const float* p = q + j * D;
   float mx = 0.0f;
@@ -132,6 +144,15 @@ __global__ __launch_bounds__(256) void k_score_prep(const float* __restrict__ q,
     const double r = bad ? 0.0 : (double)x - (double)(float)h * isc;   // exact in binary64
     dh2 = fma(r, r, dh2);
   };
+  const float qs = bad ? 0.0f : mx * (1.0f / 127.0f);
+  const float iqs = qs > 0x1p-120f ? 1.0f / qs : 0.0f;   // (a query of subnormals: all bytes 0, err8 ||q|| R)
+  double db2 = 0.0;   // ||q - qs rint(q / qs)||^2
+  auto byte = [&](float x) {
+    const float v = bad ? 0.0f : fminf(fmaxf(rintf(x * iqs), -127.0f), 127.0f);
+    const double r = bad ? 0.0 : (double)x - (double)v * (double)qs;
+    db2 = fma(r, r, db2);
+    return (uint32_t)(int)v & 255u;
+  };
   if (vec) {
 #pragma unroll
     for (int u = 0; u < kVec; ++u) {
@@ -144,11 +165,18 @@ __global__ __launch_bounds__(256) void k_score_prep(const float* __restrict__ q,
       uint2 ph;
       __builtin_memcpy(&ph, h, 8);
       *reinterpret_cast<uint2*>(qhi + j * D + d) = ph;
+      if (q8)
+        *reinterpret_cast<uint32_t*>(q8 + j * D + d) =
+            byte(c[0]) | (byte(c[1]) << 8) | (byte(c[2]) << 16) | (byte(c[3]) << 24);
     }
   } else {
-    for (int d = lane; d < D; d += 64) part(p[d], qhi[j * D + d]);
+    for (int d = lane; d < D; d += 64) {
+      part(p[d], qhi[j * D + d]);
+      if (q8) q8[j * D + d] = (int8_t)byte(p[d]);
+    }
   }
   dh2 = wave_sum_f64(dh2);
+  if (q8) db2 = wave_sum_f64(db2);
   if (lane == 0) {
     QMeta m;
     m.osc = (float)ldexp(step_f, -e);
@@ -162,6 +190,9 @@ __global__ __launch_bounds__(256) void k_score_prep(const float* __restrict__ q,
     const double dh = sqrt(dh2) * up;
     const double E = dh * R + trunc * qn + (g + 0x1p-21) * (qn + dh) * R;
     m.err = bad ? 0.0f : ru32(E * (1.0 + 0x1p-20));
+    m.osc8 = (float)(step_f * (double)qs);
+    const double db = sqrt(db2) * up;
+    m.err8 = bad ? 0.0f : ru32((db + 0x1p-21 * (qn + db)) * R * (1.0 + 0x1p-20));
     meta[j] = m;
   }
 }
@@ -174,15 +205,17 @@ struct ScoreArgs {
   int sh;                    // low bits of a code that the scan leaves out (codes of more than 12 bits)
   int64_t row_words;         // D * b / 32
   const _Float16* qhi;
+  const int8_t* q8;          // byte scan: the queries' byte parts
+  const uint32_t* coarse;    // byte scan: flags of kPrecQueries queries that take the fp16 scan
   const QMeta* meta;
   int64_t nq;
   int nqt;                   // query tiles of this launch
   int64_t tile_end;          // store tiles [0, tile_end) scanned by this launch
   float* part_s;             // sample pass: [nq][entries]
   int sample_tiles;          // sample pass: store tiles with entries of their own (later tiles fold onto them)
-  const float* thr;          // filter pass: per-query threshold
-  float* cand_s;             // filter pass: [nq][cap] scores (dense: of rows 0, 1, ...)
-  int32_t* cand_r;           //              and rows
+  const float* thr;          // filter pass: per-query threshold (fp16 scan), then the byte scan's
+  float* cand_s;             // filter pass: [nq][cap] scores and rows
+  int32_t* cand_r;
   uint32_t* cand_cnt;
   uint32_t cap;
 };
@@ -294,11 +327,19 @@ __device__ __forceinline__ uint32_t wave_kth_floor(const uint32_t (&key)[R], int
 // no row of the final top-k falls below it in hi-only terms.  Beyond 1,024
 // entries several share a key as their maximum: the k-th best key is then
 // still the score of k distinct rows, only a little lower.
+// With a byte scan to follow (coarse not NULL) also its threshold, T - err -
+// err8, and the choice between the two scans: if the entries above it tell of
+// more than kByteCands rows of the store above it (a share f of entries, each
+// the best of 32 rows, means n (-ln(1 - f)) / 32 rows), the query's group of
+// kPrecQueries takes the fp16 scan.  That happens where scores lie close
+// together for the byte scan's error (8e-3 ||q|| R for a Gaussian query), or
+// where single entries dominate the query, which widens that error.
 constexpr int kThrKeys = 16;   // keys per lane
+constexpr float kByteCands = 1024.0f;
 
-__global__ __launch_bounds__(256) void k_sample_thr(int64_t nq, int entries, int folded, int k,
+__global__ __launch_bounds__(256) void k_sample_thr(int64_t nq, int64_t n, int entries, int folded, int k,
                                                     const float* __restrict__ ps, const QMeta* __restrict__ meta,
-                                                    float* __restrict__ thr) {
+                                                    float* __restrict__ thr, uint32_t* __restrict__ coarse) {
   const int lane = threadIdx.x & 63;
   const int64_t j = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
   if (j >= nq) return;
@@ -314,8 +355,19 @@ __global__ __launch_bounds__(256) void k_sample_thr(int64_t nq, int entries, int
     for (int r = 0; r < kThrKeys; ++r)
       if (e0 + lane + r * 64 < entries) key[r] = max(key[r], code(e0 + lane + r * 64));
   const uint32_t T = wave_kth_floor<kThrKeys>(key, min(kThrKeys, (entries + 63) / 64), k);
-  if (lane == 0)
-    thr[j] = m.bad ? __builtin_nanf("") : (T == 0u ? -INFINITY : rd32((double)ord2f(T) - 2.0 * (double)m.err));
+  const double t = T == 0u ? -INFINITY : (double)ord2f(T);
+  if (lane == 0) thr[j] = m.bad ? __builtin_nanf("") : rd32(t - 2.0 * (double)m.err);
+  if (!coarse) return;
+  const float t8 = rd32(t - (double)m.err - (double)m.err8);
+  if (lane == 0) thr[nq + j] = m.bad ? __builtin_nanf("") : t8;
+  int above = 0;
+  const uint32_t o8 = f2ord(t8);
+#pragma unroll
+  for (int r = 0; r < kThrKeys; ++r) above += __popcll(__ballot(key[r] >= o8));
+  const int nkeys = min(entries, 64 * kThrKeys);
+  const float f = (float)above / (float)nkeys;
+  const float rows = -logf(fmaxf(1.0f - f, 1e-6f)) * ((float)n / 32.0f) * ((float)nkeys / (float)entries);
+  if (lane == 0 && !m.bad && rows > kByteCands) atomicOr(&coarse[j / kPrecQueries], 1u);
 }
 
 // ------------------------------------------------------------------ filter pass on the screen's pipeline
@@ -349,8 +401,6 @@ constexpr int64_t kFilterLargeMinTiles = 1024;   // large filter tiles from this
 // 81 us here; its sample pass 54 -> 16 us.  The run-time slab loop is as fast as
 // one unrolled for D = 768: 54 us at 23,969 rows x 1,024 queries, 2.30 ms at
 // 361,802 x 4,096, both as before.)
-// kDense (FilterTile only): every H is written, to entry r of the query's
-// buffer for row r (cap: the rows rounded up to whole tiles).
 // kSample (FilterTile only): the sample pass of the threshold plan over store
 // tiles [0, tile_end) (all of them whole) instead: per query and tile, the best
 // H of each of the four lanes holding the query (disjoint sets of 32 rows) at
@@ -360,81 +410,109 @@ constexpr int64_t kFilterLargeMinTiles = 1024;   // large filter tiles from this
 // sample's k-th best H: a valid base for the threshold (lower only where
 // several of the best rows share a lane).
 // a.nqt and a.tile_end count tiles of this kernel's size.
-enum { kFilter = 0, kSample = 1, kDense = 2 };
+typedef int intx4 __attribute__((ext_vector_type(4)));
+typedef int intx16 __attribute__((ext_vector_type(16)));
 
-template <class C, int B, int MODE, int SETS>
-__global__ __launch_bounds__(C::kThreads, C::kMinWaves) void k_filter(ScoreArgs a) {
-  static_assert(MODE == kFilter || (C::BM == kTB && C::TJ == 1), "128-row tiles of one query block");
+// The scan's operands: fp16 codes and queries (64 columns in the 128 bytes of a
+// row's slab), or bytes (128 columns).
+struct OpF16 {
+  typedef floatx16 Acc;
+  static constexpr int kCols = 64;
+  template <int B>
+  static constexpr int kWords = (B + 1) / 2;   // code words per thread and slab
+  static __device__ __forceinline__ Acc mfma(half8 x, half8 y, Acc c) {
+    return __builtin_amdgcn_mfma_f32_32x32x16_f16(x, y, c, 0, 0, 0);
+  }
+};
+struct OpI8 {
+  typedef intx16 Acc;
+  static constexpr int kCols = 128;
+  template <int B>
+  static constexpr int kWords = B;
+  static __device__ __forceinline__ Acc mfma(half8 x, half8 y, Acc c) {
+    return __builtin_amdgcn_mfma_i32_32x32x32_i8(__builtin_bit_cast(intx4, x), __builtin_bit_cast(intx4, y), c, 0, 0,
+                                                 0);
+  }
+};
+
+// The 32 b-bit codes of a group (B words; every code fits 8 bits) to bytes.
+template <int B>
+__device__ __forceinline__ void unpack_bytes(const uint32_t (&w)[B], uint32_t (&out)[8]) {
+  if constexpr (B == 8) {
+#pragma unroll
+    for (int i = 0; i < 8; ++i) out[i] = w[i];
+  } else {
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      const uint32_t c0 = (uint32_t)code_at<B>(w, 4 * i), c1 = (uint32_t)code_at<B>(w, 4 * i + 1);
+      const uint32_t c2 = (uint32_t)code_at<B>(w, 4 * i + 2), c3 = (uint32_t)code_at<B>(w, 4 * i + 3);
+      // bytes 0..3 of a selection come from its second operand, 4..7 from the first
+      out[i] = __builtin_amdgcn_perm(__builtin_amdgcn_perm(c3, c2, 0x0c0c0400u), __builtin_amdgcn_perm(c1, c0, 0x0c0c0400u),
+                                     0x05040100u);
+    }
+  }
+}
+
+// acc <- the raw scores of one C::BM x C::BN tile: store rows [rbase, rbase +
+// rows) against queries [qbase, qbase + qrows).
+template <class C, class Op, int B, int SETS>
+__device__ __forceinline__ void scan_tile(const ScoreArgs& a, int64_t rbase, int rows, int64_t qbase, int qrows,
+                                          _Float16* lds, typename Op::Acc (&acc)[C::TI][C::TJ]) {
   static_assert(SETS == 1 || SETS == 3, "one or three register sets");
   static_assert(C::kThreads == 4 * C::BM, "four threads per row");
-  __shared__ _Float16 lds[C::kLdsHalves];
-  const int64_t nt = a.tile_end;   // store tiles of this pass (tile_begin = 0)
-  // 32-bit index arithmetic: the host keeps the grid (nqt * nt) below 2^31
-  const uint32_t logical = (uint32_t)xcd_remap32((int)blockIdx.x, (int)(a.nqt * nt));
-  const uint32_t per = (uint32_t)(kFilterGroupQ * nt);
-  const uint32_t g = logical / per;
-  const uint32_t l = logical - g * per;
-  const uint32_t gsize = (uint32_t)min(kFilterGroupQ, a.nqt - (int)g * kFilterGroupQ);
-  const int qt = (int)(g * kFilterGroupQ + l % gsize);
-  const int64_t rbase = (int64_t)(l / gsize) * C::BM;
-  const int rows = (int)min<int64_t>(C::BM, a.n - rbase);
-  const int64_t qbase = (int64_t)qt * C::BN;
-  const int qrows = (int)min<int64_t>(C::BN, a.nq - qbase);
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  constexpr bool kBytes = Op::kCols == 128;
+  constexpr int kES = kBytes ? 1 : 2;   // bytes per query element
+  const int tid = threadIdx.x, wave = tid >> 6;
   const int wm = wave / C::WN, wn = wave % C::WN;
-  // this lane's queries and their thresholds, loaded before the GEMM
-  int64_t j[C::TJ];
-  bool jv[C::TJ];
-  float th[C::TJ], osc[C::TJ];
-#pragma unroll
-  for (int y = 0; y < C::TJ; ++y) {
-    j[y] = qbase + wn * C::TJ * 32 + y * 32 + (lane & 31);
-    jv[y] = j[y] < a.nq;
-    th[y] = (jv[y] && MODE == kFilter) ? a.thr[j[y]] : 0.0f;
-    osc[y] = jv[y] ? a.meta[j[y]].osc : 0.0f;
-  }
-
   auto sa = [&](int i) -> _Float16* { return lds + i * ((C::BM + C::BN) * kLdk); };
   auto sb = [&](int i) -> _Float16* { return lds + i * ((C::BM + C::BN) * kLdk) + C::BM * kLdk; };
-  floatx16 acc[C::TI][C::TJ];
 #pragma unroll
   for (int x = 0; x < C::TI; ++x)
 #pragma unroll
     for (int y = 0; y < C::TJ; ++y)
 #pragma unroll
-      for (int r = 0; r < 16; ++r) acc[x][y][r] = 0.0f;
+      for (int r = 0; r < 16; ++r) acc[x][y][r] = 0;
   const __amdgpu_buffer_rsrc_t rsC = __builtin_amdgcn_make_buffer_rsrc(
       const_cast<uint32_t*>(a.codes + rbase * a.row_words), (short)0, (int)(rows * a.row_words * 4), 0x00020000);
-  const __amdgpu_buffer_rsrc_t rsQ = tile_rsrc(a.qhi + qbase * a.D, qrows, a.D);
-  // this thread's share of a slab: 16 codes of row tid / 4, and kPerB 16-byte
-  // pieces of the queries; byte offsets of slab 0
-  constexpr int kNW = (B + 1) / 2;
+  const char* qb = kBytes ? reinterpret_cast<const char*>(a.q8) : reinterpret_cast<const char*>(a.qhi);
+  const __amdgpu_buffer_rsrc_t rsQ = __builtin_amdgcn_make_buffer_rsrc(
+      const_cast<char*>(qb + qbase * a.D * kES), (short)0, qrows * a.D * kES, 0x00020000);
+  // this thread's share of a slab: 16 codes (fp16) or 32 (bytes) of row tid / 4,
+  // and kPerB 16-byte pieces of the queries; byte offsets of slab 0
+  constexpr int kNW = Op::template kWords<B>;
   const int urow = tid >> 2, upart = tid & 3;
-  const uint32_t voc =
-      urow < rows ? (uint32_t)(urow * a.row_words + (upart >> 1) * B + (upart & 1) * (B / 2)) * 4u : kOffOOB;
+  const int w0 = kBytes ? upart * B : (upart >> 1) * B + (upart & 1) * (B / 2);
+  const uint32_t voc = urow < rows ? (uint32_t)(urow * a.row_words + w0) * 4u : kOffOOB;
   uint32_t voq[C::kPerB];
 #pragma unroll
   for (int q = 0; q < C::kPerB; ++q) {
     const int c = tid + C::kThreads * q;
-    voq[q] = (c >> 3) < qrows ? (uint32_t)((c >> 3) * a.D + (c & 7) * 8) * 2u : kOffOOB;
+    voq[q] = (c >> 3) < qrows ? (uint32_t)((c >> 3) * a.D * kES + (c & 7) * 16) : kOffOOB;
   }
   // columns k0 + cc (codes) and k0 + cq (queries) must lie inside the row (D is
-  // a multiple of 32, so the last slab may be half full)
-  const int cc = (upart >> 1) * 32, cq = (tid & 7) * 8;
+  // a multiple of 32, so the last slab may be partly empty)
+  const int cc = kBytes ? upart * 32 : (upart >> 1) * 32, cq = (tid & 7) * (16 / kES);
   auto load = [&](int s, uint32_t (&cw)[kNW], uint4 (&qv)[C::kPerB]) {
-    const int k0 = s * kBK;
-    load_words<kNW>(rsC, k0 + cc < a.D ? voc : kOffOOB, (uint32_t)(2 * s * B) * 4u, cw);
+    const int k0 = s * Op::kCols;
+    load_words<kNW>(rsC, k0 + cc < a.D ? voc : kOffOOB, (uint32_t)(s * (Op::kCols / 32) * B) * 4u, cw);
 #pragma unroll
     for (int q = 0; q < C::kPerB; ++q)
       qv[q] = __builtin_bit_cast(
-          uint4, __builtin_amdgcn_raw_buffer_load_b128(rsQ, k0 + cq < a.D ? voq[q] : kOffOOB, (uint32_t)k0 * 2u, 0));
+          uint4, __builtin_amdgcn_raw_buffer_load_b128(rsQ, k0 + cq < a.D ? voq[q] : kOffOOB, (uint32_t)k0 * kES, 0));
   };
   auto store = [&](int st, const uint32_t (&cw)[kNW], const uint4 (&qv)[C::kPerB]) {
-    _Float16 h[16];
-    unpack16<B>(cw, upart & 1, a.sh, h);
     _Float16* dst = sa(st) + urow * kLdk + upart * 16;
-    *reinterpret_cast<uint4*>(dst) = *reinterpret_cast<const uint4*>(h);
-    *reinterpret_cast<uint4*>(dst + 8) = *reinterpret_cast<const uint4*>(h + 8);
+    if constexpr (kBytes) {
+      uint32_t o[8];
+      unpack_bytes<B>(cw, o);
+      *reinterpret_cast<uint4*>(dst) = make_uint4(o[0], o[1], o[2], o[3]);
+      *reinterpret_cast<uint4*>(dst + 8) = make_uint4(o[4], o[5], o[6], o[7]);
+    } else {
+      _Float16 h[16];
+      unpack16<B>(cw, upart & 1, a.sh, h);
+      *reinterpret_cast<uint4*>(dst) = *reinterpret_cast<const uint4*>(h);
+      *reinterpret_cast<uint4*>(dst + 8) = *reinterpret_cast<const uint4*>(h + 8);
+    }
     slab_store_n<C::kPerB>(sb(st), qv, C::kThreads);
   };
   auto compute = [&](int st) {
@@ -448,11 +526,10 @@ __global__ __launch_bounds__(C::kThreads, C::kMinWaves) void k_filter(ScoreArgs 
 #pragma unroll
       for (int x = 0; x < C::TI; ++x)
 #pragma unroll
-        for (int y = 0; y < C::TJ; ++y)
-          acc[x][y] = __builtin_amdgcn_mfma_f32_32x32x16_f16(fa[x], fb[y], acc[x][y], 0, 0, 0);
+        for (int y = 0; y < C::TJ; ++y) acc[x][y] = Op::mfma(fa[x], fb[y], acc[x][y]);
     }
   };
-  const int S = (a.D + kBK - 1) / kBK;
+  const int S = (a.D + Op::kCols - 1) / Op::kCols;
   if constexpr (SETS == 3) {
     uint32_t cw[3][kNW];
     uint4 qv[3][C::kPerB];
@@ -490,20 +567,117 @@ __global__ __launch_bounds__(C::kThreads, C::kMinWaves) void k_filter(ScoreArgs 
       }
     }
   }
-  if constexpr (MODE == kDense) {
-    // this lane's rows, four consecutive ones per store
-    if (jv[0]) {
-      float* o = a.cand_s + j[0] * a.cap + rbase + wm * C::TI * 32;
+}
+
+// The filter's epilogue: every row with H = osc * acc at or above the query's
+// threshold goes to its candidate buffer.
+template <class C, class Acc>
+__device__ __forceinline__ void filter_append(const ScoreArgs& a, int64_t rbase, int rows, int wm,
+                                              const int64_t (&j)[C::TJ], const bool (&jv)[C::TJ],
+                                              const float (&th)[C::TJ], const float (&osc)[C::TJ],
+                                              const Acc (&acc)[C::TI][C::TJ]) {
+  const int lane = threadIdx.x & 63;
+  // a tile whose store rows are all valid needs no per-element row test
+  const bool full = rows == C::BM;
+#pragma unroll
+  for (int y = 0; y < C::TJ; ++y) {
+    // the tile's largest raw accumulator first (osc >= 0)
+    auto amx = acc[0][y][0];
+    if (full) {
 #pragma unroll
       for (int x = 0; x < C::TI; ++x)
 #pragma unroll
-        for (int g4 = 0; g4 < 4; ++g4)
-          *reinterpret_cast<float4*>(o + x * 32 + acc_row(4 * g4, lane)) =
-              make_float4(acc[x][0][4 * g4] * osc[0], acc[x][0][4 * g4 + 1] * osc[0], acc[x][0][4 * g4 + 2] * osc[0],
-                          acc[x][0][4 * g4 + 3] * osc[0]);
+        for (int r = 0; r < 16; ++r) amx = max(amx, acc[x][y][r]);
+    } else {
+      bool any = false;
+#pragma unroll
+      for (int x = 0; x < C::TI; ++x)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          const bool in = wm * C::TI * 32 + x * 32 + acc_row(r, lane) < rows;
+          amx = in ? (any ? max(amx, acc[x][y][r]) : acc[x][y][r]) : amx;
+          any |= in;
+        }
+      if (!any) continue;
     }
-    return;
+    const bool hot = jv[y] && (float)amx * osc[y] >= th[y];
+    if (__ballot(hot) == 0ull || !hot) continue;
+    uint32_t c = 0u;
+#pragma unroll
+    for (int x = 0; x < C::TI; ++x)
+#pragma unroll
+      for (int r = 0; r < 16; ++r)
+        c += (wm * C::TI * 32 + x * 32 + acc_row(r, lane) < rows && (float)acc[x][y][r] * osc[y] >= th[y]) ? 1u : 0u;
+    uint32_t idx = atomicAdd(&a.cand_cnt[j[y]], c);
+#pragma unroll
+    for (int x = 0; x < C::TI; ++x)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        const int rl_ = wm * C::TI * 32 + x * 32 + acc_row(r, lane);
+        const float sc = (float)acc[x][y][r] * osc[y];
+        if (rl_ < rows && sc >= th[y]) {
+          if (idx < a.cap) {
+            a.cand_s[j[y] * a.cap + idx] = sc;
+            a.cand_r[j[y] * a.cap + idx] = (int)(rbase + rl_);
+          }
+          ++idx;
+        }
+      }
   }
+}
+
+enum { kFilter = 0, kSample = 1, kFilterBytes = 2 };
+
+template <class C, int B, int MODE, int SETS>
+__global__ __launch_bounds__(C::kThreads, C::kMinWaves) void k_filter(ScoreArgs a) {
+  static_assert(MODE != kSample || (C::BM == kTB && C::TJ == 1), "the sample pass runs on 128-row tiles of one query block");
+  __shared__ _Float16 lds[C::kLdsHalves];
+  const int64_t nt = a.tile_end;   // store tiles of this pass (tile_begin = 0)
+  // 32-bit index arithmetic: the host keeps the grid (nqt * nt) below 2^31
+  const uint32_t logical = (uint32_t)xcd_remap32((int)blockIdx.x, (int)(a.nqt * nt));
+  const uint32_t per = (uint32_t)(kFilterGroupQ * nt);
+  const uint32_t g = logical / per;
+  const uint32_t l = logical - g * per;
+  const uint32_t gsize = (uint32_t)min(kFilterGroupQ, a.nqt - (int)g * kFilterGroupQ);
+  const int qt = (int)(g * kFilterGroupQ + l % gsize);
+  const int64_t rbase = (int64_t)(l / gsize) * C::BM;
+  const int rows = (int)min<int64_t>(C::BM, a.n - rbase);
+  const int64_t qbase = (int64_t)qt * C::BN;
+  const int qrows = (int)min<int64_t>(C::BN, a.nq - qbase);
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int wm = wave / C::WN, wn = wave % C::WN;
+  if constexpr (MODE == kFilterBytes) {
+    if (a.coarse[qbase / kPrecQueries] == 0u) {
+      int64_t j[C::TJ];
+      bool jv[C::TJ];
+      float th[C::TJ], osc[C::TJ];
+#pragma unroll
+      for (int y = 0; y < C::TJ; ++y) {
+        j[y] = qbase + wn * C::TJ * 32 + y * 32 + (lane & 31);
+        jv[y] = j[y] < a.nq;
+        th[y] = jv[y] ? a.thr[a.nq + j[y]] : 0.0f;
+        osc[y] = jv[y] ? a.meta[j[y]].osc8 : 0.0f;
+      }
+      intx16 acc[C::TI][C::TJ];
+      scan_tile<C, OpI8, B, (B <= 8 ? SETS : 1)>(a, rbase, rows, qbase, qrows, lds, acc);
+      filter_append<C>(a, rbase, rows, wm, j, jv, th, osc, acc);
+      return;
+    }
+  }
+  // this lane's queries and their thresholds, loaded before the GEMM
+  int64_t j[C::TJ];
+  bool jv[C::TJ];
+  float th[C::TJ], osc[C::TJ];
+#pragma unroll
+  for (int y = 0; y < C::TJ; ++y) {
+    j[y] = qbase + wn * C::TJ * 32 + y * 32 + (lane & 31);
+    jv[y] = j[y] < a.nq;
+    th[y] = (jv[y] && MODE != kSample) ? a.thr[j[y]] : 0.0f;
+    osc[y] = jv[y] ? a.meta[j[y]].osc : 0.0f;
+  }
+
+  floatx16 acc[C::TI][C::TJ];
+  scan_tile<C, OpF16, B, SETS>(a, rbase, rows, qbase, qrows, lds, acc);
   if constexpr (MODE == kSample) {
     // this lane's best H over its 32 rows
     float best = -INFINITY;
@@ -521,48 +695,7 @@ __global__ __launch_bounds__(C::kThreads, C::kMinWaves) void k_filter(ScoreArgs 
     }
     return;
   }
-  // a tile whose store rows are all valid needs no per-element row test
-  const bool full = rows == C::BM;
-#pragma unroll
-  for (int y = 0; y < C::TJ; ++y) {
-    // epilogue: the tile's largest raw accumulator first (osc > 0)
-    float amx = -INFINITY;
-    if (full) {
-#pragma unroll
-      for (int x = 0; x < C::TI; ++x)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) amx = fmaxf(amx, acc[x][y][r]);
-    } else {
-#pragma unroll
-      for (int x = 0; x < C::TI; ++x)
-#pragma unroll
-        for (int r = 0; r < 16; ++r)
-          amx = (wm * C::TI * 32 + x * 32 + acc_row(r, lane) < rows) ? fmaxf(amx, acc[x][y][r]) : amx;
-    }
-    const bool hot = jv[y] && amx * osc[y] >= th[y];
-    if (__ballot(hot) == 0ull || !hot) continue;
-    uint32_t c = 0u;
-#pragma unroll
-    for (int x = 0; x < C::TI; ++x)
-#pragma unroll
-      for (int r = 0; r < 16; ++r)
-        c += (wm * C::TI * 32 + x * 32 + acc_row(r, lane) < rows && acc[x][y][r] * osc[y] >= th[y]) ? 1u : 0u;
-    uint32_t idx = atomicAdd(&a.cand_cnt[j[y]], c);
-#pragma unroll
-    for (int x = 0; x < C::TI; ++x)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int rl_ = wm * C::TI * 32 + x * 32 + acc_row(r, lane);
-        const float sc = acc[x][y][r] * osc[y];
-        if (rl_ < rows && sc >= th[y]) {
-          if (idx < a.cap) {
-            a.cand_s[j[y] * a.cap + idx] = sc;
-            a.cand_r[j[y] * a.cap + idx] = (int)(rbase + rl_);
-          }
-          ++idx;
-        }
-      }
-  }
+  filter_append<C>(a, rbase, rows, wm, j, jv, th, osc, acc);
 }
 
 // large: the filter pass on FilterTileL (a.nqt and a.tile_end in its tiles).
@@ -571,9 +704,9 @@ __global__ __launch_bounds__(C::kThreads, C::kMinWaves) void k_filter(ScoreArgs 
 template <int B, int MODE>
 lam_status launch_filter(int b, bool large, int64_t grid, hipStream_t st, const ScoreArgs& a) {
   if (b == B) {
-    if constexpr (MODE == kFilter) {
+    if constexpr (MODE == kFilter || MODE == kFilterBytes) {
       if (large) {
-        hipLaunchKernelGGL((k_filter<FilterTileL, B, kFilter, 1>), dim3((unsigned)grid), dim3(FilterTileL::kThreads), 0,
+        hipLaunchKernelGGL((k_filter<FilterTileL, B, MODE, 1>), dim3((unsigned)grid), dim3(FilterTileL::kThreads), 0,
                            st, a);
         LAM_HIP(hipGetLastError());
         return LAM_OK;
@@ -584,7 +717,7 @@ lam_status launch_filter(int b, bool large, int64_t grid, hipStream_t st, const 
     LAM_HIP(hipGetLastError());
     return LAM_OK;
   }
-  if constexpr (B < kMaxBits) return launch_filter<B + 1, MODE>(b, large, grid, st, a);
+  if constexpr (B < (MODE == kFilterBytes ? 12 : kMaxBits)) return launch_filter<B + 1, MODE>(b, large, grid, st, a);
   set_error("scoring supports codes of at most %d bits (got %d)", kMaxBits, b);
   return LAM_ESTATE;
 }
@@ -706,14 +839,13 @@ __device__ __forceinline__ bool rescore_row(uint32_t t, uint32_t m, const int32_
 // query, and (-inf, -1) past the candidates.  Eight lanes share a rescored row
 // (32 rows in flight per workgroup); a lane takes whole groups of 32 codes (B
 // words).
-// DENSE: the candidates are the store's n rows in order (no query is flagged).
-template <int B, bool DENSE>
+template <int B>
 __global__ __launch_bounds__(kRescoreThreads) void k_select_rescore(
-    int64_t nq, uint32_t n, uint32_t cap, int k, const uint32_t* __restrict__ cnt, const float* __restrict__ cs,
+    int64_t nq, uint32_t cap, int k, const uint32_t* __restrict__ cnt, const float* __restrict__ cs,
     const int32_t* __restrict__ cr, const QMeta* __restrict__ meta, const int64_t* __restrict__ ids,
     const float* __restrict__ q, double step, const uint32_t* __restrict__ codes, int64_t row_words, int D,
     float* __restrict__ out_s, int64_t* __restrict__ out_i, float* __restrict__ bound, uint32_t* __restrict__ n_flag,
-    uint32_t* __restrict__ flagged) {
+    uint32_t* __restrict__ flagged, const uint32_t* __restrict__ coarse) {
   constexpr int kCap = kExactBuf;
   __shared__ int32_t rows[kCap];
   __shared__ TopBuf buf;
@@ -722,8 +854,9 @@ __global__ __launch_bounds__(kRescoreThreads) void k_select_rescore(
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int64_t j = blockIdx.x;
   if (j >= nq) return;
-  const uint32_t c = DENSE ? n : cnt[j];
+  const uint32_t c = cnt[j];
   const QMeta mj = meta[j];
+  const float err = coarse && coarse[j / kPrecQueries] == 0u ? mj.err8 : mj.err;   // of the scan that ran
   if (tid == 0 && bound) bound[j] = mj.bound;
   if (mj.bad) {
     for (int t = tid; t < k; t += kRescoreThreads) {
@@ -732,7 +865,7 @@ __global__ __launch_bounds__(kRescoreThreads) void k_select_rescore(
     }
     return;
   }
-  if (!DENSE && c > cap) {   // the exact pass redoes the query
+  if (c > cap) {   // the exact pass redoes the query
     if (tid == 0) flagged[atomicAdd(n_flag, 1u)] = (uint32_t)j;
     return;
   }
@@ -750,7 +883,7 @@ __global__ __launch_bounds__(kRescoreThreads) void k_select_rescore(
   for (int u = 0; u < 2; ++u) {
     const uint32_t i = (uint32_t)(tid + u * kRescoreThreads);
     fs[u] = i < c ? cs[j * cap + i] : 0.0f;
-    fr[u] = DENSE ? (int)i : (i < c ? cr[j * cap + i] : 0);
+    fr[u] = i < c ? cr[j * cap + i] : 0;
   }
   if (wave == 0) {
     uint32_t key[kThrKeys];
@@ -767,7 +900,7 @@ __global__ __launch_bounds__(kRescoreThreads) void k_select_rescore(
       }
     const uint32_t T = wave_kth_floor<kThrKeys>(key, (int)min((uint32_t)kThrKeys, (c + 63u) / 64u), kk);
     if (lane == 0) {
-      thr_sh = T == 0u ? -INFINITY : rd32((double)ord2f(T) - 2.0 * (double)mj.err);
+      thr_sh = T == 0u ? -INFINITY : rd32((double)ord2f(T) - 2.0 * (double)err);
       m_sh = 0u;
     }
   }
@@ -783,7 +916,7 @@ __global__ __launch_bounds__(kRescoreThreads) void k_select_rescore(
   for (uint32_t i = tid + 2 * kRescoreThreads; i < c; i += kRescoreThreads) {
     if (cs[j * cap + i] >= thr) {
       const uint32_t p = atomicAdd(&m_sh, 1u);
-      if (p < (uint32_t)kCap) rows[p] = DENSE ? (int)i : cr[j * cap + i];
+      if (p < (uint32_t)kCap) rows[p] = cr[j * cap + i];
     }
   }
   __syncthreads();
@@ -806,7 +939,7 @@ __global__ __launch_bounds__(kRescoreThreads) void k_select_rescore(
       if (tid == 0) m_sh = 0u;
       __syncthreads();
       const uint32_t i = i0 + (uint32_t)tid;
-      if (i < c && cs[j * cap + i] >= thr) rows[atomicAdd(&m_sh, 1u)] = DENSE ? (int)i : cr[j * cap + i];
+      if (i < c && cs[j * cap + i] >= thr) rows[atomicAdd(&m_sh, 1u)] = cr[j * cap + i];
       __syncthreads();
       const uint32_t mi = m_sh;
       for (uint32_t t0 = 0; t0 < mi; t0 += kSlots)
@@ -941,31 +1074,26 @@ struct ExactArgs {
   int64_t* out_i;
   float* bound;
   uint32_t *n_flag, *flagged, *done;
+  const uint32_t* coarse;   // byte scan: the flags of the queries that took the fp16 scan (else NULL)
   int splits;
 };
 
-enum { kSelect = 0, kSelectDense = 1, kExactPass = 2 };
-
+// The selection, or the exact pass over the flagged queries.
 template <int B>
-lam_status launch_exact(int b, int what, hipStream_t st, const ExactArgs& a) {
+lam_status launch_exact(int b, bool select, hipStream_t st, const ExactArgs& a) {
   if (b == B) {
-    if (what == kSelect) {
-      hipLaunchKernelGGL((k_select_rescore<B, false>), dim3((unsigned)a.nq), dim3(kRescoreThreads), 0, st, a.nq,
-                         (uint32_t)a.n, a.cap, a.k, a.cnt, a.cs, a.cr, a.meta, a.ids, a.q, a.step, a.codes,
-                         a.row_words, a.D, a.out_s, a.out_i, a.bound, a.n_flag, a.flagged);
-    } else if (what == kSelectDense) {
-      hipLaunchKernelGGL((k_select_rescore<B, true>), dim3((unsigned)a.nq), dim3(kRescoreThreads), 0, st, a.nq,
-                         (uint32_t)a.n, a.cap, a.k, a.cnt, a.cs, a.cr, a.meta, a.ids, a.q, a.step, a.codes,
-                         a.row_words, a.D, a.out_s, a.out_i, a.bound, a.n_flag, a.flagged);
-    } else {
+    if (select)
+      hipLaunchKernelGGL((k_select_rescore<B>), dim3((unsigned)a.nq), dim3(kRescoreThreads), 0, st, a.nq, a.cap, a.k,
+                         a.cnt, a.cs, a.cr, a.meta, a.ids, a.q, a.step, a.codes, a.row_words, a.D, a.out_s, a.out_i,
+                         a.bound, a.n_flag, a.flagged, a.coarse);
+    else
       hipLaunchKernelGGL((k_exact<B>), dim3(1024), dim3(kRescoreThreads), (size_t)(a.D / 32) * 33 * 8, st, a.n, a.splits,
                          (a.n + a.splits - 1) / a.splits, a.cap, a.k, a.ids, a.q, a.step, a.codes, a.row_words, a.D,
                          a.cs, a.cr, a.done, a.n_flag, a.flagged, a.out_s, a.out_i);
-    }
     LAM_HIP(hipGetLastError());
     return LAM_OK;
   }
-  if constexpr (B < kMaxBits) return launch_exact<B + 1>(b, what, st, a);
+  if constexpr (B < kMaxBits) return launch_exact<B + 1>(b, select, st, a);
   set_error("scoring supports codes of at most %d bits (got %d)", kMaxBits, b);
   return LAM_ESTATE;
 }
@@ -973,6 +1101,254 @@ lam_status launch_exact(int b, int what, hipStream_t st, const ExactArgs& a) {
 __global__ __launch_bounds__(256) void k_fill_zero(uint32_t* __restrict__ p, int64_t n) {
   const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
   if (i < n) p[i] = 0u;
+}
+
+// ------------------------------------------------------------------ small stores
+// A store of at most kCandCap rows is scored whole: k_dense forms every score
+// in fp32 from the query's fp16 hi and lo parts (q 2^e = hi + lo + r, |r| <=
+// 2^-22 |q 2^e|), and k_select_dense takes the k best, so that the call is three
+// launches.  Codes of more than 12 bits enter as their two exact fp16 halves,
+// c = 2^11 (c >> 11) + (c & 2047): 2D columns (the high halves, then the low
+// ones) against the query [2^11 q, q].
+struct DenseArgs {
+  const uint32_t* codes;
+  int64_t n;
+  int D;                // columns of a row; the scan has D or 2 D
+  int64_t row_words;
+  const _Float16* qhi;  // [nq][D or 2 D]
+  const _Float16* qlo;
+  const QMeta* meta;    // osc, bound and bad
+  int64_t nq;
+  int nqt;
+  float* scores;        // [nq][ld]
+  int ld;
+};
+
+// One wave per query: hi and lo parts of its D columns, or of [2^11 q, q] (wide).
+__global__ __launch_bounds__(256) void k_dense_prep(const float* __restrict__ q, int64_t nq, int D, int wide,
+                                                    double s, double eps, _Float16* __restrict__ qhi,
+                                                    _Float16* __restrict__ qlo, QMeta* __restrict__ meta) {
+  const int lane = threadIdx.x & 63;
+  const int64_t j = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+  if (j >= nq) return;
+  const float* p = q + j * D;
+  const int cols = wide ? 2 * D : D;
+  const float up11 = wide ? 2048.0f : 1.0f;
+  float mx = 0.0f;
+  double l1 = 0.0;
+  bool bad = false;
+  for (int d = lane * 4; d < D; d += 256) {
+    const float4 v = *reinterpret_cast<const float4*>(p + d);
+    const float c[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const float a = fabsf(c[i] * up11);
+      bad |= !(a <= 3.402823466e38f);
+      mx = fmaxf(mx, a);
+      l1 += (double)fabsf(c[i]);
+    }
+  }
+  mx = wave_max_f32(mx);
+  l1 = wave_sum_f64(l1);
+  bad = __ballot(bad) != 0ull;
+  int e = 0;
+  if (!bad && mx > 0.0f) e = 14 - ilogbf(mx);   // the largest entry times 2^e in [2^14, 2^15)
+  const float sc = ldexpf(1.0f, e);
+  for (int d = lane * 4; d < cols; d += 256) {   // (D is a multiple of 32: four columns are of one half)
+    const float4 v = *reinterpret_cast<const float4*>(p + (d < D ? d : d - D));
+    const float f = d < D ? up11 : 1.0f;
+    const float c[4] = {v.x * f, v.y * f, v.z * f, v.w * f};
+    _Float16 h[4], l[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const float x = bad ? 0.0f : c[i] * sc;   // exact power-of-two scaling
+      h[i] = (_Float16)x;
+      l[i] = (_Float16)(x - (float)h[i]);
+    }
+    uint2 ph, pl;
+    __builtin_memcpy(&ph, h, 8);
+    __builtin_memcpy(&pl, l, 8);
+    *reinterpret_cast<uint2*>(qhi + j * cols + d) = ph;
+    *reinterpret_cast<uint2*>(qlo + j * cols + d) = pl;
+  }
+  if (lane == 0) {
+    QMeta m{};
+    m.osc = (float)ldexp(s, -e);
+    m.bound = bad ? __builtin_nanf("") : ru32(eps * l1 * (1.0 + (double)(cols + 4) * 0x1p-52));
+    m.bad = bad ? 1 : 0;
+    meta[j] = m;
+  }
+}
+
+// One 128 x 128 tile (store rows x queries) per workgroup of four waves, each
+// 128 rows x 32 queries; one LDS stage (codes, hi, lo) is refilled between two
+// barriers while the next slab's loads are in flight in registers.  Two threads
+// unpack a row's slab, a group of 32 codes each.
+template <int B>
+__global__ __launch_bounds__(kWG, 2) void k_dense(DenseArgs a) {
+  constexpr bool kWide = B > 12;
+  __shared__ __attribute__((aligned(16))) _Float16 lds[3 * kTB * kLdk];
+  _Float16* sc = lds;
+  _Float16* sh = lds + kTB * kLdk;
+  _Float16* sl = lds + 2 * kTB * kLdk;
+  const int qt = (int)blockIdx.x % a.nqt;
+  const int64_t rbase = (int64_t)(blockIdx.x / a.nqt) * kTB;
+  const int rows = (int)min<int64_t>(kTB, a.n - rbase);
+  const int64_t qbase = (int64_t)qt * kTB;
+  const int qrows = (int)min<int64_t>(kTB, a.nq - qbase);
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int urow = threadIdx.x >> 1, uhalf = threadIdx.x & 1;
+  const int cols = kWide ? 2 * a.D : a.D;
+  const int64_t j = qbase + wave * 32 + (lane & 31);
+  const float osc = j < a.nq ? a.meta[j].osc : 0.0f;
+  floatx16 acc[4];
+#pragma unroll
+  for (int t = 0; t < 4; ++t)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc[t][r] = 0.0f;
+  const __amdgpu_buffer_rsrc_t rsC = __builtin_amdgcn_make_buffer_rsrc(
+      const_cast<uint32_t*>(a.codes + rbase * a.row_words), (short)0, (int)(rows * a.row_words * 4), 0x00020000);
+  const __amdgpu_buffer_rsrc_t rsH = tile_rsrc(a.qhi + qbase * cols, qrows, cols);
+  const __amdgpu_buffer_rsrc_t rsL = tile_rsrc(a.qlo + qbase * cols, qrows, cols);
+  const int G = a.D / 32;   // groups of a row; group g + G of the scan holds group g's low halves
+  auto load_slab = [&](int k0, uint32_t (&cw)[B], uint4 (&rh)[4], uint4 (&rl)[4]) {
+    const int g = k0 / 32 + uhalf;
+    const bool ok = urow < rows && k0 + 32 * uhalf < cols;
+    const uint32_t w0 = (uint32_t)(urow * a.row_words + (int64_t)(kWide && g >= G ? g - G : g) * B);
+    load_words<B>(rsC, ok ? w0 * 4u : kOffOOB, 0u, cw);
+    slab_load_n<4>(rsH, qrows, cols, k0, cols, rh, kWG);
+    slab_load_n<4>(rsL, qrows, cols, k0, cols, rl, kWG);
+  };
+  const int S = (cols + kBK - 1) / kBK;
+  uint32_t cw[B];
+  uint4 rh[4], rl[4];
+  load_slab(0, cw, rh, rl);
+  for (int s = 0; s < S; ++s) {
+    __syncthreads();   // every wave is done with the previous slab
+    {
+      const bool low = kWide && 2 * s + uhalf >= G;
+      _Float16 h[32];
+#pragma unroll
+      for (int e = 0; e < 32; ++e) {
+        int32_t c = code_at<B>(cw, e);
+        if (kWide) c = low ? (c & 2047) : (c >> 11);
+        h[e] = (_Float16)(short)c;
+      }
+      _Float16* dst = sc + urow * kLdk + uhalf * 32;
+#pragma unroll
+      for (int i = 0; i < 32; i += 8) *reinterpret_cast<uint4*>(dst + i) = *reinterpret_cast<const uint4*>(h + i);
+    }
+    slab_store_n<4>(sh, rh, kWG);
+    slab_store_n<4>(sl, rl, kWG);
+    __syncthreads();
+    load_slab((s + 1) * kBK, cw, rh, rl);   // past the last slab: zeros, no memory touched
+    __builtin_amdgcn_sched_barrier(0);      // issue the loads before the MFMAs
+#pragma unroll
+    for (int kk = 0; kk < kBK / 16; ++kk) {
+      const half8 bh = frag_load(sh, wave * 32, kk);
+      const half8 bl = frag_load(sl, wave * 32, kk);
+      half8 fa[4];
+#pragma unroll
+      for (int t = 0; t < 4; ++t) fa[t] = frag_load(sc, t * 32, kk);
+#pragma unroll
+      for (int t = 0; t < 4; ++t) acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_f16(fa[t], bh, acc[t], 0, 0, 0);
+#pragma unroll
+      for (int t = 0; t < 4; ++t) acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_f16(fa[t], bl, acc[t], 0, 0, 0);
+    }
+  }
+  if (j >= a.nq) return;
+  // this lane's rows, four consecutive ones per store (ld covers whole tiles)
+  float* o = a.scores + j * a.ld + rbase;
+#pragma unroll
+  for (int t = 0; t < 4; ++t)
+#pragma unroll
+    for (int g = 0; g < 4; ++g)
+      *reinterpret_cast<float4*>(o + t * 32 + acc_row(4 * g, lane)) =
+          make_float4(acc[t][4 * g] * osc, acc[t][4 * g + 1] * osc, acc[t][4 * g + 2] * osc, acc[t][4 * g + 3] * osc);
+}
+
+template <int B>
+lam_status launch_dense(int b, dim3 grid, hipStream_t st, const DenseArgs& a) {
+  if (b == B) {
+    hipLaunchKernelGGL((k_dense<B>), grid, dim3(kWG), 0, st, a);
+    LAM_HIP(hipGetLastError());
+    return LAM_OK;
+  }
+  if constexpr (B < kMaxBits) return launch_dense<B + 1>(b, grid, st, a);
+  set_error("scoring supports codes of at most %d bits (got %d)", kMaxBits, b);
+  return LAM_ESTATE;
+}
+
+// One workgroup per query: the k best of the n <= kCandCap scores, held 16 per
+// thread.  The largest of the waves' own k-th best is a lower bound of the
+// k-th best of all; what reaches it is sorted (through the buffer in steps when
+// more than 1,024 tie there).
+__global__ __launch_bounds__(kRescoreThreads) void k_select_dense(int64_t nq, int n, int ld, int k,
+                                                                  const float* __restrict__ scores,
+                                                                  const QMeta* __restrict__ meta,
+                                                                  const int64_t* __restrict__ ids,
+                                                                  float* __restrict__ out_s,
+                                                                  int64_t* __restrict__ out_i,
+                                                                  float* __restrict__ bound) {
+  constexpr int kPer = kCandCap / kRescoreThreads;
+  static_assert(kPer == kThrKeys, "a wave's keys are one register set");
+  __shared__ TopBuf buf;
+  __shared__ uint32_t floor_sh[kRescoreThreads / 64], cnt_sh[kRescoreThreads / 64];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int64_t j = blockIdx.x;
+  if (j >= nq) return;
+  const QMeta mj = meta[j];
+  if (tid == 0 && bound) bound[j] = mj.bound;
+  const int kk = mj.bad ? 0 : min(k, n);
+  for (int t = kk + tid; t < k; t += kRescoreThreads) {
+    out_s[j * k + t] = mj.bad ? __builtin_nanf("") : -INFINITY;
+    out_i[j * k + t] = -1;
+  }
+  if (kk == 0) return;
+  uint32_t key[kPer];
+#pragma unroll
+  for (int r = 0; r < kPer; ++r) {
+    const int i = tid + r * kRescoreThreads;
+    key[r] = i < n ? f2ord(scores[j * ld + i] + 0.0f) : 0u;
+  }
+  const uint32_t T = wave_kth_floor<kPer>(key, (n + kRescoreThreads - 1) / kRescoreThreads, kk);
+  if (lane == 0) floor_sh[wave] = T;
+  topbuf_clear(buf);
+  uint32_t F = 1u;   // (order code 0 marks no row)
+#pragma unroll
+  for (int w = 0; w < kRescoreThreads / 64; ++w) F = max(F, floor_sh[w]);
+  int c = 0;
+#pragma unroll
+  for (int r = 0; r < kPer; ++r) c += __popcll(__ballot(key[r] >= F));
+  if (lane == 0) cnt_sh[wave] = (uint32_t)c;
+  __syncthreads();
+  uint32_t m = 0u;
+#pragma unroll
+  for (int w = 0; w < kRescoreThreads / 64; ++w) m += cnt_sh[w];
+  const bool fits = m <= (uint32_t)kExactBuf;
+#pragma unroll
+  for (int r = 0; r < kPer; ++r) {
+    if (key[r] >= F)
+      topbuf_push(buf, ((unsigned long long)key[r] << 32) | (unsigned long long)(~(uint32_t)(tid + r * kRescoreThreads)));
+    if (!fits) {
+      __syncthreads();
+      topbuf_cut(buf, k, kRescoreThreads);
+    }
+  }
+  __syncthreads();
+  if (fits) {
+    uint32_t P = 1u;
+    while (P < m) P <<= 1;
+    for (uint32_t i = m + tid; i < P; i += kRescoreThreads) buf.keys[i] = 0ull;
+    __syncthreads();
+    sort_keys(buf.keys, P);
+  } else {
+    topbuf_cut(buf, k, kExactBuf);   // sorts what is left
+  }
+  for (int t = tid; t < kk; t += kRescoreThreads) {
+    out_s[j * k + t] = ord2f((uint32_t)(buf.keys[t] >> 32));
+    out_i[j * k + t] = ids[~(uint32_t)(buf.keys[t] & 0xffffffffull)];
+  }
 }
 
 }  // namespace
@@ -984,6 +1360,7 @@ struct ScoreView {
   int D;
   int b;
   int sh;
+  bool bytes;   // every code that occurs fits 8 bits
   int64_t n;
   double step;
   double eps;
@@ -1011,6 +1388,7 @@ ScoreView store_view(const lam_store* st, const uint32_t* codes) {
   int used = 1;
   while (used < 32 && ((1u << (used - 1)) - 1u) < (uint32_t)st->max_code) ++used;
   v.sh = std::max(0, used - 12);
+  v.bytes = used <= 8;
   v.n = st->size;
   v.step = st->q.step;
   v.eps = st->q.eps;
@@ -1022,15 +1400,18 @@ ScoreView store_view(const lam_store* st, const uint32_t* codes) {
 
 }  // namespace
 
-// Scoring plan (H: scores of the scan, within err of the exact scores S but for
-// a constant of the query).  A store of at most 4,096 rows is scored densely:
-// every H is written, and step 3 works on all rows.  Beyond that:
+// Scoring plan of a store of more than 4,096 rows (smaller ones: score_dense).
+// H: scores of the scan, within err of the exact scores S but for a constant of
+// the query.
 //   1. theta_j, the k-th best H of disjoint 32-row sets' best over the first S
 //      rows (S = k * n / 256, at least 4,096), minus 2 err_j: k distinct rows
 //      have S >= theta_j + err_j, so every row of the final top-k has H >=
 //      theta_j;
 //   2. a full scan appends every row with H >= theta_j to query j's candidate
-//      buffer (about k * n / S = 256 entries expected; capacity 4,096);
+//      buffer (about k * n / S = 256 entries expected; capacity 4,096).  Where
+//      all codes fit 8 bits it multiplies bytes, against theta_j of their own
+//      error bound, but for the groups of queries where that would let too
+//      many rows through;
 //   3. the candidates within 2 err_j of the k-th best H of them are scored
 //      exactly and their k best by (S desc, id asc) are the answer
 //      (k_select_rescore);
@@ -1061,6 +1442,46 @@ struct ScoreWork {
   }
 };
 
+// score_topk of a store of at most kCandCap rows.
+lam_status score_dense(lam_ctx* ctx, const ScoreView& st, const float* q, int64_t nq, int32_t k, float* scores,
+                       int64_t* ids, float* bound, ScoreWork& w, bool prof) {
+  const int64_t ntiles = (st.n + kTB - 1) / kTB;
+  const bool wide = st.b > 12;
+  const int64_t cols = (wide ? 2 : 1) * (int64_t)st.D;
+  DenseArgs a{};
+  _Float16 *qhi = nullptr, *qlo = nullptr;
+  QMeta* qmeta = nullptr;
+  LAM_TRY(w.take(ctx, S_QHI, (size_t)nq * cols * 2, &qhi));
+  LAM_TRY(w.take(ctx, S_QLO, (size_t)nq * cols * 2, &qlo));
+  LAM_TRY(w.take(ctx, S_QMETA, (size_t)nq * sizeof(QMeta), &qmeta));
+  LAM_TRY(w.take(ctx, S_CAND, (size_t)nq * ntiles * kTB * 4, &a.scores));
+  a.codes = st.codes;
+  a.n = st.n;
+  a.D = st.D;
+  a.row_words = (int64_t)st.D * st.b / 32;
+  a.qhi = qhi;
+  a.qlo = qlo;
+  a.meta = qmeta;
+  a.nq = nq;
+  a.nqt = (int)((nq + kTB - 1) / kTB);
+  a.ld = (int)(ntiles * kTB);
+  {
+    ProfScope ps(ctx, "score_prep", prof);
+    hipLaunchKernelGGL(k_dense_prep, dim3((unsigned)((nq + 3) / 4)), dim3(256), 0, ctx->stream, q, nq, st.D,
+                       wide ? 1 : 0, st.step, st.eps, qhi, qlo, qmeta);
+    LAM_HIP(hipGetLastError());
+  }
+  if (ntiles > 0) {
+    ProfScope ps(ctx, "score_mfma", prof);
+    LAM_TRY(launch_dense<1>(st.b, dim3((unsigned)(a.nqt * ntiles)), ctx->stream, a));
+  }
+  ProfScope ps(ctx, "score_merge", prof);
+  hipLaunchKernelGGL(k_select_dense, dim3((unsigned)nq), dim3(kRescoreThreads), 0, ctx->stream, nq, (int)st.n, a.ld, k,
+                     a.scores, qmeta, st.ids, scores, ids, bound);
+  LAM_HIP(hipGetLastError());
+  return LAM_OK;
+}
+
 // score_topk on the workspace w.  Every buffer is taken before the first
 // launch, so a workspace that is too small fails with nothing enqueued.  No
 // profiling events are recorded unless prof.
@@ -1072,18 +1493,18 @@ lam_status score_topk_impl(lam_ctx* ctx, const ScoreView& st, const float* q, in
   const int64_t n = st.n;
   const int nqt = (int)((nq + kTB - 1) / kTB);
   const int64_t ntiles = (n + kTB - 1) / kTB;
-  const bool dense = n <= kCandCap;
+  // the passes are one workgroup per (query tile, store tile), indexed in 32 bits
+  LAM_CHECK((int64_t)nqt * ntiles < (1LL << 31), LAM_EINVAL, "scoring grid too large");
+  if (n <= kCandCap) return score_dense(ctx, st, q, nq, k, scores, ids, bound, w, prof);
   // the sample: the store's first max(4,096, k n / 256) rows, so that at
   // most about k n / sample = 256 rows per query pass the filter (a sample of
   // k n / 1,024 rows let about 1,024 through: the corpus call 2.65-2.71 ->
   // 2.57-2.59 ms, 60 K rows at top-50 265 -> 238 us; k n / 128 was no faster)
   const int64_t sample_rows = std::max<int64_t>(4096, ((int64_t)k * n + 255) / 256);
-  const int64_t stiles = dense ? 0 : std::min<int64_t>(n / kTB, (sample_rows + kTB - 1) / kTB);   // whole tiles
+  const int64_t stiles = std::min<int64_t>(n / kTB, (sample_rows + kTB - 1) / kTB);   // whole tiles
   const int64_t sample_tiles = std::min<int64_t>(stiles, kSampleTiles);
   const int64_t entries = sample_tiles * kSampleEntries;
-  // the passes are one workgroup per (query tile, store tile), indexed in 32 bits
-  LAM_CHECK((int64_t)nqt * ntiles < (1LL << 31), LAM_EINVAL, "scoring grid too large");
-  const uint32_t cap = dense ? (uint32_t)(ntiles * kTB) : (uint32_t)kCandCap;
+  const uint32_t cap = (uint32_t)kCandCap;
 
   // every buffer first
   _Float16* qhi = nullptr;
@@ -1092,18 +1513,18 @@ lam_status score_topk_impl(lam_ctx* ctx, const ScoreView& st, const float* q, in
   float* cand_s = nullptr;
   LAM_TRY(w.take(ctx, S_QHI, (size_t)nq * D * 2, &qhi));
   LAM_TRY(w.take(ctx, S_QMETA, (size_t)nq * sizeof(QMeta), &qmeta));
-  if (dense) {
-    LAM_TRY(w.take(ctx, S_CAND, (size_t)nq * cap * 4, &cand_s));
-  } else {
-    LAM_TRY(w.take(ctx, S_PART, (size_t)nq * entries * 4, &part_s));
-    LAM_TRY(w.take(ctx, S_CAND, (size_t)nq * cap * 8 + (size_t)nq * 16 + 4, &cand_s));
-  }
-  int32_t* cand_r = dense ? nullptr : reinterpret_cast<int32_t*>(cand_s + (size_t)nq * cap);
-  uint32_t* cand_cnt = dense ? nullptr : reinterpret_cast<uint32_t*>(cand_r + (size_t)nq * cap);
-  float* thr = dense ? nullptr : reinterpret_cast<float*>(cand_cnt + nq);
-  uint32_t* flagged = dense ? nullptr : cand_cnt + 2 * nq;
-  uint32_t* done = dense ? nullptr : cand_cnt + 3 * nq;
-  uint32_t* n_flag = dense ? nullptr : cand_cnt + 4 * nq;
+  const bool bytes = st.bytes && b <= 12;
+  int8_t* q8 = nullptr;
+  if (bytes) LAM_TRY(w.take(ctx, S_Q8, (size_t)nq * D, &q8));
+  LAM_TRY(w.take(ctx, S_PART, (size_t)nq * entries * 4, &part_s));
+  LAM_TRY(w.take(ctx, S_CAND, (size_t)nq * cap * 8 + (size_t)nq * 20 + 4 + (size_t)(nq / kPrecQueries + 1) * 4, &cand_s));
+  int32_t* cand_r = reinterpret_cast<int32_t*>(cand_s + (size_t)nq * cap);
+  uint32_t* cand_cnt = reinterpret_cast<uint32_t*>(cand_r + (size_t)nq * cap);
+  float* thr = reinterpret_cast<float*>(cand_cnt + nq);   // two per query
+  uint32_t* flagged = cand_cnt + 3 * nq;
+  uint32_t* done = cand_cnt + 4 * nq;
+  uint32_t* n_flag = cand_cnt + 5 * nq;
+  uint32_t* coarse = n_flag + 1;
 
   {
     ProfScope ps(ctx, "score_prep", prof);
@@ -1116,7 +1537,7 @@ lam_status score_topk_impl(lam_ctx* ctx, const ScoreView& st, const float* q, in
     // not hold in float32 counts as holding Inf)
     const float qmax = b > 12 ? 3.402823466e38f / 2048.0f : 3.402823466e38f;
     hipLaunchKernelGGL(k_score_prep, dim3((unsigned)((nq + 3) / 4)), dim3(256), 0, ctx->stream, q, nq, D,
-                       st.step * two, st.eps, R, trunc, qmax, qhi, qmeta, cand_cnt, done, n_flag);
+                       st.step * two, st.eps, R, trunc, qmax, qhi, q8, qmeta, cand_cnt, done, n_flag, coarse);
     LAM_HIP(hipGetLastError());
   }
 
@@ -1127,6 +1548,8 @@ lam_status score_topk_impl(lam_ctx* ctx, const ScoreView& st, const float* q, in
   a.sh = st.sh;
   a.row_words = (int64_t)D * b / 32;
   a.qhi = qhi;
+  a.q8 = q8;
+  a.coarse = coarse;
   a.meta = qmeta;
   a.nq = nq;
   a.nqt = nqt;
@@ -1137,17 +1560,8 @@ lam_status score_topk_impl(lam_ctx* ctx, const ScoreView& st, const float* q, in
   a.cand_cnt = cand_cnt;
   a.cap = cap;
   ExactArgs x{nq,    n,      cap,     k,         cand_cnt, cand_s, cand_r, qmeta, st.ids,  q,    st.step, st.codes,
-              a.row_words, D, scores, ids, bound, n_flag, flagged, done, 1};
+              a.row_words, D, scores, ids, bound, n_flag, flagged, done, bytes ? coarse : nullptr, 1};
 
-  if (dense) {
-    if (n > 0) {
-      ProfScope ps(ctx, "score_mfma", prof);
-      a.tile_end = ntiles;
-      LAM_TRY((launch_filter<1, kDense>(b, false, (int64_t)nqt * ntiles, ctx->stream, a)));
-    }
-    ProfScope ps(ctx, "score_merge", prof);
-    return launch_exact<1>(b, kSelectDense, ctx->stream, x);
-  }
   {  // 1. a k-th best score of the sample -> thresholds
     ProfScope ps(ctx, "score_sample", prof);
     a.tile_end = stiles;
@@ -1159,8 +1573,8 @@ lam_status score_topk_impl(lam_ctx* ctx, const ScoreView& st, const float* q, in
                          reinterpret_cast<uint32_t*>(part_s), ne);
     }
     LAM_TRY((launch_filter<1, kSample>(b, false, (int64_t)nqt * stiles, ctx->stream, a)));
-    hipLaunchKernelGGL(k_sample_thr, dim3((unsigned)((nq + 3) / 4)), dim3(256), 0, ctx->stream, nq, (int)entries,
-                       folded ? 1 : 0, k, part_s, qmeta, thr);
+    hipLaunchKernelGGL(k_sample_thr, dim3((unsigned)((nq + 3) / 4)), dim3(256), 0, ctx->stream, nq, n, (int)entries,
+                       folded ? 1 : 0, k, part_s, qmeta, thr, bytes ? coarse : nullptr);
     LAM_HIP(hipGetLastError());
   }
   {  // 2. full scan with the thresholds: 256 x 256 tiles when the launch holds
@@ -1171,16 +1585,18 @@ lam_status score_topk_impl(lam_ctx* ctx, const ScoreView& st, const float* q, in
     const bool large = (int64_t)nqtL * ntilesL >= kFilterLargeMinTiles;
     a.nqt = large ? nqtL : nqt;
     a.tile_end = large ? ntilesL : ntiles;
-    LAM_TRY((launch_filter<1, kFilter>(b, large, (int64_t)a.nqt * a.tile_end, ctx->stream, a)));
+    const int64_t grid = (int64_t)a.nqt * a.tile_end;
+    if (bytes) LAM_TRY((launch_filter<1, kFilterBytes>(b, large, grid, ctx->stream, a)));
+    else LAM_TRY((launch_filter<1, kFilter>(b, large, grid, ctx->stream, a)));
   }
   {  // 3. select and rescore
     ProfScope ps(ctx, "score_merge", prof);
-    LAM_TRY(launch_exact<1>(b, kSelect, ctx->stream, x));
+    LAM_TRY(launch_exact<1>(b, true, ctx->stream, x));
   }
   {  // 4. the exact pass over flagged queries (returns at once otherwise)
     ProfScope ps(ctx, "score_fallback", prof);
     x.splits = (int)std::min<int64_t>(kCandCap / k, (n + 255) / 256);
-    LAM_TRY(launch_exact<1>(b, kExactPass, ctx->stream, x));
+    LAM_TRY(launch_exact<1>(b, false, ctx->stream, x));
   }
   return LAM_OK;
 }
@@ -1188,12 +1604,13 @@ lam_status score_topk_impl(lam_ctx* ctx, const ScoreView& st, const float* q, in
 // ------------------------------------------------------------------ allocation-free scoring
 // Its scratch memory: one array per device, allocated with the code object,
 // held until the process ends.  Sized for kNoAllocMaxQ queries of up to 4,096
-// dimensions: the fp16 query parts (2 D bytes per query), the query meta block,
-// the sample's entries and the candidate buffer (kCandCap entries of 8 bytes,
-// 16 bytes of counts and flags) -- 72 KB per query, 18 MB at the limits.
+// dimensions: the query parts (3 D bytes per query, 4 D for a small store), the
+// query meta block, the sample's entries and the candidate buffer (kCandCap
+// entries of 8 bytes, 20 bytes of counts and flags) -- 80 KB per query, 20 MB
+// at the limits.
 constexpr size_t kNoAllocBytes = (size_t)32 << 20;
-static_assert((size_t)kNoAllocMaxQ * (2 * 4096 + sizeof(QMeta) + (size_t)kSampleTiles * kSampleEntries * 4 +
-                                      (size_t)kCandCap * 8 + 16) + 4 + 4 * 256 <= kNoAllocBytes,
+static_assert((size_t)kNoAllocMaxQ * (4 * 4096 + sizeof(QMeta) + (size_t)kSampleTiles * kSampleEntries * 4 +
+                                      (size_t)kCandCap * 8 + 20) + 64 + 5 * 256 <= kNoAllocBytes,
               "the workspace holds a call at the limits");
 
 }  // namespace

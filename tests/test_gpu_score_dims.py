@@ -76,3 +76,35 @@ def test_wide_codes_scan(lam, d, n, bits, absmax):
     keep = [j for j in range(q.shape[0]) if j != 5]
     c = qeps.codes(x, eps).reshape(n, -1)
     _compare(gs[keep], gi[keep], c, np.arange(n), q[keep], eps, 20)
+
+
+@pytest.mark.parametrize("kind", ["gaussian", "spiky", "concentrated"])
+@pytest.mark.parametrize("d,n,nq,bits,absmax", [
+    (96, 4225, 130, 3, None),      # a partly empty slab of bytes
+    (160, 9000, 257, 7, None),     # two groups of queries
+    (768, 33001, 2100, 8, None),   # the large tile
+    (128, 6000, 40, 10, 1.9),      # 10-bit storage of 8-bit codes
+])
+def test_byte_scan(lam, kind, d, n, nq, bits, absmax):
+    """Codes that fit 8 bits are scanned as bytes: Gaussian queries; queries
+    whose largest entry dominates (a wide error bound, in one group of 256
+    queries only); rows so close together that the bound covers many of them."""
+    rng = np.random.default_rng(bits)
+    if kind == "concentrated":
+        x = synth.members(rng, np.repeat(synth.unit_rows(rng, 1, d), n, axis=0), rng.uniform(0.97, 0.99, n))
+    else:
+        x = synth.unit_rows(rng, n, d)
+    x = x.astype(np.float32)
+    top = float(np.abs(x).max())
+    s = _store_from_rows(lam, x)
+    eps = absmax / 2.0 ** bits * 1.01 if absmax else top / (2 ** bits - 1.5) if bits < 8 else top / 250.0
+    p = s.quantize(eps, absmax=absmax)
+    assert p.bits == bits and top / (2 * eps) < 127
+    q = synth.members(rng, x[rng.choice(n, nq)].astype(np.float64), rng.uniform(0.5, 0.99, nq))
+    if kind == "spiky":
+        q[: nq // 2, rng.integers(0, d)] = 3.0
+    q = q.astype(np.float32)
+    gs, gi, _ = s.score_topk(_dev(q), 10)
+    c = qeps.codes(x, eps).reshape(n, -1)
+    pick = np.unique(np.concatenate([rng.choice(nq, min(nq, 60), replace=False), [0, nq - 1]]))
+    _compare(gs.cpu().numpy()[pick], gi.cpu().numpy()[pick], c, np.arange(n), q[pick], eps, 10, tol=3e-5)
