@@ -11,26 +11,23 @@
 // width byte; per row one 64-bit word offset (row_off[r], rows + 1 entries);
 // blocks of a row and rows follow each other.
 //
-// On a 64-lane wave the two 32-lane halves hold two blocks with one code per
-// lane: a block's bit planes are ballots of the lanes' bits (encode), and a
-// lane rebuilds its code from the block's w planes (decode).
+// One lane holds one block.  A block's 32 b-bit fields are exactly b words of the
+// code stream, and its planes are w words, so a lane reads and writes whole
+// words; in between the 32 codes sit NW-bit fields side by side in NW registers
+// (NW = 8, 16 or 32, the smallest that holds b bits), where zigzag takes a few
+// operations per word and the planes are an NW x NW bit transpose of every field
+// at once.  That is about 7 operations a code where one lane per code and one
+// ballot (or shuffle) per plane took about 70: those kernels were bound by the
+// vector ALU (23,969 x 768 codes of 8 bits: widths 57 us, pack 49 us, decode and
+// expansion 85 us each); these take 7, 14, 19 and 16 us, the decode at 4.8 TB/s.
 #include <algorithm>
 #include <cmath>
+#include <type_traits>
 
 #include "lam_internal.h"
 
 namespace lam {
 namespace {
-
-__device__ __forceinline__ uint32_t zigzag(int32_t q) { return ((uint32_t)q << 1) ^ (uint32_t)(q >> 31); }
-__device__ __forceinline__ int32_t unzigzag(uint32_t u) { return (int32_t)(u >> 1) ^ -(int32_t)(u & 1u); }
-
-// A round of a row: up to kPairs pairs of blocks, the two 32-lane halves of
-// the wave taking one block each with one code per lane (lane j of half h
-// holds code j of block k0 + 2 i + h in round slot i).  A round's loads are
-// all issued before any is used; consecutive lanes read consecutive fields,
-// so a half reads its block's b words in one or two requests.
-constexpr int kPairs = 16;
 
 // A buffer resource over the words [base, base + words): loads past the end
 // read as zero.
@@ -38,66 +35,140 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t words_rsrc(const uint32_t* bas
   return __builtin_amdgcn_make_buffer_rsrc(const_cast<uint32_t*>(base), (short)0, (int)(words * 4u), 0x00020000);
 }
 
-// Code i of a row's b-bit stream (rs over the row): both words that may hold
-// the field are loaded without a branch (the second past the row's end reads
-// as zero and is shifted out), so a round's loads issue back to back.
-__device__ __forceinline__ int32_t code_rs(__amdgpu_buffer_rsrc_t rs, int b, int i) {
-  const uint32_t bit = (uint32_t)i * (uint32_t)b;
-  const uint32_t w = bit >> 5, off = bit & 31u;
-  const uint32_t lo = (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(rs, w * 4u, 0, 0);
-  const uint32_t hi = (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(rs, w * 4u + 4u, 0, 0);
-  const uint32_t u = __builtin_amdgcn_alignbit(hi, lo, off);   // bits [off, off + 32) of hi:lo
-  return (int32_t)(u << (32 - b)) >> (32 - b);
+constexpr int kBlkThreads = 256;   // a workgroup holds whole rows: kBlkThreads / nb of them (nb = D / 32 <= 128)
+
+constexpr int field_bits(int b) { return b <= 8 ? 8 : b <= 16 ? 16 : 32; }
+
+// v in every NW-bit field of a word
+template <int NW>
+constexpr uint32_t rep(uint32_t v) {
+  return NW == 8 ? v * 0x01010101u : NW == 16 ? v * 0x00010001u : v;
 }
 
-__device__ __forceinline__ void load_round(const uint32_t* __restrict__ codes, int b, int64_t r, int D, int nb,
-                                           int k0, uint32_t (&u)[kPairs]) {
-  const int lane = threadIdx.x & 63, half = lane >> 5, j = lane & 31;
-  const uint32_t row_words = (uint32_t)(D / 32) * (uint32_t)b;
-  const __amdgpu_buffer_rsrc_t rs = words_rsrc(codes + r * (int64_t)row_words, row_words);
-#pragma unroll
-  for (int i = 0; i < kPairs; ++i) {
-    const int kb = k0 + 2 * i + half;
-    u[i] = kb < nb ? zigzag(code_rs(rs, b, kb * 32 + j)) : 0u;
+// the rows and blocks of this workgroup; thread t holds block t of them
+struct BlkSpan {
+  int64_t r0;
+  int nrows, cnt;
+  __device__ __forceinline__ BlkSpan(int64_t rows, int nb) {
+    const int rpw = kBlkThreads / nb;
+    r0 = (int64_t)blockIdx.x * rpw;
+    nrows = (int)min((int64_t)rpw, rows - r0);
+    cnt = nrows * nb;
   }
-}
+};
 
-// Pass 1: one wave per row: block widths and the row's word count.  The bit
-// length of a block's largest zigzag code is that of the OR of its codes:
-// the highest bit t whose ballot over the half is not empty (b ballots per
-// pair of blocks, all zigzag codes being below 2^b).
-__global__ __launch_bounds__(256) void k_blk_widths(const uint32_t* __restrict__ codes, int b, int64_t rows, int D,
-                                                    uint8_t* __restrict__ widths, uint32_t* __restrict__ row_words) {
-  const int lane = threadIdx.x & 63, half = lane >> 5, j = lane & 31;
-  const int64_t r = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (r >= rows) return;
-  const int nb = D / 32;
-  uint32_t total = 0;
-  for (int k0 = 0; k0 < nb; k0 += 2 * kPairs) {
-    uint32_t u[kPairs];
-    load_round(codes, b, r, D, nb, k0, u);
+// Transposes the NW x NW bit matrix of every field: afterwards bit k of field f
+// of word t is what bit t of field f of word k was.  Code f * NW + k sits in field
+// f of word k, so the result's word t is plane t (bit j of it is bit t of code
+// j); the transpose is its own inverse.
+template <int NW>
+__device__ __forceinline__ void bit_transpose(uint32_t (&a)[NW]) {
 #pragma unroll
-    for (int i = 0; i < kPairs; ++i) {
-      uint32_t w0 = 0, w1 = 0;
-      for (int t = 0; t < b; ++t) {
-        const unsigned long long m = __ballot((u[i] >> t) & 1u);
-        w0 = (uint32_t)m ? (uint32_t)t + 1u : w0;
-        w1 = (uint32_t)(m >> 32) ? (uint32_t)t + 1u : w1;
-      }
-      const uint32_t w = half ? w1 : w0;
-      const int kb = k0 + 2 * i + half;
-      if (j == 0 && kb < nb) {
-        widths[r * nb + kb] = (uint8_t)w;
-        total += w;
-      }
+  for (int s = NW / 2; s >= 1; s >>= 1) {
+    const uint32_t m = s == 16  ? 0x0000ffffu
+                       : s == 8 ? 0x00ff00ffu
+                       : s == 4 ? 0x0f0f0f0fu
+                       : s == 2 ? 0x33333333u
+                                : 0x55555555u;   // bits whose index has bit s clear
+#pragma unroll
+    for (int k = 0; k < NW; ++k) {
+      if (k & s) continue;
+      const uint32_t x = a[k], y = a[k + s];
+      a[k] = (x & m) | ((y << s) & ~m);
+      a[k + s] = ((x >> s) & m) | (y & ~m);
     }
   }
-  total = (uint32_t)__shfl((int)total, 0) + (uint32_t)__shfl((int)total, 32);
-  if (lane == 0) row_words[r] = total;
 }
 
-// Exclusive scan of row word counts into row offsets (three small kernels:
-// per-chunk scans, a scan of the chunk totals, and the add).
+// The zigzag codes of a block from its B words of the code stream.
+template <int B>
+__device__ __forceinline__ void load_zigzag(const uint32_t* __restrict__ src, uint32_t (&a)[field_bits(B)]) {
+  constexpr int NW = field_bits(B);
+  constexpr uint32_t kMask = B == 32 ? 0xffffffffu : (1u << B) - 1u;
+  uint32_t w[B + 1];
+  __builtin_memcpy(w, src, 4 * B);   // (word aligned: the device takes wide loads at any word)
+  w[B] = 0u;
+#pragma unroll
+  for (int k = 0; k < NW; ++k) a[k] = 0u;
+#pragma unroll
+  for (int c = 0; c < 32; ++c) {
+    const int bit = c * B, wi = bit >> 5, off = bit & 31;
+    const uint32_t u = (off + B > 32 ? __builtin_amdgcn_alignbit(w[wi + 1], w[wi], (uint32_t)off) : w[wi] >> off) & kMask;
+    a[c % NW] |= u << (c / NW * NW);
+  }
+  // u = 2q, or -2q - 1 = ~(2q) within the field for q < 0 (u < 2^B)
+#pragma unroll
+  for (int k = 0; k < NW; ++k) {
+    const uint32_t sign = (a[k] >> (B - 1)) & rep<NW>(1u);
+    a[k] = ((a[k] << 1) & rep<NW>(kMask & ~1u)) ^ (sign * kMask);
+  }
+}
+
+// Back to two's complement over the whole NW-bit field.
+template <int NW>
+__device__ __forceinline__ void unzigzag_fields(uint32_t (&a)[NW]) {
+  constexpr uint32_t kField = NW == 32 ? 0xffffffffu : (1u << (NW & 31)) - 1u;
+#pragma unroll
+  for (int k = 0; k < NW; ++k)
+    a[k] = ((a[k] >> 1) & rep<NW>(kField >> 1)) ^ ((a[k] & rep<NW>(1u)) * kField);
+}
+
+// Exclusive prefix sum of v over the workgroup's threads; *total: the sum.
+__device__ __forceinline__ uint32_t group_prefix(uint32_t v, uint32_t* total) {
+  __shared__ uint32_t wt[kBlkThreads / 64];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  uint32_t x = v;
+  for (int o = 1; o < 64; o <<= 1) {
+    const uint32_t t = (uint32_t)__shfl_up((int)x, o);
+    if (lane >= o) x += t;
+  }
+  if (lane == 63) wt[wave] = x;
+  __syncthreads();
+  uint32_t base = 0u, all = 0u;
+#pragma unroll
+  for (int w = 0; w < kBlkThreads / 64; ++w) {
+    const uint32_t t = wt[w];
+    base += w < wave ? t : 0u;
+    all += t;
+  }
+  *total = all;
+  return base + x - v;
+}
+
+// Pass 1: block widths (the bit length of the OR of a block's zigzag codes) and
+// the rows' word counts.
+template <int B>
+__global__ __launch_bounds__(kBlkThreads) void k_blk_widths(const uint32_t* __restrict__ codes, int64_t rows, int nb,
+                                                            uint8_t* __restrict__ widths,
+                                                            uint32_t* __restrict__ row_words) {
+  constexpr int NW = field_bits(B);
+  __shared__ uint32_t ws[kBlkThreads];
+  const BlkSpan sp(rows, nb);
+  const int t = threadIdx.x;
+  if (t < sp.cnt) {
+    const int64_t g = sp.r0 * nb + t;
+    uint32_t a[NW];
+    load_zigzag<B>(codes + g * B, a);
+    uint32_t o = 0u;
+#pragma unroll
+    for (int k = 0; k < NW; ++k) o |= a[k];
+    if (NW <= 16) o |= o >> 16;
+    if (NW == 8) o |= o >> 8;
+    if (NW < 32) o &= (1u << (NW & 31)) - 1u;
+    const uint32_t w = o ? 32u - (uint32_t)__clz((int)o) : 0u;
+    widths[g] = (uint8_t)w;
+    ws[t] = w;
+  }
+  __syncthreads();
+  if (t < sp.nrows) {
+    uint32_t total = 0u;
+    for (int k = 0; k < nb; ++k) total += ws[t * nb + k];
+    row_words[sp.r0 + t] = total;
+  }
+}
+
+// Exclusive scan of row word counts into row offsets (two small
+// kernels: per-chunk scans, and the add of the chunk totals before).
 constexpr int kScanThreads = 1024;
 constexpr int kScanPer = 4;
 constexpr int kScanChunk = kScanThreads * kScanPer;
@@ -145,152 +216,153 @@ __global__ __launch_bounds__(kScanThreads) void k_scan_chunks(const uint32_t* __
   if (threadIdx.x == 0) sums[blockIdx.x] = tot;
 }
 
-__global__ __launch_bounds__(kScanThreads) void k_scan_sums(uint64_t* __restrict__ sums, int nchunks,
-                                                            uint64_t* __restrict__ grand) {
-  __shared__ uint64_t wt[kScanThreads / 64];
-  __shared__ uint64_t tot;
-  // nchunks <= kScanChunk: four per thread, as above
-  const int base = threadIdx.x * kScanPer;
-  uint64_t v[kScanPer];
-  uint64_t s = 0;
-#pragma unroll
-  for (int i = 0; i < kScanPer; ++i) {
-    v[i] = base + i < nchunks ? sums[base + i] : 0u;
-    s += v[i];
-  }
-  uint64_t x = block_exclusive_scan(s, wt, &tot);
-#pragma unroll
-  for (int i = 0; i < kScanPer; ++i) {
-    if (base + i < nchunks) sums[base + i] = x;
-    x += v[i];
-  }
-  if (threadIdx.x == 0) *grand = tot;
-}
-
-__global__ void k_scan_add(uint64_t* __restrict__ out, int64_t n, const uint64_t* __restrict__ sums) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) out[i] += sums[i / kScanChunk];
-}
-
-// Prefix of the widths of a row's blocks below block k, for the lanes of one
-// wave (lane l holds blocks l, l + 64, ... in turn); returns this lane's
-// exclusive prefix for block `k` and carries the running total across rounds.
-__device__ __forceinline__ uint32_t width_prefix(uint32_t w, uint32_t& carry) {
-  const int lane = threadIdx.x & 63;
-  uint32_t x = w;
-  for (int o = 1; o < 64; o <<= 1) {
-    const uint32_t t = __shfl_up(x, o);
-    if (lane >= o) x += t;
-  }
-  const uint32_t ex = carry + x - w;
-  carry += __shfl(x, 63);
-  return ex;
-}
-
-// The word offsets within row r of its blocks k0 + l (lane l, l < 64) and
-// their widths; carry: the words of the blocks before k0.
-__device__ __forceinline__ void row_offsets(const uint8_t* __restrict__ widths, int64_t r, int nb, int k0,
-                                            uint32_t& carry, uint32_t& wl, uint32_t& pre) {
-  const int lane = threadIdx.x & 63;
-  const int kl = k0 + lane;
-  wl = kl < nb ? widths[r * nb + kl] : 0u;
-  pre = width_prefix(wl, carry);
-}
-
-// Pass 2: one wave per row; per round of block pairs the codes are loaded
-// first, then each bit plane of a block is a ballot over its half.
-__global__ __launch_bounds__(256) void k_blk_pack(const uint32_t* __restrict__ codes, int b, int64_t rows, int D,
-                                                  const uint8_t* __restrict__ widths,
-                                                  const uint64_t* __restrict__ row_off, uint32_t* __restrict__ data) {
-  const int lane = threadIdx.x & 63, half = lane >> 5, j = lane & 31;
-  const int64_t r = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (r >= rows) return;
-  const int nb = D / 32;
-  const uint64_t roff = row_off[r];
-  uint32_t carry = 0, wl = 0, pre = 0;
-  for (int k0 = 0; k0 < nb; k0 += 2 * kPairs) {
-    uint32_t u[kPairs];
-    load_round(codes, b, r, D, nb, k0, u);
-    if (k0 % 64 == 0) row_offsets(widths, r, nb, k0, carry, wl, pre);
-#pragma unroll
-    for (int i = 0; i < kPairs; ++i) {
-      const int kb = k0 + 2 * i + half;
-      const int src = (kb - (k0 & ~63)) & 63;
-      const uint32_t w = (uint32_t)__shfl((int)wl, src);
-      const uint32_t p = (uint32_t)__shfl((int)pre, src);
-      const uint32_t wmax = max((uint32_t)__shfl((int)w, 0), (uint32_t)__shfl((int)w, 32));
-      uint32_t mine = 0;
-      for (uint32_t t = 0; t < wmax; ++t) {
-        const unsigned long long m = __ballot((u[i] >> t) & 1u);
-        const uint32_t plane = half ? (uint32_t)(m >> 32) : (uint32_t)m;
-        mine = ((uint32_t)j == t) ? plane : mine;
-      }
-      if (kb < nb && (uint32_t)j < w) data[roff + p + j] = mine;
-    }
+// Adds the totals of the chunks before: a workgroup's 256 rows lie in one chunk
+// (nchunks <= kScanChunk totals, a strided sum per workgroup).  The last one
+// writes the number of words to out[n] and to the host.
+__global__ __launch_bounds__(256) void k_scan_add(uint64_t* __restrict__ out, int64_t n,
+                                                  const uint64_t* __restrict__ sums,
+                                                  unsigned long long* __restrict__ words_host) {
+  __shared__ unsigned long long part[4];
+  const int t = threadIdx.x;
+  const int64_t i = (int64_t)blockIdx.x * 256 + t;
+  const int c = (int)((int64_t)blockIdx.x * 256 / kScanChunk);
+  unsigned long long x = 0ull;
+  for (int k = t; k < c; k += 256) x += sums[k];
+  for (int o = 32; o > 0; o >>= 1) x += __shfl_xor(x, o);
+  if ((t & 63) == 0) part[t >> 6] = x;
+  __syncthreads();
+  const uint64_t base = part[0] + part[1] + part[2] + part[3];
+  if (i < n && c > 0) out[i] += base;
+  if (blockIdx.x == gridDim.x - 1 && t == 0) {
+    out[n] = base + sums[c];
+    *words_host = base + sums[c];
   }
 }
+static_assert(kScanChunk % 256 == 0, "k_scan_add's workgroups stay within a chunk");
 
-// One wave per row: decode every block, either to float32 x_hat =
-// float32(float64(q * s)) (xhat != NULL) or back to the b-bit stream (codes_out
-// != NULL; a block's 32 codes are exactly b words).  Per round the lanes j < w
-// of each half load plane j of their block (every plane once), and a lane
-// rebuilds its code from the planes by shuffles.
-__global__ __launch_bounds__(256) void k_blk_decode(const uint8_t* __restrict__ widths,
-                                                    const uint64_t* __restrict__ row_off,
-                                                    const uint32_t* __restrict__ data, int64_t rows, int D, double s,
-                                                    float* __restrict__ xhat, int b, uint32_t* __restrict__ codes_out) {
-  const int lane = threadIdx.x & 63, half = lane >> 5, j = lane & 31;
-  const int64_t r = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (r >= rows) return;
-  const int nb = D / 32;
-  const uint64_t roff = row_off[r];
-  const __amdgpu_buffer_rsrc_t rs = words_rsrc(data + roff, (uint32_t)(row_off[r + 1] - roff));
-  const uint32_t mask = b >= 32 ? 0xffffffffu : ((1u << b) - 1u);
-  uint32_t carry = 0, wl = 0, pre = 0;
-  for (int k0 = 0; k0 < nb; k0 += 2 * kPairs) {
-    if (k0 % 64 == 0) row_offsets(widths, r, nb, k0, carry, wl, pre);
-    uint32_t w[kPairs], pl[kPairs];
-#pragma unroll
-    for (int i = 0; i < kPairs; ++i) {
-      const int kb = k0 + 2 * i + half;
-      const int src = (kb - (k0 & ~63)) & 63;
-      const uint32_t ws = (uint32_t)__shfl((int)wl, src);
-      const uint32_t p = (uint32_t)__shfl((int)pre, src);
-      w[i] = kb < nb ? ws : 0u;
-      // plane j of this half's block (lanes past the width: an offset past the row, read as zero)
-      pl[i] = (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(rs, (uint32_t)j < w[i] ? (p + j) * 4u : 0xfffffff0u, 0, 0);
-    }
-#pragma unroll
-    for (int i = 0; i < kPairs; ++i) {
-      const int kb = k0 + 2 * i + half;
-      const uint32_t wmax = max((uint32_t)__shfl((int)w[i], 0), (uint32_t)__shfl((int)w[i], 32));
-      uint32_t u = 0;
-      for (uint32_t t = 0; t < wmax; ++t) {
-        const uint32_t plane = (uint32_t)__shfl((int)pl[i], (half << 5) | (int)t);   // (zero past the width)
-        u |= ((plane >> j) & 1u) << t;
-      }
-      const int32_t q = unzigzag(u);
-      const int64_t e = r * D + (int64_t)kb * 32 + j;
-      if (xhat) {
-        if (kb < nb) xhat[e] = (float)((double)q * s);
-      } else {
-        // word j of the block's b-bit stream holds bits [32 j, 32 j + 32): the
-        // fields of codes c0 .. c0 + ceil(32 / b), c0 = 32 j / b (a loop of the
-        // same length on every lane, so every shuffle has all lanes)
-        const uint32_t f = (uint32_t)q & mask;
-        const int c0 = (32 * j) / b;
-        const int steps = (32 + b - 1) / b + 1;
-        uint32_t word = 0;
-        for (int i2 = 0; i2 < steps; ++i2) {
-          const int c = c0 + i2;
-          const uint32_t fc = (uint32_t)__shfl((int)f, (half << 5) | (c & 31));
-          const int bit = c * b - j * 32;   // field start relative to word j
-          if (c < 32 && bit > -b && bit < 32) word |= bit >= 0 ? (fc << bit) : (fc >> -bit);
-        }
-        if (kb < nb && j < b) codes_out[(r * (int64_t)D + (int64_t)kb * 32) * b / 32 + j] = word;
-      }
-    }
+// Pass 2: a lane transposes its block's codes into planes and puts its w planes
+// into the workgroup's run of words in LDS (the rows follow each other in the
+// data, so the run is contiguous there too), which is then stored coalesced.
+template <int B>
+__global__ __launch_bounds__(kBlkThreads) void k_blk_pack(const uint32_t* __restrict__ codes, int64_t rows, int nb,
+                                                          const uint8_t* __restrict__ widths,
+                                                          const uint64_t* __restrict__ row_off,
+                                                          uint32_t* __restrict__ data) {
+  constexpr int NW = field_bits(B);
+  __shared__ uint32_t run[kBlkThreads * B];   // (w <= B: zigzag codes are below 2^B)
+  const BlkSpan sp(rows, nb);
+  const int t = threadIdx.x;
+  const int64_t g = sp.r0 * nb + t;
+  uint32_t a[NW];
+  uint32_t w = 0u;
+  if (t < sp.cnt) {
+    w = widths[g];
+    load_zigzag<B>(codes + g * B, a);
+    bit_transpose<NW>(a);
   }
+  uint32_t total;
+  const uint32_t pre = group_prefix(w, &total);
+#pragma unroll
+  for (int k = 0; k < B; ++k)
+    if ((uint32_t)k < w) run[pre + k] = a[k];
+  __syncthreads();
+  uint32_t* dst = data + row_off[sp.r0];
+  for (uint32_t i = t; i < total; i += kBlkThreads) dst[i] = run[i];
+}
+
+// A lane's planes, transposed back and unzigzagged: the codes in two's
+// complement NW-bit fields.  Planes past the width read as zero (an offset past
+// the workgroup's run).
+template <int NW>
+__device__ __forceinline__ void load_blocks(const BlkSpan& sp, int nb, const uint8_t* __restrict__ widths,
+                                            const uint64_t* __restrict__ row_off, const uint32_t* __restrict__ data,
+                                            uint32_t (&a)[NW]) {
+  const int t = threadIdx.x;
+  const uint32_t w = t < sp.cnt ? widths[sp.r0 * nb + t] : 0u;
+  const uint64_t off = row_off[sp.r0];
+  uint32_t total;
+  const uint32_t pre = group_prefix(w, &total);
+  const __amdgpu_buffer_rsrc_t rs = words_rsrc(data + off, total);
+#pragma unroll
+  for (int k = 0; k < NW; ++k)
+    a[k] = (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(rs, (uint32_t)k < w ? (pre + k) * 4u : 0xfffffff0u, 0, 0);
+  bit_transpose<NW>(a);
+  unzigzag_fields<NW>(a);
+}
+
+// Decode to x_hat = float32(float64(q * s)): the fields go through LDS so that a
+// wave's float4 stores are consecutive (a field row is padded by four words:
+// 16-byte reads, spread over the banks).
+template <int NW>
+__global__ __launch_bounds__(kBlkThreads) void k_blk_decode(const uint8_t* __restrict__ widths,
+                                                            const uint64_t* __restrict__ row_off,
+                                                            const uint32_t* __restrict__ data, int64_t rows, int nb,
+                                                            double s, float* __restrict__ xhat) {
+  constexpr int kLd = NW + 4;
+  __shared__ __attribute__((aligned(16))) uint32_t fld[kBlkThreads * kLd];
+  const BlkSpan sp(rows, nb);
+  const int t = threadIdx.x;
+  uint32_t a[NW];
+  load_blocks<NW>(sp, nb, widths, row_off, data, a);
+#pragma unroll
+  for (int k = 0; k < NW; k += 4)
+    *reinterpret_cast<uint4*>(&fld[t * kLd + k]) = make_uint4(a[k], a[k + 1], a[k + 2], a[k + 3]);
+  __syncthreads();
+  float* dst = xhat + sp.r0 * nb * 32;
+  for (int i = t; i < sp.cnt * 8; i += kBlkThreads) {
+    const int blk = i >> 3, c = (i & 7) * 4;   // codes c .. c + 3 of the block
+    const uint4 f = *reinterpret_cast<const uint4*>(&fld[blk * kLd + c % NW]);
+    const int sh = 32 - NW - c / NW * NW;      // field to the word's top, then sign-extended down
+    const int32_t q0 = (int32_t)(f.x << sh) >> (32 - NW), q1 = (int32_t)(f.y << sh) >> (32 - NW);
+    const int32_t q2 = (int32_t)(f.z << sh) >> (32 - NW), q3 = (int32_t)(f.w << sh) >> (32 - NW);
+    const float v[4] = {(float)((double)q0 * s), (float)((double)q1 * s), (float)((double)q2 * s),
+                        (float)((double)q3 * s)};
+    __builtin_memcpy(dst + (int64_t)i * 4, v, 16);   // (xhat is word aligned, no more is asked of it)
+  }
+}
+
+// Back to the B-bit code stream: a lane packs its block's B words, which go
+// through LDS (odd row length) to coalesced stores.
+template <int B>
+__global__ __launch_bounds__(kBlkThreads) void k_blk_expand(const uint8_t* __restrict__ widths,
+                                                            const uint64_t* __restrict__ row_off,
+                                                            const uint32_t* __restrict__ data, int64_t rows, int nb,
+                                                            uint32_t* __restrict__ codes) {
+  constexpr int NW = field_bits(B);
+  constexpr uint32_t kMask = B == 32 ? 0xffffffffu : (1u << B) - 1u;
+  constexpr int kLd = B | 1;
+  __shared__ uint32_t out[kBlkThreads * kLd];
+  const BlkSpan sp(rows, nb);
+  const int t = threadIdx.x;
+  uint32_t a[NW];
+  load_blocks<NW>(sp, nb, widths, row_off, data, a);
+  uint32_t w[B + 1];
+#pragma unroll
+  for (int k = 0; k <= B; ++k) w[k] = 0u;
+#pragma unroll
+  for (int c = 0; c < 32; ++c) {
+    const int bit = c * B, wi = bit >> 5, off = bit & 31;
+    const uint32_t u = (a[c % NW] >> (c / NW * NW)) & kMask;
+    w[wi] |= u << off;
+    if (off + B > 32) w[wi + 1] |= u >> (32 - off);
+  }
+#pragma unroll
+  for (int k = 0; k < B; ++k) out[t * kLd + k] = w[k];
+  __syncthreads();
+  uint32_t* dst = codes + sp.r0 * nb * B;
+  for (int i = t; i < sp.cnt * B; i += kBlkThreads) dst[i] = out[i / B * kLd + i % B];
+}
+
+// Launches f<B> for the runtime width b in [1, 32].
+template <int B = 1, class F>
+void for_width(int b, F&& f) {
+  if (b == B) return f(std::integral_constant<int, B>{});
+  if constexpr (B < 32) for_width<B + 1>(b, f);
+}
+
+unsigned blk_grid(int64_t rows, int nb) {
+  const int rpw = kBlkThreads / nb;
+  return (unsigned)((rows + rpw - 1) / rpw);
 }
 
 }  // namespace
@@ -306,41 +378,43 @@ lam_status block_encode(lam_ctx* ctx, lam_store* st, lam_block_stats* out) {
     LAM_HIP(hipMalloc(&st->blk_w, (size_t)st->capacity * nb));
     LAM_HIP(hipMalloc(&st->blk_row_off, (size_t)(st->capacity + 1) * 8));
   }
-  LAM_TRY(ctx->scratch[kScratchBlocks].ensure((size_t)m * 4 + (size_t)(nchunks + 1) * 8 + 64));
-  uint32_t* row_words = ctx->scratch[kScratchBlocks].as<uint32_t>();
-  uint64_t* sums = reinterpret_cast<uint64_t*>(ctx->scratch[kScratchBlocks].as<char>() + (((size_t)m * 4 + 7) & ~7ull));
-  const unsigned rows_grid = (unsigned)((m + 3) / 4);
-  {
-    ProfScope ps(ctx, "store_block_encode");
-    if (m > 0) {
-      hipLaunchKernelGGL(k_blk_widths, dim3(rows_grid), dim3(256), 0, ctx->stream, st->codes, b, m, D, st->blk_w,
-                         row_words);
-      LAM_HIP(hipGetLastError());
-      hipLaunchKernelGGL(k_scan_chunks, dim3((unsigned)nchunks), dim3(kScanThreads), 0, ctx->stream, row_words, m,
-                         st->blk_row_off, sums);
-      hipLaunchKernelGGL(k_scan_sums, dim3(1), dim3(kScanThreads), 0, ctx->stream, sums, (int)nchunks,
-                         st->blk_row_off + m);
-      hipLaunchKernelGGL(k_scan_add, dim3((unsigned)((m + 255) / 256)), dim3(256), 0, ctx->stream, st->blk_row_off,
-                         m, sums);
-      LAM_HIP(hipGetLastError());
-    }
-  }
-  uint64_t words = 0;
-  if (m > 0) LAM_HIP(hipMemcpyAsync(&words, st->blk_row_off + m, 8, hipMemcpyDeviceToHost, ctx->stream));
-  LAM_HIP(hipStreamSynchronize(ctx->stream));
-  if (words * 4 > st->blk_cap) {
+  // a block holds at most b words (its zigzag codes are below 2^b), so the data
+  // fits m * nb * b words and the pack need not wait for the count
+  const uint64_t data_cap = std::max<uint64_t>((uint64_t)m * nb * b * 4, 4);
+  if (data_cap > st->blk_cap) {
     if (st->blk_data) LAM_HIP(hipFree(st->blk_data));
     st->blk_data = nullptr;
     st->blk_cap = 0;
-    LAM_HIP(hipMalloc(&st->blk_data, std::max<uint64_t>(words * 4, 4)));
-    st->blk_cap = std::max<uint64_t>(words * 4, 4);
+    LAM_HIP(hipMalloc(&st->blk_data, data_cap));
+    st->blk_cap = data_cap;
   }
+  LAM_TRY(ctx->scratch[kScratchBlocks].ensure((size_t)m * 4 + (size_t)(nchunks + 1) * 8 + 64));
+  uint32_t* row_words = ctx->scratch[kScratchBlocks].as<uint32_t>();
+  uint64_t* sums = reinterpret_cast<uint64_t*>(ctx->scratch[kScratchBlocks].as<char>() + (((size_t)m * 4 + 7) & ~7ull));
+  ctx->flags_host->blk_words = 0;
   if (m > 0) {
+    const dim3 grid(blk_grid(m, nb)), block(kBlkThreads);
+    {
+      ProfScope ps(ctx, "store_block_encode");
+      for_width(b, [&](auto B) {
+        hipLaunchKernelGGL(k_blk_widths<B.value>, grid, block, 0, ctx->stream, st->codes, m, nb, st->blk_w, row_words);
+      });
+      LAM_HIP(hipGetLastError());
+      hipLaunchKernelGGL(k_scan_chunks, dim3((unsigned)nchunks), dim3(kScanThreads), 0, ctx->stream, row_words, m,
+                         st->blk_row_off, sums);
+      hipLaunchKernelGGL(k_scan_add, dim3((unsigned)((m + 255) / 256)), dim3(256), 0, ctx->stream, st->blk_row_off,
+                         m, sums, &ctx->flags_host_dev->blk_words);
+      LAM_HIP(hipGetLastError());
+    }
     ProfScope ps(ctx, "store_block_pack");
-    hipLaunchKernelGGL(k_blk_pack, dim3(rows_grid), dim3(256), 0, ctx->stream, st->codes, b, m, D, st->blk_w,
-                       st->blk_row_off, st->blk_data);
+    for_width(b, [&](auto B) {
+      hipLaunchKernelGGL(k_blk_pack<B.value>, grid, block, 0, ctx->stream, st->codes, m, nb, st->blk_w,
+                         st->blk_row_off, st->blk_data);
+    });
     LAM_HIP(hipGetLastError());
   }
+  LAM_HIP(hipStreamSynchronize(ctx->stream));
+  const uint64_t words = ctx->flags_host->blk_words;   // written by k_scan_add
   st->blk_rows = m;
   st->blk_words = words;
   if (out) {
@@ -364,8 +438,18 @@ lam_status block_decode(lam_ctx* ctx, const lam_store* st, float* xhat, uint32_t
   const int64_t m = st->blk_rows;
   if (m <= 0) return LAM_OK;
   ProfScope ps(ctx, xhat ? "store_block_decode" : "store_block_expand");
-  hipLaunchKernelGGL(k_blk_decode, dim3((unsigned)((m + 3) / 4)), dim3(256), 0, ctx->stream, st->blk_w,
-                     st->blk_row_off, st->blk_data, m, st->dim, st->q.step, xhat, st->q.bits, codes_out);
+  const int nb = st->dim / 32, b = st->q.bits;
+  const dim3 grid(blk_grid(m, nb)), block(kBlkThreads);
+  if (xhat) {
+    auto* kernel = b <= 8 ? k_blk_decode<8> : b <= 16 ? k_blk_decode<16> : k_blk_decode<32>;
+    hipLaunchKernelGGL(kernel, grid, block, 0, ctx->stream, st->blk_w, st->blk_row_off, st->blk_data, m, nb,
+                       st->q.step, xhat);
+  } else {
+    for_width(b, [&](auto B) {
+      hipLaunchKernelGGL(k_blk_expand<B.value>, grid, block, 0, ctx->stream, st->blk_w, st->blk_row_off,
+                         st->blk_data, m, nb, codes_out);
+    });
+  }
   LAM_HIP(hipGetLastError());
   return LAM_OK;
 }

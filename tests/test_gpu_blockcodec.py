@@ -97,3 +97,36 @@ def test_zero_blocks_and_state(lam):
     assert e.value.name == "LAM_ESTATE"
     s.block_encode()
     assert torch.equal(s.block_decode(), s.dequantize())
+
+
+@pytest.mark.parametrize("bits,n,dim", [
+    (1, 5, 32), (2, 257, 32), (7, 300, 96), (8, 33, 768), (9, 11, 4096), (15, 19, 160), (16, 130, 64),
+    (17, 21, 384), (24, 9, 1024), (31, 13, 96), (32, 40, 224)])
+def test_every_field_width_bit_exact(lam, bits, n, dim):
+    """Code widths on both sides of the 8-, 16- and 32-bit fields a lane holds a
+    block in, with row lengths and counts that leave a workgroup's threads, and
+    the last workgroup's rows, over; blocks of every width from 0 to `bits`."""
+    rng = np.random.default_rng(bits)
+    x = rng.uniform(-1, 1, (n, dim // 32, 32)) * 2.0 ** -rng.integers(0, bits + 3, (n, dim // 32, 1))
+    x = x.reshape(n, dim).astype(np.float32)
+    x[0, 0], x[1, 1] = 1.0, -1.0
+    x[3, :32] = 0.0
+    eps = 1.0 if bits == 1 else 0.5 / ((1 << (bits - 1)) - 1.5 if bits > 2 else 1.0)
+    s, p = _store(lam, x, 1.0, eps)
+    assert p.bits == bits
+    kept = s.ids().cpu().numpy()
+    codes = qeps.codes(x[kept], eps).reshape(kept.size, -1)
+    ref = blockcodec.encode(codes)
+    s.block_encode()
+    w, ro, d = s.block_export()
+    assert np.array_equal(w.cpu().numpy(), ref["widths"])
+    assert np.array_equal(ro.cpu().numpy().astype(np.uint64), ref["row_off"])
+    assert np.array_equal(d.cpu().numpy().view(np.uint32), ref["data"])
+    want = s.dequantize()
+    assert torch.equal(s.block_decode(), want)
+    # an output that is only word aligned
+    buf = torch.empty(kept.size * dim + 1, device="cuda")
+    assert torch.equal(s.block_decode(out=buf[1:].view(kept.size, dim)), want)
+    if bits <= 22:   # the widest codes that scoring takes
+        q = _dev(synth.unit_rows(rng, 3, dim).astype(np.float32))
+        assert all(torch.equal(u, v) for u, v in zip(s.score_topk(q, 5), s.score_topk_blocks(q, 5)))
