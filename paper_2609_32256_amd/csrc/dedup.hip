@@ -33,8 +33,7 @@
 //                binary64 feeds the measured bound delta_hat.
 // The resolve and the append are one launch (k_resolve_append): each
 // workgroup resolves the chunk's rows up to its own last one in its LDS and
-// appends its 16 rows.  The banded store keeps them apart (k_resolve,
-// k_lsh_insert, k_append), since its index insertion sits between them.
+// appends its 16 rows (a banded store's also join its index there).
 //
 // Error bound of the screen (dot-product units), for rows a, b:
 //   |c16 - a.b| <= K1 (||a||^2 + ||b||^2)/2 + K2 (||a||_1 + ||b||_1) + K3
@@ -525,6 +524,7 @@ __device__ bool pair_within(const float* pa, const float* pb, int D, double d2, 
   static_assert(G == 16 || G == 32 || G == 64, "a group is a power of two within one wave");
   const int gl = (int)threadIdx.x & (G - 1);
   double s = 0.0;
+#pragma unroll 4
   for (int d = gl * 4; d < D; d += 4 * G) {
     const float4 u = *reinterpret_cast<const float4*>(pa + d);
     const float4 v = *reinterpret_cast<const float4*>(pb + d);
@@ -570,9 +570,10 @@ __device__ bool pair_within(const float* pa, const float* pb, int D, double d2, 
 // Algorithm "admit" with a band index (Section 2.2, L1): the codes of a row at
 // the band step are cut into bands of r coordinates; a retained row is a
 // candidate of an arrival when some band holds equal codes in both.  A 64-bit
-// key of (band, codes) finds equal bands through open-addressing indexes (one
-// over the retained rows, one over the chunk); the codes themselves are
-// compared before a pair counts, so key collisions never make candidates.
+// key of (band, codes) finds equal bands through an open-addressing index over
+// the retained rows and, for the chunk, a table per band in LDS; the codes
+// themselves are compared before a pair counts, so key collisions never make
+// candidates.
 //
 // One workgroup per arrival collects its distinct candidates in an LDS set,
 // then decides them with the merge predicate: retained rows first, where the
@@ -605,19 +606,16 @@ struct LshArgs {
   int r, nb;                  // band width, bands per row
   double s, inv_s, eps;       // band step 2 eps, its inverse, eps
   float inv_s32;
-  unsigned long long* ckey;   // chunk band keys (nB x nb)
-  // the store's index
-  const unsigned long long* skey;
-  const int32_t* shead;
-  const int32_t* snext;
-  const unsigned long long* srowkey;
-  uint64_t smask;
-  // the chunk's own index (rebuilt per chunk)
-  unsigned long long* bkey;
-  int32_t* bhead;
+  unsigned long long* ckey;   // chunk band keys (nb x nB, a band's rows together)
+  // per band and chunk row: the first entry of the rows with the same key, -1
+  // for none -- store index entries, and chunk rows (bnext: the next chunk row)
+  int32_t* sfirst;
+  int32_t* bfirst;
   int32_t* bnext;
-  uint64_t bmask;
-  uint64_t bslots;            // slots of the chunk's index
+  // the store's index
+  const unsigned long long* sslot;
+  const int32_t* snext;
+  uint64_t smask;
   const StoreMeta* meta;
   int m_exact;                // store size when known, else -1
   // decisions
@@ -652,71 +650,163 @@ __device__ __forceinline__ bool band_matches(const LshArgs& a, const int32_t* co
   return true;
 }
 
-// Slot holding key h in an index (linear probing), or -1 if absent.
-__device__ __forceinline__ int64_t find_slot(const unsigned long long* keys, uint64_t mask, unsigned long long h) {
-  uint64_t sl = h & mask;
-  for (;;) {
-    const unsigned long long k = keys[sl];
-    if (k == h) return (int64_t)sl;
-    if (k == 0ull) return -1;
-    sl = (sl + 1) & mask;
+// float32 rows p and q (16-byte aligned) have equal codes in band b; bands of a
+// multiple of four coordinates are read as float4, both rows' at once
+__device__ __forceinline__ bool bands_equal(const LshArgs& a, const float* p, const float* q, int b) {
+  if (a.r & 3) {
+    for (int t = b * a.r; t < (b + 1) * a.r; ++t)
+      if (band_code(a, q[t]) != band_code(a, p[t])) return false;
+    return true;
   }
+  bool same = true;
+#pragma unroll 2
+  for (int t = b * a.r; t < (b + 1) * a.r; t += 4) {
+    const float4 u = *reinterpret_cast<const float4*>(p + t);
+    const float4 v = *reinterpret_cast<const float4*>(q + t);
+    same &= band_code(a, u.x) == band_code(a, v.x);
+    same &= band_code(a, u.y) == band_code(a, v.y);
+    same &= band_code(a, u.z) == band_code(a, v.z);
+    same &= band_code(a, u.w) == band_code(a, v.w);
+  }
+  return same;
 }
 
-// Inserts entry e under key h (an index is at most half full, so a free or
-// matching slot is always found).
-__device__ __forceinline__ void index_insert(unsigned long long* keys, int32_t* head, int32_t* next, uint64_t mask,
+// A slot of the store's index holds the upper half of a key and, plus one, the
+// newest entry under it (0: empty).  One word takes one device-wide atomic per
+// insertion and one load per lookup, where a key and a head took two each;
+// keys that share the upper half and a probe sequence share a list, which is
+// harmless since codes are compared.
+__device__ __forceinline__ unsigned long long slot_word(unsigned long long h, int32_t e) {
+  return (h & 0xffffffff00000000ull) | (uint32_t)(e + 1);
+}
+__device__ __forceinline__ bool slot_has(unsigned long long w, unsigned long long h) { return (w ^ h) >> 32 == 0ull; }
+__device__ __forceinline__ int32_t slot_entry(unsigned long long w) { return (int32_t)((uint32_t)w - 1u); }
+
+// The newest entry under key h (linear probing; w: the word of h's first slot),
+// or -1 if absent.
+__device__ __forceinline__ int32_t find_entry(const unsigned long long* slots, uint64_t mask, unsigned long long h,
+                                              unsigned long long w) {
+  for (uint64_t sl = h & mask; w != 0ull; w = slots[sl]) {
+    if (slot_has(w, h)) return slot_entry(w);
+    sl = (sl + 1) & mask;
+  }
+  return -1;
+}
+
+// Inserts entry e under key h (the index is at most half full, so a free or
+// matching slot is always found).  A claimed slot's upper half never changes,
+// so an entry joins its list by exchanging the lower half (rows that share a
+// band by the thousand do not retry against each other).
+__device__ __forceinline__ void index_insert(unsigned long long* slots, int32_t* next, uint64_t mask,
                                              unsigned long long h, int32_t e) {
-  uint64_t sl = h & mask;
-  for (;;) {
-    const unsigned long long k = atomicCAS(&keys[sl], 0ull, h);
-    if (k == 0ull || k == h) break;
-    sl = (sl + 1) & mask;
-  }
-  next[e] = atomicExch(&head[sl], e);
-}
-
-// Band keys of the chunk's rows; the same grid clears the chunk's index.
-__global__ __launch_bounds__(256) void k_lsh_keys(LshArgs a) {
-  const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if ((uint64_t)t < a.bslots) {
-    a.bkey[t] = 0ull;
-    a.bhead[t] = -1;
-  }
-  if (t >= (int64_t)a.nB * a.nb) return;
-  const int i = (int)(t / a.nb), b = (int)(t % a.nb);
-  const float* p = a.xc + (int64_t)i * a.D + b * a.r;
-  unsigned long long h = mix64((unsigned long long)b + 1ull);
-  for (int k = 0; k < a.r; ++k) h = mix64(h ^ (unsigned long long)(uint32_t)band_code(a, p[k]));
-  a.ckey[t] = h ? h : 1ull;   // 0 marks an empty slot
-}
-
-// The chunk's own index over all its rows (cleared by k_lsh_keys).
-__global__ __launch_bounds__(256) void k_lsh_index_chunk(LshArgs a) {
-  const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= (int64_t)a.nB * a.nb) return;
-  index_insert(a.bkey, a.bhead, a.bnext, a.bmask, a.ckey[t], (int32_t)t);
-}
-
-// Walks the store's and the chunk's lists of arrival i's band b and hands each
-// row whose band codes equal the arrival's to f(entry) (entry: store position,
-// or kChunkBit | chunk row j for j < i).  Stops early when f returns false.
-template <class F>
-__device__ __forceinline__ void band_rows(const LshArgs& a, int i, int b, int m, const int32_t* code, F&& f) {
-  const unsigned long long h = a.ckey[(int64_t)i * a.nb + b];
-  if (m > 0) {
-    const int64_t sl = find_slot(a.skey, a.smask, h);
-    for (int32_t e = sl >= 0 ? a.shead[sl] : -1; e >= 0; e = a.snext[e]) {
-      const int pos = e / a.nb;
-      if (e - pos * a.nb != b || pos >= m) continue;
-      if (band_matches(a, code, a.xs + (int64_t)pos * a.D, b) && !f((uint32_t)pos)) return;
+  const unsigned long long mine = slot_word(h, e);
+  for (uint64_t sl = h & mask;; sl = (sl + 1) & mask) {
+    const unsigned long long w = atomicCAS(&slots[sl], 0ull, mine);
+    if (w == 0ull) {
+      next[e] = -1;
+      return;
+    }
+    if (slot_has(w, h)) {
+      next[e] = slot_entry(atomicExch(reinterpret_cast<uint32_t*>(&slots[sl]), (uint32_t)mine));
+      return;
     }
   }
-  const int64_t sl = find_slot(a.bkey, a.bmask, h);
-  for (int32_t e = sl >= 0 ? a.bhead[sl] : -1; e >= 0; e = a.bnext[e]) {
-    const int j = e / a.nb;
-    if (e - j * a.nb != b || j >= i) continue;
-    if (band_matches(a, code, a.xc + (int64_t)j * a.D, b) && !f(kChunkBit | (uint32_t)j)) return;
+}
+
+// One workgroup per band: the keys of the chunk's rows in this band, the store's
+// entries with the same key, and the chunk's own rows grouped by key in an LDS
+// table (at most half full), linked through bnext.  It was an index over (row,
+// band) in global memory: a launch to clear it and form the keys, one to insert
+// 98,304 entries by two device-wide atomics each, and two dependent lookups per
+// band in the admission (1,024 rows x 96 bands: 21 us for both launches; this one
+// takes 9.7, bound by its chain of row load, hash, store lookup and LDS insert).
+constexpr int kBandThreads = 1024;
+
+template <int SLOTS>
+__global__ __launch_bounds__(kBandThreads) void k_lsh_bands(LshArgs a) {
+  constexpr int kRows = SLOTS / 2 / kBandThreads;   // rows per thread
+  static_assert(kRows >= 1 && (SLOTS & (SLOTS - 1)) == 0, "a power of two, half of it rows");
+  __shared__ unsigned long long key[SLOTS];
+  __shared__ int32_t head[SLOTS];
+  const int b = (int)blockIdx.x, tid = (int)threadIdx.x;
+  for (int k = tid; k < SLOTS; k += kBandThreads) {
+    key[k] = 0ull;
+    head[k] = -1;
+  }
+  const int m = a.m_exact >= 0 ? a.m_exact : a.meta->m;
+  unsigned long long h[kRows], k0[kRows];
+#pragma unroll
+  for (int u = 0; u < kRows; ++u) {
+    const int i = min(tid + u * kBandThreads, a.nB - 1);
+    const float* p = a.xc + (int64_t)i * a.D + b * a.r;
+    h[u] = mix64((unsigned long long)b + 1ull);
+    auto mix = [&](float v) { h[u] = mix64(h[u] ^ (unsigned long long)(uint32_t)band_code(a, v)); };
+    if ((a.r & 3) == 0) {   // (the band starts at 16 bytes)
+#pragma unroll 2
+      for (int k = 0; k < a.r; k += 4) {
+        const float4 v = *reinterpret_cast<const float4*>(p + k);
+        mix(v.x);
+        mix(v.y);
+        mix(v.z);
+        mix(v.w);
+      }
+    } else {
+      for (int k = 0; k < a.r; ++k) mix(p[k]);
+    }
+    h[u] = h[u] ? h[u] : 1ull;   // 0 marks an empty slot
+    k0[u] = m > 0 ? a.sslot[h[u] & a.smask] : 0ull;
+  }
+  __syncthreads();
+  int slot[kRows], prev[kRows];
+#pragma unroll
+  for (int u = 0; u < kRows; ++u) {
+    const int i = tid + u * kBandThreads;
+    if (i >= a.nB) break;
+    int sl = (int)(h[u] & (SLOTS - 1));
+    for (;;) {
+      const unsigned long long k = atomicCAS(&key[sl], 0ull, h[u]);
+      if (k == 0ull || k == h[u]) break;
+      sl = (sl + 1) & (SLOTS - 1);
+    }
+    slot[u] = sl;
+    prev[u] = atomicExch(&head[sl], i);
+    const int64_t t = (int64_t)b * a.nB + i;
+    a.ckey[t] = h[u];
+    a.bnext[t] = prev[u];
+    a.sfirst[t] = find_entry(a.sslot, a.smask, h[u], k0[u]);
+  }
+  __syncthreads();
+#pragma unroll
+  for (int u = 0; u < kRows; ++u) {
+    const int i = tid + u * kBandThreads;
+    if (i >= a.nB) break;
+    const int32_t hd = head[slot[u]];
+    a.bfirst[(int64_t)b * a.nB + i] = hd == i && prev[u] < 0 ? -1 : hd;   // (a row alone with its key has no list)
+  }
+}
+
+// Walks the rows sharing arrival i's key of a band, retained rows (which = 0:
+// store positions below m) or earlier chunk rows (which = 1), and hands each to
+// f(entry) (entry: store position, or kChunkBit | chunk row) when
+// same(row, b) finds its band codes equal too.  Stops early when f returns
+// false.
+template <class Same, class F>
+__device__ __forceinline__ void band_rows(const LshArgs& a, int i, int b, int which, int m, Same&& same, F&& f) {
+  // (the next entry is loaded with the row it follows: one round trip a step)
+  const int64_t t = (int64_t)b * a.nB;
+  if (which == 0) {
+    for (int32_t e = a.sfirst[t + i], nx; e >= 0; e = nx) {
+      nx = a.snext[e];
+      const int pos = e / a.nb;
+      if (e - pos * a.nb != b || pos >= m) continue;
+      if (same(a.xs + (int64_t)pos * a.D, b) && !f((uint32_t)pos)) return;
+    }
+  } else {
+    for (int32_t j = a.bfirst[t + i], nx; j >= 0; j = nx) {
+      nx = a.bnext[t + j];
+      if (j >= i) continue;
+      if (same(a.xc + (int64_t)j * a.D, b) && !f(kChunkBit | (uint32_t)j)) return;
+    }
   }
 }
 
@@ -733,6 +823,7 @@ __device__ bool screened_within(const LshArgs& a, int i, const float* pb32, cons
   const int gl = (int)threadIdx.x & (G - 1);
   const _Float16* pa16 = a.xc16 + (int64_t)i * a.D;
   float acc = 0.0f;
+#pragma unroll 4
   for (int d = gl * 8; d < a.D; d += 8 * G) {
     const half8 u = *reinterpret_cast<const half8*>(pa16 + d);
     const half8 v = *reinterpret_cast<const half8*>(pb16 + d);
@@ -752,8 +843,8 @@ __device__ bool screened_within(const LshArgs& a, int i, const float* pb32, cons
 static_assert(kSetSlots == 1 << 12, "set_hash yields 12 bits");
 
 __global__ __launch_bounds__(kAdmitThreads) void k_lsh_admit(LshArgs a) {
-  extern __shared__ int32_t s_code[];   // the arrival's band codes (D)
-  __shared__ uint32_t set[kSetSlots];
+  extern __shared__ int32_t s_code[];   // the arrival's band codes (D), for the pair list
+  __shared__ __attribute__((aligned(16))) uint32_t set[kSetSlots];
   __shared__ uint32_t list[kSetMax + kAdmitThreads];
   __shared__ uint32_t n_set, n_store, n_chunk;
   __shared__ int32_t hit, skip;
@@ -766,8 +857,8 @@ __global__ __launch_bounds__(kAdmitThreads) void k_lsh_admit(LshArgs a) {
   if (skip) return;
   const int m = a.m_exact >= 0 ? a.m_exact : a.meta->m;
   const float* p = a.xc + (int64_t)i * a.D;
-  for (int d = tid; d < a.D; d += kAdmitThreads) s_code[d] = band_code(a, p[d]);
-  for (int k = tid; k < kSetSlots; k += kAdmitThreads) set[k] = kSetEmpty;
+  for (int k = tid * 4; k < kSetSlots; k += kAdmitThreads * 4)
+    *reinterpret_cast<uint4*>(&set[k]) = make_uint4(kSetEmpty, kSetEmpty, kSetEmpty, kSetEmpty);
   if (tid == 0) {
     n_set = 0u;
     n_store = 0u;
@@ -777,16 +868,24 @@ __global__ __launch_bounds__(kAdmitThreads) void k_lsh_admit(LshArgs a) {
   __syncthreads();
 
   // 1. distinct candidates into the set (at most kSetMax + one per thread:
-  //    an insert starts only while the count is below kSetMax)
+  //    an insert starts only while the count is below kSetMax) and, as each is
+  //    first seen, into one of two lists: store positions from the front, chunk
+  //    rows from the back.  A thread takes one side of one band.
   volatile uint32_t* vn = &n_set;
-  for (int b = tid; b < a.nb && *vn < (uint32_t)kSetMax; b += kAdmitThreads) {
-    band_rows(a, i, b, m, s_code, [&](uint32_t v) {
+  for (int w = tid; w < 2 * a.nb && *vn < (uint32_t)kSetMax; w += kAdmitThreads) {
+    const int which = w >= a.nb ? 1 : 0;
+    band_rows(a, i, w - which * a.nb, which, m,
+              [&](const float* q, int b) { return bands_equal(a, p, q, b); }, [&](uint32_t v) {
       if (*vn >= (uint32_t)kSetMax) return false;
       uint32_t sl = set_hash(v);
       for (;;) {
         const uint32_t old = atomicCAS(&set[sl], kSetEmpty, v);
         if (old == kSetEmpty) {
           atomicAdd(&n_set, 1u);
+          if (v & kChunkBit)
+            list[kSetMax + kAdmitThreads - 1 - atomicAdd(&n_chunk, 1u)] = v & ~kChunkBit;
+          else
+            list[atomicAdd(&n_store, 1u)] = v;
           break;
         }
         if (old == v) break;
@@ -800,9 +899,14 @@ __global__ __launch_bounds__(kAdmitThreads) void k_lsh_admit(LshArgs a) {
   if (n_set >= (uint32_t)kSetMax) {
     // 1'. too many candidates: each pair once, for its lowest equal band, to
     //     the pair list (decided by k_verify)
-    for (int b = tid; b < a.nb; b += kAdmitThreads) {
-      band_rows(a, i, b, m, s_code, [&](uint32_t v) {
-        const bool chunk = (v & kChunkBit) != 0u;
+    for (int d = tid; d < a.D; d += kAdmitThreads) s_code[d] = band_code(a, p[d]);
+    __syncthreads();
+    for (int w = tid; w < 2 * a.nb; w += kAdmitThreads) {
+      const int which = w >= a.nb ? 1 : 0;
+      const int b = w - which * a.nb;
+      band_rows(a, i, b, which, m, [&](const float* q, int bb) { return band_matches(a, s_code, q, bb); },
+                [&](uint32_t v) {
+        const bool chunk = which != 0;
         const int y = (int)(v & ~kChunkBit);
         const float* q = (chunk ? a.xc : a.xs) + (int64_t)y * a.D;
         for (int b2 = 0; b2 < b; ++b2)
@@ -823,19 +927,9 @@ __global__ __launch_bounds__(kAdmitThreads) void k_lsh_admit(LshArgs a) {
   }
   if (tid == 0) atomicAdd(&a.flags->n_cand, (unsigned long long)n_set);
 
-  // 2. the set as two lists: store positions from the front, chunk rows from the back
-  for (int k = tid; k < kSetSlots; k += kAdmitThreads) {
-    const uint32_t v = set[k];
-    if (v == kSetEmpty) continue;
-    if (v & kChunkBit)
-      list[kSetMax + kAdmitThreads - 1 - atomicAdd(&n_chunk, 1u)] = v & ~kChunkBit;
-    else
-      list[atomicAdd(&n_store, 1u)] = v;
-  }
-  __syncthreads();
   const int ns = (int)n_store, nc = (int)n_chunk;
 
-  // 3. retained candidates, by groups of kGroup lanes (a wave's groups take
+  // 2. retained candidates, by groups of kGroup lanes (a wave's groups take
   //    consecutive entries): the lowest within delta is the representative,
   //    so a candidate above the lowest hit so far is skipped.  (Each reading
   //    of hit is the same for every lane of a group: they read it in one
@@ -861,7 +955,7 @@ __global__ __launch_bounds__(kAdmitThreads) void k_lsh_admit(LshArgs a) {
   if (hit != kNone) {
     if (tid == 0) a.firstHit[i] = hit;
   } else {
-    // 4. no retained row within delta: the chunk's earlier arrivals, for the resolve
+    // 3. no retained row within delta: the chunk's earlier arrivals, for the resolve
     const uint32_t* cl = list + kSetMax + kAdmitThreads - nc;
     for (int k = grp; k < nc; k += kGroups) {
       const int j = (int)cl[k];
@@ -884,38 +978,29 @@ __global__ __launch_bounds__(kAdmitThreads) void k_lsh_admit(LshArgs a) {
   if (glead) note_margin(a.flags, mmin);
 }
 
-// Kept rows of the chunk join the store's index under their store positions.
-__global__ __launch_bounds__(256) void k_lsh_insert(LshArgs a, const int32_t* __restrict__ pos,
-                                                    unsigned long long* skey, int32_t* shead, int32_t* snext,
-                                                    unsigned long long* srowkey) {
-  if (skip_all(a.flags)) return;
-  const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= (int64_t)a.nB * a.nb) return;
-  const int i = (int)(t / a.nb), b = (int)(t % a.nb);
-  const int p = pos[i];
-  if (p < 0) return;
-  const unsigned long long h = a.ckey[t];
-  const int32_t e = p * a.nb + b;
-  srowkey[e] = h;
-  index_insert(skey, shead, snext, a.smask, h, e);
-}
+// The store's index as the append inserts into it.
+struct LshInsert {
+  const unsigned long long* ckey;   // band keys of the chunk's rows
+  unsigned long long* sslot;
+  int32_t* snext;
+  unsigned long long* srowkey;
+  uint64_t smask;
+  int nb;
+};
 
 // Empties the store's index, then (second kernel) puts back the entries of the
 // first rows of the store from their recorded band keys.
-__global__ __launch_bounds__(256) void k_lsh_clear_index(unsigned long long* key, int32_t* head, uint64_t slots) {
+__global__ __launch_bounds__(256) void k_lsh_clear_index(unsigned long long* slot, uint64_t slots) {
   const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
-  for (uint64_t t = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; t < slots; t += stride) {
-    key[t] = 0ull;
-    head[t] = -1;
-  }
+  for (uint64_t t = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; t < slots; t += stride) slot[t] = 0ull;
 }
 
-__global__ __launch_bounds__(256) void k_lsh_reinsert(unsigned long long* key, int32_t* head, int32_t* next,
+__global__ __launch_bounds__(256) void k_lsh_reinsert(unsigned long long* slot, int32_t* next,
                                                       const unsigned long long* rowkey, uint64_t mask,
                                                       int64_t n_entries) {
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
   for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < n_entries; e += stride)
-    index_insert(key, head, next, mask, rowkey[e], (int32_t)e);
+    index_insert(slot, next, mask, rowkey[e], (int32_t)e);
 }
 
 // ------------------------------------------------------------------ verify
@@ -992,9 +1077,6 @@ struct ResolveArgs {
   StoreMeta* meta;
   int64_t c0;               // offset of the chunk in the call (global id = meta->n_seen + c0 + row)
   int64_t* rep;             // caller output for the chunk (global ids, -1 kept)
-  int32_t* pos;             // store position of kept rows, -1 if dropped
-  int32_t* rep_row;         // >= 0 store row, <= -2 chunk row (-(j+2)), -1 kept
-  uint64_t* kept_words;     // kept mask of the chunk (64 words)
   DevFlags* flags;
 };
 
@@ -1003,8 +1085,8 @@ static_assert(kChunk % kResolveThreads == 0, "whole rows per thread");
 constexpr int kEdgeCap = 20480;    // in-chunk candidate entries held in LDS (list form)
 constexpr int kBitsCap = 8704;     // candidate bitmap words of active rows held in LDS (bitmap form)
 
-// LDS of the in-chunk resolve.  rrow: the decision of each row as rep_row
-// encodes it; posv: the store position of each kept row (-1 if dropped).
+// LDS of the in-chunk resolve.  rrow: the decision of each row (>= 0 dropped for
+// that store row, <= -2 for chunk row -(j + 2), -1 kept); posv: the store position of each kept row (-1 if dropped).
 // The active rows' in-chunk candidates are held in one of two forms: their
 // bitmap words as loaded (bitmap form, when they fit), or ascending lists.
 struct ResolveLds {
@@ -1377,52 +1459,12 @@ __device__ void resolve_core(const ResolveArgs& a, ResolveLds& L, int n, int m0,
   __syncthreads();
 }
 
-// The resolve as a kernel of its own (one workgroup): decisions to rep, pos,
-// rep_row and the kept mask in global memory, the store size advanced.
-__global__ __launch_bounds__(kResolveThreads) void k_resolve(ResolveArgs a) {
-  __shared__ ResolveLds L;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  // the first phase's loads (hits and edge flags of this thread's rows, the
-  // status words, the store's counts) are all issued before any is used
-  constexpr int kRowsPerThread = kChunk / kResolveThreads;
-  int32_t hit_r[kRowsPerThread];
-  uint32_t edge_r[kRowsPerThread];
-#pragma unroll
-  for (int u = 0; u < kRowsPerThread; ++u) {
-    const int r = min(tid + u * kResolveThreads, a.nB - 1);
-    hit_r[u] = a.firstHit[r];
-    edge_r[u] = a.hasEdge[r];
-  }
-  const bool skip = skip_all(a.flags);
-  const int m0 = a.meta->m;
-  const int64_t gbase = a.meta->n_seen + a.c0;   // updated only at the end of a call
-  if (skip) return;   // (the status words do not change while this single workgroup runs)
-  resolve_core<kResolveThreads>(a, L, a.nB, m0, hit_r, edge_r);
-  for (int r = tid; r < a.nB; r += kResolveThreads) {
-    const int32_t rr = L.rrow[r];
-    a.rep[r] = rr >= 0 ? a.store_ids[rr] : (rr == -1 ? -1 : gbase + (-rr - 2));
-    a.rep_row[r] = rr;
-    a.pos[r] = L.posv[r];
-  }
-  for (int w = wave; w < 64; w += kResolveThreads / 64) {
-    const int r = w * 64 + lane;
-    const uint64_t b = __ballot(r < a.nB && L.st[r] == 1);
-    if (lane == 0) a.kept_words[w] = b;
-  }
-  if (tid == 0) {
-    a.meta->m = m0 + (int)L.total;
-    atomicAdd(&a.flags->n_kept, L.total);
-  }
-}
-
 // ------------------------------------------------------------------ append
 struct AppendArgs {
   const float* xc;
   const _Float16* x16c;
   const float* hnc;
   const float* etc;
-  const int32_t* pos;
-  const int32_t* rep_row;
   int64_t c0;               // offset of the chunk in the call
   int D;
   float* xs;
@@ -1439,7 +1481,6 @@ struct AppendArgs {
   DevFlags* flags_out;      // host-mapped copy of the status words, or NULL
 };
 
-constexpr int kAppendRows = 4;  // rows per workgroup of k_append (one wave each)
 constexpr int kAppendVec = 4;   // float4 of a row per lane held in registers (D <= 1,024)
 
 // Loads row r of the chunk into registers (D <= 1,024: the whole row, zeros
@@ -1457,7 +1498,7 @@ __device__ __forceinline__ void append_load(const AppendArgs& a, int r, float4 (
 // One wave's work for chunk row r (its data in v, from append_load): a kept
 // row (store position p >= 0) is copied into the store, with its terms and
 // global id, and raises amax / hmax (|x| and ||x||^2 / 2 as float bits); for a
-// dropped row ||x - x_rep||^2 (rr: the representative as rep_row encodes it)
+// dropped row ||x - x_rep||^2 (rr: the representative as ResolveLds::rrow encodes it)
 // is summed in binary64 in a fixed order into dmax (every lane).
 __device__ __forceinline__ void append_row(const AppendArgs& a, int r, int p, int rr, float hn, float et,
                                            int64_t gbase, const float4 (&v)[kAppendVec], double& dmax,
@@ -1584,9 +1625,7 @@ __device__ __forceinline__ void append_maxima(const AppendArgs& a, double dmax, 
 // everything else it reads was written by earlier launches.  Called by every
 // thread of every workgroup.
 template <class F>
-__device__ __forceinline__ void append_finish(const AppendArgs& a, bool count_every_chunk, uint32_t kept_here,
-                                              F&& last_work) {
-  if (!a.last_chunk && !count_every_chunk) return;
+__device__ __forceinline__ void append_finish(const AppendArgs& a, uint32_t kept_here, F&& last_work) {
   __shared__ bool last;
   __shared__ uint32_t kept_total;
   unsigned long long* done_kept = reinterpret_cast<unsigned long long*>(&a.cc->blocks_done);
@@ -1637,35 +1676,6 @@ __device__ __forceinline__ void append_finish(const AppendArgs& a, bool count_ev
   if (threadIdx.x == 0) *done_kept = 0ull;
 }
 
-// One wave per row, four rows per workgroup, decisions from k_resolve.  Kept
-// rows are copied into the store; for dropped rows ||x - x_rep||^2 is formed
-// in binary64 (fixed order) and the workgroup's maximum goes to the measured
-// bound with one atomic.
-__global__ __launch_bounds__(256) void k_append(AppendArgs a, int nB) {
-  const int wave = threadIdx.x >> 6;
-  const int r = (int)blockIdx.x * kAppendRows + wave;   // one row per wave
-  const int rc = min(r, nB - 1);
-  // Every load that depends on no other is issued before any is used: the
-  // row's decision, its terms, the status words, the arrival count and (for
-  // D <= 1,024) the row itself through a buffer resource (zeros past the row).
-  const int p = a.pos[rc];
-  const int rr = a.rep_row[rc];
-  const float hn = a.hnc[rc], et = a.etc[rc];
-  const bool skip = skip_all(a.flags);
-  // every workgroup reads n_seen before the last one (below) advances it
-  const int64_t gbase = a.meta->n_seen + a.c0;
-  const uint32_t am0 = a.meta->absmax_bits, hm0 = a.meta->hnmax_bits;   // the store's maxima so far
-  float4 v[kAppendVec];
-  append_load(a, rc, v);
-  double dmax = 0.0;
-  uint32_t amax = 0u, hmax = 0u;
-  if (!skip && r < nB) append_row(a, r, p, rr, hn, et, gbase, v, dmax, amax, hmax);
-  __shared__ double part[4];
-  __shared__ uint32_t apart[4], hpart[4];
-  append_maxima<4>(a, dmax, amax, hmax, am0, hm0, part, apart, hpart);
-  append_finish(a, false, 0u, [](uint32_t) {});
-}
-
 // The in-chunk resolve and the append in one launch.  Workgroup b appends
 // rows [16 b, 16 b + 16) of the chunk, one wave per row; it first resolves,
 // in its own LDS, every row up to its last one (a decision depends only on
@@ -1674,10 +1684,14 @@ __global__ __launch_bounds__(256) void k_append(AppendArgs a, int nB) {
 // decisions' round trip through global memory.  Every workgroup reads the
 // store size at its start and adds its own kept count to the chunk's; the
 // last one to finish advances the store size.
+// LSH: the kept rows also join the store's band index, under the positions the
+// workgroup just resolved.  (As launches of their own, resolve, insertion and
+// append took 26 us for 1,024 rows of 768 in 96 bands.)
 constexpr int kAppendGroupThreads = kResolveThreads;
 constexpr int kAppendGroupRows = kAppendGroupThreads / 64;
 
-__global__ __launch_bounds__(kAppendGroupThreads) void k_resolve_append(ResolveArgs ra, AppendArgs a, int nB,
+template <bool LSH>
+__global__ __launch_bounds__(kAppendGroupThreads) void k_resolve_append(ResolveArgs ra, AppendArgs a, LshInsert ix, int nB,
                                                                          float* max_cos,
                                                                          const uint32_t* maxcos_store,
                                                                          const float* G) {
@@ -1725,6 +1739,17 @@ __global__ __launch_bounds__(kAppendGroupThreads) void k_resolve_append(ResolveA
         if (lane == 0) max_cos[r] = mc;
       }
     }
+    if constexpr (LSH) {
+      const int row0 = (int)blockIdx.x * kAppendGroupRows;
+      for (int t = tid; t < (nres - row0) * ix.nb; t += T) {
+        const int row = row0 + t / ix.nb, b = t % ix.nb;
+        if (L.posv[row] < 0) continue;
+        const unsigned long long h = ix.ckey[(int64_t)b * nB + row];
+        const int32_t e = L.posv[row] * ix.nb + b;
+        ix.srowkey[e] = h;
+        index_insert(ix.sslot, ix.snext, ix.smask, h, e);
+      }
+    }
     // kept rows among this workgroup's own
     const int first = (int)blockIdx.x * kAppendGroupRows;
     const uint64_t k = __ballot(lane < nres - first && L.st[first + lane] == 1);
@@ -1733,27 +1758,11 @@ __global__ __launch_bounds__(kAppendGroupThreads) void k_resolve_append(ResolveA
   __shared__ double part[T / 64];
   __shared__ uint32_t apart[T / 64], hpart[T / 64];
   append_maxima<T / 64>(a, dmax, amax, hmax, am0, hm0, part, apart, hpart);
-  append_finish(a, true, kept_here, [&](uint32_t total) {
+  append_finish(a, kept_here, [&](uint32_t total) {
     if (skip) return;
     a.meta->m = m0 + (int)total;
     atomicAdd(&a.flags->n_kept, total);
   });
-}
-
-// ------------------------------------------------------------------ max cos
-// max over store rows (from the screen) and over kept chunk rows j < i of the
-// screened dot product.
-__global__ __launch_bounds__(256) void k_maxcos(int nB, const uint32_t* maxcos_store, const float* G,
-                                                const uint64_t* kept_words, float* out, DevFlags* flags) {
-  if (skip_all(flags)) return;
-  const int lane = threadIdx.x & 63;
-  const int i = blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (i >= nB) return;
-  float m = ord2f(maxcos_store[i]);
-  for (int j = lane; j < i; j += 64)
-    if ((kept_words[j >> 6] >> (j & 63)) & 1ull) m = fmaxf(m, G[(int64_t)i * nB + j]);
-  for (int o = 32; o > 0; o >>= 1) m = fmaxf(m, __shfl_xor(m, o));
-  if (lane == 0) out[i] = m;
 }
 
 }  // namespace
@@ -1775,12 +1784,10 @@ lam_status store_alloc(lam_store* st) {
     uint64_t slots = 1;
     while (slots < 2 * entries) slots <<= 1;
     st->lsh_slots = slots;
-    LAM_HIP(hipMalloc(&st->lsh_key, slots * 8));
-    LAM_HIP(hipMalloc(&st->lsh_head, slots * 4));
+    LAM_HIP(hipMalloc(&st->lsh_slot, slots * 8));
     LAM_HIP(hipMalloc(&st->lsh_next, entries * 4));
     LAM_HIP(hipMalloc(&st->lsh_rowkey, entries * 8));
-    LAM_HIP(hipMemset(st->lsh_key, 0, slots * 8));
-    LAM_HIP(hipMemset(st->lsh_head, 0xff, slots * 4));   // -1: empty list
+    LAM_HIP(hipMemset(st->lsh_slot, 0, slots * 8));   // empty
   }
   LAM_HIP(hipDeviceSynchronize());
   st->thr = exact_threshold(st->tau);
@@ -1790,14 +1797,14 @@ lam_status store_alloc(lam_store* st) {
 lam_status lsh_reset(lam_ctx* ctx, lam_store* st, int64_t keep_rows) {
   if (st->lsh_r <= 0) return LAM_OK;
   const unsigned g = (unsigned)std::min<uint64_t>((st->lsh_slots + 255) / 256, 8192);
-  hipLaunchKernelGGL(k_lsh_clear_index, dim3(g), dim3(256), 0, ctx->stream, st->lsh_key, st->lsh_head,
+  hipLaunchKernelGGL(k_lsh_clear_index, dim3(g), dim3(256), 0, ctx->stream, st->lsh_slot,
                      st->lsh_slots);
   LAM_HIP(hipGetLastError());
   const int64_t ne = keep_rows * st->lsh_nb;
   if (ne > 0) {
     const unsigned g2 = (unsigned)std::min<int64_t>((ne + 255) / 256, 8192);
-    hipLaunchKernelGGL(k_lsh_reinsert, dim3(g2), dim3(256), 0, ctx->stream, st->lsh_key, st->lsh_head,
-                       st->lsh_next, st->lsh_rowkey, (uint64_t)(st->lsh_slots - 1), ne);
+    hipLaunchKernelGGL(k_lsh_reinsert, dim3(g2), dim3(256), 0, ctx->stream, st->lsh_slot, st->lsh_next,
+                       st->lsh_rowkey, (uint64_t)(st->lsh_slots - 1), ne);
     LAM_HIP(hipGetLastError());
   }
   return LAM_OK;
@@ -1807,11 +1814,11 @@ void store_free(lam_store* st) {
   for (void* p : {(void*)st->x32, (void*)st->x16, (void*)st->hn, (void*)st->et, (void*)st->ids,
                   (void*)st->stat_dev, (void*)st->codes})
     if (p) (void)hipFree(p);
-  for (void* p : {(void*)st->blk_w, (void*)st->blk_row_off, (void*)st->blk_data, (void*)st->lsh_key,
-                  (void*)st->lsh_head, (void*)st->lsh_next, (void*)st->lsh_rowkey})
+  for (void* p : {(void*)st->blk_w, (void*)st->blk_row_off, (void*)st->blk_data, (void*)st->lsh_slot,
+                  (void*)st->lsh_next, (void*)st->lsh_rowkey})
     if (p) (void)hipFree(p);
-  st->lsh_key = st->lsh_rowkey = nullptr;
-  st->lsh_head = st->lsh_next = nullptr;
+  st->lsh_slot = st->lsh_rowkey = nullptr;
+  st->lsh_next = nullptr;
   st->blk_w = nullptr;
   st->blk_row_off = nullptr;
   st->blk_data = nullptr;
@@ -1945,7 +1952,7 @@ lam_status dedup_ingest(lam_ctx* ctx, lam_store* st, const float* x, int64_t n, 
   // scratch
   LAM_TRY(ctx->scratch[S_X16].ensure((size_t)n * D * 2));
   LAM_TRY(ctx->scratch[S_ROWF].ensure((size_t)n * 8));
-  const size_t chunk_bytes = (size_t)CH * 4 * 6 + 64 * 8 + sizeof(ChunkCounters) + 256;
+  const size_t chunk_bytes = (size_t)CH * 4 * 3 + 8 + sizeof(ChunkCounters) + 256;
   LAM_TRY(ctx->scratch[S_CHUNK].ensure(chunk_bytes));
   LAM_TRY(ctx->scratch[S_BITMAP].ensure((size_t)CH * W * 8));
   if (want_max) LAM_TRY(ctx->scratch[S_G].ensure((size_t)CH * CH * 4));
@@ -1956,28 +1963,24 @@ lam_status dedup_ingest(lam_ctx* ctx, lam_store* st, const float* x, int64_t n, 
   int32_t* firstHit = reinterpret_cast<int32_t*>(cb);
   uint32_t* hasEdge = reinterpret_cast<uint32_t*>(cb + (size_t)CH * 4);
   uint32_t* maxcos = reinterpret_cast<uint32_t*>(cb + (size_t)CH * 8);
-  int32_t* pos = reinterpret_cast<int32_t*>(cb + (size_t)CH * 12);
-  int32_t* rep_row = reinterpret_cast<int32_t*>(cb + (size_t)CH * 16);
-  uint64_t* kept_words = reinterpret_cast<uint64_t*>(cb + (size_t)CH * 24);
-  ChunkCounters* cc = reinterpret_cast<ChunkCounters*>(cb + (size_t)CH * 24 + 64 * 8);
+  ChunkCounters* cc = reinterpret_cast<ChunkCounters*>(cb + (((size_t)CH * 12 + 7) & ~(size_t)7));
   uint64_t* bitmap = ctx->scratch[S_BITMAP].as<uint64_t>();
   float* G = want_max ? ctx->scratch[S_G].as<float>() : nullptr;
 
-  // banded candidates: chunk keys and the chunk's own index
+  // banded candidates: the chunk's band keys and, per row and band, where the
+  // rows with the same key begin
   LshArgs la{};
+  LshInsert ix{};
   if (lsh) {
     const int nb = st->lsh_nb;
     const uint64_t ce = (uint64_t)CH * nb;
-    uint64_t bslots = 1;
-    while (bslots < 2 * ce) bslots <<= 1;
-    LAM_TRY(ctx->scratch[kScratchLsh].ensure(ce * 8 + bslots * 8 + bslots * 4 + ce * 4));
+    LAM_TRY(ctx->scratch[kScratchLsh].ensure(ce * 20));
     char* lb = ctx->scratch[kScratchLsh].as<char>();
     la.ckey = reinterpret_cast<unsigned long long*>(lb);
-    la.bkey = reinterpret_cast<unsigned long long*>(lb + ce * 8);
-    la.bhead = reinterpret_cast<int32_t*>(lb + ce * 8 + bslots * 8);
-    la.bnext = reinterpret_cast<int32_t*>(lb + ce * 8 + bslots * 12);
-    la.bslots = bslots;
-    la.bmask = bslots - 1;
+    la.sfirst = reinterpret_cast<int32_t*>(lb + ce * 8);
+    la.bfirst = reinterpret_cast<int32_t*>(lb + ce * 12);
+    la.bnext = reinterpret_cast<int32_t*>(lb + ce * 16);
+    ix = LshInsert{la.ckey, st->lsh_slot, st->lsh_next, st->lsh_rowkey, st->lsh_slots - 1, nb};
     la.xs = st->x32;
     la.xs16 = st->x16;
     la.hns = st->hn;
@@ -1990,10 +1993,8 @@ lam_status dedup_ingest(lam_ctx* ctx, lam_store* st, const float* x, int64_t n, 
     la.s = 2.0 * st->lsh_eps;
     la.inv_s = 1.0 / la.s;
     la.inv_s32 = (float)la.inv_s;
-    la.skey = st->lsh_key;
-    la.shead = st->lsh_head;
+    la.sslot = st->lsh_slot;
     la.snext = st->lsh_next;
-    la.srowkey = st->lsh_rowkey;
     la.smask = st->lsh_slots - 1;
     la.meta = meta;
     la.d2 = st->d2;
@@ -2049,13 +2050,13 @@ lam_status dedup_ingest(lam_ctx* ctx, lam_store* st, const float* x, int64_t n, 
         la.m_exact = (!async && c0 == 0) ? (int)m_before : -1;
         la.pairs = pairs;
         la.pair_cap = cap;
-        const int64_t ne = (int64_t)nB * la.nb;
-        const int64_t nt = std::max<int64_t>(ne, (int64_t)la.bslots);
         {
-          ProfScope ps(ctx, "lsh_keys");
-          hipLaunchKernelGGL(k_lsh_keys, dim3((unsigned)((nt + 255) / 256)), dim3(256), 0, ctx->stream, la);
-          LAM_HIP(hipGetLastError());
-          hipLaunchKernelGGL(k_lsh_index_chunk, dim3((unsigned)((ne + 255) / 256)), dim3(256), 0, ctx->stream, la);
+          ProfScope ps(ctx, "lsh_bands");
+          const dim3 g((unsigned)la.nb), b(kBandThreads);
+          if (nB <= kBandThreads)
+            hipLaunchKernelGGL(k_lsh_bands<2 * kBandThreads>, g, b, 0, ctx->stream, la);
+          else
+            hipLaunchKernelGGL(k_lsh_bands<2 * kChunk>, g, b, 0, ctx->stream, la);
           LAM_HIP(hipGetLastError());
         }
         {
@@ -2137,42 +2138,17 @@ lam_status dedup_ingest(lam_ctx* ctx, lam_store* st, const float* x, int64_t n, 
         hipLaunchKernelGGL(k_verify, dim3(256), dim3(256), 0, ctx->stream, va);
         LAM_HIP(hipGetLastError());
       }
-      ResolveArgs ra{nB, W, firstHit, hasEdge, bitmap, st->ids, meta, c0, rep + c0, pos, rep_row, kept_words,
-                     ctx->flags_dev};
-      AppendArgs aa{xc, x16, hnc + c0, etc + c0, pos, rep_row, c0, D, st->x32, st->x16, st->hn, st->et, st->ids,
+      ResolveArgs ra{nB, W, firstHit, hasEdge, bitmap, st->ids, meta, c0, rep + c0, ctx->flags_dev};
+      AppendArgs aa{xc, x16, hnc + c0, etc + c0, c0, D, st->x32, st->x16, st->hn, st->et, st->ids,
                     ctx->flags_dev, cc, meta, n, last_chunk ? 1 : 0, async ? 1 : 0,
                     (last_chunk && !async) ? ctx->flags_host_dev : nullptr};
-      if (!lsh) {
-        // resolve, largest cosines and append in one launch
+      {
+        // resolve, largest cosines, append and index insertion in one launch
         ProfScope ps(ctx, "dedup_resolve_append");
-        hipLaunchKernelGGL(k_resolve_append, dim3((unsigned)((nB + kAppendGroupRows - 1) / kAppendGroupRows)),
-                           dim3(kAppendGroupThreads), 0, ctx->stream, ra, aa, nB, want_max ? max_cos + c0 : nullptr,
-                           maxcos, G);
-        LAM_HIP(hipGetLastError());
-        continue;
-      }
-      {
-        ProfScope ps(ctx, "dedup_resolve");
-        hipLaunchKernelGGL(k_resolve, dim3(1), dim3(kResolveThreads), 0, ctx->stream, ra);
-        LAM_HIP(hipGetLastError());
-      }
-      if (want_max) {
-        hipLaunchKernelGGL(k_maxcos, dim3((unsigned)((nB + 3) / 4)), dim3(256), 0, ctx->stream, nB, maxcos, G,
-                           kept_words, max_cos + c0, ctx->flags_dev);
-        LAM_HIP(hipGetLastError());
-      }
-      if (lsh) {
-        // kept rows join the store's index before the append of the last
-        // chunk hands the status words back (and zeroes them)
-        ProfScope ps(ctx, "lsh_insert");
-        hipLaunchKernelGGL(k_lsh_insert, dim3((unsigned)(((int64_t)nB * la.nb + 255) / 256)), dim3(256), 0,
-                           ctx->stream, la, pos, st->lsh_key, st->lsh_head, st->lsh_next, st->lsh_rowkey);
-        LAM_HIP(hipGetLastError());
-      }
-      {
-        ProfScope ps(ctx, "dedup_append");
-        hipLaunchKernelGGL(k_append, dim3((unsigned)((nB + kAppendRows - 1) / kAppendRows)), dim3(256), 0,
-                           ctx->stream, aa, nB);
+        auto* kernel = lsh ? k_resolve_append<true> : k_resolve_append<false>;
+        hipLaunchKernelGGL(kernel, dim3((unsigned)((nB + kAppendGroupRows - 1) / kAppendGroupRows)),
+                           dim3(kAppendGroupThreads), 0, ctx->stream, ra, aa, ix, nB,
+                           want_max ? max_cos + c0 : nullptr, maxcos, G);
         LAM_HIP(hipGetLastError());
       }
     }

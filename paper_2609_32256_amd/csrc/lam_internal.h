@@ -117,8 +117,8 @@ struct lam_store {
   int32_t lsh_nb = 0;                // bands per row
   double lsh_eps = 0.0;              // Q_eps step of the band codes
   uint64_t lsh_slots = 0;            // index slots (a power of two)
-  unsigned long long* lsh_key = nullptr;   // slot key (0 = empty)
-  int32_t* lsh_head = nullptr;       // slot -> newest entry (entry = store position * nb + band)
+  unsigned long long* lsh_slot = nullptr;  // upper half of the key | newest entry + 1 (0 = empty;
+                                           // entry = store position * nb + band)
   int32_t* lsh_next = nullptr;       // entry -> older entry with the same key, -1 at the end
   unsigned long long* lsh_rowkey = nullptr;  // band keys of retained rows (position * nb + band)
   int64_t size = 0;           // exact when !pending

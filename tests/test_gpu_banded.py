@@ -152,6 +152,23 @@ def test_extreme_band_widths(lam, r, rel):
     assert sum(st["n_ambiguous_pairs"] for st in stats) == _expected_candidates(x, eps, r, rep, [0, 500, 1000])
 
 
+@pytest.mark.parametrize("n,d,r,splits", [
+    (1025, 96, 6, [0, 1, 1025]), (1026, 96, 3, [0, 1025, 1026]), (1100, 160, 20, [0, 1100]), (66, 4096, 8, [0, 64, 66])])
+def test_table_edges(lam, n, d, r, splits):
+    """Calls on both sides of the 1,024 rows up to which a band's table is the
+    small one, calls of one and two rows, bands that are and are not whole
+    float4s, more bands than an append workgroup inserts in one round, and one
+    band that a hundred rows of the same call share."""
+    x = _rows(seed=n + d, n=n, d=d)
+    x[n // 8: n // 8 + min(100, n // 2), :r] = 0.0
+    eps = 0.25 / np.sqrt(d)
+    ref = lsh.greedy_lsh(x, 0.95, eps, r)
+    s, rep, _ = _ingest(lam, x, 0.95, eps, r, splits)
+    assert np.array_equal(rep, ref["rep"])
+    assert np.array_equal(s.ids().cpu().numpy(), ref["kept"])
+    assert abs(s.info().delta_hat_run - ref["delta_hat"]) <= 1e-12
+
+
 def test_invalid_input_of_a_call_that_does_not_wait(lam):
     """A call that does not wait and holds a NaN leaves the store and its band
     index unchanged; the next call that waits reports it once."""
