@@ -47,6 +47,7 @@
 #include <cmath>
 #include <cstdlib>
 #include <cstring>
+#include <utility>
 #include <vector>
 
 #include "exact.h"
@@ -508,6 +509,23 @@ using ScreenTile = Tile<2, 4, 2, 1, 4>;
 // ScreenTile.  (Eight waves of 128 x 64 run as fast but need every register
 // of two waves per SIMD and spill on the rare path.)
 using ScreenTileL = Tile<4, 4, 2, 2, 4>;
+// The dimensions with a fully unrolled reduction (64 per slab), the usual widths
+// of encoders; the large tile exists for these only (with a rolled loop it
+// spills).  Against the rolled small tile, streams in calls of 4,096 rows: D = 128
+// 3.45 -> 2.98 ms (100,000 rows), 384 4.68 -> 4.17 (90,000), 512 3.66 -> 3.27
+// (70,000), 1,536 3.16 -> 2.77 (40,000); launches that keep the small tile gain
+// 0 to 2.5 % from the unrolled reduction.
+using UnrolledSlabs = std::integer_sequence<int, 2, 4, 6, 8, 12, 16, 24>;
+
+// Calls f(integral_constant of D / 64) when D is such a dimension.
+template <int... NS, class F>
+bool with_slabs(std::integer_sequence<int, NS...>, int D, F&& f) {
+  return ((D == NS * 64 && (f(std::integral_constant<int, NS>{}), true)) || ...);
+}
+bool unrolled_dim(int D) {
+  return with_slabs(UnrolledSlabs{}, D, [](auto) {});
+}
+
 constexpr int64_t kLargeTileMinTiles = 768;   // automatic choice: large tiles from this many
 
 // ------------------------------------------------------------------ merge predicate of one pair
@@ -2095,7 +2113,7 @@ lam_status dedup_ingest(lam_ctx* ctx, lam_store* st, const float* x, int64_t n, 
         const int64_t nt = (nB + rows - 1) / rows;
         return ((m_grid + rows - 1) / rows) * nt + nt * (nt + 1) / 2;
       };
-      const bool large_ok = !want_max && (D == 768 || D == 1024);
+      const bool large_ok = !want_max && unrolled_dim(D);
       const bool large = large_ok && (ctx->screen_tile == LAM_SCREEN_TILE_LARGE ||
                                       (ctx->screen_tile == LAM_SCREEN_TILE_AUTO &&
                                        grid_of(ScreenTileL::BN) >= kLargeTileMinTiles));
@@ -2110,25 +2128,21 @@ lam_status dedup_ingest(lam_ctx* ctx, lam_store* st, const float* x, int64_t n, 
         // timed by the launch itself when profiled (the dominant kernel)
         hipEvent_t e0, e1;
         LAM_TRY(prof_launch_events(ctx, "dedup_screen", &e0, &e1));
-        // the common dims get a fully unrolled reduction
         const dim3 g((unsigned)grid);
-        if (large) {
-          const dim3 b(ScreenTileL::kThreads);
-          if (D == 768)
-            hipExtLaunchKernelGGL((k_screen<ScreenTileL, false, 12, 1>), g, b, 0, ctx->stream, e0, e1, 0, sa);
+        auto launch = [&](auto ns) {
+          if (large)
+            hipExtLaunchKernelGGL((k_screen<ScreenTileL, false, ns.value, 1>), g, dim3(ScreenTileL::kThreads), 0,
+                                  ctx->stream, e0, e1, 0, sa);
           else
-            hipExtLaunchKernelGGL((k_screen<ScreenTileL, false, 16, 1>), g, b, 0, ctx->stream, e0, e1, 0, sa);
-        } else {
-          const dim3 b(ScreenTile::kThreads);
-          if (want_max)
-            hipExtLaunchKernelGGL((k_screen<ScreenTile, true, 0>), g, b, 0, ctx->stream, e0, e1, 0, sa);
-          else if (D == 768)
-            hipExtLaunchKernelGGL((k_screen<ScreenTile, false, 12>), g, b, 0, ctx->stream, e0, e1, 0, sa);
-          else if (D == 1024)
-            hipExtLaunchKernelGGL((k_screen<ScreenTile, false, 16>), g, b, 0, ctx->stream, e0, e1, 0, sa);
-          else
-            hipExtLaunchKernelGGL((k_screen<ScreenTile, false, 0>), g, b, 0, ctx->stream, e0, e1, 0, sa);
-        }
+            hipExtLaunchKernelGGL((k_screen<ScreenTile, false, ns.value>), g, dim3(ScreenTile::kThreads), 0,
+                                  ctx->stream, e0, e1, 0, sa);
+        };
+        if (want_max)
+          hipExtLaunchKernelGGL((k_screen<ScreenTile, true, 0>), g, dim3(ScreenTile::kThreads), 0, ctx->stream, e0,
+                                e1, 0, sa);
+        else if (!with_slabs(UnrolledSlabs{}, D, launch))
+          hipExtLaunchKernelGGL((k_screen<ScreenTile, false, 0>), g, dim3(ScreenTile::kThreads), 0, ctx->stream, e0,
+                                e1, 0, sa);
         LAM_HIP(hipGetLastError());
       }
       VerifyArgs va{pairs, status, cc, cap, xc, st->x32, D, st->d2, st->thr, firstHit, bitmap, W, hasEdge,

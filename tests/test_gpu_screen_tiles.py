@@ -64,6 +64,17 @@ def test_large_tile_async_and_chunked(lam):
     assert abs(info.delta_hat_run - ref["delta_hat"]) <= 1e-12
 
 
+@pytest.mark.parametrize("dim", [128, 256, 384, 512, 1536])
+@pytest.mark.parametrize("policy", ["large", "small"])
+def test_unrolled_dims_parity(lam, policy, dim):
+    """Every other unrolled reduction in both tiles, with ragged row counts."""
+    x = synth.subset_ingest(seed=dim, n=2900, n_traj=70, d=dim)["x"]
+    ref = dedup.greedy(x, 0.95, block=512)
+    rep, info = _ingest(lam, _ctx(lam, policy), x, 0.95, 1111)
+    assert np.array_equal(rep, ref["rep"])
+    assert abs(info.delta_hat_run - ref["delta_hat"]) <= 1e-12
+
+
 @pytest.mark.parametrize("policy", ["large", "small"])
 def test_d1024_parity(lam, policy):
     """D = 1,024 (16 slabs) on a clustered stream of 9,000 rows, both tiles."""
