@@ -138,11 +138,24 @@ lam_status clear_flags(lam_ctx* ctx) {
   return LAM_OK;
 }
 
-lam_status read_flags(lam_ctx* ctx) {
-  LAM_HIP(hipMemcpyAsync(ctx->flags_host, ctx->flags_dev, sizeof(DevFlags), hipMemcpyDeviceToHost, ctx->stream));
+// The status words to host memory, and zero again: one launch in place of a
+// copy (a blit of 3 us behind a slower enqueue) and the next call's clearing.
+__global__ void k_take_words(uint32_t* p, uint32_t* host, int n) {
+  const int i = threadIdx.x;
+  if (i >= n) return;
+  host[i] = p[i];
+  p[i] = 0u;
+}
+
+lam_status take_flags(lam_ctx* ctx) {
+  hipLaunchKernelGGL(k_take_words, dim3(1), dim3(64), 0, ctx->stream, reinterpret_cast<uint32_t*>(ctx->flags_dev),
+                     reinterpret_cast<uint32_t*>(ctx->flags_host_dev), (int)(sizeof(DevFlags) / 4));
+  LAM_HIP(hipGetLastError());
   LAM_HIP(hipStreamSynchronize(ctx->stream));
+  ctx->flags_zero = true;
   return LAM_OK;
 }
+static_assert(sizeof(DevFlags) <= 64 * 4, "one wave moves the status words");
 
 // Shared body of lam_quantize and lam_store_quantize.
 // known_valid: the caller knows every |x| to be finite and at most a positive
@@ -155,12 +168,12 @@ lam_status quantize_impl(lam_ctx* ctx, const float* x, int64_t n, double eps, fl
   // argument checks that do not depend on the data
   LAM_TRY(qeps_plan_host(eps, 0.0f, mode, n, &p));
   LAM_CHECK(std::isfinite(absmax), LAM_EINVAL, "absmax must be finite");
-  if (!ctx->flags_zero) LAM_TRY(clear_flags(ctx));   // (already zero after an ingest or a clean quantize)
+  if (!ctx->flags_zero) LAM_TRY(clear_flags(ctx));   // (already zero after an ingest or a quantize)
   ctx->flags_zero = false;
   float a = absmax;
   if (!(absmax > 0.0f)) {
     LAM_TRY(launch_absmax(ctx, x, n, &ctx->flags_dev->absmax_bits, store_path ? "store_absmax" : "qeps_absmax"));
-    LAM_TRY(read_flags(ctx));
+    LAM_TRY(take_flags(ctx));
     const uint32_t bits = ctx->flags_host->absmax_bits;
     LAM_CHECK(bits < 0x7f800000u, LAM_EINVAL, "input holds NaN or Inf");
     memcpy(&a, &bits, 4);
@@ -174,22 +187,18 @@ lam_status quantize_impl(lam_ctx* ctx, const float* x, int64_t n, double eps, fl
   LAM_CHECK(codes != nullptr || n == 0, LAM_EINVAL, "codes buffer is NULL");
   LAM_CHECK(cap >= p.code_bytes, LAM_EINVAL, "codes capacity %llu < %llu bytes needed",
             (unsigned long long)cap, (unsigned long long)p.code_bytes);
+  ctx->flags_zero = false;
   LAM_TRY(launch_encode(ctx, x, n, p, codes, &ctx->flags_dev->nonfinite, store_path ? "store_encode" : "qeps_encode"));
   if (known_valid && absmax > 0.0f) {
     ctx->flags_zero = true;   // cleared above and left untouched by valid input
     if (out) *out = p;
     return LAM_OK;
   }
-  LAM_TRY(read_flags(ctx));
+  LAM_TRY(take_flags(ctx));
   LAM_CHECK(ctx->flags_host->nonfinite == 0, LAM_EINVAL, "input holds NaN or Inf (%u elements)",
             ctx->flags_host->nonfinite);
   LAM_CHECK(ctx->flags_host->out_of_range == 0, LAM_ERANGE, "%u elements exceed the declared absmax %g",
             ctx->flags_host->out_of_range, (double)a);
-  // a declared absmax and valid input leave every status word at zero, which
-  // the next call need not clear again (the host copy is exact: the stream was
-  // synchronised after the encode)
-  static const DevFlags kZero{};
-  ctx->flags_zero = memcmp(ctx->flags_host, &kZero, sizeof(DevFlags)) == 0;
   if (out) *out = p;
   return LAM_OK;
 }

@@ -175,9 +175,10 @@ struct ProfScope {
   ~ProfScope() { if (slot != (size_t)-1) prof_end(ctx, slot); }
 };
 
-// status words: cleared by a kernel, read back with a stream synchronisation
+// status words: cleared by a kernel, taken (copied to the host mirror and
+// cleared) with a stream synchronisation
 lam_status clear_flags(lam_ctx* ctx);
-lam_status read_flags(lam_ctx* ctx);
+lam_status take_flags(lam_ctx* ctx);
 
 // ------------------------------------------------------------------ Q_eps (qeps.hip)
 lam_status qeps_plan_host(double eps, float absmax, int mode, int64_t n, lam_qparams* out);
