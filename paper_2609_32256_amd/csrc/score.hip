@@ -33,14 +33,23 @@ constexpr int kNoRow = 0x7fffffff;
 
 enum ScoreScratch { S_QHI = 7, S_QMETA, S_PART, S_CAND, S_Q8, S_QLO = S_Q8 };
 
+enum QKind : int {
+  kScanned = 0,    // the scan finds the candidates
+  kInvalid = 1,    // the query holds NaN/Inf
+  kUnscanned = 2,  // its scales leave float32's normal range (tiny or zero queries): the exact pass answers it
+};
+
 struct QMeta {
   float osc;     // float32(s * 2^(sh - e)): multiplies the raw accumulator
   float bound;   // eps * ||q||_1 rounded up, or NaN for an invalid query
-  int bad;       // query holds NaN/Inf
+  int kind;      // a QKind
+  int far;       // small stores: the score is the accumulator times osc 2^-126
   float err;     // >= |H + c - score| for every store row, c a constant of the query (rounded up)
   float osc8;    // the same two for the byte scan: float32(s * qs), qs = max|q| / 127
   float err8;
 };
+
+__device__ __forceinline__ bool normal_f32(float x) { return x >= 0x1p-126f && x <= 3.402823466e38f; }
 
 constexpr int kPrecQueries = 256;   // queries that share the choice of the scan's operands
 
@@ -68,11 +77,17 @@ __device__ __forceinline__ float rd32(double d) {
 //              trunc = s (2^sh - 1) / 2 sqrt(D);
 //   fp32 sum:  g = 2 (D + 64) 2^-24 of s 2^sh sum |h_d top_d| <= (||q|| + ||q - h||) R
 //              (two roundings per addition, in any order);
-//   scalings:  osc and the final product, 2^-24 each;
-//   S:         the rescoring sums in binary64 and rounds once to float32.
-// |H + c - S| <= ||q - h|| R + trunc ||q|| + (g + 2^-21)(||q|| + ||q - h||) R.
+//   scalings:  osc and the final product, 2^-24 each, or 2^-150 where the
+//              product is subnormal;
+//   S:         the rescoring sums in binary64 and rounds once to float32 (2^-24,
+//              or 2^-150 where S is subnormal).
+// |H + c - S| <= ||q - h|| R + trunc ||q|| + (g + 2^-21)(||q|| + ||q - h||) R + 2^-149.
 // The byte scan (q8 not NULL; codes of at most 8 bits, so trunc = 0) has h = qs
-// rint(q / qs) and exact int32 sums: err8 = (||q - h|| + 2^-21 (||q|| + ||q - h||)) R.
+// rint(q / qs) and exact int32 sums: err8 = (||q - h|| + 2^-21 (||q|| + ||q - h||)) R + 2^-149.
+// Both hold for scales osc and osc8 that are normal float32 values (2^-24) and a
+// finite 2^e; a query that has another (max|q| below about 2^-105, or 0) is not
+// scanned.  Sample and byte scan differ in their scale, so an error of one of
+// them would not cancel in the comparison with the threshold.
 // qmax: the largest |q| taken (a query row above it, or holding NaN/Inf, is
 // invalid).  cand_cnt, done: this query's candidate count and finished
 // workgroups of the exact pass, n_flag the number of flagged queries, and coarse,
@@ -135,7 +150,7 @@ __global__ __launch_bounds__(256) void k_score_prep(const float* __restrict__ q,
   l2 = wave_sum_f64(l2);
   bad = __ballot(bad) != 0ull;
   int e = 0;
-  if (!bad && mx > 0.0f) e = 14 - ilogbf(mx);   // max |q| 2^e in [2^14, 2^15)
+  if (!bad && mx > 0.0f) e = min(127, 14 - ilogbf(mx));   // max |q| 2^e in [2^14, 2^15), where 2^e is finite
   const float sc = ldexpf(1.0f, e);
   const double isc = ldexp(1.0, -e);
   double dh2 = 0.0;   // ||q - h||^2
@@ -145,7 +160,7 @@ __global__ __launch_bounds__(256) void k_score_prep(const float* __restrict__ q,
     dh2 = fma(r, r, dh2);
   };
   const float qs = bad ? 0.0f : mx * (1.0f / 127.0f);
-  const float iqs = qs > 0x1p-120f ? 1.0f / qs : 0.0f;   // (a query of subnormals: all bytes 0, err8 ||q|| R)
+  const float iqs = qs > 0x1p-120f ? 1.0f / qs : 0.0f;   // (else all bytes 0, err8 ||q|| R)
   double db2 = 0.0;   // ||q - qs rint(q / qs)||^2
   auto byte = [&](float x) {
     const float v = bad ? 0.0f : fminf(fmaxf(rintf(x * iqs), -127.0f), 127.0f);
@@ -178,21 +193,22 @@ __global__ __launch_bounds__(256) void k_score_prep(const float* __restrict__ q,
   dh2 = wave_sum_f64(dh2);
   if (q8) db2 = wave_sum_f64(db2);
   if (lane == 0) {
-    QMeta m;
+    QMeta m{};
     m.osc = (float)ldexp(step_f, -e);
     // (a binary64 sum of D non-negative terms is below the exact one by at most
     // (D - 1) 2^-53 relative, in any order; products and sqrt add 2^-53 each)
     const double up = 1.0 + (double)(D + 4) * 0x1p-52;
     m.bound = bad ? __builtin_nanf("") : ru32(eps * l1 * up);
-    m.bad = bad ? 1 : 0;
     const double g = 2.0 * (double)(D + 64) * 0x1p-24;
     const double qn = sqrt(l2) * up;
     const double dh = sqrt(dh2) * up;
-    const double E = dh * R + trunc * qn + (g + 0x1p-21) * (qn + dh) * R;
+    const double E = dh * R + trunc * qn + (g + 0x1p-21) * (qn + dh) * R + 0x1p-149;
     m.err = bad ? 0.0f : ru32(E * (1.0 + 0x1p-20));
     m.osc8 = (float)(step_f * (double)qs);
     const double db = sqrt(db2) * up;
-    m.err8 = bad ? 0.0f : ru32((db + 0x1p-21 * (qn + db)) * R * (1.0 + 0x1p-20));
+    m.err8 = bad ? 0.0f : ru32(((db + 0x1p-21 * (qn + db)) * R + 0x1p-149) * (1.0 + 0x1p-20));
+    const bool fits = mx >= 0x1p-113f && normal_f32(m.osc) && (!q8 || normal_f32(m.osc8));
+    m.kind = bad ? kInvalid : fits ? kScanned : kUnscanned;
     meta[j] = m;
   }
 }
@@ -356,10 +372,10 @@ __global__ __launch_bounds__(256) void k_sample_thr(int64_t nq, int64_t n, int e
       if (e0 + lane + r * 64 < entries) key[r] = max(key[r], code(e0 + lane + r * 64));
   const uint32_t T = wave_kth_floor<kThrKeys>(key, min(kThrKeys, (entries + 63) / 64), k);
   const double t = T == 0u ? -INFINITY : (double)ord2f(T);
-  if (lane == 0) thr[j] = m.bad ? __builtin_nanf("") : rd32(t - 2.0 * (double)m.err);
+  if (lane == 0) thr[j] = m.kind != kScanned ? __builtin_nanf("") : rd32(t - 2.0 * (double)m.err);
   if (!coarse) return;
   const float t8 = rd32(t - (double)m.err - (double)m.err8);
-  if (lane == 0) thr[nq + j] = m.bad ? __builtin_nanf("") : t8;
+  if (lane == 0) thr[nq + j] = m.kind != kScanned ? __builtin_nanf("") : t8;
   int above = 0;
   const uint32_t o8 = f2ord(t8);
 #pragma unroll
@@ -367,7 +383,7 @@ __global__ __launch_bounds__(256) void k_sample_thr(int64_t nq, int64_t n, int e
   const int nkeys = min(entries, 64 * kThrKeys);
   const float f = (float)above / (float)nkeys;
   const float rows = -logf(fmaxf(1.0f - f, 1e-6f)) * ((float)n / 32.0f) * ((float)nkeys / (float)entries);
-  if (lane == 0 && !m.bad && rows > kByteCands) atomicOr(&coarse[j / kPrecQueries], 1u);
+  if (lane == 0 && m.kind == kScanned && rows > kByteCands) atomicOr(&coarse[j / kPrecQueries], 1u);
 }
 
 // ------------------------------------------------------------------ filter pass on the screen's pipeline
@@ -834,8 +850,8 @@ __device__ __forceinline__ bool rescore_row(uint32_t t, uint32_t m, const int32_
 // wave 0 takes the one of wave_kth_floor (beyond 1,024 candidates several
 // share a key as their maximum), which costs the same for every k.  Up to 1,024
 // such rows are sorted at once; more (many near-equal scores) go through the
-// buffer in steps of 256 candidates.  An overflowed candidate buffer flags the
-// query for the exact pass.  Also writes the bound, NaN outputs for an invalid
+// buffer in steps of 256 candidates.  An overflowed candidate buffer, or a query
+// that is not scanned, flags the query for the exact pass.  Also writes the bound, NaN outputs for an invalid
 // query, and (-inf, -1) past the candidates.  Eight lanes share a rescored row
 // (32 rows in flight per workgroup); a lane takes whole groups of 32 codes (B
 // words).
@@ -858,14 +874,14 @@ __global__ __launch_bounds__(kRescoreThreads) void k_select_rescore(
   const QMeta mj = meta[j];
   const float err = coarse && coarse[j / kPrecQueries] == 0u ? mj.err8 : mj.err;   // of the scan that ran
   if (tid == 0 && bound) bound[j] = mj.bound;
-  if (mj.bad) {
+  if (mj.kind == kInvalid) {
     for (int t = tid; t < k; t += kRescoreThreads) {
       out_s[j * k + t] = __builtin_nanf("");
       out_i[j * k + t] = -1;
     }
     return;
   }
-  if (c > cap) {   // the exact pass redoes the query
+  if (mj.kind == kUnscanned || c > cap) {   // left to the exact pass
     if (tid == 0) flagged[atomicAdd(n_flag, 1u)] = (uint32_t)j;
     return;
   }
@@ -1117,7 +1133,7 @@ struct DenseArgs {
   int64_t row_words;
   const _Float16* qhi;  // [nq][D or 2 D]
   const _Float16* qlo;
-  const QMeta* meta;    // osc, bound and bad
+  const QMeta* meta;    // osc, far, bound and kind
   int64_t nq;
   int nqt;
   float* scores;        // [nq][ld]
@@ -1153,7 +1169,6 @@ __global__ __launch_bounds__(256) void k_dense_prep(const float* __restrict__ q,
   bad = __ballot(bad) != 0ull;
   int e = 0;
   if (!bad && mx > 0.0f) e = 14 - ilogbf(mx);   // the largest entry times 2^e in [2^14, 2^15)
-  const float sc = ldexpf(1.0f, e);
   for (int d = lane * 4; d < cols; d += 256) {   // (D is a multiple of 32: four columns are of one half)
     const float4 v = *reinterpret_cast<const float4*>(p + (d < D ? d : d - D));
     const float f = d < D ? up11 : 1.0f;
@@ -1161,7 +1176,7 @@ __global__ __launch_bounds__(256) void k_dense_prep(const float* __restrict__ q,
     _Float16 h[4], l[4];
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      const float x = bad ? 0.0f : c[i] * sc;   // exact power-of-two scaling
+      const float x = bad ? 0.0f : ldexpf(c[i], e);   // exact (2^e itself may overflow)
       h[i] = (_Float16)x;
       l[i] = (_Float16)(x - (float)h[i]);
     }
@@ -1173,9 +1188,11 @@ __global__ __launch_bounds__(256) void k_dense_prep(const float* __restrict__ q,
   }
   if (lane == 0) {
     QMeta m{};
-    m.osc = (float)ldexp(s, -e);
+    // s 2^-e as osc 2^-126 where float32 could not hold it as a normal value
+    m.far = ldexp(s, -e) < 0x1p-120 ? 1 : 0;
+    m.osc = fminf((float)ldexp(s, m.far ? 126 - e : -e), 3.402823466e38f);
     m.bound = bad ? __builtin_nanf("") : ru32(eps * l1 * (1.0 + (double)(cols + 4) * 0x1p-52));
-    m.bad = bad ? 1 : 0;
+    m.kind = bad ? kInvalid : kScanned;
     meta[j] = m;
   }
 }
@@ -1201,6 +1218,7 @@ __global__ __launch_bounds__(kWG, 2) void k_dense(DenseArgs a) {
   const int cols = kWide ? 2 * a.D : a.D;
   const int64_t j = qbase + wave * 32 + (lane & 31);
   const float osc = j < a.nq ? a.meta[j].osc : 0.0f;
+  const bool far = j < a.nq && a.meta[j].far != 0;
   floatx16 acc[4];
 #pragma unroll
   for (int t = 0; t < 4; ++t)
@@ -1259,12 +1277,14 @@ __global__ __launch_bounds__(kWG, 2) void k_dense(DenseArgs a) {
   if (j >= a.nq) return;
   // this lane's rows, four consecutive ones per store (ld covers whole tiles)
   float* o = a.scores + j * a.ld + rbase;
+  const float far2 = far ? 0x1p-126f : 1.0f;
 #pragma unroll
   for (int t = 0; t < 4; ++t)
 #pragma unroll
     for (int g = 0; g < 4; ++g)
       *reinterpret_cast<float4*>(o + t * 32 + acc_row(4 * g, lane)) =
-          make_float4(acc[t][4 * g] * osc, acc[t][4 * g + 1] * osc, acc[t][4 * g + 2] * osc, acc[t][4 * g + 3] * osc);
+          make_float4(acc[t][4 * g] * osc * far2, acc[t][4 * g + 1] * osc * far2, acc[t][4 * g + 2] * osc * far2,
+                      acc[t][4 * g + 3] * osc * far2);
 }
 
 template <int B>
@@ -1299,9 +1319,10 @@ __global__ __launch_bounds__(kRescoreThreads) void k_select_dense(int64_t nq, in
   if (j >= nq) return;
   const QMeta mj = meta[j];
   if (tid == 0 && bound) bound[j] = mj.bound;
-  const int kk = mj.bad ? 0 : min(k, n);
+  const bool bad = mj.kind == kInvalid;
+  const int kk = bad ? 0 : min(k, n);
   for (int t = kk + tid; t < k; t += kRescoreThreads) {
-    out_s[j * k + t] = mj.bad ? __builtin_nanf("") : -INFINITY;
+    out_s[j * k + t] = bad ? __builtin_nanf("") : -INFINITY;
     out_i[j * k + t] = -1;
   }
   if (kk == 0) return;
