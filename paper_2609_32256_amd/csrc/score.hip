@@ -338,6 +338,15 @@ __device__ __forceinline__ uint32_t wave_kth_floor(const uint32_t (&key)[R], int
   return T;
 }
 
+// The score that a floor of order keys stands for, within float32's finite range
+// from above, so that an error bound can be taken off it (a row whose score
+// overflows has a larger one); -inf for the keys below every finite score,
+// whose low bits wave_kth_floor drops.
+__device__ __forceinline__ double floor_score(uint32_t T) {
+  constexpr float kMax = 3.402823466e38f;
+  return T < f2ord(-kMax) ? -INFINITY : fmin((double)ord2f(T), (double)kMax);
+}
+
 // One wave per query: the threshold of the filter pass from the sample's
 // entries (scores of distinct rows): the k-th best, lowered by 2 err, so that
 // no row of the final top-k falls below it in hi-only terms.  Beyond 1,024
@@ -371,7 +380,7 @@ __global__ __launch_bounds__(256) void k_sample_thr(int64_t nq, int64_t n, int e
     for (int r = 0; r < kThrKeys; ++r)
       if (e0 + lane + r * 64 < entries) key[r] = max(key[r], code(e0 + lane + r * 64));
   const uint32_t T = wave_kth_floor<kThrKeys>(key, min(kThrKeys, (entries + 63) / 64), k);
-  const double t = T == 0u ? -INFINITY : (double)ord2f(T);
+  const double t = floor_score(T);
   if (lane == 0) thr[j] = m.kind != kScanned ? __builtin_nanf("") : rd32(t - 2.0 * (double)m.err);
   if (!coarse) return;
   const float t8 = rd32(t - (double)m.err - (double)m.err8);
@@ -916,7 +925,7 @@ __global__ __launch_bounds__(kRescoreThreads) void k_select_rescore(
       }
     const uint32_t T = wave_kth_floor<kThrKeys>(key, (int)min((uint32_t)kThrKeys, (c + 63u) / 64u), kk);
     if (lane == 0) {
-      thr_sh = T == 0u ? -INFINITY : rd32((double)ord2f(T) - 2.0 * (double)err);
+      thr_sh = rd32(floor_score(T) - 2.0 * (double)err);
       m_sh = 0u;
     }
   }

@@ -1,7 +1,7 @@
 """GPU parity of scoring at the ends of float32's range: queries so small that
-their scale, their scores or their entries are subnormal, on stores below and
-above 4,096 rows and for codes that are scanned as bytes, as float16 values and
-without their low bits."""
+their scale, their scores or their entries are subnormal, and queries so large
+that scores overflow, on stores below and above 4,096 rows and for codes that
+are scanned as bytes, as float16 values and without their low bits."""
 import numpy as np
 import pytest
 
@@ -49,3 +49,33 @@ def test_tiny_queries(lam, n, d, bits):
             assert np.all(S[j, row] >= kth[j] - 2 * tol) and np.all(np.diff(S[j, row]) <= 2 * tol), (e, j)
     beta = score.bound(q, eps)
     assert np.all(gb >= beta) and np.all(gb.astype(np.float64) - beta <= 2.0 ** -149 + beta * 2.0 ** -22)
+
+
+@pytest.mark.parametrize("n", [3000, 6000])
+@pytest.mark.parametrize("eps", [1.0, 0.05])
+def test_overflowing_scores(lam, n, eps):
+    """Rows of entries up to 200 against queries near float32's largest value:
+    every score -inf, every score +inf, both, and one finite query among them.
+    The k best are those of the scores rounded to float32, equal ones by id."""
+    rng = np.random.default_rng(int(100 * eps) + n)
+    d, k = 32, 10
+    x = rng.uniform(1.0, 200.0, (n, d)).astype(np.float32)
+    x[:, 0] = rng.uniform(-200.0, 200.0, n).astype(np.float32)
+    s = _store_from_rows(lam, x)
+    s.quantize(eps)
+    q = np.zeros((7, d), np.float32)
+    q[0, 1:] = -3e38
+    q[1, 1:] = 3e38
+    q[2, 0] = 3e38
+    q[3, 0] = -3e38
+    q[4] = rng.standard_normal(d)
+    q[5, 1:] = -1.1e35                     # the best scores finite, about half of all -inf
+    q[6, 1:] = 1.1e35                      # about half of all +inf
+    gs, gi, _ = (t.cpu().numpy() for t in s.score_topk(_dev(q), k))
+    with np.errstate(over="ignore"):
+        want = score.scores(q, qeps.codes(x, eps).reshape(n, -1), eps).astype(np.float32)
+    ts, ti = score.topk(want, np.arange(n), k)
+    for j in (0, 1, 2, 3, 6):
+        assert np.array_equal(gs[j], ts[j]) and np.array_equal(gi[j], ti[j]), j
+    for j in (4, 5):
+        assert np.allclose(gs[j], ts[j], rtol=1e-5) and np.all(gi[j] >= 0), j
