@@ -36,14 +36,15 @@ enum ScoreScratch { S_QHI = 7, S_QMETA, S_PART, S_CAND, S_Q8, S_QLO = S_Q8 };
 enum QKind : int {
   kScanned = 0,    // the scan finds the candidates
   kInvalid = 1,    // the query holds NaN/Inf
-  kUnscanned = 2,  // its scales leave float32's normal range (tiny or zero queries): the exact pass answers it
+  kUnscanned = 2,  // its scales leave float32's normal range (a tiny query): the exact pass answers it
+  kZero = 3,       // every score is 0: the first k rows
 };
 
 struct QMeta {
   float osc;     // float32(s * 2^(sh - e)): multiplies the raw accumulator
+                 // (small stores: negative where the scale is -osc 2^-126)
   float bound;   // eps * ||q||_1 rounded up, or NaN for an invalid query
   int kind;      // a QKind
-  int far;       // small stores: the score is the accumulator times osc 2^-126
   float err;     // >= |H + c - score| for every store row, c a constant of the query (rounded up)
   float osc8;    // the same two for the byte scan: float32(s * qs), qs = max|q| / 127
   float err8;
@@ -85,7 +86,7 @@ __device__ __forceinline__ float rd32(double d) {
 // The byte scan (q8 not NULL; codes of at most 8 bits, so trunc = 0) has h = qs
 // rint(q / qs) and exact int32 sums: err8 = (||q - h|| + 2^-21 (||q|| + ||q - h||)) R + 2^-149.
 // Both hold for scales osc and osc8 that are normal float32 values (2^-24) and a
-// finite 2^e; a query that has another (max|q| below about 2^-105, or 0) is not
+// finite 2^e; a query that has another (max|q| below about 2^-105) is not
 // scanned.  Sample and byte scan differ in their scale, so an error of one of
 // them would not cancel in the comparison with the threshold.
 // qmax: the largest |q| taken (a query row above it, or holding NaN/Inf, is
@@ -208,7 +209,7 @@ __global__ __launch_bounds__(256) void k_score_prep(const float* __restrict__ q,
     const double db = sqrt(db2) * up;
     m.err8 = bad ? 0.0f : ru32(((db + 0x1p-21 * (qn + db)) * R + 0x1p-149) * (1.0 + 0x1p-20));
     const bool fits = mx >= 0x1p-113f && normal_f32(m.osc) && (!q8 || normal_f32(m.osc8));
-    m.kind = bad ? kInvalid : fits ? kScanned : kUnscanned;
+    m.kind = bad ? kInvalid : mx == 0.0f ? kZero : fits ? kScanned : kUnscanned;
     meta[j] = m;
   }
 }
@@ -797,18 +798,20 @@ __device__ __forceinline__ void sort_keys(unsigned long long* keys, uint32_t P) 
 }
 
 // The best k of any number of keys: keys above the k-th found so far are
-// appended to a buffer, which is sorted and cut back to k when the next step
-// might not fit.
-constexpr int kExactBuf = 1024;
+// appended to a buffer of N, which is sorted and cut back to k when the next
+// step might not fit.
+constexpr int kTopKeys = 1024;   // the selections' buffer
 
+template <int N>
 struct TopBuf {
-  unsigned long long keys[kExactBuf];
+  unsigned long long keys[N];
   unsigned long long floor;   // keys up to it are not in the top k
   uint32_t cnt;
 };
 
 // Called by the whole workgroup; ends with a barrier.
-__device__ __forceinline__ void topbuf_clear(TopBuf& b) {
+template <int N>
+__device__ __forceinline__ void topbuf_clear(TopBuf<N>& b) {
   if (threadIdx.x == 0) {
     b.cnt = 0u;
     b.floor = 0ull;
@@ -816,23 +819,59 @@ __device__ __forceinline__ void topbuf_clear(TopBuf& b) {
   __syncthreads();
 }
 
-__device__ __forceinline__ void topbuf_push(TopBuf& b, unsigned long long key) {
+template <int N>
+__device__ __forceinline__ void topbuf_push(TopBuf<N>& b, unsigned long long key) {
   if (key > b.floor) b.keys[atomicAdd(&b.cnt, 1u)] = key;
 }
 
 // Called by the whole workgroup past a barrier: room for `room` more keys.
-__device__ __forceinline__ void topbuf_cut(TopBuf& b, int k, uint32_t room) {
+template <int N>
+__device__ __forceinline__ void topbuf_cut(TopBuf<N>& b, int k, uint32_t room) {
   const uint32_t c = b.cnt;
   __syncthreads();   // every thread has the same count before any pushes again
-  if (c + room <= (uint32_t)kExactBuf) return;
-  for (uint32_t i = c + threadIdx.x; i < (uint32_t)kExactBuf; i += kRescoreThreads) b.keys[i] = 0ull;
+  if (c + room <= (uint32_t)N) return;
+  for (uint32_t i = c + threadIdx.x; i < (uint32_t)N; i += kRescoreThreads) b.keys[i] = 0ull;
   __syncthreads();
-  sort_keys(b.keys, kExactBuf);
+  sort_keys(b.keys, N);
   if (threadIdx.x == 0) {
     b.cnt = min(c, (uint32_t)k);
     b.floor = c >= (uint32_t)k ? b.keys[k - 1] : 0ull;
   }
   __syncthreads();
+}
+
+// The same by one wave (all its lanes), which alone touches b meanwhile: LDS
+// operations of a wave complete in order, so the steps need no barrier.
+template <int N>
+__device__ __forceinline__ void topbuf_cut_wave(TopBuf<N>& b, int k, uint32_t room) {
+  const uint32_t c = b.cnt, lane = threadIdx.x & 63u;
+  if (c + room <= (uint32_t)N) return;
+  auto step = []() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+  };
+  for (uint32_t i = c + lane; i < (uint32_t)N; i += 64) b.keys[i] = 0ull;
+  step();
+#pragma unroll 1   // (unrolled, the steps' addresses and masks take every register)
+  for (uint32_t size = 2; size <= (uint32_t)N; size <<= 1) {
+#pragma unroll 1
+    for (uint32_t stride = size >> 1; stride > 0; stride >>= 1) {
+#pragma unroll
+      for (uint32_t t = 0; t < (uint32_t)N / 2; t += 64) {
+        const uint32_t p = t + lane, i = 2 * p - (p & (stride - 1)), l = i | stride;   // pair p of this stride
+        const unsigned long long x = b.keys[i], y = b.keys[l];
+        const bool swap = (i & size) == 0 ? x < y : x > y;
+        b.keys[i] = swap ? y : x;
+        b.keys[l] = swap ? x : y;
+      }
+      step();
+    }
+  }
+  if (lane == 0) {
+    b.cnt = min(c, (uint32_t)k);
+    b.floor = c >= (uint32_t)k ? b.keys[k - 1] : 0ull;
+  }
+  step();
 }
 
 // The exact score of row t of a list of m rows in LDS, by the eight lanes of
@@ -871,9 +910,9 @@ __global__ __launch_bounds__(kRescoreThreads) void k_select_rescore(
     const float* __restrict__ q, double step, const uint32_t* __restrict__ codes, int64_t row_words, int D,
     float* __restrict__ out_s, int64_t* __restrict__ out_i, float* __restrict__ bound, uint32_t* __restrict__ n_flag,
     uint32_t* __restrict__ flagged, const uint32_t* __restrict__ coarse) {
-  constexpr int kCap = kExactBuf;
+  constexpr int kCap = kTopKeys;
   __shared__ int32_t rows[kCap];
-  __shared__ TopBuf buf;
+  __shared__ TopBuf<kTopKeys> buf;
   __shared__ uint32_t m_sh;
   __shared__ float thr_sh;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -887,6 +926,13 @@ __global__ __launch_bounds__(kRescoreThreads) void k_select_rescore(
     for (int t = tid; t < k; t += kRescoreThreads) {
       out_s[j * k + t] = __builtin_nanf("");
       out_i[j * k + t] = -1;
+    }
+    return;
+  }
+  if (mj.kind == kZero) {   // (a store on this path has more than k rows)
+    for (int t = tid; t < k; t += kRescoreThreads) {
+      out_s[j * k + t] = 0.0f;
+      out_i[j * k + t] = ids[t];
     }
     return;
   }
@@ -972,7 +1018,7 @@ __global__ __launch_bounds__(kRescoreThreads) void k_select_rescore(
       __syncthreads();
       topbuf_cut(buf, k, kRescoreThreads);
     }
-    topbuf_cut(buf, k, kExactBuf);   // sorts what is left
+    topbuf_cut(buf, k, kTopKeys);   // sorts what is left
   }
   for (int t = tid; t < kk; t += kRescoreThreads) {
     out_s[j * k + t] = ord2f((uint32_t)(buf.keys[t] >> 32));
@@ -980,105 +1026,198 @@ __global__ __launch_bounds__(kRescoreThreads) void k_select_rescore(
   }
 }
 
-// The exact pass over the flagged queries (those whose candidates overflowed):
-// a work item is one flagged query and one of `splits` ranges of store rows,
-// all scored exactly.  Eight lanes share four rows at a time (the query's
-// values, held in LDS in binary64, serve all four, and their sums are
-// independent chains), 128 rows per step.  The range's best k go to the query's
-// candidate buffer (no longer needed; splits * k <= cap entries), and the last
-// of a query's workgroups merges them the same way.  Launched always; without
+// The exact pass over the flagged queries (those whose candidates overflowed, or
+// that are not scanned): a work item is a group of up to four flagged queries
+// and a range of store rows, all scored exactly.  Eight lanes
+// share four rows at a time, 128 rows per step: a code is unpacked and converted
+// to binary64 once for the group's queries, and a query's value read from LDS
+// (in binary64) once for the four rows.  A range's best k go to the queries' candidate
+// buffers (no longer needed), and the last of a
+// group's workgroups merges them the same way.  Launched always; without
 // flagged queries every workgroup returns after one load.
-// Per flagged query 0.11 ms at 361,802 rows, D = 768 (bound by reading the codes
-// and by the conversions to binary64; 0.21 ms with one row at a time) and 18 us
-// at 60,000 x 384.  The former pass kept sorted lists of the k best in every
-// lane of an MFMA scan, for all 128 queries of a flagged query's tile: one
-// flagged query in 128 cost 0.77 ms, now 0.28 ms; all 128 flagged 4.8 ms, now
-// 14 ms (top-10, D = 768), or 16 ms, now 2.4 ms (top-50, 60,000 x 384).
-constexpr int kExactRows = 4;   // rows per slot and step
+// A call of 128 queries against 361,802 rows, D = 768, top-10, of which 1, 8 or
+// all are flagged by 5,000 equal rows: 0.36, 0.52 and 2.6 ms (one query per work
+// item and 885 rows per range: 0.39, 1.01 and 13.9 ms; sorted per-lane lists
+// behind an fp16 scan of the whole 128-query tile: 0.99, 1.27 and 9.1 ms).  128
+// flagged of 300 against 60,000 x 384, top-50: 0.84 ms (2.45; lists 40 ms); 1,000
+// of 1,000 against 30,000 x 768: 2.0 ms (19; lists 1.35 ms, the one case found
+// where their fp16 products were faster than the binary64 ones here).
+constexpr int kExactRows = 4;      // rows per slot and step
+constexpr int kExactQueries = 4;   // flagged queries per work item
+constexpr int kExactPerCU = 3;     // workgroups that a CU holds at the usual code widths
+constexpr int kExactKeys = 256;    // >= 64 + one step's rows
+constexpr int kExactStep = kRescoreThreads / kRescoreLanes * kExactRows;
+
+// LDS doubles per group of 32 columns: a column's Q values side by side, groups
+// padded to distinct banks.
+constexpr int exact_ld(int Q) { return 32 * Q + (Q == 1 ? 1 : 2); }
+
+// (double)c for any int32, by the exponent of 2^52: an exclusive-or and a
+// subtraction, where v_cvt_f64_i32 takes four times as long as either.
+__device__ __forceinline__ double exact_f64(int32_t c) {
+  return __hiloint2double(0x43300000, c ^ (int32_t)0x80000000) - 0x1.000008p52;
+}
+
+// Sums of N values over the eight lanes of a slot: while a lane holds several it
+// hands half of them over at each step, so lane sl ends with max(1, N / 8)
+// sums, those from index exact_first(N, sl).
+template <int N, int O>
+__device__ __forceinline__ void oct_sums(double* v, int sl) {
+  if constexpr (O > 0) {
+    if constexpr (N > 1) {
+      const bool up = (sl & O) != 0;
+#pragma unroll
+      for (int i = 0; i < N / 2; ++i) {
+        const double give = up ? v[i] : v[i + N / 2];
+        v[i] = (up ? v[i + N / 2] : v[i]) + __shfl_xor(give, O);
+      }
+      oct_sums<N / 2, O / 2>(v, sl);
+    } else {
+      v[0] += __shfl_xor(v[0], O);
+      oct_sums<1, O / 2>(v, sl);
+    }
+  }
+}
+
+// The rows [r0, r1) against the Q queries in qs (nq of them real), into their
+// buffers.
+template <int B, int Q>
+__device__ __forceinline__ void exact_range(const uint32_t* __restrict__ codes, int64_t row_words, int64_t n, int64_t r0,
+                                            int64_t r1, int ngroups, const double* qs, double step, int k, int nq,
+                                            TopBuf<kExactKeys>* buf) {
+  constexpr int kSlots = kRescoreThreads / kRescoreLanes;
+  constexpr int N = Q * kExactRows, kMine = N >= kRescoreLanes ? N / kRescoreLanes : 1;
+  static_assert(kRescoreLanes == 8 && (N == 4 || N == 16), "sums over eight lanes");
+  const int slot = (int)threadIdx.x / kRescoreLanes, sl = (int)threadIdx.x % kRescoreLanes;
+  for (int64_t r = r0; r < r1; r += kExactStep) {
+    double acc[N];   // query u, row v at u * kExactRows + v
+    const uint32_t* w[kExactRows];
+#pragma unroll
+    for (int i = 0; i < N; ++i) acc[i] = 0.0;
+#pragma unroll
+    for (int v = 0; v < kExactRows; ++v)
+      w[v] = codes + min(r + v * kSlots + slot, n - 1) * row_words;   // (a row past the range is not used)
+    for (int g = sl; g < ngroups; g += kRescoreLanes) {
+      uint32_t cw[kExactRows][B];
+#pragma unroll
+      for (int v = 0; v < kExactRows; ++v)
+#pragma unroll
+        for (int i = 0; i < B; ++i) cw[v][i] = w[v][g * B + i];
+      const double* qg = qs + g * exact_ld(Q);
+#pragma unroll
+      for (int e = 0; e < 32; ++e) {
+        double qe[Q];
+#pragma unroll
+        for (int u = 0; u < Q; ++u) qe[u] = qg[e * Q + u];
+#pragma unroll
+        for (int v = 0; v < kExactRows; ++v) {
+          const double c = exact_f64(code_at<B>(cw[v], e));
+#pragma unroll
+          for (int u = 0; u < Q; ++u) acc[u * kExactRows + v] = fma(qe[u], c, acc[u * kExactRows + v]);
+        }
+      }
+    }
+    oct_sums<N, kRescoreLanes / 2>(acc, sl);
+    // the lane's sums: with 16 of them two each, with 4 one for two lanes
+    const int first = N == 16 ? sl * 2 : sl >> 1;
+    if (N == 16 || (sl & 1) == 0) {
+#pragma unroll
+      for (int i = 0; i < kMine; ++i) {
+        const int u = (first + i) / kExactRows;
+        const int64_t row = r + (int64_t)((first + i) % kExactRows) * kSlots + slot;
+        if (row < r1 && u < nq) topbuf_push(buf[u], score_key(acc[i], step, (uint32_t)row));
+      }
+    }
+    __syncthreads();
+    if ((int)threadIdx.x >> 6 < Q) topbuf_cut_wave(buf[threadIdx.x >> 6], k, kExactStep);
+    __syncthreads();
+  }
+}
 
 template <int B>
-__global__ __launch_bounds__(kRescoreThreads) void k_exact(
-    int64_t n, int splits, int64_t rows_per_split, uint32_t cap, int k, const int64_t* __restrict__ ids,
+__global__ __launch_bounds__(kRescoreThreads, B <= 13 ? kExactPerCU : 2) void k_exact(
+    int64_t n, uint32_t cap, int k, const int64_t* __restrict__ ids,
     const float* __restrict__ q, double step, const uint32_t* __restrict__ codes, int64_t row_words, int D,
     float* __restrict__ cs, int32_t* __restrict__ cr, uint32_t* __restrict__ done, const uint32_t* __restrict__ n_flag,
     const uint32_t* __restrict__ flagged, float* __restrict__ out_s, int64_t* __restrict__ out_i) {
   const uint32_t nf = *n_flag;
   if (nf == 0u) return;
-  extern __shared__ double qd[];   // the query, one pad per group of 32
-  __shared__ TopBuf buf;
+  extern __shared__ __attribute__((aligned(16))) double qs[];   // the group's queries (exact_ld per 32 columns)
+  __shared__ TopBuf<kExactKeys> buf[kExactQueries];
   __shared__ bool last;
-  const int tid = threadIdx.x;
-  const int slot = tid / kRescoreLanes, sl = tid % kRescoreLanes;
-  constexpr int kSlots = kRescoreThreads / kRescoreLanes;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int ngroups = D / 32;
-  const uint64_t items = (uint64_t)nf * (uint64_t)splits;
+  // ranges of at least two steps whose lists fit the candidate buffer; groups
+  // only where they leave every CU kExactPerCU workgroups, and then no more
+  // ranges than give it four times that (every range costs its lists' sorts)
+  constexpr uint64_t kFill = (uint64_t)kExactPerCU * 256;
+  const uint64_t most = min((uint64_t)(cap / (uint32_t)k), ((uint64_t)n + 2 * kExactStep - 1) / (2 * kExactStep));
+  const uint32_t per = (uint64_t)nf * most >= kExactQueries * kFill ? kExactQueries : 1u;
+  const uint64_t groups = ((uint64_t)nf + per - 1) / per;
+  const int splits = (int)min(most, (4 * kFill + groups - 1) / groups);
+  const int64_t rows_per_split = (n + splits - 1) / splits;
+  const uint64_t items = groups * (uint64_t)splits;
   for (uint64_t it = blockIdx.x; it < items; it += gridDim.x) {
-    const int64_t j = flagged[it / (uint64_t)splits];
+    const uint32_t* fl = flagged + it / (uint64_t)splits * per;
+    const int nq = (int)min(per, nf - (uint32_t)(fl - flagged));
     const int sp = (int)(it % (uint64_t)splits);
     const int64_t r0 = sp * rows_per_split, r1 = min(n, r0 + rows_per_split);
-    for (int d = tid; d < D; d += kRescoreThreads) qd[d + (d >> 5)] = (double)q[j * D + d];
-    topbuf_clear(buf);
-    for (int64_t r = r0; r < r1; r += kSlots * kExactRows) {
-      double acc[kExactRows];
-      const uint32_t* w[kExactRows];
-#pragma unroll
-      for (int u = 0; u < kExactRows; ++u) {
-        acc[u] = 0.0;
-        w[u] = codes + min(r + u * kSlots + slot, n - 1) * row_words;   // (a row past the range is not used)
-      }
-      for (int g = sl; g < ngroups; g += kRescoreLanes) {
-        uint32_t cw[kExactRows][B];
-#pragma unroll
-        for (int u = 0; u < kExactRows; ++u)
-#pragma unroll
-          for (int i = 0; i < B; ++i) cw[u][i] = w[u][g * B + i];
-#pragma unroll
-        for (int e = 0; e < 32; ++e) {
-          const double qe = qd[g * 33 + e];
-#pragma unroll
-          for (int u = 0; u < kExactRows; ++u) acc[u] = fma(qe, (double)code_at<B>(cw[u], e), acc[u]);
-        }
-      }
-#pragma unroll
-      for (int u = 0; u < kExactRows; ++u) {
-        for (int o = kRescoreLanes / 2; o > 0; o >>= 1) acc[u] += __shfl_xor(acc[u], o);
-        const int64_t row = r + u * kSlots + slot;
-        if (row < r1 && sl == 0) topbuf_push(buf, score_key(acc[u], step, (uint32_t)row));
-      }
-      __syncthreads();
-      topbuf_cut(buf, k, kSlots * kExactRows);
+    const int Q = nq == 1 ? 1 : kExactQueries;
+    for (int u = 0; u < Q; ++u) {
+      const float* qj = q + (int64_t)fl[min(u, nq - 1)] * D;   // (a place without a query repeats the last)
+      for (int d = tid; d < D; d += kRescoreThreads) qs[(d >> 5) * exact_ld(Q) + (d & 31) * Q + u] = (double)qj[d];
+      topbuf_clear(buf[u]);
     }
-    topbuf_cut(buf, k, kExactBuf);   // sorts what is left
-    for (int t = tid; t < k; t += kRescoreThreads) {
-      const unsigned long long key = t < (int)buf.cnt ? buf.keys[t] : 0ull;
-      cs[j * cap + sp * k + t] = __uint_as_float((uint32_t)(key >> 32));
-      cr[j * cap + sp * k + t] = (int32_t)(uint32_t)key;
+    if (nq == 1)
+      exact_range<B, 1>(codes, row_words, n, r0, r1, ngroups, qs, step, k, nq, buf);
+    else
+      exact_range<B, kExactQueries>(codes, row_words, n, r0, r1, ngroups, qs, step, k, nq, buf);
+    if (wave < nq) {
+      topbuf_cut_wave(buf[wave], k, kExactKeys);   // sorts what is left
+      const int64_t j = fl[wave];
+      if (lane < k) {
+        const unsigned long long key = lane < (int)buf[wave].cnt ? buf[wave].keys[lane] : 0ull;
+        cs[j * cap + sp * k + lane] = __uint_as_float((uint32_t)(key >> 32));
+        cr[j * cap + sp * k + lane] = (int32_t)(uint32_t)key;
+      }
     }
-    // release this range's keys, count it, and let the query's last range
-    // acquire all of them
+    // release this range's keys, count it (on the group's first query), and let
+    // the group's last range acquire all of them
     __threadfence();
     __syncthreads();
-    if (tid == 0) last = atomicAdd(&done[j], 1u) == (uint32_t)(splits - 1);
+    if (tid == 0) last = atomicAdd(&done[fl[0]], 1u) == (uint32_t)(splits - 1);
     __syncthreads();
     if (!last) continue;
     __threadfence();
-    topbuf_clear(buf);
-    for (int t0 = 0; t0 < splits * k; t0 += kRescoreThreads) {
-      const int t = t0 + tid;
-      if (t < splits * k)
-        topbuf_push(buf, ((unsigned long long)__float_as_uint(cs[j * cap + t]) << 32) |
-                             (unsigned long long)(uint32_t)cr[j * cap + t]);
-      __syncthreads();
-      topbuf_cut(buf, k, kRescoreThreads);
-    }
-    topbuf_cut(buf, k, kExactBuf);
-    for (int t = tid; t < k; t += kRescoreThreads) {   // (a flagged query has more than k rows)
-      out_s[j * k + t] = ord2f((uint32_t)(buf.keys[t] >> 32));
-      out_i[j * k + t] = ids[~(uint32_t)(buf.keys[t] & 0xffffffffull)];
+    // a wave merges one query's ranges
+    for (int u = 0; u < nq; ++u) topbuf_clear(buf[u]);
+    if (wave < nq) {
+      TopBuf<kExactKeys>& b = buf[wave];
+      const int64_t j = fl[wave];
+      constexpr int kAhead = 8;   // keys per lane loaded together
+      for (int t0 = 0; t0 < splits * k; t0 += 64 * kAhead) {
+        unsigned long long key[kAhead];
+#pragma unroll
+        for (int a = 0; a < kAhead; ++a) {
+          const int64_t t = j * cap + min(t0 + a * 64 + lane, splits * k - 1);
+          key[a] = ((unsigned long long)__float_as_uint(cs[t]) << 32) | (unsigned long long)(uint32_t)cr[t];
+        }
+#pragma unroll
+        for (int a = 0; a < kAhead; ++a) {
+          if (t0 + a * 64 + lane < splits * k) topbuf_push(b, key[a]);
+          topbuf_cut_wave(b, k, 64);
+        }
+      }
+      topbuf_cut_wave(b, k, kExactKeys);
+      if (lane < k) {   // (a flagged query has more than k rows)
+        out_s[j * k + lane] = ord2f((uint32_t)(b.keys[lane] >> 32));
+        out_i[j * k + lane] = ids[~(uint32_t)(b.keys[lane] & 0xffffffffull)];
+      }
     }
     __syncthreads();
   }
 }
+static_assert(kExactKeys >= 64 + kExactStep, "a cut leaves room for a step");
 
 // The rows scored exactly: arguments shared by the selection and the exact pass.
 struct ExactArgs {
@@ -1100,7 +1239,6 @@ struct ExactArgs {
   float* bound;
   uint32_t *n_flag, *flagged, *done;
   const uint32_t* coarse;   // byte scan: the flags of the queries that took the fp16 scan (else NULL)
-  int splits;
 };
 
 // The selection, or the exact pass over the flagged queries.
@@ -1112,8 +1250,7 @@ lam_status launch_exact(int b, bool select, hipStream_t st, const ExactArgs& a) 
                          a.cnt, a.cs, a.cr, a.meta, a.ids, a.q, a.step, a.codes, a.row_words, a.D, a.out_s, a.out_i,
                          a.bound, a.n_flag, a.flagged, a.coarse);
     else
-      hipLaunchKernelGGL((k_exact<B>), dim3(1024), dim3(kRescoreThreads), (size_t)(a.D / 32) * 33 * 8, st, a.n, a.splits,
-                         (a.n + a.splits - 1) / a.splits, a.cap, a.k, a.ids, a.q, a.step, a.codes, a.row_words, a.D,
+      hipLaunchKernelGGL((k_exact<B>), dim3(1024), dim3(kRescoreThreads), (size_t)(a.D / 32) * exact_ld(kExactQueries) * 8, st, a.n, a.cap, a.k, a.ids, a.q, a.step, a.codes, a.row_words, a.D,
                          a.cs, a.cr, a.done, a.n_flag, a.flagged, a.out_s, a.out_i);
     LAM_HIP(hipGetLastError());
     return LAM_OK;
@@ -1142,7 +1279,7 @@ struct DenseArgs {
   int64_t row_words;
   const _Float16* qhi;  // [nq][D or 2 D]
   const _Float16* qlo;
-  const QMeta* meta;    // osc, far, bound and kind
+  const QMeta* meta;    // osc, bound and kind
   int64_t nq;
   int nqt;
   float* scores;        // [nq][ld]
@@ -1197,9 +1334,10 @@ __global__ __launch_bounds__(256) void k_dense_prep(const float* __restrict__ q,
   }
   if (lane == 0) {
     QMeta m{};
-    // s 2^-e as osc 2^-126 where float32 could not hold it as a normal value
-    m.far = ldexp(s, -e) < 0x1p-120 ? 1 : 0;
-    m.osc = fminf((float)ldexp(s, m.far ? 126 - e : -e), 3.402823466e38f);
+    // s 2^-e, times 2^126 and negative where float32 could not hold it as a normal value
+    const bool far = ilogb(s) - e < -120;
+    m.osc = fminf((float)ldexp(s, far ? 126 - e : -e), 3.402823466e38f);
+    if (far) m.osc = -m.osc;
     m.bound = bad ? __builtin_nanf("") : ru32(eps * l1 * (1.0 + (double)(cols + 4) * 0x1p-52));
     m.kind = bad ? kInvalid : kScanned;
     meta[j] = m;
@@ -1227,7 +1365,6 @@ __global__ __launch_bounds__(kWG, 2) void k_dense(DenseArgs a) {
   const int cols = kWide ? 2 * a.D : a.D;
   const int64_t j = qbase + wave * 32 + (lane & 31);
   const float osc = j < a.nq ? a.meta[j].osc : 0.0f;
-  const bool far = j < a.nq && a.meta[j].far != 0;
   floatx16 acc[4];
 #pragma unroll
   for (int t = 0; t < 4; ++t)
@@ -1286,14 +1423,17 @@ __global__ __launch_bounds__(kWG, 2) void k_dense(DenseArgs a) {
   if (j >= a.nq) return;
   // this lane's rows, four consecutive ones per store (ld covers whole tiles)
   float* o = a.scores + j * a.ld + rbase;
-  const float far2 = far ? 0x1p-126f : 1.0f;
+  auto put = [&](float sa, float sb) {
 #pragma unroll
-  for (int t = 0; t < 4; ++t)
+    for (int t = 0; t < 4; ++t)
 #pragma unroll
-    for (int g = 0; g < 4; ++g)
-      *reinterpret_cast<float4*>(o + t * 32 + acc_row(4 * g, lane)) =
-          make_float4(acc[t][4 * g] * osc * far2, acc[t][4 * g + 1] * osc * far2, acc[t][4 * g + 2] * osc * far2,
-                      acc[t][4 * g + 3] * osc * far2);
+      for (int g = 0; g < 4; ++g)
+        *reinterpret_cast<float4*>(o + t * 32 + acc_row(4 * g, lane)) =
+            make_float4(acc[t][4 * g] * sa * sb, acc[t][4 * g + 1] * sa * sb, acc[t][4 * g + 2] * sa * sb,
+                        acc[t][4 * g + 3] * sa * sb);
+  };
+  if (osc >= 0.0f) put(osc, 1.0f);
+  else put(-osc, 0x1p-126f);
 }
 
 template <int B>
@@ -1321,7 +1461,7 @@ __global__ __launch_bounds__(kRescoreThreads) void k_select_dense(int64_t nq, in
                                                                   float* __restrict__ bound) {
   constexpr int kPer = kCandCap / kRescoreThreads;
   static_assert(kPer == kThrKeys, "a wave's keys are one register set");
-  __shared__ TopBuf buf;
+  __shared__ TopBuf<kTopKeys> buf;
   __shared__ uint32_t floor_sh[kRescoreThreads / 64], cnt_sh[kRescoreThreads / 64];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int64_t j = blockIdx.x;
@@ -1355,7 +1495,7 @@ __global__ __launch_bounds__(kRescoreThreads) void k_select_dense(int64_t nq, in
   uint32_t m = 0u;
 #pragma unroll
   for (int w = 0; w < kRescoreThreads / 64; ++w) m += cnt_sh[w];
-  const bool fits = m <= (uint32_t)kExactBuf;
+  const bool fits = m <= (uint32_t)kTopKeys;
 #pragma unroll
   for (int r = 0; r < kPer; ++r) {
     if (key[r] >= F)
@@ -1373,7 +1513,7 @@ __global__ __launch_bounds__(kRescoreThreads) void k_select_dense(int64_t nq, in
     __syncthreads();
     sort_keys(buf.keys, P);
   } else {
-    topbuf_cut(buf, k, kExactBuf);   // sorts what is left
+    topbuf_cut(buf, k, kTopKeys);   // sorts what is left
   }
   for (int t = tid; t < kk; t += kRescoreThreads) {
     out_s[j * k + t] = ord2f((uint32_t)(buf.keys[t] >> 32));
@@ -1590,7 +1730,7 @@ lam_status score_topk_impl(lam_ctx* ctx, const ScoreView& st, const float* q, in
   a.cand_cnt = cand_cnt;
   a.cap = cap;
   ExactArgs x{nq,    n,      cap,     k,         cand_cnt, cand_s, cand_r, qmeta, st.ids,  q,    st.step, st.codes,
-              a.row_words, D, scores, ids, bound, n_flag, flagged, done, bytes ? coarse : nullptr, 1};
+              a.row_words, D, scores, ids, bound, n_flag, flagged, done, bytes ? coarse : nullptr};
 
   {  // 1. a k-th best score of the sample -> thresholds
     ProfScope ps(ctx, "score_sample", prof);
@@ -1625,7 +1765,6 @@ lam_status score_topk_impl(lam_ctx* ctx, const ScoreView& st, const float* q, in
   }
   {  // 4. the exact pass over flagged queries (returns at once otherwise)
     ProfScope ps(ctx, "score_fallback", prof);
-    x.splits = (int)std::min<int64_t>(kCandCap / k, (n + 255) / 256);
     LAM_TRY(launch_exact<1>(b, false, ctx->stream, x));
   }
   return LAM_OK;

@@ -108,3 +108,37 @@ def test_byte_scan(lam, kind, d, n, nq, bits, absmax):
     c = qeps.codes(x, eps).reshape(n, -1)
     pick = np.unique(np.concatenate([rng.choice(nq, min(nq, 60), replace=False), [0, nq - 1]]))
     _compare(gs.cpu().numpy()[pick], gi.cpu().numpy()[pick], c, np.arange(n), q[pick], eps, 10, tol=3e-5)
+
+
+@pytest.mark.parametrize("d,n,nq,flagged,k,bits", [
+    (96, 9000, 40, 7, 10, 15),        # few flagged queries: one per work item
+    (64, 6000, 150, 131, 64, 10),     # groups of four, the last one of three
+    (768, 20000, 300, 257, 1, 9),     # the last one of one
+    (4096, 5000, 140, 130, 10, 8),    # the widest rows, the last one of two
+])
+def test_many_flagged_queries(lam, d, n, nq, flagged, k, bits):
+    """4,400 rows of the same codes lead for `flagged` of the queries, which
+    overflow and are scored exactly, several to a work item; the others, and
+    all-zero ones among them, are not disturbed."""
+    rng = np.random.default_rng(d + n)
+    v = synth.unit_rows(rng, 1, d)
+    x = synth.unit_rows(rng, n, d)
+    eps = float(max(np.abs(x).max(), np.abs(v).max())) / (2.0 ** bits - 2.5)
+    g = np.sort(rng.permutation(n)[:4400])
+    x[g] = np.round(v / (2 * eps)) * (2 * eps) + rng.uniform(-0.4, 0.4, (4400, d)) * eps
+    x = x.astype(np.float32)
+    s = _store_from_rows(lam, x)
+    assert s.quantize(eps).bits == bits
+    c = qeps.codes(x, eps).reshape(n, -1)
+    assert np.all(c[g] == c[g[0]]) and s.info().size == n
+    q = synth.unit_rows(rng, nq, d)
+    f = np.sort(rng.permutation(nq)[:flagged])
+    q[f] = v + 0.3 / np.sqrt(d) * rng.standard_normal((flagged, d))
+    q = q.astype(np.float32)
+    rest = np.setdiff1d(np.arange(nq), f)
+    q[rest[:3]] = 0.0
+    gs, gi, _ = (t.cpu().numpy() for t in s.score_topk(_dev(q), k))
+    assert np.array_equal(gi[f], np.broadcast_to(g[:k], (flagged, k)))
+    assert np.array_equal(gi[rest[:3]], np.broadcast_to(np.arange(k), (3, k))) and np.all(gs[rest[:3]] == 0.0)
+    pick = np.concatenate([rest[3:23], f[:20], f[-3:]])
+    _compare(gs[pick], gi[pick], c, np.arange(n), q[pick], eps, k, tol=2e-5)
