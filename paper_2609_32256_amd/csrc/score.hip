@@ -52,7 +52,9 @@ struct QMeta {
 
 __device__ __forceinline__ bool normal_f32(float x) { return x >= 0x1p-126f && x <= 3.402823466e38f; }
 
-constexpr int kPrecQueries = 256;   // queries that share the choice of the scan's operands
+// Queries that share the choice of the scan's operands: the columns of the
+// larger tile, which are multiplied by one instruction stream.
+constexpr int kPrecQueries = 256;
 
 __device__ __forceinline__ float ru32(double d) {
   float f = (float)d;
@@ -355,17 +357,29 @@ __device__ __forceinline__ double floor_score(uint32_t T) {
 // still the score of k distinct rows, only a little lower.
 // With a byte scan to follow (coarse not NULL) also its threshold, T - err -
 // err8, and the choice between the two scans: if the entries above it tell of
-// more than kByteCands rows of the store above it (a share f of entries, each
-// the best of 32 rows, means n (-ln(1 - f)) / 32 rows), the query's group of
+// more than `most` rows of the store above it (a share f of entries, each the
+// best of 32 rows, means n (-ln(1 - f)) / 32 rows), the query's group of
 // kPrecQueries takes the fp16 scan.  That happens where scores lie close
 // together for the byte scan's error (8e-3 ||q|| R for a Gaussian query), or
 // where single entries dominate the query, which widens that error.
 constexpr int kThrKeys = 16;   // keys per lane
-constexpr float kByteCands = 1024.0f;
+// The rows above the threshold from which the fp16 scan is the faster one, in a
+// launch of many 128 x 128 tiles and in one of fewer than kByteTiles (two for
+// each of the 512 places of the chip), where the candidates' stores and the
+// longer selection are not hidden behind other tiles.  Whole calls, fp16 against
+// bytes: 600 rows above in 720 tiles (178 queries x 46,046 rows x 1,024, top-20)
+// 93 : 104 us, in 360 tiles (64 queries) 79 : 98, in 1,440 tiles (512 queries)
+// 115 : 113, in 2,814 tiles (300 x 120,001 x 384, top-50) 134 : 114; 300 rows in
+// 469 tiles (128 x 60,000 x 128, top-20) 65 : 69; 1,000 rows in 782 tiles (64 x
+// 100,000 x 768) 86 : 103.  In 6,256 tiles (1,024 queries) bytes lead up to the
+// buffer's size: 1,500 rows 252 : 200, 3,000 rows 251 : 247.
+constexpr float kByteCands = 1024.0f, kByteCandsFew = 256.0f;
+constexpr int64_t kByteTiles = 1024;
 
 __global__ __launch_bounds__(256) void k_sample_thr(int64_t nq, int64_t n, int entries, int folded, int k,
                                                     const float* __restrict__ ps, const QMeta* __restrict__ meta,
-                                                    float* __restrict__ thr, uint32_t* __restrict__ coarse) {
+                                                    float* __restrict__ thr, uint32_t* __restrict__ coarse,
+                                                    float most) {
   const int lane = threadIdx.x & 63;
   const int64_t j = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
   if (j >= nq) return;
@@ -393,7 +407,9 @@ __global__ __launch_bounds__(256) void k_sample_thr(int64_t nq, int64_t n, int e
   const int nkeys = min(entries, 64 * kThrKeys);
   const float f = (float)above / (float)nkeys;
   const float rows = -logf(fmaxf(1.0f - f, 1e-6f)) * ((float)n / 32.0f) * ((float)nkeys / (float)entries);
-  if (lane == 0 && m.kind == kScanned && rows > kByteCands) atomicOr(&coarse[j / kPrecQueries], 1u);
+  // (a plain store: every writer stores the same; atomics on one word took 10 us
+  // when all of 1,024 queries set it)
+  if (lane == 0 && m.kind == kScanned && rows > most) coarse[j / kPrecQueries] = 1u;
 }
 
 // ------------------------------------------------------------------ filter pass on the screen's pipeline
@@ -402,6 +418,7 @@ using FilterTile = Tile<2, 4, 2, 1, 4>;
 // registers, one workgroup per CU: half the code and query loads per flop of
 // FilterTile; for the filter pass of stores with many tiles
 using FilterTileL = Tile<4, 4, 2, 2, 4>;
+static_assert(kPrecQueries % FilterTileL::BN == 0 && kPrecQueries % FilterTile::BN == 0, "a tile's queries share their operands");
 constexpr int kMaxBits = 22;       // code widths that can be scored
 constexpr int kFilterGroupQ = 8;   // query tiles per group in the tile order
 constexpr int kSampleEntries = 4;  // entries per query and 128-row store tile of the sample pass
@@ -1744,7 +1761,8 @@ lam_status score_topk_impl(lam_ctx* ctx, const ScoreView& st, const float* q, in
     }
     LAM_TRY((launch_filter<1, kSample>(b, false, (int64_t)nqt * stiles, ctx->stream, a)));
     hipLaunchKernelGGL(k_sample_thr, dim3((unsigned)((nq + 3) / 4)), dim3(256), 0, ctx->stream, nq, n, (int)entries,
-                       folded ? 1 : 0, k, part_s, qmeta, thr, bytes ? coarse : nullptr);
+                       folded ? 1 : 0, k, part_s, qmeta, thr, bytes ? coarse : nullptr,
+                       (int64_t)nqt * ntiles >= kByteTiles ? kByteCands : kByteCandsFew);
     LAM_HIP(hipGetLastError());
   }
   {  // 2. full scan with the thresholds: 256 x 256 tiles when the launch holds
