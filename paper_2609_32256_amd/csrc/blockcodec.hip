@@ -243,13 +243,15 @@ static_assert(kScanChunk % 256 == 0, "k_scan_add's workgroups stay within a chun
 // Pass 2: a lane transposes its block's codes into planes and puts its w planes
 // into the workgroup's run of words in LDS (the rows follow each other in the
 // data, so the run is contiguous there too), which is then stored coalesced.
+// Nothing is written when the encoding has more than cap words.
 template <int B>
 __global__ __launch_bounds__(kBlkThreads) void k_blk_pack(const uint32_t* __restrict__ codes, int64_t rows, int nb,
                                                           const uint8_t* __restrict__ widths,
                                                           const uint64_t* __restrict__ row_off,
-                                                          uint32_t* __restrict__ data) {
+                                                          uint32_t* __restrict__ data, uint64_t cap) {
   constexpr int NW = field_bits(B);
   __shared__ uint32_t run[kBlkThreads * B];   // (w <= B: zigzag codes are below 2^B)
+  if (row_off[rows] > cap) return;
   const BlkSpan sp(rows, nb);
   const int t = threadIdx.x;
   const int64_t g = sp.r0 * nb + t;
@@ -378,22 +380,24 @@ lam_status block_encode(lam_ctx* ctx, lam_store* st, lam_block_stats* out) {
     LAM_HIP(hipMalloc(&st->blk_w, (size_t)st->capacity * nb));
     LAM_HIP(hipMalloc(&st->blk_row_off, (size_t)(st->capacity + 1) * 8));
   }
-  // a block holds at most b words (its zigzag codes are below 2^b), so the data
-  // fits m * nb * b words and the pack need not wait for the count
-  const uint64_t data_cap = std::max<uint64_t>((uint64_t)m * nb * b * 4, 4);
-  if (data_cap > st->blk_cap) {
-    if (st->blk_data) LAM_HIP(hipFree(st->blk_data));
-    st->blk_data = nullptr;
-    st->blk_cap = 0;
-    LAM_HIP(hipMalloc(&st->blk_data, data_cap));
-    st->blk_cap = data_cap;
-  }
   LAM_TRY(ctx->scratch[kScratchBlocks].ensure((size_t)m * 4 + (size_t)(nchunks + 1) * 8 + 64));
   uint32_t* row_words = ctx->scratch[kScratchBlocks].as<uint32_t>();
   uint64_t* sums = reinterpret_cast<uint64_t*>(ctx->scratch[kScratchBlocks].as<char>() + (((size_t)m * 4 + 7) & ~7ull));
+  const dim3 grid(blk_grid(m, nb)), block(kBlkThreads);
+  auto pack = [&]() -> lam_status {
+    ProfScope ps(ctx, "store_block_pack");
+    for_width(b, [&](auto B) {
+      hipLaunchKernelGGL(k_blk_pack<B.value>, grid, block, 0, ctx->stream, st->codes, m, nb, st->blk_w,
+                         st->blk_row_off, st->blk_data, st->blk_cap / 4);
+    });
+    LAM_HIP(hipGetLastError());
+    return LAM_OK;
+  };
   ctx->flags_host->blk_words = 0;
+  // the data buffer holds what the encoding needs and no more.  A pack into the
+  // buffer of an earlier encoding is queued before the count is known (it writes
+  // nothing if that is too small), so that the device does not idle meanwhile.
   if (m > 0) {
-    const dim3 grid(blk_grid(m, nb)), block(kBlkThreads);
     {
       ProfScope ps(ctx, "store_block_encode");
       for_width(b, [&](auto B) {
@@ -406,15 +410,19 @@ lam_status block_encode(lam_ctx* ctx, lam_store* st, lam_block_stats* out) {
                          m, sums, &ctx->flags_host_dev->blk_words);
       LAM_HIP(hipGetLastError());
     }
-    ProfScope ps(ctx, "store_block_pack");
-    for_width(b, [&](auto B) {
-      hipLaunchKernelGGL(k_blk_pack<B.value>, grid, block, 0, ctx->stream, st->codes, m, nb, st->blk_w,
-                         st->blk_row_off, st->blk_data);
-    });
-    LAM_HIP(hipGetLastError());
+    if (st->blk_data) LAM_TRY(pack());
   }
   LAM_HIP(hipStreamSynchronize(ctx->stream));
   const uint64_t words = ctx->flags_host->blk_words;   // written by k_scan_add
+  if (words * 4 > st->blk_cap || !st->blk_data) {
+    if (st->blk_data) LAM_HIP(hipFree(st->blk_data));
+    st->blk_data = nullptr;
+    st->blk_cap = 0;
+    const uint64_t need = std::max<uint64_t>(words * 4, 4);
+    LAM_HIP(hipMalloc(&st->blk_data, need));
+    st->blk_cap = need;
+    if (m > 0) LAM_TRY(pack());
+  }
   st->blk_rows = m;
   st->blk_words = words;
   if (out) {

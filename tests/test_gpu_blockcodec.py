@@ -130,3 +130,34 @@ def test_every_field_width_bit_exact(lam, bits, n, dim):
     if bits <= 22:   # the widest codes that scoring takes
         q = _dev(synth.unit_rows(rng, 3, dim).astype(np.float32))
         assert all(torch.equal(u, v) for u, v in zip(s.score_topk(q, 5), s.score_topk_blocks(q, 5)))
+
+
+def test_encoding_memory_and_regrowth(lam):
+    """The device holds the encoding in about its own size, not the codes' (one
+    wide block in 32 per row here), and a store encoded again at a finer, then a
+    coarser step gives the oracle's encoding each time (a buffer that has to
+    grow, and one that is larger than needed)."""
+    rng = np.random.default_rng(91)
+    n, dim = 20000, 1024
+    x = np.zeros((n, dim), np.float32)
+    x[:, 64:96] = rng.uniform(-1, 1, (n, 32)).astype(np.float32)
+    x[0, 64] = 1.0
+    s, p = _store(lam, x, 1.0, 2.0 ** -12)
+    s.info()
+    torch.cuda.synchronize()
+    before = torch.cuda.mem_get_info()[0]
+    st = s.block_encode()
+    torch.cuda.synchronize()
+    used = before - torch.cuda.mem_get_info()[0]
+    assert st["data_bytes"] * 16 < p.code_bytes
+    assert used <= st["total_bytes"] + 4 * n + (8 << 20), (used, st["total_bytes"], p.code_bytes)
+    for eps in (2.0 ** -15, 2.0 ** -9, 2.0 ** -17):
+        s.quantize(eps)
+        s.block_encode()
+        ref = blockcodec.encode(qeps.codes(x[:300], eps).reshape(300, dim))
+        w, ro, d = s.block_export()
+        assert np.array_equal(w.cpu().numpy().reshape(n, -1)[:300], ref["widths"].reshape(300, -1))
+        assert np.array_equal(ro.cpu().numpy().astype(np.uint64)[:301], ref["row_off"])
+        words = int(ref["row_off"][-1])
+        assert np.array_equal(d.cpu().numpy().view(np.uint32)[:words], ref["data"][:words])
+        assert torch.equal(s.block_decode(), s.dequantize())
