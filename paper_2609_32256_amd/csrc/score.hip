@@ -358,7 +358,7 @@ __device__ __forceinline__ double floor_score(uint32_t T) {
 // With a byte scan to follow (coarse not NULL) also its threshold, T - err -
 // err8, and the choice between the two scans: if the entries above it tell of
 // more than `most` rows of the store above it (a share f of entries, each the
-// best of 32 rows, means n (-ln(1 - f)) / 32 rows), the query's group of
+// best of `per` rows, means n (-ln(1 - f)) / per rows), the query's group of
 // kPrecQueries takes the fp16 scan.  That happens where scores lie close
 // together for the byte scan's error (8e-3 ||q|| R for a Gaussian query), or
 // where single entries dominate the query, which widens that error.
@@ -379,7 +379,7 @@ constexpr int64_t kByteTiles = 1024;
 __global__ __launch_bounds__(256) void k_sample_thr(int64_t nq, int64_t n, int entries, int folded, int k,
                                                     const float* __restrict__ ps, const QMeta* __restrict__ meta,
                                                     float* __restrict__ thr, uint32_t* __restrict__ coarse,
-                                                    float most) {
+                                                    float most, float per) {
   const int lane = threadIdx.x & 63;
   const int64_t j = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
   if (j >= nq) return;
@@ -406,7 +406,7 @@ __global__ __launch_bounds__(256) void k_sample_thr(int64_t nq, int64_t n, int e
   for (int r = 0; r < kThrKeys; ++r) above += __popcll(__ballot(key[r] >= o8));
   const int nkeys = min(entries, 64 * kThrKeys);
   const float f = (float)above / (float)nkeys;
-  const float rows = -logf(fmaxf(1.0f - f, 1e-6f)) * ((float)n / 32.0f) * ((float)nkeys / (float)entries);
+  const float rows = -logf(fmaxf(1.0f - f, 1e-6f)) * ((float)n / per) * ((float)nkeys / (float)entries);
   // (a plain store: every writer stores the same; atomics on one word took 10 us
   // when all of 1,024 queries set it)
   if (lane == 0 && m.kind == kScanned && rows > most) coarse[j / kPrecQueries] = 1u;
@@ -1762,7 +1762,8 @@ lam_status score_topk_impl(lam_ctx* ctx, const ScoreView& st, const float* q, in
     LAM_TRY((launch_filter<1, kSample>(b, false, (int64_t)nqt * stiles, ctx->stream, a)));
     hipLaunchKernelGGL(k_sample_thr, dim3((unsigned)((nq + 3) / 4)), dim3(256), 0, ctx->stream, nq, n, (int)entries,
                        folded ? 1 : 0, k, part_s, qmeta, thr, bytes ? coarse : nullptr,
-                       (int64_t)nqt * ntiles >= kByteTiles ? kByteCands : kByteCandsFew);
+                       (int64_t)nqt * ntiles >= kByteTiles ? kByteCands : kByteCandsFew,
+                       32.0f * (float)stiles / (float)sample_tiles);
     LAM_HIP(hipGetLastError());
   }
   {  // 2. full scan with the thresholds: 256 x 256 tiles when the launch holds
