@@ -91,13 +91,13 @@ lam_status lam_ctx_profile_read(lam_ctx* ctx, const char* kernel, double* total_
 
 /* Tile of the similarity screen (Algorithm "admit": the store and in-chunk
  * screens of lam_dedup_ingest on an unbanded store).  Two MFMA tilings
- * compute the same decisions: 128 x 128 tiles (two workgroups per CU), and,
- * at D = 128, 256, 384, 512, 768, 1,024 and 1,536, 256 x 256 tiles (one
- * workgroup per CU, half the operand loads per flop), faster for launches of
- * many tiles and slower for small ones.  policy: LAM_SCREEN_TILE_AUTO (default: the large tile for a
- * launch of at least 768 large tiles), LAM_SCREEN_TILE_SMALL or
- * LAM_SCREEN_TILE_LARGE (every launch, where the dimension allows it).  A
- * tuning and testing setting of the context; LAM_EINVAL for another value. */
+ * compute the same decisions: 128 x 128 tiles (two workgroups per CU) and
+ * 256 x 256 tiles (one workgroup per CU, half the operand loads per flop),
+ * faster for launches of many tiles and slower for small ones.  policy:
+ * LAM_SCREEN_TILE_AUTO (default: the large tile for a launch of at least 768
+ * large tiles), LAM_SCREEN_TILE_SMALL or LAM_SCREEN_TILE_LARGE (every launch,
+ * but for calls that ask for max_cos).  A tuning and testing setting of the
+ * context; LAM_EINVAL for another value. */
 enum { LAM_SCREEN_TILE_AUTO = 0, LAM_SCREEN_TILE_SMALL = 1, LAM_SCREEN_TILE_LARGE = 2 };
 lam_status lam_ctx_set_screen_tile(lam_ctx* ctx, int policy);
 

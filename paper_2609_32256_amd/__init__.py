@@ -205,7 +205,7 @@ class Context:
 
     def set_screen_tile(self, policy):
         """The screen's tile: "auto" (by launch size), "small" (128 x 128) or
-        "large" (256 x 256 where D is 128, 256, 384, 512, 768, 1,024 or 1,536).  Decisions are the same."""
+        "large" (256 x 256).  Decisions are the same."""
         code = {"auto": 0, "small": 1, "large": 2}.get(policy, policy)
         _check(_lib.lam_ctx_set_screen_tile(self._h, int(code)))
 

@@ -47,7 +47,7 @@
 #include <cmath>
 #include <cstdlib>
 #include <cstring>
-#include <utility>
+#include <type_traits>
 #include <vector>
 
 #include "exact.h"
@@ -291,7 +291,7 @@ __device__ __forceinline__ void push_pairs(const ScreenArgs& a, int i, int kind,
 // A rows.
 // NS > 0: the reduction has exactly NS slabs of 64 (D = 64 NS), fully
 // unrolled; NS = 0: any D.  Each is its own kernel, so each gets its own
-// register allocation (the unrolled ones need no scratch memory).
+// register allocation (none needs scratch memory).
 template <class C, bool WANT_MAX, int NS, int SETS = 3>
 __global__ __launch_bounds__(C::kThreads, C::kMinWaves) void k_screen(ScreenArgs a) {
   static_assert(C::BM == C::BN, "the in-chunk triangle needs square tiles");
@@ -509,21 +509,24 @@ using ScreenTile = Tile<2, 4, 2, 1, 4>;
 // ScreenTile.  (Eight waves of 128 x 64 run as fast but need every register
 // of two waves per SIMD and spill on the rare path.)
 using ScreenTileL = Tile<4, 4, 2, 2, 4>;
-// The dimensions with a fully unrolled reduction (64 per slab), the usual widths
-// of encoders; the large tile exists for these only (with a rolled loop it
-// spills).  Against the rolled small tile, streams in calls of 4,096 rows: D = 128
-// 3.45 -> 2.98 ms (100,000 rows), 384 4.68 -> 4.17 (90,000), 512 3.66 -> 3.27
-// (70,000), 1,536 3.16 -> 2.77 (40,000); launches that keep the small tile gain
-// 0 to 2.5 % from the unrolled reduction.
-using UnrolledSlabs = std::integer_sequence<int, 2, 4, 6, 8, 12, 16, 24>;
+// The reduction is unrolled for every multiple of 64 (its slabs) up to a limit of
+// each tile; other and larger dimensions take a run-time loop.  The lines, in
+// streams at run-time loop : unrolled, ms.  Large tile, calls of 4,096 rows:
+// D = 128 3.12 : 3.01 (100,000 rows), 256 2.87 : 2.85, 384 4.27 : 4.25, 768 3.340
+// : 3.325 (60,000 rows), 1,024 16.51 : 16.43 (131,072 rows), 1,536 2.79 : 2.79
+// (40,000 rows).  Small tile, calls of 500 to 2,000 rows: 384 0.636 : 0.626, 768
+// 1.64 : 1.61, 1,280 1.775 : 1.756 (the gain shrinks as the slabs grow in number).
+// (Large against small tile at dimensions that had only the small one, calls of
+// 4,096 rows: 192 4.08 -> 3.60, 640 3.27 -> 2.96, 2,048 2.53 -> 2.26, 4,096
+// 2.34 -> 2.14.)
+constexpr int kUnrolledSlabs = 24, kUnrolledSlabsL = 16;
 
-// Calls f(integral_constant of D / 64) when D is such a dimension.
-template <int... NS, class F>
-bool with_slabs(std::integer_sequence<int, NS...>, int D, F&& f) {
-  return ((D == NS * 64 && (f(std::integral_constant<int, NS>{}), true)) || ...);
-}
-bool unrolled_dim(int D) {
-  return with_slabs(UnrolledSlabs{}, D, [](auto) {});
+// Calls f(integral_constant of D / 64) when that is a whole number up to MAX.
+template <int MAX, int NS = 1, class F>
+bool with_slabs(int D, F&& f) {
+  if (D == NS * 64) return f(std::integral_constant<int, NS>{}), true;
+  if constexpr (NS < MAX) return with_slabs<MAX, NS + 1>(D, f);
+  return false;
 }
 
 constexpr int64_t kLargeTileMinTiles = 768;   // automatic choice: large tiles from this many
@@ -2113,7 +2116,7 @@ lam_status dedup_ingest(lam_ctx* ctx, lam_store* st, const float* x, int64_t n, 
         const int64_t nt = (nB + rows - 1) / rows;
         return ((m_grid + rows - 1) / rows) * nt + nt * (nt + 1) / 2;
       };
-      const bool large_ok = !want_max && unrolled_dim(D);
+      const bool large_ok = !want_max;
       const bool large = large_ok && (ctx->screen_tile == LAM_SCREEN_TILE_LARGE ||
                                       (ctx->screen_tile == LAM_SCREEN_TILE_AUTO &&
                                        grid_of(ScreenTileL::BN) >= kLargeTileMinTiles));
@@ -2129,20 +2132,21 @@ lam_status dedup_ingest(lam_ctx* ctx, lam_store* st, const float* x, int64_t n, 
         hipEvent_t e0, e1;
         LAM_TRY(prof_launch_events(ctx, "dedup_screen", &e0, &e1));
         const dim3 g((unsigned)grid);
-        auto launch = [&](auto ns) {
-          if (large)
-            hipExtLaunchKernelGGL((k_screen<ScreenTileL, false, ns.value, 1>), g, dim3(ScreenTileL::kThreads), 0,
-                                  ctx->stream, e0, e1, 0, sa);
-          else
-            hipExtLaunchKernelGGL((k_screen<ScreenTile, false, ns.value>), g, dim3(ScreenTile::kThreads), 0,
-                                  ctx->stream, e0, e1, 0, sa);
+        auto launch = [&](auto kernel, int threads) {
+          hipExtLaunchKernelGGL(kernel, g, dim3(threads), 0, ctx->stream, e0, e1, 0, sa);
         };
-        if (want_max)
-          hipExtLaunchKernelGGL((k_screen<ScreenTile, true, 0>), g, dim3(ScreenTile::kThreads), 0, ctx->stream, e0,
-                                e1, 0, sa);
-        else if (!with_slabs(UnrolledSlabs{}, D, launch))
-          hipExtLaunchKernelGGL((k_screen<ScreenTile, false, 0>), g, dim3(ScreenTile::kThreads), 0, ctx->stream, e0,
-                                e1, 0, sa);
+        if (large) {
+          if (!with_slabs<kUnrolledSlabsL>(D, [&](auto ns) {
+                launch(k_screen<ScreenTileL, false, ns.value, 1>, ScreenTileL::kThreads);
+              }))
+            launch(k_screen<ScreenTileL, false, 0, 1>, ScreenTileL::kThreads);
+        } else if (want_max) {
+          launch(k_screen<ScreenTile, true, 0>, ScreenTile::kThreads);
+        } else if (!with_slabs<kUnrolledSlabs>(D, [&](auto ns) {
+                     launch(k_screen<ScreenTile, false, ns.value>, ScreenTile::kThreads);
+                   })) {
+          launch(k_screen<ScreenTile, false, 0>, ScreenTile::kThreads);
+        }
         LAM_HIP(hipGetLastError());
       }
       VerifyArgs va{pairs, status, cc, cap, xc, st->x32, D, st->d2, st->thr, firstHit, bitmap, W, hasEdge,

@@ -140,21 +140,25 @@ __device__ __forceinline__ void slab_store_n(_Float16* __restrict__ s, const uin
 // and column wn*TJ*32 + tj*32 + lane%32 of B, with wm = wave / WN, wn = wave %
 // WN.
 //
-// Pipeline: global loads run two slabs ahead of the MFMAs in two register
-// sets (three slabs ahead in three sets when NS > 0 and SETS = 3; one slab
-// ahead in one set when SETS = 1, for tiles whose accumulators leave no room
-// for more: the loads of slab s + 2 are issued once slab s + 1 is in LDS, so
-// they have one slab's MFMAs to land); slab s is multiplied from LDS stage
-// s % 2 while slab s + 1 is written to the other stage, so one barrier per
-// slab suffices and the LDS writes overlap the MFMAs.  With NS > 0 the
-// reduction has exactly NS slabs (kdim = 64 NS) and the loop is unrolled,
-// which lets the compiler wait for exactly the loads each LDS store needs
-// (across a loop back edge it waits for all of them), and loads past the last
-// slab are dropped at compile time.  NS = 0 takes kdim at run time; there the
-// loads past the last slab are issued too (they fall outside the buffer
-// bound, read zeros and touch no memory), so that no load sits behind a
-// branch.  go_on() runs once the first slabs' loads are in flight; if it
-// returns false the tile is abandoned and gemm_tile returns false.
+// Pipeline: slab s is multiplied from LDS stage s % 2 while slab s + 1 is
+// written to the other stage, so one barrier per slab suffices and the LDS
+// writes overlap the MFMAs.  Global loads run ahead of the LDS stores:
+//   NS > 0: the reduction has exactly NS slabs (kdim = 64 NS) and the loop is
+//     unrolled, which lets the compiler wait for exactly the loads each LDS store
+//     needs (across a loop back edge it waits for all of them); loads past the
+//     last slab are dropped at compile time.  SETS = 3: three slabs ahead in
+//     three register sets; SETS = 1: one set, for tiles whose accumulators leave
+//     no room for more (the loads of slab s + 2 are issued once slab s + 1 is in
+//     LDS, so they have one slab's MFMAs to land);
+//   NS = 0, SETS = 3: kdim at run time, loads two slabs ahead in two sets;
+//   NS = 0, SETS = 1: kdim at run time, two slabs (both stages) per trip, one set:
+//     a thread's offsets are formed once and a slab's is one scalar (formed per
+//     load, as with two sets, they spill beside that tile's accumulators).
+// With kdim at run time loads past the last slab are issued too (they fall
+// outside the buffer bound, read zeros and touch no memory), so that no load
+// sits behind a branch.  go_on() runs once the first slabs' loads are in flight;
+// if it returns false the tile is abandoned and gemm_tile returns false.  Ends
+// with a barrier.
 template <class C, int NS = 0, int SETS = 3, class Go>
 __device__ __forceinline__ bool gemm_tile(const _Float16* __restrict__ A, int ra, const _Float16* __restrict__ B,
                                           int rb, int64_t ld, int kdim, _Float16* lds,
@@ -185,91 +189,114 @@ __device__ __forceinline__ bool gemm_tile(const _Float16* __restrict__ A, int ra
     }
   };
   const __amdgpu_buffer_rsrc_t rsA = tile_rsrc(A, ra, ld), rsB = tile_rsrc(B, rb, ld);
-  static_assert(SETS == 3 || (SETS == 1 && NS > 0), "three register sets, or one with an unrolled reduction");
-  // (NS > 0: the caller guarantees kdim = 64 NS <= ld)
-  if constexpr (NS > 0) {
-    // exactly NS slabs: loads past the last slab are not issued
+  static_assert(SETS == 3 || SETS == 1, "three register sets, or one");
+  const int S = (kdim + kBK - 1) / kBK;
+  if constexpr (SETS == 1 && NS == 0) {
+    uint32_t va[C::kPerA], vb[C::kPerB];   // byte offsets of this thread's pieces of slab 0
+#pragma unroll
+    for (int q = 0; q < C::kPerA; ++q) {
+      const int c = threadIdx.x + C::kThreads * q;
+      va[q] = (c >> 3) < ra ? (uint32_t)((c >> 3) * ld * 2 + (c & 7) * 16) : kOffOOB;
+    }
+#pragma unroll
+    for (int q = 0; q < C::kPerB; ++q) {
+      const int c = threadIdx.x + C::kThreads * q;
+      vb[q] = (c >> 3) < rb ? (uint32_t)((c >> 3) * ld * 2 + (c & 7) * 16) : kOffOOB;
+    }
+    static_assert(C::kThreads % 8 == 0, "a thread's pieces share their columns");
+    const int col = ((int)threadIdx.x & 7) * 8;
+    auto load = [&](int s, uint4 (&xa)[C::kPerA], uint4 (&xb)[C::kPerB]) {
+      const int k0 = s * kBK;
+      const bool in = k0 + col < kdim;
+#pragma unroll
+      for (int q = 0; q < C::kPerA; ++q)
+        xa[q] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(rsA, in ? va[q] : kOffOOB, k0 * 2, 0));
+#pragma unroll
+      for (int q = 0; q < C::kPerB; ++q)
+        xb[q] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(rsB, in ? vb[q] : kOffOOB, k0 * 2, 0));
+    };
+    auto store = [&](int st, const uint4 (&xa)[C::kPerA], const uint4 (&xb)[C::kPerB]) {
+      slab_store_n<C::kPerA>(sa(st), xa, C::kThreads);
+      slab_store_n<C::kPerB>(sb(st), xb, C::kThreads);
+    };
+    uint4 xa[C::kPerA], xb[C::kPerB];
+    load(0, xa, xb);
+    if (!go_on()) return false;
+    store(0, xa, xb);
+    load(1, xa, xb);
+    __syncthreads();
+    for (int s = 0; s < S; s += 2) {
+#pragma unroll
+      for (int u = 0; u < 2; ++u) {
+        compute(u);
+        if (s + u + 1 >= S) break;
+        store(u ^ 1, xa, xb);
+        load(s + u + 2, xa, xb);
+        __syncthreads();
+      }
+    }
+    __syncthreads();
+  } else if constexpr (NS > 0) {
+    // exactly NS slabs (the caller guarantees kdim = 64 NS <= ld): loads past
+    // the last slab are not issued
     auto load = [&](int slab, uint4 (&xa)[C::kPerA], uint4 (&xb)[C::kPerB]) {
       if (slab < NS) {
         slab_load_n<C::kPerA>(rsA, ra, ld, slab * kBK, kdim, xa, C::kThreads);
         slab_load_n<C::kPerB>(rsB, rb, ld, slab * kBK, kdim, xb, C::kThreads);
       }
     };
-    if constexpr (SETS == 1) {
-      uint4 xa[C::kPerA], xb[C::kPerB];
-      load(0, xa, xb);
-      if (!go_on()) return false;
-      slab_store_n<C::kPerA>(sa(0), xa, C::kThreads);
-      slab_store_n<C::kPerB>(sb(0), xb, C::kThreads);
-      load(1, xa, xb);
-      __syncthreads();
+    // each slab's loads are issued SETS slabs before its LDS store (set and
+    // stage indices are compile-time constants after unrolling)
+    uint4 xa[SETS][C::kPerA], xb[SETS][C::kPerB];
 #pragma unroll
-      for (int s = 0; s < NS; ++s) {
-        compute(s & 1);
-        if (s + 1 < NS) {
-          slab_store_n<C::kPerA>(sa((s + 1) & 1), xa, C::kThreads);
-          slab_store_n<C::kPerB>(sb((s + 1) & 1), xb, C::kThreads);
-          load(s + 2, xa, xb);
-        }
-        __syncthreads();
-      }
-      return true;
-    } else {
-      // three register sets, so each slab's loads are issued three slabs
-      // before its LDS store (set and stage indices are compile-time
-      // constants after unrolling)
-      uint4 xa[3][C::kPerA], xb[3][C::kPerB];
-#pragma unroll
-      for (int u = 0; u < 3; ++u) load(u, xa[u], xb[u]);
-      if (!go_on()) return false;
-      slab_store_n<C::kPerA>(sa(0), xa[0], C::kThreads);
-      slab_store_n<C::kPerB>(sb(0), xb[0], C::kThreads);
-      load(3, xa[0], xb[0]);
-      __syncthreads();
-#pragma unroll
-      for (int s = 0; s < NS; ++s) {
-        compute(s & 1);
-        if (s + 1 < NS) {
-          const int u = (s + 1) % 3;
-          slab_store_n<C::kPerA>(sa((s + 1) & 1), xa[u], C::kThreads);
-          slab_store_n<C::kPerB>(sb((s + 1) & 1), xb[u], C::kThreads);
-          load(s + 4, xa[u], xb[u]);
-        }
-        __syncthreads();
-      }
-      return true;
-    }
-  }
-  const int S = (kdim + kBK - 1) / kBK;
-  uint4 a0[C::kPerA], b0[C::kPerB], a1[C::kPerA], b1[C::kPerB];
-  slab_load_n<C::kPerA>(rsA, ra, ld, 0, kdim, a0, C::kThreads);
-  slab_load_n<C::kPerB>(rsB, rb, ld, 0, kdim, b0, C::kThreads);
-  slab_load_n<C::kPerA>(rsA, ra, ld, kBK, kdim, a1, C::kThreads);
-  slab_load_n<C::kPerB>(rsB, rb, ld, kBK, kdim, b1, C::kThreads);
-  // the caller may stop here (its check's own loads overlap the first slabs')
-  if (!go_on()) return false;
-  slab_store_n<C::kPerA>(sa(0), a0, C::kThreads);
-  slab_store_n<C::kPerB>(sb(0), b0, C::kThreads);
-  slab_load_n<C::kPerA>(rsA, ra, ld, 2 * kBK, kdim, a0, C::kThreads);
-  slab_load_n<C::kPerB>(rsB, rb, ld, 2 * kBK, kdim, b0, C::kThreads);
-  __syncthreads();
-#pragma unroll
-  for (int s = 0; s < (NS > 0 ? NS : S); s += 2) {
-    // even slab s from stage 0; slab s + 1 (a1/b1) goes to stage 1
-    compute(0);
-    slab_store_n<C::kPerA>(sa(1), a1, C::kThreads);
-    slab_store_n<C::kPerB>(sb(1), b1, C::kThreads);
-    slab_load_n<C::kPerA>(rsA, ra, ld, (s + 3) * kBK, kdim, a1, C::kThreads);
-    slab_load_n<C::kPerB>(rsB, rb, ld, (s + 3) * kBK, kdim, b1, C::kThreads);
+    for (int u = 0; u < SETS; ++u) load(u, xa[u], xb[u]);
+    if (!go_on()) return false;
+    slab_store_n<C::kPerA>(sa(0), xa[0], C::kThreads);
+    slab_store_n<C::kPerB>(sb(0), xb[0], C::kThreads);
+    load(SETS, xa[0], xb[0]);
     __syncthreads();
-    if (s + 1 >= S) break;
-    // odd slab s + 1 from stage 1; slab s + 2 (a0/b0) goes to stage 0
-    compute(1);
+#pragma unroll
+    for (int s = 0; s < NS; ++s) {
+      compute(s & 1);
+      if (s + 1 < NS) {
+        const int u = (s + 1) % SETS;
+        slab_store_n<C::kPerA>(sa((s + 1) & 1), xa[u], C::kThreads);
+        slab_store_n<C::kPerB>(sb((s + 1) & 1), xb[u], C::kThreads);
+        load(s + 1 + SETS, xa[u], xb[u]);
+      }
+      __syncthreads();
+    }
+  } else {
+    uint4 a0[C::kPerA], b0[C::kPerB], a1[C::kPerA], b1[C::kPerB];
+    slab_load_n<C::kPerA>(rsA, ra, ld, 0, kdim, a0, C::kThreads);
+    slab_load_n<C::kPerB>(rsB, rb, ld, 0, kdim, b0, C::kThreads);
+    slab_load_n<C::kPerA>(rsA, ra, ld, kBK, kdim, a1, C::kThreads);
+    slab_load_n<C::kPerB>(rsB, rb, ld, kBK, kdim, b1, C::kThreads);
+    // the caller may stop here (its check's own loads overlap the first slabs')
+    if (!go_on()) return false;
     slab_store_n<C::kPerA>(sa(0), a0, C::kThreads);
     slab_store_n<C::kPerB>(sb(0), b0, C::kThreads);
-    slab_load_n<C::kPerA>(rsA, ra, ld, (s + 4) * kBK, kdim, a0, C::kThreads);
-    slab_load_n<C::kPerB>(rsB, rb, ld, (s + 4) * kBK, kdim, b0, C::kThreads);
+    slab_load_n<C::kPerA>(rsA, ra, ld, 2 * kBK, kdim, a0, C::kThreads);
+    slab_load_n<C::kPerB>(rsB, rb, ld, 2 * kBK, kdim, b0, C::kThreads);
     __syncthreads();
+#pragma unroll
+    for (int s = 0; s < S; s += 2) {
+      // even slab s from stage 0; slab s + 1 (a1/b1) goes to stage 1
+      compute(0);
+      slab_store_n<C::kPerA>(sa(1), a1, C::kThreads);
+      slab_store_n<C::kPerB>(sb(1), b1, C::kThreads);
+      slab_load_n<C::kPerA>(rsA, ra, ld, (s + 3) * kBK, kdim, a1, C::kThreads);
+      slab_load_n<C::kPerB>(rsB, rb, ld, (s + 3) * kBK, kdim, b1, C::kThreads);
+      __syncthreads();
+      if (s + 1 >= S) break;
+      // odd slab s + 1 from stage 1; slab s + 2 (a0/b0) goes to stage 0
+      compute(1);
+      slab_store_n<C::kPerA>(sa(0), a0, C::kThreads);
+      slab_store_n<C::kPerB>(sb(0), b0, C::kThreads);
+      slab_load_n<C::kPerA>(rsA, ra, ld, (s + 4) * kBK, kdim, a0, C::kThreads);
+      slab_load_n<C::kPerB>(rsB, rb, ld, (s + 4) * kBK, kdim, b0, C::kThreads);
+      __syncthreads();
+    }
   }
   return true;
 }

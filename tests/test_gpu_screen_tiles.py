@@ -75,6 +75,18 @@ def test_unrolled_dims_parity(lam, policy, dim):
     assert abs(info.delta_hat_run - ref["delta_hat"]) <= 1e-12
 
 
+@pytest.mark.parametrize("dim", [32, 96, 160, 640, 1056, 1600, 4096])
+@pytest.mark.parametrize("policy", ["large", "small"])
+def test_every_dim_parity(lam, policy, dim):
+    """Dimensions of half a slab, of whole slabs and a half, of an odd number of
+    slabs and of more than are unrolled, in both tiles, with ragged row counts."""
+    x = synth.subset_ingest(seed=dim, n=2100, n_traj=50, d=dim)["x"]
+    ref = dedup.greedy(x, 0.95, block=512)
+    rep, info = _ingest(lam, _ctx(lam, policy), x, 0.95, 1111)
+    assert np.array_equal(rep, ref["rep"])
+    assert abs(info.delta_hat_run - ref["delta_hat"]) <= 1e-12
+
+
 @pytest.mark.parametrize("policy", ["large", "small"])
 def test_d1024_parity(lam, policy):
     """D = 1,024 (16 slabs) on a clustered stream of 9,000 rows, both tiles."""
