@@ -78,3 +78,45 @@ def test_large_filter_ties_by_id(lam, k):
     ts, ti = score.topk(S, np.arange(n), k)
     assert np.array_equal(gi.cpu().numpy(), ti)
     assert np.all(np.abs(gs.cpu().numpy().astype(np.float64) - ts) <= TOL)
+
+
+@pytest.mark.parametrize("d,bits", [(1024, 10), (1024, 12), (256, 13), (256, 16), (256, 22)])
+def test_large_filter_fp16_widths(lam, d, bits):
+    """Codes that use the whole of an even or odd width above 8 bits (the fp16
+    operands), and codes of more than 12 bits (scanned without their low bits),
+    on the large tile with a ragged last query tile."""
+    rng = np.random.default_rng(d + bits)
+    n, nq = 70001, 1000
+    assert _large(nq, n)
+    x = synth.unit_rows(rng, n, d).astype(np.float32)
+    s = _store_from_rows(lam, x)
+    eps = float(np.abs(x).max()) / (2.0 ** bits - 1.5)
+    assert s.quantize(eps).bits == bits
+    c = qeps.codes(x, eps).reshape(n, -1)
+    assert np.abs(c).max() > 2 ** (bits - 2)
+    q = synth.unit_rows(rng, nq, d)
+    q[::2] = synth.members(rng, x[rng.choice(n, nq // 2)].astype(np.float64), rng.uniform(0.5, 0.99, nq // 2))
+    q = q.astype(np.float32)
+    gs, gi, _ = s.score_topk(_dev(q), 10)
+    pick = np.concatenate([np.arange(0, nq, 17), [nq - 1]])
+    _compare(gs.cpu().numpy()[pick], gi.cpu().numpy()[pick], c, np.arange(n), q[pick], eps, 10)
+
+
+@pytest.mark.parametrize("bits", [8, 10])
+@pytest.mark.parametrize("n", [200001, 1100003])
+def test_many_sample_entries(lam, n, bits):
+    """At k = 64 the sample grows with the store: past 1,024 entries per query
+    keys are folded onto a lane's registers (200,001 rows: 1,564 entries), past
+    2,048 tiles the tiles onto entries (1,100,003 rows: 2,149 tiles)."""
+    rng = np.random.default_rng(n + bits)
+    d, k, nq = 32, 64, 150
+    x = synth.unit_rows(rng, n, d).astype(np.float32)
+    s = _store_from_rows(lam, x)
+    assert s.info().size == n
+    eps = float(np.abs(x).max()) / (2.0 ** bits - 1.5)
+    assert s.quantize(eps).bits == bits
+    q = synth.unit_rows(rng, nq, d).astype(np.float32)
+    gs, gi, _ = s.score_topk(_dev(q), k)
+    pick = np.concatenate([np.arange(0, nq, 9), [nq - 1]])
+    c = qeps.codes(x, eps).reshape(n, -1)
+    _compare(gs.cpu().numpy()[pick], gi.cpu().numpy()[pick], c, np.arange(n), q[pick], eps, k)
