@@ -6,7 +6,7 @@ import numpy as np
 import pytest
 
 import synth
-from oracle import qeps
+from oracle import qeps, score
 from test_gpu_score import _compare, _dev, _flip_store, _store_from_rows
 
 pytestmark = pytest.mark.gpu
@@ -78,6 +78,28 @@ def test_wide_codes_scan(lam, d, n, bits, absmax):
     _compare(gs[keep], gi[keep], c, np.arange(n), q[keep], eps, 20)
 
 
+def _rows_above(q, c, eps, k):
+    """Per query, the rows that the sample tells of above the byte scan's
+    threshold, by the rule that chooses between the scans (past a limit, 256 in a
+    launch of fewer than 1,024 tiles and 1,024 in others, the query's group of 256
+    takes the fp16 scan), from binary64 scores."""
+    q = q.astype(np.float64)
+    n, d = c.shape
+    R = np.sqrt(((c * (2 * eps)) ** 2).sum(1).max()) + eps * np.sqrt(d)
+    mx = np.abs(q).max(1, keepdims=True)
+    e = 14 - np.floor(np.log2(mx))
+    h = (q * 2.0 ** e).astype(np.float16) * 2.0 ** -e
+    v = np.rint(q / (mx / 127)) * (mx / 127)
+    qn, dh, db = (np.linalg.norm(a, axis=1) for a in (q, q - h, q - v))
+    err = (dh + (2 * (d + 64) * 2.0 ** -24 + 2.0 ** -21) * (qn + dh) + db + 2.0 ** -21 * (qn + db)) * R
+    tiles = min(n // 128, -(-max(4096, -(-k * n // 256)) // 128))
+    best = score.scores(q, c[:tiles * 128], eps).reshape(len(q), tiles * 2, 8, 2, 4).max(axis=(2, 4))
+    best = best.reshape(len(q), -1)                       # each entry the best of 32 rows
+    kth = np.sort(best, axis=1)[:, -k]
+    f = (best >= (kth - err)[:, None]).mean(1)
+    return -np.log(np.maximum(1 - f, 1e-6)) * n / 32
+
+
 @pytest.mark.parametrize("kind", ["gaussian", "spiky", "concentrated"])
 @pytest.mark.parametrize("d,n,nq,bits,absmax", [
     (96, 4225, 130, 3, None),      # a partly empty slab of bytes
@@ -106,6 +128,13 @@ def test_byte_scan(lam, kind, d, n, nq, bits, absmax):
     q = q.astype(np.float32)
     gs, gi, _ = s.score_topk(_dev(q), 10)
     c = qeps.codes(x, eps).reshape(n, -1)
+    # the scan that each group of 256 queries takes, from inputs clear of the limit
+    above = _rows_above(q, c, eps, 10)
+    limit = 1024 if -(-nq // 128) * -(-n // 128) >= 1024 else 256
+    above = np.array([above[g:g + 256].max() for g in range(0, nq, 256)])
+    fp16 = {("spiky", 768): [True] * 5 + [False] * 4, ("concentrated", 768): [True] * 9,
+            ("concentrated", 160): [True, False], ("concentrated", 128): [True]}.get((kind, d), [False] * len(above))
+    assert np.all(above[fp16] > 1.4 * limit) and np.all(above[np.logical_not(fp16)] < limit / 1.4)
     pick = np.unique(np.concatenate([rng.choice(nq, min(nq, 60), replace=False), [0, nq - 1]]))
     _compare(gs.cpu().numpy()[pick], gi.cpu().numpy()[pick], c, np.arange(n), q[pick], eps, 10, tol=3e-5)
 
