@@ -286,8 +286,11 @@ lam_status lam_store_export(lam_ctx* ctx, const lam_store* store, int64_t* ids_d
  * the store size.  bound_dev (optional): eps * ||q_j||_1 rounded up to float32.
  * 1 <= k <= 64.  Codes of up to 22 bits are scored.  With codes of 13 bits and
  * more a query with |q| * 2^11 beyond float32 range counts as holding Inf.
- * Context scratch: 32 KB and 2 dim bytes per query, for at most 65,536 queries
- * at once.  ESTATE if the
+ * Context scratch, for at most 65,536 queries at once: per query 32 KB of
+ * candidates, 0.5 to 32 KB of sample entries (16 bytes per sampled tile of 128
+ * rows) and 2 dim bytes, or 3 dim for codes that fit 8 bits; for a store of at most
+ * 4,096 rows, 4 dim bytes (8 dim for codes of 13 bits and more) and 4 bytes per
+ * stored row.  ESTATE if the
  * store is not quantized (or has rows added since), or if its codes are wider
  * than 22 bits (quantize with a larger eps: 22 bits hold absmax / (2 eps) <
  * 2,097,151.5).  A query row holding NaN/Inf gets (NaN, -1) in all k slots

@@ -31,10 +31,6 @@ constexpr int kBK = 64;           // reduction slab per LDS stage (halves)
 constexpr int kLdk = kBK + 8;     // padded LDS row length (halves)
 constexpr int kWG = 256;          // threads per workgroup
 
-struct SlabRegs {
-  uint4 v[4];  // 4 x 16 B per thread = one 128 x 64 fp16 slab per workgroup
-};
-
 // Slab loads go through buffer resources: a descriptor bounds the tile's rows
 // in bytes and the hardware returns zeros for an offset past the bound, so a
 // chunk outside the tile costs no branch (an offset select instead).  Keeping
@@ -60,29 +56,6 @@ __device__ __forceinline__ float buf_f32(__amdgpu_buffer_rsrc_t rs, bool ok, int
 __device__ __forceinline__ uint4 chunk_load(__amdgpu_buffer_rsrc_t rs, bool ok, int64_t off_halves) {
   const uint32_t off = ok ? (uint32_t)(off_halves * 2) : kOffOOB;
   return __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(rs, off, 0, 0));
-}
-
-// Loads rows [0, rows) x halves [k0, k0 + 64) of a row-major fp16 matrix with
-// leading dimension ld (halves); rows past `rows` and columns past `kmax` read
-// as zero.  rows * ld * 2 must fit in 31 bits.
-__device__ __forceinline__ void slab_load(const _Float16* __restrict__ base, int rows, int64_t ld, int k0,
-                                          int kmax, SlabRegs& r) {
-  const __amdgpu_buffer_rsrc_t rs = tile_rsrc(base, rows, ld);
-#pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    const int c = threadIdx.x + kWG * q;
-    const int row = c >> 3, col = (c & 7) * 8;
-    r.v[q] = chunk_load(rs, row < rows && k0 + col < kmax, (int64_t)row * ld + k0 + col);
-  }
-}
-
-__device__ __forceinline__ void slab_store(_Float16* __restrict__ s, const SlabRegs& r) {
-#pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    const int c = threadIdx.x + kWG * q;
-    const int row = c >> 3, col = (c & 7) * 8;
-    *reinterpret_cast<uint4*>(s + row * kLdk + col) = r.v[q];
-  }
 }
 
 __device__ __forceinline__ half8 frag_load(const _Float16* __restrict__ s, int row0, int kk) {
@@ -114,6 +87,9 @@ struct Tile {
   static_assert(kChunksA % kThreads == 0 && kChunksB % kThreads == 0, "slab must split evenly");
 };
 
+// Loads rows [0, rows) x halves [k0, k0 + 64) of a row-major fp16 matrix with
+// leading dimension ld (halves) as N 16-byte pieces per thread; rows past `rows`
+// and columns past `kmax` read as zero.  rows * ld * 2 must fit in 31 bits.
 template <int N>
 __device__ __forceinline__ void slab_load_n(__amdgpu_buffer_rsrc_t rs, int rows, int64_t ld, int k0, int kmax,
                                             uint4 (&r)[N], int nthreads) {

@@ -3,9 +3,12 @@
 // the per-coordinate bound of Q_eps, Appendix "Rank invariance, in full").
 //
 // score(j, y) = s * sum_d q_j,d * code_y,d  (s = 2 eps), i.e. q_j . x_hat_y with
-// the exact dequantized row: a binary64 sum, rounded once to float32.
+// the exact dequantized row: a binary64 sum, rounded once to float32, in a store
+// of more than 4,096 rows; an fp32 sum of the query's fp16 hi and lo parts, of
+// every row, in a smaller one (k_dense).
 //
-// The matrix units find the few rows that can be in a query's top-k.  A scan
+// In a larger store the matrix units find the few rows that can be in a query's
+// top-k.  A scan
 // forms H, the score from fp16 operands: the query's fp16 part h (each query
 // scaled by a power of two 2^e_j, max |q| into [2^14, 2^15)) times the codes,
 // unpacked from their b-bit words straight into fp16 LDS slabs (no dequantized
@@ -29,8 +32,7 @@
 namespace lam {
 namespace {
 
-constexpr int kNoRow = 0x7fffffff;
-
+// (S_QLO shares a slot: a call takes the byte parts or, for a small store, the lo parts)
 enum ScoreScratch { S_QHI = 7, S_QMETA, S_PART, S_CAND, S_Q8, S_QLO = S_Q8 };
 
 enum QKind : int {
@@ -439,11 +441,11 @@ constexpr int64_t kFilterLargeMinTiles = 1024;   // large filter tiles from this
 // groups of 8 query tiles against every store tile, query tile fastest, each
 // XCD a contiguous range, so an XCD holds its query tiles in L2 while the codes
 // stream past.  Every row with H >= the query's threshold is appended to its
-// candidate buffer.  (120,001 rows x 300 queries at D = 384, 9-bit codes: 106
-// us in the former one-stage kernel with two waves' worth of loads in flight,
-// 81 us here; its sample pass 54 -> 16 us.  The run-time slab loop is as fast as
-// one unrolled for D = 768: 54 us at 23,969 rows x 1,024 queries, 2.30 ms at
-// 361,802 x 4,096, both as before.)
+// candidate buffer.  The tile loop's latency bounds the small launches: 1,024
+// queries x 23,969 rows x 768 at 8 bits take 53.8 us in fp16 (twelve slabs) and
+// 37.7 us in bytes (six); 300 x 120,001 x 384, 81.6 and 62.8 us (106 us in a
+// one-stage fp16 kernel with two waves' worth of loads in flight, whose sample
+// pass took 54 us, here 13).  4,096 x 361,802 x 768 in bytes: 2.04 ms.
 // kSample (FilterTile only): the sample pass of the threshold plan over store
 // tiles [0, tile_end) (all of them whole) instead: per query and tile, the best
 // H of each of the four lanes holding the query (disjoint sets of 32 rows) at
@@ -1776,7 +1778,7 @@ lam_status score_topk_impl(lam_ctx* ctx, const ScoreView& st, const float* q, in
     a.tile_end = large ? ntilesL : ntiles;
     const int64_t grid = (int64_t)a.nqt * a.tile_end;
     if (bytes) LAM_TRY((launch_filter<1, kFilterBytes>(b, large, grid, ctx->stream, a)));
-    else LAM_TRY((launch_filter<1, kFilter>(b, large, grid, ctx->stream, a)));
+    else LAM_TRY((launch_filter<9, kFilter>(b, large, grid, ctx->stream, a)));   // (codes of up to 8 bits fit bytes)
   }
   {  // 3. select and rescore
     ProfScope ps(ctx, "score_merge", prof);
@@ -1925,8 +1927,9 @@ lam_status score_certify(lam_ctx* ctx, const lam_store* st, const float* q, int6
   // error bound of the float32 score per unit of ||q||_1: kappa (A + eps).
   // It is stated for float32 sums of hi and lo query parts, and for codes of
   // more than 12 bits for the sums of their two halves (twice the terms, and
-  // sum |q'_d' x_hat'_d'| <= ||q||_1 (A + eps + 2^12 s)); the scores are
-  // binary64 sums rounded once, far inside it.
+  // sum |q'_d' x_hat'_d'| <= ||q||_1 (A + eps + 2^12 s)), which is what a store of
+  // at most 4,096 rows returns; the binary64 sums of a larger one, rounded once,
+  // are far inside it.
   const bool wide = st->q.bits > 12;
   const double Dt = (wide ? 2.0 : 1.0) * st->dim;
   const double u = std::ldexp(1.0, -24);

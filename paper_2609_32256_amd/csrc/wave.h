@@ -40,23 +40,6 @@ __device__ __forceinline__ uint32_t wave_max_u32(uint32_t v) {
   return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
 }
 
-__device__ __forceinline__ unsigned long long wave_max_u64(unsigned long long key) {
-  uint32_t lo = (uint32_t)key, hi = (uint32_t)(key >> 32);
-#define LAM_STEP(ctrl, rmask)                                                          \
-  {                                                                                    \
-    const uint32_t olo = (uint32_t)LAM_DPP_MOVE(lo, lo, ctrl, rmask);                  \
-    const uint32_t ohi = (uint32_t)LAM_DPP_MOVE(hi, hi, ctrl, rmask);                  \
-    const bool gt = ohi > hi || (ohi == hi && olo > lo);                               \
-    lo = gt ? olo : lo;                                                                \
-    hi = gt ? ohi : hi;                                                                \
-  }
-  LAM_WAVE_DPP_STEPS(LAM_STEP)
-#undef LAM_STEP
-  const uint32_t rlo = (uint32_t)__builtin_amdgcn_readlane((int)lo, 63);
-  const uint32_t rhi = (uint32_t)__builtin_amdgcn_readlane((int)hi, 63);
-  return ((unsigned long long)rhi << 32) | rlo;
-}
-
 __device__ __forceinline__ double wave_sum_f64(double v) {
 #define LAM_STEP(ctrl, rmask)                                                                     \
   {                                                                                               \
