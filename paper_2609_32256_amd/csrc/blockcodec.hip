@@ -411,6 +411,8 @@ lam_status block_encode(lam_ctx* ctx, lam_store* st, lam_block_stats* out) {
       LAM_HIP(hipGetLastError());
     }
     if (st->blk_data) LAM_TRY(pack());
+  } else {
+    LAM_HIP(hipMemsetAsync(st->blk_row_off, 0, sizeof(uint64_t), ctx->stream));   // (the call waits: it is never captured)
   }
   LAM_HIP(hipStreamSynchronize(ctx->stream));
   const uint64_t words = ctx->flags_host->blk_words;   // written by k_scan_add

@@ -161,3 +161,19 @@ def test_encoding_memory_and_regrowth(lam):
         words = int(ref["row_off"][-1])
         assert np.array_equal(d.cpu().numpy().view(np.uint32)[:words], ref["data"][:words])
         assert torch.equal(s.block_decode(), s.dequantize())
+
+
+def test_empty_store(lam):
+    """The encoding of an empty store has one row offset, 0, in memory that held
+    other rows before."""
+    n, dim = 4096, 64
+    a = lam.Store(dim, 1.0, n)
+    a.ingest(_dev(np.random.default_rng(5).uniform(-1, 1, (n, dim)).astype(np.float32)))
+    a.info()
+    del a
+    stores = [lam.Store(dim, 1.0, c) for c in (n * dim // 2 - 1, n * dim // 4 - 1, n * dim // 8 - 1)]
+    for s in stores:
+        s.quantize(1e-3)
+        assert s.block_encode()["rows"] == 0
+        w, ro, d = s.block_export()
+        assert w.numel() == 0 and d.numel() == 0 and ro.cpu().tolist() == [0]
