@@ -368,13 +368,14 @@ constexpr int kThrKeys = 16;   // keys per lane
 // The rows above the threshold from which the fp16 scan is the faster one, in a
 // launch of many 128 x 128 tiles and in one of fewer than kByteTiles (two for
 // each of the 512 places of the chip), where the candidates' stores and the
-// longer selection are not hidden behind other tiles.  Whole calls, fp16 against
-// bytes: 600 rows above in 720 tiles (178 queries x 46,046 rows x 1,024, top-20)
-// 93 : 104 us, in 360 tiles (64 queries) 79 : 98, in 1,440 tiles (512 queries)
-// 115 : 113, in 2,814 tiles (300 x 120,001 x 384, top-50) 134 : 114; 300 rows in
-// 469 tiles (128 x 60,000 x 128, top-20) 65 : 69; 1,000 rows in 782 tiles (64 x
-// 100,000 x 768) 86 : 103.  In 6,256 tiles (1,024 queries) bytes lead up to the
-// buffer's size: 1,500 rows 252 : 200, 3,000 rows 251 : 247.
+// longer selection are not hidden behind other tiles.  Whole calls, fp16 : bytes,
+// us.  512 to 1,024 rows above: in 360 tiles (64 queries x 46,046 rows x 1,024,
+// top-20) 79 : 98, 720 tiles (178 queries) 93 : 104, 782 (64 x 100,000 x 768) 85 :
+// 98, 1,440 (512 x 46,046 x 1,024) 115 : 113, 1,563 (16 x 200,000 x 768, top-64)
+// 147 : 118, 2,814 (300 x 120,001 x 384, top-50) 134 : 114.  256 to 512: 469 (128
+// x 60,000 x 128, top-20) 65 : 69, 2,827 (1 x 361,802 x 768) 156 : 116.  In 6,256
+// tiles (1,024 x 100,000 x 768) bytes still lead with 1,024 to 2,048 rows, 252 :
+// 200, and draw level towards the buffer's 4,096, 251 : 247.
 constexpr float kByteCands = 1024.0f, kByteCandsFew = 256.0f;
 constexpr int64_t kByteTiles = 1024;
 
