@@ -999,7 +999,8 @@ __global__ __launch_bounds__(kAdmitThreads) void k_lsh_admit(LshArgs a) {
   if (glead) note_margin(a.flags, mmin);
 }
 
-// The store's index as the append inserts into it.
+// The store's index as kept rows join it, in the append's workgroups (pos NULL)
+// or, from the positions that these leave in pos, in a launch of its own.
 struct LshInsert {
   const unsigned long long* ckey;   // band keys of the chunk's rows
   unsigned long long* sslot;
@@ -1007,7 +1008,36 @@ struct LshInsert {
   unsigned long long* srowkey;
   uint64_t smask;
   int nb;
+  int32_t* pos;                     // store position of each chunk row, -1 if it is not kept
 };
+
+// A workgroup of the append inserts its 16 rows' entries 1,024 at a time, each
+// step a chain of dependent device-wide accesses (about 5 us), so many bands go
+// to a launch that spreads them over the chip; in a large chunk that launch has
+// as many atomics to wait for, and the line lies higher.  Streams, us, inserted by
+// the append : by its own launch: 1,024-row calls, 96 bands 695 : 718 (12,000
+// rows), 128 733 : 760, 192 1,185 : 1,207, 256 1,432 : 1,450; 400-row calls, 64
+// bands 409 : 430 (4,000 rows), 96 485 : 483, 192 623 : 580; calls of 16 rows, 128
+// bands 385 : 357 (160 rows), 144 425 : 376, 192 490 : 412, 2,048 3,300 : 1,883; of
+// 47 rows, 256 bands 551 : 435, 384 1,066 : 838; of 64 rows, 4,096 bands 5,632 :
+// 3,566.
+constexpr int kMergedBands = 96, kMergedBandsLarge = 256, kMergedLargeRows = 1024;
+
+__device__ __forceinline__ void insert_entry(const LshInsert& ix, int nB, int row, int b, int pos) {
+  const unsigned long long h = ix.ckey[(int64_t)b * nB + row];
+  const int32_t e = pos * ix.nb + b;
+  ix.srowkey[e] = h;
+  index_insert(ix.sslot, ix.snext, ix.smask, h, e);
+}
+
+// Every entry of the chunk's kept rows, one thread each.
+__global__ __launch_bounds__(256) void k_lsh_insert(LshInsert ix, int nB) {
+  const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (t >= (int64_t)nB * ix.nb) return;
+  const int row = (int)(t / ix.nb), b = (int)(t % ix.nb);
+  const int p = ix.pos[row];
+  if (p >= 0) insert_entry(ix, nB, row, b, p);
+}
 
 // Empties the store's index, then (second kernel) puts back the entries of the
 // first rows of the store from their recorded band keys.
@@ -1706,8 +1736,9 @@ __device__ __forceinline__ void append_finish(const AppendArgs& a, uint32_t kept
 // store size at its start and adds its own kept count to the chunk's; the
 // last one to finish advances the store size.
 // LSH: the kept rows also join the store's band index, under the positions the
-// workgroup just resolved.  (As launches of their own, resolve, insertion and
-// append took 26 us for 1,024 rows of 768 in 96 bands.)
+// workgroup just resolved, or (many bands) leave these for k_lsh_insert.  (As
+// launches of their own, resolve, insertion and append took 26 us for 1,024 rows
+// of 768 in 96 bands.)
 constexpr int kAppendGroupThreads = kResolveThreads;
 constexpr int kAppendGroupRows = kAppendGroupThreads / 64;
 
@@ -1762,19 +1793,18 @@ __global__ __launch_bounds__(kAppendGroupThreads) void k_resolve_append(ResolveA
     }
     if constexpr (LSH) {
       const int row0 = (int)blockIdx.x * kAppendGroupRows;
-      for (int t = tid; t < (nres - row0) * ix.nb; t += T) {
-        const int row = row0 + t / ix.nb, b = t % ix.nb;
-        if (L.posv[row] < 0) continue;
-        const unsigned long long h = ix.ckey[(int64_t)b * nB + row];
-        const int32_t e = L.posv[row] * ix.nb + b;
-        ix.srowkey[e] = h;
-        index_insert(ix.sslot, ix.snext, ix.smask, h, e);
+      for (int t = tid; !ix.pos && t < (nres - row0) * ix.nb; t += T) {
+        const int row = row0 + t / ix.nb;
+        if (L.posv[row] >= 0) insert_entry(ix, nB, row, t % ix.nb, L.posv[row]);
       }
     }
     // kept rows among this workgroup's own
     const int first = (int)blockIdx.x * kAppendGroupRows;
     const uint64_t k = __ballot(lane < nres - first && L.st[first + lane] == 1);
     kept_here = (uint32_t)__popcll(k);
+  }
+  if constexpr (LSH) {
+    if (ix.pos && lane == 0 && r < nB) ix.pos[r] = skip ? -1 : L.posv[r];
   }
   __shared__ double part[T / 64];
   __shared__ uint32_t apart[T / 64], hpart[T / 64];
@@ -1973,7 +2003,7 @@ lam_status dedup_ingest(lam_ctx* ctx, lam_store* st, const float* x, int64_t n, 
   // scratch
   LAM_TRY(ctx->scratch[S_X16].ensure((size_t)n * D * 2));
   LAM_TRY(ctx->scratch[S_ROWF].ensure((size_t)n * 8));
-  const size_t chunk_bytes = (size_t)CH * 4 * 3 + 8 + sizeof(ChunkCounters) + 256;
+  const size_t chunk_bytes = (size_t)CH * 4 * 4 + 8 + sizeof(ChunkCounters) + 256;
   LAM_TRY(ctx->scratch[S_CHUNK].ensure(chunk_bytes));
   LAM_TRY(ctx->scratch[S_BITMAP].ensure((size_t)CH * W * 8));
   if (want_max) LAM_TRY(ctx->scratch[S_G].ensure((size_t)CH * CH * 4));
@@ -1984,7 +2014,8 @@ lam_status dedup_ingest(lam_ctx* ctx, lam_store* st, const float* x, int64_t n, 
   int32_t* firstHit = reinterpret_cast<int32_t*>(cb);
   uint32_t* hasEdge = reinterpret_cast<uint32_t*>(cb + (size_t)CH * 4);
   uint32_t* maxcos = reinterpret_cast<uint32_t*>(cb + (size_t)CH * 8);
-  ChunkCounters* cc = reinterpret_cast<ChunkCounters*>(cb + (((size_t)CH * 12 + 7) & ~(size_t)7));
+  int32_t* pos = reinterpret_cast<int32_t*>(cb + (size_t)CH * 12);   // (banded stores of many bands)
+  ChunkCounters* cc = reinterpret_cast<ChunkCounters*>(cb + (((size_t)CH * 16 + 7) & ~(size_t)7));
   uint64_t* bitmap = ctx->scratch[S_BITMAP].as<uint64_t>();
   float* G = want_max ? ctx->scratch[S_G].as<float>() : nullptr;
 
@@ -2001,7 +2032,7 @@ lam_status dedup_ingest(lam_ctx* ctx, lam_store* st, const float* x, int64_t n, 
     la.sfirst = reinterpret_cast<int32_t*>(lb + ce * 8);
     la.bfirst = reinterpret_cast<int32_t*>(lb + ce * 12);
     la.bnext = reinterpret_cast<int32_t*>(lb + ce * 16);
-    ix = LshInsert{la.ckey, st->lsh_slot, st->lsh_next, st->lsh_rowkey, st->lsh_slots - 1, nb};
+    ix = LshInsert{la.ckey, st->lsh_slot, st->lsh_next, st->lsh_rowkey, st->lsh_slots - 1, nb, nullptr};
     la.xs = st->x32;
     la.xs16 = st->x16;
     la.hns = st->hn;
@@ -2160,13 +2191,20 @@ lam_status dedup_ingest(lam_ctx* ctx, lam_store* st, const float* x, int64_t n, 
       AppendArgs aa{xc, x16, hnc + c0, etc + c0, c0, D, st->x32, st->x16, st->hn, st->et, st->ids,
                     ctx->flags_dev, cc, meta, n, last_chunk ? 1 : 0, async ? 1 : 0,
                     (last_chunk && !async) ? ctx->flags_host_dev : nullptr};
+      ix.pos = lsh && ix.nb > (nB >= kMergedLargeRows ? kMergedBandsLarge : kMergedBands) ? pos : nullptr;
       {
-        // resolve, largest cosines, append and index insertion in one launch
+        // resolve, largest cosines, append and (few bands) index insertion in one launch
         ProfScope ps(ctx, "dedup_resolve_append");
         auto* kernel = lsh ? k_resolve_append<true> : k_resolve_append<false>;
         hipLaunchKernelGGL(kernel, dim3((unsigned)((nB + kAppendGroupRows - 1) / kAppendGroupRows)),
                            dim3(kAppendGroupThreads), 0, ctx->stream, ra, aa, ix, nB,
                            want_max ? max_cos + c0 : nullptr, maxcos, G);
+        LAM_HIP(hipGetLastError());
+      }
+      if (ix.pos) {
+        ProfScope ps(ctx, "lsh_insert");
+        hipLaunchKernelGGL(k_lsh_insert, dim3((unsigned)(((int64_t)nB * ix.nb + 255) / 256)), dim3(256), 0, ctx->stream,
+                           ix, nB);
         LAM_HIP(hipGetLastError());
       }
     }

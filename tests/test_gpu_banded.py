@@ -169,6 +169,49 @@ def test_table_edges(lam, n, d, r, splits):
     assert abs(s.info().delta_hat_run - ref["delta_hat"]) <= 1e-12
 
 
+@pytest.mark.parametrize("d,r", [(512, 4), (544, 4), (4096, 8)])
+def test_many_bands(lam, d, r):
+    """Bands on both sides of the 128 up to which the append's workgroups insert
+    a row's entries (128, 136 and 512):
+    calls of 16 rows, of one and of more than a workgroup's; a call that holds a
+    NaN in between, which must leave the index as it was."""
+    x = _rows(seed=d + r, n=700, d=d)
+    eps = 0.25 / np.sqrt(d)
+    ref = lsh.greedy_lsh(x, 0.95, eps, r)
+    s = lam.Store(d, 0.95, 1400, eps_band=eps, band_width=r)
+    xd = torch.from_numpy(x).cuda()
+    bad = xd[150:450].clone()
+    bad[299, 3] = float("nan")
+    reps = []
+    for a, b in [(0, 16), (16, 17), (17, 150), (150, 650), (650, 700)]:
+        if a == 150:
+            s.ingest(bad, sync=False)
+            with pytest.raises(lam.LamError):
+                s.info()
+        reps.append(s.ingest(xd[a:b])[0])
+    assert np.array_equal(torch.cat(reps).cpu().numpy(), ref["rep"])
+    assert np.array_equal(s.ids().cpu().numpy(), ref["kept"])
+
+
+@pytest.mark.parametrize("d,r", [(512, 2), (544, 2)])
+def test_many_bands_of_a_large_call(lam, d, r):
+    """256 and 272 bands, calls of 1,024 rows (up to 256 bands inserted by the
+    append) and of 1,023: the decisions of the screened store, since one row in
+    four is a copy moved by less than the exact test's radius and the step is
+    coarse enough for every such pair to share a band."""
+    rng = np.random.default_rng(d)
+    x = synth.unit_rows(rng, 4094, d)
+    x[1::4] = synth.members(rng, x[0::4][:x[1::4].shape[0]], rng.uniform(0.96, 0.999, x[1::4].shape[0]))
+    x = x.astype(np.float32)
+    eps = 1.0 / np.sqrt(d)
+    xd = torch.from_numpy(x).cuda()
+    b = lam.Store(d, 0.95, 4094, eps_band=eps, band_width=r)
+    e = lam.Store(d, 0.95, 4094)
+    for i, j in [(0, 1024), (1024, 2047), (2047, 3071), (3071, 4094)]:
+        assert torch.equal(b.ingest(xd[i:j])[0], e.ingest(xd[i:j])[0])
+    assert torch.equal(b.ids(), e.ids()) and b.info().delta_hat_run == e.info().delta_hat_run
+
+
 def test_invalid_input_of_a_call_that_does_not_wait(lam):
     """A call that does not wait and holds a NaN leaves the store and its band
     index unchanged; the next call that waits reports it once."""
