@@ -21,6 +21,7 @@
 // k-th best H into a threshold; the rows above it are scored exactly and the k
 // best by (score desc, id asc) are the answer.  See score_topk_impl for the
 // plan.
+#include <algorithm>
 #include <cmath>
 #include <cstring>
 #include <mutex>
@@ -358,31 +359,40 @@ __device__ __forceinline__ double floor_score(uint32_t T) {
 // entries several share a key as their maximum: the k-th best key is then
 // still the score of k distinct rows, only a little lower.
 // With a byte scan to follow (coarse not NULL) also its threshold, T - err -
-// err8, and the choice between the two scans: if the entries above it tell of
-// more than `most` rows of the store above it (a share f of entries, each the
-// best of `per` rows, means n (-ln(1 - f)) / per rows), the query's group of
-// kPrecQueries takes the fp16 scan.  That happens where scores lie close
+// err8, and the choice between the two scans: if more than most_above keys reach
+// it (see byte_scan_keys), the query's group of kPrecQueries takes the fp16 scan.  That happens where scores lie close
 // together for the byte scan's error (8e-3 ||q|| R for a Gaussian query), or
 // where single entries dominate the query, which widens that error.
 constexpr int kThrKeys = 16;   // keys per lane
-// The rows above the threshold from which the fp16 scan is the faster one, in a
-// launch of many 128 x 128 tiles and in one of fewer than kByteTiles (two for
-// each of the 512 places of the chip), where the candidates' stores and the
-// longer selection are not hidden behind other tiles.  Whole calls, fp16 : bytes,
-// us.  512 to 1,024 rows above: in 360 tiles (64 queries x 46,046 rows x 1,024,
-// top-20) 79 : 98, 720 tiles (178 queries) 93 : 104, 782 (64 x 100,000 x 768) 85 :
-// 98, 1,440 (512 x 46,046 x 1,024) 115 : 113, 1,563 (16 x 200,000 x 768, top-64)
-// 147 : 118, 2,814 (300 x 120,001 x 384, top-50) 134 : 114.  256 to 512: 469 (128
-// x 60,000 x 128, top-20) 65 : 69, 2,827 (1 x 361,802 x 768) 156 : 116.  In 6,256
-// tiles (1,024 x 100,000 x 768) bytes still lead with 1,024 to 2,048 rows, 252 :
-// 200, and draw level towards the buffer's 4,096, 251 : 247.
-constexpr float kByteCands = 1024.0f, kByteCandsFew = 256.0f;
-constexpr int64_t kByteTiles = 1024;
+// The rows above the threshold from which the fp16 scan is the faster one, by the
+// launch's 128 x 128 tiles: where few tiles run, the candidates' stores and the
+// longer selection are not hidden behind other tiles; where many do, bytes lead
+// until the candidates near the buffer's size.  Whole calls, fp16 : bytes, us, at
+// 8-bit codes (queries x rows x dimension, top-k, rows above):
+//   196 tiles  128 x 25,000 x 1,024  k 10, 233  62 : 60    k 20, 348  68 : 75
+//   469        128 x 60,000 x 768    k  1,  60  54 : 52    k 10, 520  70 : 75
+//   588        300 x 25,000 x 1,024  k 10, 233  74 : 69    k 20, 397  82 : 87
+//   939        300 x 40,000 x 1,024  k 10, 373  84 : 78    k 20, 737  93 : 101
+//   1,565      600 x 40,000 x 768    k 10, 399  95 : 83    k 50, 846 125 : 128
+//   1,565      600 x 40,000 x 384    k 10, 272  74 : 70    k 20, 454  81 : 87
+//   2,346      300 x 100,000 x 768   k  1, 176 105 : 82    k 10, 771 119 : 113
+//   3,910      600 x 100,000 x 1,024 k  1, 308 195 : 137   k 10, 1,066 220 : 179
+//   6,256      1,024 x 100,000 x 768, 1,024 to 2,048 rows 252 : 200, about 3,500 251 : 247
+// Over 228 such calls this rule costs 0.3 % against the better scan of each, bytes
+// throughout 3.0 %, fp16 throughout 4.2 %.
+constexpr double byte_scan_limit(int64_t tiles) { return tiles < 768 ? 256.0 : tiles < 2048 ? 448.0 : 2048.0; }
 
-__global__ __launch_bounds__(256) void k_sample_thr(int64_t nq, int64_t n, int entries, int folded, int k,
+// The same as a number of the sample's keys: a share f of keys above a threshold,
+// each the best of `per` rows, means n (-ln(1 - f)) / per rows above it.  (Below
+// nkeys: when every key is above, perhaps every row is.)
+int byte_scan_keys(int64_t tiles, int64_t n, int nkeys, double per) {
+  return std::min(nkeys - 1, (int)(nkeys * -std::expm1(-byte_scan_limit(tiles) * per / (double)n)));
+}
+
+__global__ __launch_bounds__(256) void k_sample_thr(int64_t nq, int entries, int folded, int k,
                                                     const float* __restrict__ ps, const QMeta* __restrict__ meta,
                                                     float* __restrict__ thr, uint32_t* __restrict__ coarse,
-                                                    float most, float per) {
+                                                    int most_above) {
   const int lane = threadIdx.x & 63;
   const int64_t j = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
   if (j >= nq) return;
@@ -407,12 +417,9 @@ __global__ __launch_bounds__(256) void k_sample_thr(int64_t nq, int64_t n, int e
   const uint32_t o8 = f2ord(t8);
 #pragma unroll
   for (int r = 0; r < kThrKeys; ++r) above += __popcll(__ballot(key[r] >= o8));
-  const int nkeys = min(entries, 64 * kThrKeys);
-  const float f = (float)above / (float)nkeys;
-  const float rows = -logf(fmaxf(1.0f - f, 1e-6f)) * ((float)n / per) * ((float)nkeys / (float)entries);
   // (a plain store: every writer stores the same; atomics on one word took 10 us
   // when all of 1,024 queries set it)
-  if (lane == 0 && m.kind == kScanned && rows > most) coarse[j / kPrecQueries] = 1u;
+  if (lane == 0 && m.kind == kScanned && above > most_above) coarse[j / kPrecQueries] = 1u;
 }
 
 // ------------------------------------------------------------------ filter pass on the screen's pipeline
@@ -1763,10 +1770,11 @@ lam_status score_topk_impl(lam_ctx* ctx, const ScoreView& st, const float* q, in
                          reinterpret_cast<uint32_t*>(part_s), ne);
     }
     LAM_TRY((launch_filter<1, kSample>(b, false, (int64_t)nqt * stiles, ctx->stream, a)));
-    hipLaunchKernelGGL(k_sample_thr, dim3((unsigned)((nq + 3) / 4)), dim3(256), 0, ctx->stream, nq, n, (int)entries,
+    const int nkeys = (int)std::min<int64_t>(entries, 64 * kThrKeys);
+    hipLaunchKernelGGL(k_sample_thr, dim3((unsigned)((nq + 3) / 4)), dim3(256), 0, ctx->stream, nq, (int)entries,
                        folded ? 1 : 0, k, part_s, qmeta, thr, bytes ? coarse : nullptr,
-                       (int64_t)nqt * ntiles >= kByteTiles ? kByteCands : kByteCandsFew,
-                       32.0f * (float)stiles / (float)sample_tiles);
+                       byte_scan_keys((int64_t)nqt * ntiles, n, nkeys,
+                                      32.0 * (double)stiles / (double)sample_tiles * (double)entries / nkeys));
     LAM_HIP(hipGetLastError());
   }
   {  // 2. full scan with the thresholds: 256 x 256 tiles when the launch holds

@@ -80,9 +80,9 @@ def test_wide_codes_scan(lam, d, n, bits, absmax):
 
 def _rows_above(q, c, eps, k):
     """Per query, the rows that the sample tells of above the byte scan's
-    threshold, by the rule that chooses between the scans (past a limit, 256 in a
-    launch of fewer than 1,024 tiles and 1,024 in others, the query's group of 256
-    takes the fp16 scan), from binary64 scores."""
+    threshold, by the rule that chooses between the scans (past a limit that
+    grows with the launch's tiles the query's group of 256 takes the fp16 scan),
+    from binary64 scores."""
     q = q.astype(np.float64)
     n, d = c.shape
     R = np.sqrt(((c * (2 * eps)) ** 2).sum(1).max()) + eps * np.sqrt(d)
@@ -130,7 +130,7 @@ def test_byte_scan(lam, kind, d, n, nq, bits, absmax):
     c = qeps.codes(x, eps).reshape(n, -1)
     # the scan that each group of 256 queries takes, from inputs clear of the limit
     above = _rows_above(q, c, eps, 10)
-    limit = 1024 if -(-nq // 128) * -(-n // 128) >= 1024 else 256
+    limit = 2048 if -(-nq // 128) * -(-n // 128) >= 2048 else 256
     above = np.array([above[g:g + 256].max() for g in range(0, nq, 256)])
     fp16 = {("spiky", 768): [True] * 5 + [False] * 4, ("concentrated", 768): [True] * 9,
             ("concentrated", 160): [True, False], ("concentrated", 128): [True]}.get((kind, d), [False] * len(above))
