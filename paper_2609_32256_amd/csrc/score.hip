@@ -453,7 +453,7 @@ constexpr int64_t kFilterLargeMinTiles = 1024;   // large filter tiles from this
 // queries x 23,969 rows x 768 at 8 bits take 53.8 us in fp16 (twelve slabs) and
 // 37.7 us in bytes (six); 300 x 120,001 x 384, 81.6 and 62.8 us (106 us in a
 // one-stage fp16 kernel with two waves' worth of loads in flight, whose sample
-// pass took 54 us, here 13).  4,096 x 361,802 x 768 in bytes: 2.04 ms.
+// pass took 54 us, here 13).  4,096 x 361,802 x 768 in bytes: 1.68 ms.
 // kSample (FilterTile only): the sample pass of the threshold plan over store
 // tiles [0, tile_end) (all of them whole) instead: per query and tile, the best
 // H of each of the four lanes holding the query (disjoint sets of 32 rows) at
@@ -1067,7 +1067,7 @@ __global__ __launch_bounds__(kRescoreThreads) void k_select_rescore(
 // item and 885 rows per range: 0.39, 1.01 and 13.9 ms; sorted per-lane lists
 // behind an fp16 scan of the whole 128-query tile: 0.99, 1.27 and 9.1 ms).  128
 // flagged of 300 against 60,000 x 384, top-50: 0.84 ms (2.45; lists 40 ms); 1,000
-// of 1,000 against 30,000 x 768: 2.0 ms (19; lists 1.35 ms, the one case found
+// of 1,000 against 30,000 x 768: 1.9 ms (19; lists 1.35 ms, the one case found
 // where their fp16 products were faster than the binary64 ones here).
 constexpr int kExactRows = 4;      // rows per slot and step
 constexpr int kExactQueries = 4;   // flagged queries per work item

@@ -304,8 +304,8 @@ def test_rescoring_restores_the_exact_order(lam, k, d):
 @pytest.mark.parametrize("d", [64, 768])
 def test_rescoring_cap_falls_back_exactly(lam, d):
     """600 rows tied with row 200 (identical codes) sit within the rescoring
-    band of query 2 (row 200's codes win it): more than the rescoring cap, so
-    the query is redone by the exact pass; the k best are the tied rows in id
+    band of query 2 (row 200's codes win it): many rows to rescore, though fewer
+    than the 1,024 that are sorted at once; the k best are the tied rows in id
     order."""
     x, q = _flip_store(d=d, group=600)
     s = _store_from_rows(lam, x)
@@ -326,7 +326,7 @@ def test_selection_over_many_candidates(lam, near, k, d):
     directions; after them each query has `near` rows whose cosines with it
     run from 0.5 to 0.99, all above the sample's k-th score, so the filter
     pass hands the selection about `near` candidates per query (several per
-    lane of its per-lane lists), and the top-k must match the oracle."""
+    lane), and the top-k must match the oracle."""
     rng = np.random.default_rng(21)
     nq = 4
     q = synth.unit_rows(rng, nq, d)

@@ -41,8 +41,9 @@ def test_large_filter_odd_width(lam, k):
 
 
 def test_large_filter_d1024_even_width(lam):
-    """70,000 rows at D = 1,024, codes of 10 bits (absmax 1 declared), 1,000
-    queries (four query tiles, the last one ragged)."""
+    """70,000 rows at D = 1,024, codes of 10 bits (absmax 1 declared) that fit 8
+    and are scanned as bytes, 1,000 queries (four query tiles, the last one
+    ragged)."""
     rng = np.random.default_rng(42)
     n, d, nq = 70000, 1024, 1000
     assert _large(nq, n)

@@ -1,5 +1,6 @@
-"""GPU parity of scoring for codes of 13 to 22 bits (the split form: each code
-as c >> 11 and c & 2047 against [2^11 q, q]) against the oracle's binary64
+"""GPU parity of scoring for codes of 13 to 22 bits (small stores: each code as
+c >> 11 and c & 2047 against [2^11 q, q]; larger ones: scanned without their low
+bits, the candidates scored from the whole codes) against the oracle's binary64
 scores of the plain codes: the same tolerance and order checks as for narrow
 codes, on both scoring plans, the certificate and scoring from blocks."""
 import numpy as np
@@ -34,7 +35,7 @@ def _wide_store(lam, x, b):
 @pytest.mark.parametrize("b", [13, 16, 22])
 @pytest.mark.parametrize("k,d", [(10, 768), (50, 64)])
 def test_small_store_lists(lam, b, k, d):
-    """At most the sample size: one pass of per-lane lists over all rows."""
+    """At most 4,096 rows: every row scored."""
     rng = np.random.default_rng(100 + b)
     n = 3000
     x = synth.unit_rows(rng, n, d).astype(np.float32)
@@ -69,7 +70,7 @@ def test_large_store_threshold_plan(lam, b, k, d):
 
 def test_certificate_on_wide_codes(lam):
     """Sound (certified => exact margin above 2 (beta + ||q|| delta_hat)) with
-    the split form's error constant; the top-k equals lam_score_topk's."""
+    the error constant of the two halves; the top-k equals lam_score_topk's."""
     import torch
     rng = np.random.default_rng(23)
     d, n, b = 768, 3000, 18
