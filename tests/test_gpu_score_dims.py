@@ -171,3 +171,18 @@ def test_many_flagged_queries(lam, d, n, nq, flagged, k, bits):
     assert np.array_equal(gi[rest[:3]], np.broadcast_to(np.arange(k), (3, k))) and np.all(gs[rest[:3]] == 0.0)
     pick = np.concatenate([rest[3:23], f[:20], f[-3:]])
     _compare(gs[pick], gi[pick], c, np.arange(n), q[pick], eps, k, tol=2e-5)
+
+
+@pytest.mark.parametrize("n", [300, 4500])
+def test_more_queries_than_one_pass(lam, n):
+    """65,536 queries share one pass's scratch; a call of more gives each query
+    what a smaller call gives it."""
+    import torch
+    rng = np.random.default_rng(n)
+    x = synth.unit_rows(rng, n, 32).astype(np.float32)
+    s = _store_from_rows(lam, x)
+    s.quantize(2e-3)
+    q = torch.randn((65536 + 777, 32), generator=torch.Generator(device="cuda").manual_seed(n), device="cuda")
+    got = s.score_topk(q, 7)
+    for a, b in [(0, 130), (65400, 65536), (65536, 66313)]:
+        assert all(torch.equal(g[a:b], w) for g, w in zip(got, s.score_topk(q[a:b].contiguous(), 7)))
